@@ -487,7 +487,7 @@ __device__ __forceinline__ void run_prim(int dtype, const void* fin, const char*
 }
 
 // ------------------------------------------------------------------------------------------
-// Fold steps (make_fold_prim): the two data movers
+// Fold steps (make_fold_prim): the data movers
 // ------------------------------------------------------------------------------------------
 // a buffer resource over memory whose address every lane holds alike (it came out of LDS)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(u64 addr, uint32_t bytes) {
@@ -497,114 +497,171 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(u64 addr, uint32_
 __device__ __forceinline__ uint4 rs_ld16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, AUX_DEVICE));   // out of range reads return 0
 }
-
-constexpr int FOLD_SRC = 8;    // sources read together
-constexpr int FOLD_U = 2;      // vectors per thread and source in flight
+__device__ __forceinline__ void rs_st16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, (int)off, 0, AUX_DEVICE);        // out of range stores are dropped
+}
 
 // dst[d][i] = src[0][i] (op) src[1][i] (op) ... (op) src[nsrc-1][i], left to right, for every destination d: the
-// source table lists the ranks in the ring's order of combination.  Sources are other ranks' send buffers:
-// device-coherent loads; the destinations are recv buffers of this and of other ranks, whose workgroups post the
-// completion: device-coherent stores, which are in memory when the step counts itself done.
-template <int DT, int NTH>
-__device__ __forceinline__ void fold_slice(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, uint32_t bytes,
+// source table lists the ranks in the ring's order of combination.  The workgroup's pieces of the span (FoldGeom):
+// `first`, `first + stride`, ... up to `bytes`.  Sources are other ranks' send buffers: device-coherent loads; the
+// destinations are recv buffers of this and of other ranks, whose workgroups post the completion: device-coherent
+// stores, which are in memory when the step counts itself done.
+//
+// What bounds it is HBM (2R streams, every byte once).  About sixteen 16-byte loads are in flight per thread whatever
+// the number of sources; with 2, 4 or 8 of them (and as many destinations, or one) all buffer resources stay in
+// scalar registers over the whole job (looked up for every round they cost 0.4 us per round and side: the one job of
+// an 8 KiB all-reduce took 3.4 us, now 1.7; a 25 MiB bf16 bucket, with the pieces below, 92 -> 75 us).  A buffer's resource ends with the last whole 16 bytes of the span: loads
+// behind it return 0 and stores behind it are dropped, so the last round needs no predicates.
+// Next round's loads before this round's combine, 512 movers, non-temporal or plain cached accesses measured the
+// same (838-845 us for 256 MiB per rank, fp32, R = 8) or, non-temporal below the size of the memory-side cache,
+// worse (8 MiB: 25 against 20.5 us).
+template <int DT, int NS, bool ALL, int NTH>
+__device__ __forceinline__ void fold_fixed(const u64* src_tab, const u64* dst_tab, uint32_t whole, uint32_t first, uint32_t stride,
                                            uint32_t tid, int op) {
-  const uint32_t nvec = bytes >> 4;
-  for (uint32_t i = tid; i < nvec; i += FOLD_U * NTH) {
-    uint4 acc[FOLD_U];
-    for (uint32_t base = 0; base < nsrc; base += FOLD_SRC) {
-      uint4 w[FOLD_SRC][FOLD_U];
+  constexpr int U = 16 / NS, ND = ALL ? NS : 1;
+  __amdgpu_buffer_rsrc_t S[NS], D[ND];
 #pragma unroll
-      for (int k = 0; k < FOLD_SRC; ++k) {
+  for (int k = 0; k < NS; ++k) S[k] = uniform_rsrc(src_tab[k], whole);
+#pragma unroll
+  for (int k = 0; k < ND; ++k) D[k] = uniform_rsrc(dst_tab[k], whole);
+  for (uint32_t at = first; at < whole; at += U * stride) {
+    const uint32_t o = at + tid * 16u;
+    uint4 w[NS][U];
+#pragma unroll
+    for (int k = 0; k < NS; ++k)
+#pragma unroll
+      for (int u = 0; u < U; ++u) w[k][u] = rs_ld16(S[k], o + u * stride);
+#pragma unroll
+    for (int k = 1; k < NS; ++k) op_batch<DT, U>(w[0], w[k], op);
+#pragma unroll
+    for (int k = 0; k < ND; ++k)
+#pragma unroll
+      for (int u = 0; u < U; ++u) rs_st16(D[k], o + u * stride, w[0][u]);
+  }
+}
+
+// the same for any number of sources and destinations: addresses out of the tables as they are needed
+template <int DT, int NTH>
+__device__ __forceinline__ void fold_any(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, uint32_t whole,
+                                         uint32_t first, uint32_t stride, uint32_t tid, int op) {
+  constexpr int U = 2, NS = 8;      // vectors per source and sources in flight
+  for (uint32_t at = first; at < whole; at += U * stride) {
+    const uint32_t o = at + tid * 16u;
+    uint4 acc[U];
+    for (uint32_t base = 0; base < nsrc; base += NS) {
+      uint4 w[NS][U];
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
         if (base + k < nsrc) {
-          const __amdgpu_buffer_rsrc_t r = uniform_rsrc(src_tab[base + k], bytes);
+          const __amdgpu_buffer_rsrc_t r = uniform_rsrc(src_tab[base + k], whole);
 #pragma unroll
-          for (int u = 0; u < FOLD_U; ++u) w[k][u] = rs_ld16(r, (i + u * NTH) << 4);
+          for (int u = 0; u < U; ++u) w[k][u] = rs_ld16(r, o + u * stride);
         }
       }
 #pragma unroll
-      for (int k = 0; k < FOLD_SRC; ++k) {
+      for (int k = 0; k < NS; ++k) {
         if (base + k < nsrc) {
           if (base + k == 0) {
 #pragma unroll
-            for (int u = 0; u < FOLD_U; ++u) acc[u] = w[0][u];
-          } else op_batch<DT, FOLD_U>(acc, w[k], op);
+            for (int u = 0; u < U; ++u) acc[u] = w[0][u];
+          } else op_batch<DT, U>(acc, w[k], op);
         }
       }
     }
     for (uint32_t d = 0; d < ndst; ++d) {
-      const __amdgpu_buffer_rsrc_t r = uniform_rsrc(dst_tab[d], bytes);
+      const __amdgpu_buffer_rsrc_t r = uniform_rsrc(dst_tab[d], whole);
 #pragma unroll
-      for (int u = 0; u < FOLD_U; ++u)
-        if (i + u * NTH < nvec) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, acc[u]), r, (int)((i + u * NTH) << 4), 0, AUX_DEVICE);
+      for (int u = 0; u < U; ++u) rs_st16(r, o + u * stride, acc[u]);
     }
   }
-  // the sub-vector tail of a message whose length is no multiple of 16 bytes
-  const uint32_t done = nvec << 4;
-  if (done < bytes) {
-    constexpr uint32_t EB = (DT == DT_F32 || DT == DT_I32) ? 4u : 2u;
-    for (uint32_t o = done + tid * EB; o < bytes; o += NTH * EB) {
-      uint32_t v = 0;
-      for (uint32_t k = 0; k < nsrc; ++k) {
-        const Slot<AUX_DEVICE> src((const void*)(uintptr_t)src_tab[k], bytes);
-        const uint32_t x = EB == 4 ? src.ld4(o) : (uint32_t)src.ld2(o);
-        v = k == 0 ? x : (EB == 4 ? op_word<DT>(v, x, op) : (uint32_t)op_half<DT>((uint16_t)v, (uint16_t)x, op));
-      }
+}
+
+// One source handed out to every destination (all-gather, broadcast): ND destinations, or any number (ND = 0).
+// What bounds it is the writes (R per byte read).  Reading once instead of every rank reading everything (R reads and R
+// writes per byte): host to host, bf16, R = 8, broadcast of 100 MiB 270 -> 208 us, all-gather of 32 MiB 104 -> 80 us.
+template <int ND, int NTH>
+__device__ __forceinline__ void fold_copy(const u64* src_tab, const u64* dst_tab, uint32_t ndst, uint32_t whole, uint32_t first,
+                                          uint32_t stride, uint32_t tid) {
+  constexpr int U = 4;
+  const __amdgpu_buffer_rsrc_t S = uniform_rsrc(src_tab[0], whole);
+  __amdgpu_buffer_rsrc_t D[ND ? ND : 1];
+#pragma unroll
+  for (int k = 0; k < ND; ++k) D[k] = uniform_rsrc(dst_tab[k], whole);
+  for (uint32_t at = first; at < whole; at += U * stride) {
+    const uint32_t o = at + tid * 16u;
+    uint4 w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) w[u] = rs_ld16(S, o + u * stride);
+    if (ND) {
+#pragma unroll
+      for (int k = 0; k < ND; ++k)
+#pragma unroll
+        for (int u = 0; u < U; ++u) rs_st16(D[k], o + u * stride, w[u]);
+    } else {
       for (uint32_t d = 0; d < ndst; ++d) {
-        const Slot<AUX_DEVICE> dst((void*)(uintptr_t)dst_tab[d], bytes);
-        if (EB == 4) dst.st4(o, v); else dst.st2(o, (uint16_t)v);
+        const __amdgpu_buffer_rsrc_t r = uniform_rsrc(dst_tab[d], whole);
+#pragma unroll
+        for (int u = 0; u < U; ++u) rs_st16(r, o + u * stride, w[u]);
       }
     }
   }
+}
+
+// the bytes behind the last whole 16 of a span, element by element (fold or copy)
+template <int DT, int NTH>
+__device__ __forceinline__ void fold_tail(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, uint32_t whole,
+                                          uint32_t bytes, uint32_t tid, int op) {
+  constexpr uint32_t EB = (DT == DT_F32 || DT == DT_I32) ? 4u : 2u;
+  const uint32_t o = whole + tid * EB;
+  if (o >= bytes) return;
+  uint32_t v = 0;
+  for (uint32_t k = 0; k < nsrc; ++k) {
+    const __amdgpu_buffer_rsrc_t r = uniform_rsrc(src_tab[k], bytes);
+    const uint32_t x = EB == 4 ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)o, 0, AUX_DEVICE)
+                               : (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)o, 0, AUX_DEVICE);
+    v = k == 0 ? x : (EB == 4 ? op_word<DT>(v, x, op) : (uint32_t)op_half<DT>((uint16_t)v, (uint16_t)x, op));
+  }
+  for (uint32_t d = 0; d < ndst; ++d) {
+    const __amdgpu_buffer_rsrc_t r = uniform_rsrc(dst_tab[d], bytes);
+    if (EB == 4) __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)o, 0, AUX_DEVICE);
+    else __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, (int)o, 0, AUX_DEVICE);
+  }
+}
+
+// A reduction has one source per rank and one destination, or as many destinations as sources.
+template <int DT, int NTH>
+__device__ __forceinline__ void fold_reduce(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, uint32_t bytes,
+                                            uint32_t first, uint32_t stride, uint32_t tid, int op) {
+  const uint32_t whole = bytes & ~15u;
+  const bool all = ndst > 1;
+  if (nsrc == 8 && all) fold_fixed<DT, 8, true, NTH>(src_tab, dst_tab, whole, first, stride, tid, op);
+  else if (nsrc == 8) fold_fixed<DT, 8, false, NTH>(src_tab, dst_tab, whole, first, stride, tid, op);
+  else if (nsrc == 4 && all) fold_fixed<DT, 4, true, NTH>(src_tab, dst_tab, whole, first, stride, tid, op);
+  else if (nsrc == 4) fold_fixed<DT, 4, false, NTH>(src_tab, dst_tab, whole, first, stride, tid, op);
+  else if (nsrc == 2 && all) fold_fixed<DT, 2, true, NTH>(src_tab, dst_tab, whole, first, stride, tid, op);
+  else if (nsrc == 2) fold_fixed<DT, 2, false, NTH>(src_tab, dst_tab, whole, first, stride, tid, op);
+  else fold_any<DT, NTH>(src_tab, nsrc, dst_tab, ndst, whole, first, stride, tid, op);
+  if (whole < bytes && first == 0) fold_tail<DT, NTH>(src_tab, nsrc, dst_tab, ndst, whole, bytes, tid, op);
 }
 
 template <int NTH>
 __device__ __forceinline__ void fold_dispatch(int dtype, const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst,
-                                              uint32_t bytes, uint32_t tid) {
+                                              uint32_t bytes, uint32_t first, uint32_t stride, uint32_t tid) {
+  if (nsrc == 1) {
+    const uint32_t whole = bytes & ~15u;
+    if (ndst == 8) fold_copy<8, NTH>(src_tab, dst_tab, ndst, whole, first, stride, tid);
+    else if (ndst == 4) fold_copy<4, NTH>(src_tab, dst_tab, ndst, whole, first, stride, tid);
+    else fold_copy<0, NTH>(src_tab, dst_tab, ndst, whole, first, stride, tid);
+    // (every element type is a multiple of 2 bytes)
+    if (whole < bytes && first == 0) fold_tail<DT_F16, NTH>(src_tab, 1, dst_tab, ndst, whole, bytes, tid, OP_SUM);
+    return;
+  }
   const int op = dtype >> 4;
   switch (dtype & 15) {
-    case DT_F32: fold_slice<DT_F32, NTH>(src_tab, nsrc, dst_tab, ndst, bytes, tid, op); break;
-    case DT_BF16: fold_slice<DT_BF16, NTH>(src_tab, nsrc, dst_tab, ndst, bytes, tid, op); break;
-    case DT_F16: fold_slice<DT_F16, NTH>(src_tab, nsrc, dst_tab, ndst, bytes, tid, op); break;
-    default: fold_slice<DT_I32, NTH>(src_tab, nsrc, dst_tab, ndst, bytes, tid, op); break;
-  }
-}
-
-// The gather step: segment s is len[s] bytes copied from src[s] (a rank's send buffer: device-coherent loads)
-// to dst[s] (the own recv buffer); the loads of up to eight segments travel together.
-template <int NTH>
-__device__ __forceinline__ void gather_slices(const u64* src_tab, const u64* dst_tab, const uint32_t* len_tab, uint32_t nseg,
-                                              uint32_t maxbytes, uint32_t tid) {
-  const uint32_t maxvec = maxbytes >> 4;
-  for (uint32_t base = 0; base < nseg; base += FOLD_SRC) {
-    for (uint32_t i = tid; i < maxvec; i += FOLD_U * NTH) {
-      uint4 w[FOLD_SRC][FOLD_U];
-#pragma unroll
-      for (int k = 0; k < FOLD_SRC; ++k) {
-        if (base + k < nseg) {
-          const __amdgpu_buffer_rsrc_t r = uniform_rsrc(src_tab[base + k], len_tab[base + k]);
-#pragma unroll
-          for (int u = 0; u < FOLD_U; ++u) w[k][u] = rs_ld16(r, (i + u * NTH) << 4);
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < FOLD_SRC; ++k) {
-        if (base + k < nseg) {
-          v4u_user* D = (v4u_user*)(uintptr_t)dst_tab[base + k];
-          const uint32_t nv = len_tab[base + k] >> 4;
-#pragma unroll
-          for (int u = 0; u < FOLD_U; ++u) if (i + u * NTH < nv) st_user(&D[i + u * NTH], w[k][u]);
-        }
-      }
-    }
-  }
-  // sub-vector tails (only the message's last chunk can have one); every dtype is a multiple of 2 bytes
-  for (uint32_t s2 = 0; s2 < nseg; ++s2) {
-    const uint32_t len = len_tab[s2], done = (len >> 4) << 4;
-    if (done < len) {
-      const Slot<AUX_DEVICE> src((const void*)(uintptr_t)src_tab[s2], len);
-      uint16_t* D = (uint16_t*)(uintptr_t)dst_tab[s2];
-      for (uint32_t o = done + (tid << 1); o < len; o += NTH << 1) D[o >> 1] = src.ld2(o);
-    }
+    case DT_F32: fold_reduce<DT_F32, NTH>(src_tab, nsrc, dst_tab, ndst, bytes, first, stride, tid, op); break;
+    case DT_BF16: fold_reduce<DT_BF16, NTH>(src_tab, nsrc, dst_tab, ndst, bytes, first, stride, tid, op); break;
+    case DT_F16: fold_reduce<DT_F16, NTH>(src_tab, nsrc, dst_tab, ndst, bytes, first, stride, tid, op); break;
+    default: fold_reduce<DT_I32, NTH>(src_tab, nsrc, dst_tab, ndst, bytes, first, stride, tid, op); break;
   }
 }
 
@@ -615,10 +672,8 @@ struct Job {                         // what the scheduler wave hands to the mov
   const void* fin; const char* sb; char* rb; void* fout;
   uint32_t bytes; int dtype;
   uint32_t coll, prim;               // for the timeline trace only
-  uint32_t mode;                     // 0: the four pointers above; 1: fold step (sources and destinations in the job's tables);
-                                     // 2: gather step (segments in the job's tables, bytes = the longest one)
-  uint32_t nseg;                     // sources of a fold step, segments of a gather step
-  uint32_t ndst;                     // destinations of a fold step
+  uint32_t nsrc, ndst;               // not 0: step with data of a collective in fold steps (that many sources and destinations in the job's tables)
+  uint32_t first, stride;            // ... the workgroup's pieces of the span of `bytes` (FoldGeom)
 };
 
 // What publishing and retiring a posted job needs.  Written by the scheduler when it posts the
@@ -639,9 +694,8 @@ struct Shared {
   uint32_t slot_claim[DFX_CTX_SLOTS];  // readiness scan: which entry of the scan gets to fill a slot (scan step << 8 | lane)
   Job job[2];                        // posted jobs, indexed by job number & 1
   Flight fl[2];
-  u64 tab_src[2][64];                // fold / gather steps: source addresses of the job, in order
-  u64 tab_dst[2][64];                // fold steps: where the result goes; gather steps: where each segment goes
-  uint32_t tab_len[2][64];           // gather steps: bytes of each segment
+  u64 tab_src[2][64];                // fold steps: source addresses of the job, in the order of combination
+  u64 tab_dst[2][64];                // ... and where the result goes
   uint32_t job_seq;                  // jobs posted so far (scheduler -> movers)
   uint32_t wave_done[2];             // mover waves that have finished job k, at index k & 1
   uint32_t jobs_done;                // jobs finished and published (movers -> scheduler)
@@ -789,8 +843,8 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
         }
       } else
 #endif
-      if (j.mode == 1) fold_dispatch<GTHREADS>(j.dtype, sh.tab_src[seen & 1], j.nseg, sh.tab_dst[seen & 1], j.ndst, j.bytes, mtid);
-      else if (j.mode == 2) gather_slices<GTHREADS>(sh.tab_src[seen & 1], sh.tab_dst[seen & 1], sh.tab_len[seen & 1], j.nseg, j.bytes, mtid);
+      if (j.nsrc) fold_dispatch<GTHREADS>(j.dtype, sh.tab_src[seen & 1], bcast0(j.nsrc), sh.tab_dst[seen & 1], bcast0(j.ndst), bcast0(j.bytes),
+                                          bcast0(j.first), bcast0(j.stride), mtid);
       else if (coh) run_prim<AUX_DEVICE, GTHREADS>(j.dtype, j.fin, j.sb, j.rb, j.fout, j.bytes, mtid);
       else run_prim<AUX_CACHED, GTHREADS>(j.dtype, j.fin, j.sb, j.rb, j.fout, j.bytes, mtid);
       // this wave's stores (and loads) have been performed before it counts itself done
@@ -1185,7 +1239,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 const uint4 d1 = e[7];    // dyn: recvd | preempted | cidx
                 e2c = fl; e3c = fi; e5c = ge; e6c = d0; e7c = d1;
                 const bool e_fold = ((ge.z >> 24) & DFX_CTX_FOLD) != 0;
-                Prim pq = e_fold ? make_fold_prim((int)((ge.z >> 8) & 0xffu), d0.y)
+                Prim pq = e_fold ? make_fold_prim(d0.y)
                                  : make_prim((int)((ge.z >> 8) & 0xffu), a.R, (ge.z >> 24) & 3u, d0.y, ((ge.z >> 24) & DFX_CTX_DIRECT) != 0);
                 if (!e_fold && ((ge.z >> 24) & DFX_CTX_DIRECT))
                   pq = chain_drain_round(pq, (int)((ge.z >> 8) & 0xffu), true, d0.x, e[4].w);   // bytes 64..79: fifo_in | slice_elems | rounds
@@ -1283,7 +1337,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
       // ================= next primitive of the collective in hand =================
       const DfxCooked& S = sh.slot[sl].st;
       const bool fold = (S.bc_pos & DFX_CTX_FOLD) != 0;
-      const Prim q = fold ? make_fold_prim((int)S.kind, p)
+      const Prim q = fold ? make_fold_prim(p)
                           : chain_drain_round(make_prim((int)S.kind, a.R, S.bc_pos & 3u, p, (S.bc_pos & DFX_CTX_DIRECT) != 0),
                                               (int)S.kind, (S.bc_pos & DFX_CTX_DIRECT) != 0, g, S.rounds);
       // fold steps wait for one of the channel's shared counters: every rank has published the invocation
@@ -1323,7 +1377,10 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
 
       // ---- slice geometry and the job's four pointers
       const int kind = S.kind, dtype = S.dtype;   // dtype: element type | reducing function << 4
-      const SliceGeom geo = slice_geometry(S, a.R, g, cidx);
+      FoldGeom fg = {};
+      SliceGeom geo = {};
+      if (fold) { fg = fold_geometry(S, a.R, rank, g); geo.eb = fg.eb; geo.bytes = S.slice_elems * fg.eb; }
+      else geo = slice_geometry(S, a.R, g, cidx);
       const uint32_t eb = geo.eb, bytes = geo.bytes;
       const u64 soff = geo.soff, doff = geo.doff;
       const size_t slot_bytes = (size_t)S.slice_elems * eb;
@@ -1436,55 +1493,34 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           }
           jfin = q.din_send ? (const void*)((const char*)prev_send + soff * eb) : (const void*)((const char*)prev_recv + doff * eb);
         }
-        uint32_t jmode = 0, jnseg = 0, jndst = 0, jbytes_fold = 0;
-        if (q.fold == 1 || q.fold == 2) {
+        uint32_t jnsrc = 0, jndst = 0;
+        if (q.fold == 1) {
           // The addresses every rank published for this invocation (before it counted itself published, which a
-          // wait of this invocation has seen for all of them): lane k looks up one rank.
-          // fold_peer / fold_chunk say which rank and which chunk entry k is about.  Every entry reads a send buffer;
-          // the result of a fold step goes to the own recv buffer (reduce-scatter), to the root's (reduce: its address
-          // is looked up by the lane behind the R sources, hence at most 63 ranks) or to every entry's rank's
-          // (all-reduce: each lane reads both addresses of its rank).
+          // wait of this invocation has seen for all of them): lane k looks up entry k's rank (fold_peer).
           const int kd = (int)S.kind;
           const uint32_t root = S.nslots;                       // (a collective in fold steps keeps its root there)
-          const uint32_t nk = fold_entries(kd, q.fold, a.R);
-          const uint32_t target = q.fold == 1 ? fold_dest(kd) : 0u;
-          const bool want_root_recv = target == 1u;             // one more look-up, in lane nk
-          const bool root_lane = want_root_recv && lane == nk;
-          const uint32_t peer = root_lane ? root : fold_peer(kd, q.fold, a.R, rank, root, lane);
-          bool bad = want_root_recv && nk >= 64u;
-          if (lane < nk + (want_root_recv ? 1u : 0u)) {
+          const bool copies = fold_copies(kd), to_all = fold_to_all(kd);
+          bool bad = false;
+          if (lane < a.R) {
+            const uint32_t peer = fold_peer(kd, a.R, rank, root, lane);
             const Slot<AUX_DEVICE> line((const void*)fold_line(S.flags_out, rank, peer, S.nchan), DFX_FLAG_STRIDE);
             uint4 w = uint4{0, 0, 0, 0}, wr = w;
             for (uint32_t tries = 0; tries < 1024u; ++tries) {
-              w = line.ld16(root_lane ? DFX_DIRECT_OFF : DFX_DIRECT_OFF + 16);
-              if (target == 2u) wr = line.ld16(DFX_DIRECT_OFF);
-              if (w.z == inv_seq + 1u && (target != 2u || wr.z == inv_seq + 1u)) break;
+              w = line.ld16(DFX_DIRECT_OFF + 16);
+              wr = line.ld16(DFX_DIRECT_OFF);
+              if (w.z == inv_seq + 1u && wr.z == inv_seq + 1u) break;
               __builtin_amdgcn_s_sleep(2);
             }
-            bad = bad || w.z != inv_seq + 1u || (target == 2u && wr.z != inv_seq + 1u);
-            const u64 base = ((u64)w.y << 32) | w.x;
-            const u64 peer_recv = ((u64)wr.y << 32) | wr.x;
-            const SliceGeom gk = slice_geometry(S, a.R, g, fold_chunk(kd, q.fold, rank, peer));
-            // (a broadcast's one source goes in pieces: entry k is the k-th piece of the share)
-            const bool pieces = q.fold == 2 && kd == KIND_BC;
-            const uint32_t off = pieces ? bc_piece_off(gk.bytes, lane) : 0u;
-            if (root_lane) sh.tab_dst[posted & 1][0] = base + gk.doff * gk.eb;
-            else {
-              sh.tab_src[posted & 1][lane] = base + gk.soff * gk.eb + off;
-              if (!(want_root_recv && lane == 0))
-                sh.tab_dst[posted & 1][lane] = (target == 2u ? peer_recv : (u64)S.recvbuf) + gk.doff * gk.eb + off;
-              sh.tab_len[posted & 1][lane] = pieces ? bc_piece_len(gk.bytes, lane) : gk.bytes;
-            }
+            bad = w.z != inv_seq + 1u || wr.z != inv_seq + 1u;
+            const u64 src = (((u64)w.y << 32) | w.x) + fg.soff * fg.eb, dst = (((u64)wr.y << 32) | wr.x) + fg.doff * fg.eb;
+            if (!copies) sh.tab_src[posted & 1][lane] = src;
+            else if (lane + 1 == a.R) sh.tab_src[posted & 1][0] = src;
+            if (to_all) sh.tab_dst[posted & 1][lane] = dst;
+            else if (lane + 1 == a.R) sh.tab_dst[posted & 1][0] = dst;
           }
           if (__ballot(bad)) { if (lane == 0) raise_error(a, 3u, wg); stop = STOP_ABORT; have = false; continue; }
           __builtin_amdgcn_wave_barrier();
-          jmode = q.fold; jnseg = nk; jndst = target == 2u ? nk : 1u;
-          const SliceGeom own = slice_geometry(S, a.R, g, rank);
-          if (q.fold == 1) jbytes_fold = own.bytes;
-          else {                                                    // the longest segment: a channel's share of a full chunk
-            jbytes_fold = (uint32_t)S.slice_elems * own.eb;
-            if (kd == KIND_BC) jbytes_fold = bc_piece_bytes(jbytes_fold);
-          }
+          jnsrc = copies ? 1u : a.R; jndst = to_all ? a.R : 1u;
         }
         // ---- post the slice (an empty one is only a handshake: the movers just raise the counters);
         // this claims the slots: the data follows, the counters after it
@@ -1496,8 +1532,9 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           Job j;
           j.fin = jfin; j.fout = jfout; j.sb = jsb; j.rb = jrb;
           j.bytes = (q.drain || (!q.recv && !q.from_send)) ? 0u : bytes;   // drain and notify-only steps move nothing
-          if (q.fold) j.bytes = jbytes_fold;                               // (the last fold step: nothing)
-          j.mode = jmode; j.nseg = jnseg; j.ndst = jndst;
+          if (q.fold) { j.bytes = fg.bytes; j.first = fg.first; j.stride = fg.stride; }
+          else j.first = j.stride = 0;
+          j.nsrc = jnsrc; j.ndst = jndst;
           j.dtype = dtype; j.coll = coll; j.prim = (q.drain || q.fold == 3) ? 0xffu : p;   // (prim: for the timeline only)
           sh.job[posted & 1] = j;
           Flight f;

@@ -55,66 +55,84 @@ struct Prim {
   // (the recv buffer is the caller's again once the completion is posted).
   bool notify, din, drain;
   bool din_send;   // the input is the previous rank's SEND buffer (first reduce step of a direct all-reduce / reduce-scatter)
-  // Fold steps of a short collective (see make_fold_prim): fold = 1 a fold step, 2 a gather step, 3 a last wait
-  // that moves nothing; 0 = none of them.  fwait: the channel's shared counter the wait phase looks at
-  // (0 published, 1 folded, 2 gathered); fadd: the counter the step adds to when its data is in memory (0 = none).
+  // Fold steps of a short collective (see make_fold_prim): fold = 1 the step with data, 3 the last wait, which
+  // moves nothing; 0 = neither.  fwait: the channel's shared counter the wait phase looks at
+  // (0 published, 1 done); fadd: the counter the step adds to when its data is in memory (0 = none).
   uint8_t fold, fwait, fadd;
 };
 
 // Short collectives in fold steps.  Every rank's buffers lie in the same HBM, so the dependent hops of a ring or
 // a chain (a few microseconds each, whatever the size) can be replaced by steps that wait on all ranks at once:
-//   fold step:   when every rank has published this invocation's buffers, a rank reads one chunk out of all R
-//                send buffers and combines them in the ring's (the chain's) own order -- the same association as
-//                the hops would give, hence the same bits -- and writes the result where it belongs: its own recv
-//                buffer, the root's, or everybody's;
-//   gather step: copies chunks out of other ranks' send buffers into the own recv buffer;
-//   last wait:   no data; when every rank has got far enough, nobody reads this rank's buffers any more and
-//                the completion may be posted.
-// all-reduce:      fold (rank r: chunk r, x[r+1] (op) ... (op) x[r], into chunk r of ALL R recv buffers: every input is
-//                  read once and every output written once), last wait (all folded: every chunk of the own recv
-//                  buffer has arrived and nobody reads the own send buffer any more)
-// reduce-scatter:  fold (rank r: block r into its recv buffer), last wait (all folded: the send buffers are free)
-// reduce:          fold (rank r: chunk r of the message, x[root+1] (op) ... (op) x[root], into the ROOT's recv
-//                  buffer), last wait (all folded)
-// all-gather:      gather (all R blocks out of the send buffers), last wait (all gathered)
-// broadcast:       gather (the channel's share of the root's send buffer), last wait (all gathered)
+//   step with data: when every rank has published this invocation's buffers, a rank does its part of the work
+//                reading other ranks' send buffers where they lie and writing the result straight into the recv
+//                buffers it belongs to; reductions combine in the ring's (the chain's) own order -- the same
+//                association as the hops would give, hence the same bits;
+//   last wait:   no data; when every rank has done its part, every byte of the own recv buffer has arrived, nobody
+//                reads this rank's send buffer any more, and the completion may be posted.
+// What rank r reads and writes in its step with data:
+//   all-reduce:      chunk r out of all R send buffers, x[r+1] (op) ... (op) x[r]     -> chunk r of all R recv buffers
+//   reduce-scatter:  block r out of all R send buffers, in the same order             -> the own recv buffer
+//   reduce:          chunk r out of all R send buffers, x[root+1] (op) ... (op) x[root] -> chunk r of the root's recv buffer
+//   all-gather:      the own send buffer, once                                        -> block r of all R recv buffers
+//   broadcast:       every R-th piece of the root's send buffer                       -> the same of all R recv buffers
+// So every input is read once and every output written once, whatever the kind.  (All-gather and broadcast hand
+// their data out instead of every rank fetching all of it: one read per byte instead of R.)
 // Each step is a bounded wait followed by the data, like any primitive: nothing is touched before the wait has
-// succeeded, so a collective stuck in any of them is preempted like any other.
+// succeeded, so a collective stuck in either of them is preempted like any other.
 DFX_HD uint32_t fold_nprim(int) { return 2u; }
-DFX_HD Prim make_fold_prim(int kind, uint32_t p) {
+DFX_HD Prim make_fold_prim(uint32_t p) {
   Prim q;
   q.recv = q.send = q.notify = q.din = q.drain = q.din_send = false;
   q.from_send = q.to_recv = false;
-  const bool reduces = (kind == KIND_AR || kind == KIND_RS || kind == KIND_RD);
-  if (p == 0) { q.fold = reduces ? 1 : 2; q.fwait = 0; q.fadd = reduces ? 1 : 2; q.from_send = true; q.to_recv = true; }
-  else { q.fold = 3; q.fwait = reduces ? 1 : 2; q.fadd = 0; }
+  if (p == 0) { q.fold = 1; q.fwait = 0; q.fadd = 1; q.from_send = true; q.to_recv = true; }
+  else { q.fold = 3; q.fwait = 1; q.fadd = 0; }
   return q;
 }
 
-// The tables of a fold or gather step (Prim::fold 1 or 2).  Entry k of a fold step is a source, listed in the order
-// of combination, which begins behind this rank (all-reduce, reduce-scatter: the ring's order for this rank's chunk)
-// or behind the root (reduce: the chain's); every entry is about the rank's own chunk.  Entry k of a gather step is
-// a segment: all-gather: block k out of rank k's send buffer; broadcast: the k-th of eight pieces of the channel's
-// share of the root's send buffer (one source cut up, so that as many loads travel together as in an all-gather).
-constexpr uint32_t DFX_BC_PIECES = 8;
-DFX_HD uint32_t fold_entries(int kind, uint32_t step, uint32_t R) { return (step == 2 && kind == KIND_BC) ? DFX_BC_PIECES : R; }
-DFX_HD uint32_t bc_piece_bytes(uint32_t share_bytes) { return (((share_bytes + DFX_BC_PIECES - 1) / DFX_BC_PIECES) + 15u) & ~15u; }
-// piece k of a share of share_bytes: where it begins and how long it is (0 = nothing left for it)
-DFX_HD uint32_t bc_piece_off(uint32_t share_bytes, uint32_t k) { return k * bc_piece_bytes(share_bytes); }
-DFX_HD uint32_t bc_piece_len(uint32_t share_bytes, uint32_t k) {
-  const uint32_t pb = bc_piece_bytes(share_bytes), off = k * pb;
-  return off >= share_bytes ? 0u : (share_bytes - off < pb ? share_bytes - off : pb);
+// The tables of a step with data.  Entry k is about rank fold_peer(.., k); the entries begin behind this rank (behind
+// the root: reduce, broadcast), which makes their order the order of combination and the last entry, R - 1, this rank
+// (the root).  A kind that combines reads every entry's send buffer, a kind that copies only the last entry's;
+// a kind with results for everybody writes every entry's recv buffer, the others only the last entry's.
+DFX_HD uint32_t fold_peer(int kind, uint32_t R, uint32_t rank, uint32_t root, uint32_t k) {
+  const uint32_t r = ((kind == KIND_RD || kind == KIND_BC) ? root : rank) + 1u + k;
+  return r >= R ? r - R : r;
 }
-DFX_HD uint32_t fold_peer(int kind, uint32_t step, uint32_t R, uint32_t rank, uint32_t root, uint32_t k) {
-  if (step == 2) return kind == KIND_BC ? root : k % R;
-  return ((kind == KIND_RD ? root : rank) + 1u + k) % R;
+DFX_HD bool fold_copies(int kind) { return kind == KIND_AG || kind == KIND_BC; }
+DFX_HD bool fold_to_all(int kind) { return kind != KIND_RS && kind != KIND_RD; }
+
+// Where slice g of a collective in fold steps lies: a span of the chunk (block, message) that the workgroups which
+// share it take piece by piece in turn, DFX_FOLD_PIECE bytes each: this workgroup's pieces begin `first` bytes into the
+// span and follow each other `stride` bytes apart, the last one cut off at `bytes`.  The workgroups that share a
+// span advance through it side by side, so that together they sweep one compact stretch of every buffer: with
+// one contiguous part per workgroup (256 x 16 streams megabytes apart) the same kernel loop took 85-87 us for 24 MiB
+// per rank and 22.5 us for 8 MiB, in pieces 78 and 20 us (fp32, R = 8; 256 MiB 845 -> 830 us).
+// The bytes behind the last whole 16 of a span belong to the workgroup whose pieces begin at 0.
+constexpr uint32_t DFX_FOLD_PIECE = DFX_MOVERS * 16u;
+struct FoldGeom { uint64_t soff, doff; uint32_t bytes, first, stride, eb; };
+DFX_HD FoldGeom fold_geometry(const DfxCooked& S, uint32_t R, uint32_t rank, uint32_t g) {
+  const int kind = S.kind, dt = S.dtype & 15;
+  FoldGeom o;
+  o.eb = (dt == DT_F32 || dt == DT_I32) ? 4u : 2u;
+  const uint64_t count = S.count, block = S.block_elems, span = (uint64_t)S.nchan * S.slice_elems;
+  // a chunk or block of its own for every rank, or one stretch that all ranks' workgroups share
+  const bool chunks = kind == KIND_AR || (kind == KIND_RD && block != count);
+  const bool shared = kind == KIND_BC || (kind == KIND_RD && !chunks);
+  uint64_t start = 0, len = count;
+  if (chunks) {
+    start = (uint64_t)rank * block;
+    len = start >= count ? 0 : (count - start < block ? count - start : block);
+  }
+  const uint64_t lo = (uint64_t)g * span < len ? (uint64_t)g * span : len;
+  const uint64_t n = len - lo < span ? len - lo : span;
+  o.soff = o.doff = start + lo;
+  if (kind == KIND_RS) o.soff += (uint64_t)rank * count;
+  if (kind == KIND_AG) o.doff += (uint64_t)rank * count;
+  o.bytes = (uint32_t)n * o.eb;
+  const uint32_t sharers = shared ? S.nchan * R : S.nchan;
+  o.first = (shared ? S.vch * R + rank : (uint32_t)S.vch) * DFX_FOLD_PIECE;
+  o.stride = sharers * DFX_FOLD_PIECE;
+  return o;
 }
-DFX_HD uint32_t fold_chunk(int kind, uint32_t step, uint32_t rank, uint32_t peer) {
-  return step == 1 ? rank : (kind == KIND_BC ? 0u : peer);
-}
-// Where a fold step's result goes: 0 the own recv buffer (reduce-scatter), 1 the root's (reduce), 2 the recv buffer
-// of every entry's rank (all-reduce).
-DFX_HD uint32_t fold_dest(int kind) { return kind == KIND_AR ? 2u : (kind == KIND_RD ? 1u : 0u); }
 
 // Where a fold collective's lines are, from a workgroup's own line: the line of rank r on the same channel,
 // and the channel's shared line.
@@ -251,8 +269,7 @@ DFX_HD SliceGeom slice_geometry(const DfxCooked& S, uint32_t R, uint32_t g, uint
   o.eb = (dt == DT_F32 || dt == DT_I32) ? 4u : 2u;
   const uint32_t slice_elems = S.slice_elems, vch = S.vch;
   const uint64_t count = S.count, block_elems = S.block_elems, part_elems = S.part_elems;
-  // (a reduce in fold steps is cut into R chunks like an all-reduce: rank r combines chunk r)
-  const bool ring_chunks = R > 1 && (kind == KIND_AR || (kind == KIND_RD && (S.bc_pos & DFX_CTX_FOLD)));
+  const bool ring_chunks = R > 1 && kind == KIND_AR;
   uint64_t blen = count;
   if (ring_chunks) {
     const uint64_t start = (uint64_t)cidx * block_elems;

@@ -411,7 +411,8 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
     slice_cap = std::min(std::max(want, lo), hi);
   }
   // fold steps: no slots; slices of fold_slice_bytes, or (0) one slice, the whole channel share
-  if (fold) slice_cap = cfg.fold_slice_bytes ? cfg.fold_slice_bytes : (1ull << 31);
+  // (all channels' slices together stay below 1 GiB: byte offsets inside one span fit 32 bits)
+  if (fold) slice_cap = std::min<uint64_t>(cfg.fold_slice_bytes ? cfg.fold_slice_bytes : 1ull << 30, ((1ull << 30) / C) & ~15ull);
   uint64_t slot_bytes = std::min<uint64_t>(slice_cap, round_up(part * eb, 16));
   const uint64_t slice_elems = slot_bytes / eb;
   const uint64_t rounds = std::max<uint64_t>(1, ceil_div(part, slice_elems));
@@ -1202,35 +1203,34 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
       uint64_t sent = 0, recvd = 0, steps = 0;
       for (;;) {
         if (fold) {
-          // fold steps: the same look-ups as the scheduler makes when it posts a fold or a gather step
-          const Prim fq = make_fold_prim(kind, p);
-          const uint32_t rt = S.nslots;      // the root
-          if (fq.fold == 1 || fq.fold == 2) {
-            const uint32_t nk = fold_entries(kind, fq.fold, R);
-            const uint32_t target = fq.fold == 1 ? fold_dest(kind) : 0u;
-            if (nk > 64u || (target == 1u && nk > 63u)) return fail("rank %u channel %u: %u table entries for 64 lanes", r, v, nk);
-            for (uint32_t k = 0; k < nk; ++k) {
-              const uint32_t peer = fold_peer(kind, fq.fold, R, r, rt, k);
-              if (peer >= R) return fail("rank %u channel %u fold step %u: entry %u names rank %u", r, v, p, k, peer);
-              SliceGeom gk = slice_geometry(S, R, g, fold_chunk(kind, fq.fold, r, peer));
-              if ((uint64_t)gk.bytes > (uint64_t)S.slice_elems * gk.eb) return fail("rank %u channel %u: a segment longer than the share", r, v);
-              if (fq.fold == 2 && kind == KIND_BC) {          // entry k is the k-th piece of the share
-                const uint32_t off = bc_piece_off(gk.bytes, k), len = bc_piece_len(gk.bytes, k);
-                if (len > bc_piece_bytes((uint32_t)S.slice_elems * gk.eb)) return fail("rank %u channel %u: piece %u longer than the job's bound", r, v, k);
-                if (off % gk.eb) return fail("rank %u channel %u: piece %u splits an element", r, v, k);
-                gk.soff += off / gk.eb; gk.doff += off / gk.eb; gk.bytes = len;
-              }
-              if (!gk.bytes) continue;
-              const uint64_t rd = gk.soff * gk.eb;            // every entry reads its rank's send buffer
-              if (rd + gk.bytes > send_bytes) return fail("rank %u channel %u fold step %u: read of rank %u's buffer %llu+%u of %llu", r, v, p, peer, (unsigned long long)rd, gk.bytes, (unsigned long long)send_bytes);
-              if ((kind == KIND_AG || kind == KIND_RS) && (rd & 15u)) return fail("rank %u channel %u fold step %u: a 16-byte read at offset %llu", r, v, p, (unsigned long long)rd);
-              // a fold step writes its result to the own recv buffer (once, entry 0 stands for it), the root's, or
-              // the recv buffer of every entry's rank; a gather step writes every segment to the own recv buffer
-              if (fq.fold == 1 && target != 2u && k != 0) continue;
-              const uint64_t wr = gk.doff * gk.eb;
-              if (wr + gk.bytes > recv_bytes) return fail("rank %u channel %u fold step %u: recv buffer write %llu+%u of %llu", r, v, p, (unsigned long long)wr, gk.bytes, (unsigned long long)recv_bytes);
-              written[target == 2u ? peer : (target == 1u ? rt : r)].push_back({wr, wr + gk.bytes});
+          // fold steps: the same look-ups as the scheduler makes when it posts a step with data, the same pieces as
+          // the movers walk through
+          const Prim fq = make_fold_prim(p);
+          if (fq.fold == 1) {
+            const uint32_t rt = S.nslots;      // the root
+            const FoldGeom fg = fold_geometry(S, R, r, g);
+            const bool copies = fold_copies(kind), to_all = fold_to_all(kind);
+            const uint64_t src = fg.soff * fg.eb, dst = fg.doff * fg.eb;
+            if (R > 64) return fail("%u table entries for 64 lanes", R);
+            if (fg.bytes > (1u << 30) || fg.first % 16 || fg.stride % 16 || !fg.stride) return fail("rank %u channel %u: a span of %u bytes, pieces from %u every %u", r, v, fg.bytes, fg.first, fg.stride);
+            if (fg.bytes && ((src | dst) & 15u)) return fail("rank %u channel %u step %u: 16-byte accesses at offsets %llu, %llu", r, v, p, (unsigned long long)src, (unsigned long long)dst);
+            if (fg.bytes && src + fg.bytes > send_bytes) return fail("rank %u channel %u: read of send buffers %llu+%u of %llu", r, v, (unsigned long long)src, fg.bytes, (unsigned long long)send_bytes);
+            if (fg.bytes && dst + fg.bytes > recv_bytes) return fail("rank %u channel %u: write of recv buffers %llu+%u of %llu", r, v, (unsigned long long)dst, fg.bytes, (unsigned long long)recv_bytes);
+            // entries: every rank once, the last one this rank (the root), which is the only one a copy reads and a
+            // result for one rank is written to
+            uint64_t seen = 0;
+            for (uint32_t k = 0; k < R; ++k) {
+              const uint32_t peer = fold_peer(kind, R, r, rt, k);
+              if (peer >= R || (seen >> peer & 1u)) return fail("rank %u channel %u: entry %u names rank %u", r, v, k, peer);
+              seen |= 1ull << peer;
+              if (!to_all && k + 1 < R) continue;
+              const uint32_t whole = fg.bytes & ~15u;
+              for (uint64_t at = fg.first; at < whole; at += fg.stride)
+                written[peer].push_back({dst + at, dst + std::min<uint64_t>(at + DFX_FOLD_PIECE, whole)});
+              if (whole < fg.bytes && fg.first == 0) written[peer].push_back({dst + whole, dst + fg.bytes});
             }
+            const uint32_t lastp = fold_peer(kind, R, r, rt, R - 1);
+            if ((copies || !to_all) && lastp != ((kind == KIND_BC || kind == KIND_RD) ? rt : r)) return fail("rank %u channel %u: the last entry is rank %u", r, v, lastp);
           }
           const SeqPos nx = next_fold_position(S.rounds, g, p, cidx);
           g = nx.g; p = nx.p; cidx = nx.cidx;

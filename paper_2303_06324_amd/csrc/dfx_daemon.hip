@@ -31,6 +31,10 @@
 //     connector slots are ordinary cached memory; the publishing wave issues an agent-scope
 //     release fence (L2 write-back) before it raises the counter, and every mover wave an
 //     agent-scope acquire fence (invalidate) before its loads of a slot.
+//   fold steps
+//     device-coherent accesses throughout: the send buffers are read and the recv buffers written with sc1, which
+//     bypasses the L2s, so neither the fetch of such a collective invalidates a cache nor its completion writes one
+//     back (an L2 write-back or invalidate costs 0.6 - 1 us on an idle device, and an XCD's 32 workgroups queue for it).
 //   SQ / CQ / host control words are host-visible and use system scope.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -58,6 +62,7 @@ enum { STOP_NONE = 0, STOP_ABORT = 1, STOP_QUIT = 2, STOP_EXIT = 3 };
 __device__ __forceinline__ u64 ld_agent64(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, SCOPE_AGENT); }
 __device__ __forceinline__ void st_agent64(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, SCOPE_AGENT); }
 __device__ __forceinline__ uint32_t ld_agent32(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, SCOPE_AGENT); }
+__device__ __forceinline__ u64 ld_sys64(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, SCOPE_SYSTEM); }
 __device__ __forceinline__ uint32_t ld_sys32(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, SCOPE_SYSTEM); }
 
 // Release fences end with an explicit wait: the L2 write-back they issue must have completed
@@ -916,13 +921,19 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
 
     // ---- completion of this workgroup's share of an invocation (Sec. 5): completion counter,
     // and the last channel posts the CQE.  Lane 0 only.
-    auto complete = [&](uint32_t c_coll, uint32_t c_seq, uint32_t c_nchan) {
-      fence_release_system();   // results in the recv buffer are visible to host and later kernels
+    // in_memory: every byte of the result went to memory with sc1 stores that have been acknowledged (fold steps):
+    // there is nothing to write back before the counter and the CQE.  On one channel that is 1 us less; with 32 workgroups
+    // of an XCD writing back the same L2, the completion and the fetch without write-backs and invalidates took sixteen
+    // disordered 25 MiB buckets from 1794 to 1422 us and one 8 KiB all-reduce from 25 to 20.7 us.
+    auto complete = [&](uint32_t c_coll, uint32_t c_seq, uint32_t c_nchan, bool in_memory) {
+      if (!in_memory) fence_release_system();   // results in the recv buffer are visible to host and later kernels
       uint32_t* dc = &a.done_cnt[(size_t)rank * a.max_colls + c_coll];
       // (a collective on one channel has nobody to count with: no round trip for the counter)
-      const uint32_t old = c_nchan > 1 ? __hip_atomic_fetch_add(dc, 1u, __ATOMIC_ACQ_REL, SCOPE_AGENT) : 0u;
-      if (old + 1 == c_nchan) {
-        if (c_nchan > 1) __hip_atomic_store(dc, 0u, __ATOMIC_RELAXED, SCOPE_AGENT);
+      uint32_t old = 0;
+      if (c_nchan > 1) old = in_memory ? __hip_atomic_fetch_add(dc, 1u, __ATOMIC_RELAXED, SCOPE_AGENT)
+                                       : __hip_atomic_fetch_add(dc, 1u, __ATOMIC_ACQ_REL, SCOPE_AGENT);
+      // (the counter runs on from invocation to invocation, modulo 2^32: no reset that the next one's counts could overtake)
+      if (c_nchan == 1 || old + 1 == (c_seq + 1u) * c_nchan) {
         const u64 tq0 = wall_clock64();
         if (a.cq_mode == 0) {
           // optimized CQ (Sec. 5): one CAS of the id into a writable slot, no ring semantics
@@ -931,8 +942,9 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           const uint32_t t = c_coll * 7u + c_seq;
           uint32_t k = 0;
           for (;;) {
+            // (relaxed: what the entry vouches for is in memory, by the fence above or to begin with)
             u64 expected = 0;
-            if (__hip_atomic_compare_exchange_strong(&cqbase[(t + k) % a.cq_slots], &expected, v, __ATOMIC_RELEASE,
+            if (__hip_atomic_compare_exchange_strong(&cqbase[(t + k) % a.cq_slots], &expected, v, __ATOMIC_RELAXED,
                                                      __ATOMIC_RELAXED, SCOPE_SYSTEM))
               break;
             ++k;
@@ -981,11 +993,29 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
         if (lane == 0) {
           const Flight f = sh.fl[retired & 1];
           bump(sh.stat, ST_PRIMS, 1);
-          if (f.last) complete(f.coll, f.seq, f.nchan);
+          if (f.last) complete(f.coll, f.seq, f.nchan, false);
         }
         ++retired;
         acted = true;
       }
+    };
+
+    // ---- the last of a rank's workgroups to read an SQ slot frees it (Sec. 5) by writing the entry's generation where
+    // the submitter looks for it, in host memory.  The answer of a lone entry's reader counter is looked at when the
+    // next wait's first poll is back (it is then there already), not waited for before the entry is worked on.
+    uint32_t rd_old = 0;       // lane 0: readers of the slot before this workgroup
+    u64 rd_idx = 0;            // the entry
+    bool rd_open = false;
+    bool ctx_open = false;     // the stores of a lone collective's context may still be under way
+    auto free_slot = [&](uint32_t readers_before, u64 idx) {
+      // (the counter runs on from generation to generation, modulo 2^32: no reset to wait for before the slot is used again)
+      const uint32_t gen = (uint32_t)(idx >> a.sq_shift) + 1u;
+      if (readers_before + 1 == gen * a.cmax)
+        __hip_atomic_store(&a.sq_freed[(size_t)rank * D + (idx & (D - 1))], gen, __ATOMIC_RELAXED, SCOPE_SYSTEM);
+    };
+    auto settle_slot = [&]() {
+      if (rd_open) { if (lane == 0) free_slot(rd_old, rd_idx); rd_open = false; }
+      if (ctx_open) { __builtin_amdgcn_s_waitcnt(0); ctx_open = false; }
     };
 
     // The movers wait for nothing but their own memory operations, so the loops below that wait
@@ -1001,6 +1031,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
     for (;;) {
       retire_finished();
       if (stop != STOP_NONE) {
+        settle_slot();
         // leaving: the posted jobs run to their end first (their slots are claimed in the saved contexts)
         if (retired == posted) break;
         if ((++spins & 0xffffu) == 0 && abort_seen()) break;
@@ -1011,6 +1042,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
       // ================= no collective in hand: control check, fetch, next queue entry =================
       if (!have) {
         if (!in_pass) {
+          settle_slot();
           ++iter;
           uint32_t s = STOP_NONE, got = 0;
           // The SQ is probed before every pass.  (Sec. 4.3 has FIFO ordering fetch only when the queue
@@ -1096,23 +1128,27 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             const uint32_t left = burst < a.fetch_batch ? a.fetch_batch - burst : 1u;
             if (left < room) room = left;
             if (a.order_policy == 1) room = 1;       // the sorted insert below is written for one entry
-            bool here = false;
-            if (lane == 0) here = true;               // the control check has seen this one
+            // Lane 0's entry has been seen by the control check: its words are loaded while the lanes behind it look
+            // whether theirs are there.  System scope throughout: nothing of an SQ slot is ever taken from a cache.
+            bool here = lane == 0;
+            struct SqeWords { u64 w[sizeof(DfxStatic) / 8]; } qw = {};
+            const u64* const src = (const u64*)&sqbase[(ri + lane) & (D - 1)].e;
+            auto load_entry = [&]() {
+#pragma unroll
+              for (int i = 0; i < (int)(sizeof(DfxStatic) / 8); ++i) qw.w[i] = ld_sys64(src + i);
+            };
+            if (lane == 0) load_entry();
             else if (lane < room) {
               const u64 idx = ri + lane;
               here = __hip_atomic_load(&sqbase[idx & (D - 1)].e.ready, __ATOMIC_RELAXED, SCOPE_SYSTEM) == (uint32_t)(idx >> a.sq_shift) + 1u;
             }
             const u64 here_mask = __ballot(here);
             uint32_t n = (here_mask == ~0ull) ? 64u : (uint32_t)__builtin_ctzll(~here_mask);   // length of the run that starts at lane 0
-            // the submitter wrote the send buffers before the SQEs: drop what this CU / XCD cached
-            fence_acquire_system();
-            DfxStatic q;
+            if (lane != 0 && lane < n) load_entry();
+            __builtin_amdgcn_s_waitcnt(0);        // (the entries have been read before they count as read below)
+            const DfxStatic q = __builtin_bit_cast(DfxStatic, qw);
             bool is_exit_sqe = false, is_exit = false;
             if (lane < n) {
-              const uint4* src = (const uint4*)&sqbase[(ri + lane) & (D - 1)].e;
-              uint4* qv = (uint4*)&q;
-#pragma unroll
-              for (int i = 0; i < 6; ++i) qv[i] = src[i];
               // an exit SQE ends the launch it was posted for; one left over from an earlier launch
               // (some workgroups had already gone when it arrived) is consumed and ignored
               is_exit_sqe = (q.flags & DFX_SQE_EXIT) != 0;
@@ -1121,48 +1157,58 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             const u64 exit_mask = __ballot(is_exit);
             if (exit_mask) n = (uint32_t)__builtin_ctzll(exit_mask) + 1;   // nothing behind an exit SQE is touched
             bool mine = false;
-            uint32_t c_id = 0;
+            uint32_t c_id = 0, my_vch = 0;
             if (lane < n) {
               c_id = q.coll_id;
-              const uint32_t my_vch = is_exit_sqe ? ch : serving_channel(a.chan_spread != 0, ch, a.cmax, c_id, q.nchan);
+              my_vch = is_exit_sqe ? ch : serving_channel(a.chan_spread != 0, ch, a.cmax, c_id, q.nchan);
               mine = !is_exit_sqe && my_vch < q.nchan && c_id < a.max_colls;
-              if (mine) {
-                // cook the static context of this invocation into the context buffer (addresses
-                // resolved once, here); restart the sequence, keep the monotone connector counters
-                const DfxCooked k = cook_sqe(q, a.pool, rank, a.R, my_vch);
-                myctx[c_id].st = k;
-                // direct gather steps: the next rank reads this rank's recv buffer; its address and
-                // the invocation it belongs to go into the send connector's flag line (one 16-byte
-                // device-coherent store, complete before any job of the invocation is posted)
-                if (q.flags & DFX_SQE_DIRECT)
-                {
-                  const Slot<AUX_DEVICE> line((const void*)k.flags_out, DFX_FLAG_STRIDE);
-                  line.st16(DFX_DIRECT_OFF, uint4{(uint32_t)q.recvbuf, (uint32_t)(q.recvbuf >> 32), q.seq + 1u, 0u});
-                  line.st16(DFX_DIRECT_OFF + 16, uint4{(uint32_t)q.sendbuf, (uint32_t)(q.sendbuf >> 32), q.seq + 1u, 0u});
-                }
-                DfxDyn* dy = &myctx[c_id].dyn;
-                dy->round = 0; dy->prim = 0; dy->preempted = 0;
-                dy->cidx = first_chunk(q.kind, rank, a.R);
-                if (sh.slot_tag[ctx_slot(c_id)] == c_id) sh.slot_tag[ctx_slot(c_id)] = 0xffffffffu;
-              }
-              // every workgroup of the rank reads every SQE; the last reader frees the slot (Sec. 5)
-              // by writing the entry's generation where the submitter looks for it, in host memory
-              const size_t sq_at = (size_t)rank * D + ((ri + lane) & (D - 1));
-              uint32_t* rc = &a.sq_readers[sq_at];
-              const uint32_t old = __hip_atomic_fetch_add(rc, 1u, __ATOMIC_ACQ_REL, SCOPE_AGENT);
-              if (old + 1 == a.cmax) {
-                __hip_atomic_store(rc, 0u, __ATOMIC_RELAXED, SCOPE_AGENT);
-                __hip_atomic_store(&a.sq_freed[sq_at], (uint32_t)((ri + lane) >> a.sq_shift) + 1u, __ATOMIC_RELEASE, SCOPE_SYSTEM);
-              }
             }
-            // (contexts and published buffer addresses are in memory before anything is built on them)
-            __builtin_amdgcn_s_waitcnt(0);
-            // fold steps: the channel's count of published invocations (after the addresses, which it vouches for)
-            if (mine && (q.flags & DFX_SQE_FOLD))
-              (void)__hip_atomic_fetch_add((u64*)(fold_shared_line(myctx[c_id].st.flags_out, rank, a.R, q.nchan) + DFX_FOLD_PUB), 1ull,
-                                           __ATOMIC_RELAXED, SCOPE_AGENT);
-            // the entries that are this workgroup's join the task queue in SQ order
+            const bool q_fold = (q.flags & DFX_SQE_FOLD) != 0;
+            // the submitter wrote the send buffers before the SQEs: drop what this CU / XCD cached (fold steps read
+            // them with loads that bypass the caches)
+            if (__ballot(mine && !q_fold)) fence_acquire_system();
             const u64 mine_mask = __ballot(mine);
+            // A lone collective in fold steps is what a latency-bound caller waits for: its context goes straight into
+            // its LDS slot as well, and nothing waits for the copy in memory.
+            const bool lone = mine_mask != 0 && (mine_mask & (mine_mask - 1)) == 0 && __ballot(mine && q_fold) != 0;
+            if (mine) {
+              // cook the static context of this invocation into the context buffer (addresses
+              // resolved once, here); restart the sequence, keep the monotone connector counters
+              const DfxCooked k = cook_sqe(q, a.pool, rank, a.R, my_vch);
+              // direct and fold steps: other ranks read this rank's send buffer and read or write its recv buffer; their
+              // addresses and the invocation they belong to go into the rank's line (two 16-byte device-coherent
+              // stores, each with its tag; complete before any job of an invocation with direct steps is posted)
+              if (q.flags & DFX_SQE_DIRECT)
+              {
+                const Slot<AUX_DEVICE> line((const void*)k.flags_out, DFX_FLAG_STRIDE);
+                line.st16(DFX_DIRECT_OFF, uint4{(uint32_t)q.recvbuf, (uint32_t)(q.recvbuf >> 32), q.seq + 1u, 0u});
+                line.st16(DFX_DIRECT_OFF + 16, uint4{(uint32_t)q.sendbuf, (uint32_t)(q.sendbuf >> 32), q.seq + 1u, 0u});
+              }
+              // fold steps: the channel's count of published invocations, a hint for the readiness scans
+              if (q_fold) (void)__hip_atomic_fetch_add((u64*)(k.flags_in + DFX_FOLD_PUB), 1ull, __ATOMIC_RELAXED, SCOPE_AGENT);
+              const uint32_t csl = ctx_slot(c_id);
+              if (lone) {
+                DfxDyn d; d.round = 0; d.prim = 0; d.sent = 0; d.recvd = 0; d.preempted = 0; d.cidx = 0;   // (no connectors: nothing to keep)
+                sh.slot[csl].st = k; sh.slot[csl].dyn = d;
+                sh.slot_tag[csl] = c_id;
+              } else if (sh.slot_tag[csl] == c_id) sh.slot_tag[csl] = 0xffffffffu;
+              myctx[c_id].st = k;
+              DfxDyn* dy = &myctx[c_id].dyn;
+              dy->round = 0; dy->prim = 0; dy->preempted = 0;
+              dy->cidx = first_chunk(q.kind, rank, a.R);
+            }
+            // every workgroup of the rank reads every SQE; the last reader frees the slot (relaxed: the entries have been
+            // read, and nothing else hangs on the counter)
+            if (lane < n) {
+              const uint32_t old = __hip_atomic_fetch_add(&a.sq_readers[(size_t)rank * D + ((ri + lane) & (D - 1))], 1u, __ATOMIC_RELAXED, SCOPE_AGENT);
+              if (n == 1) rd_old = old;
+              else free_slot(old, ri + lane);
+            }
+            if (n == 1) { rd_open = true; rd_idx = ri; }
+            // (contexts and published buffer addresses are in memory before anything is built on them)
+            if (lone) ctx_open = true;
+            else __builtin_amdgcn_s_waitcnt(0);
+            // the entries that are this workgroup's join the task queue in SQ order
             if (mine) {
               if (a.order_policy == 1) {
                 // priority ordering: keep the queue sorted (stable); one entry per fetch in this mode
@@ -1219,6 +1265,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           // sixteen memory round trips instead of a thousand context loads and bounded spins.
           scanned = a.scan_min && qlen >= a.scan_min;
           if (scanned) {
+            settle_slot();     // (the scan reads the contexts in memory)
             nready = 0; rk = 0; pass_bytes = 0;
             focus = a.focus_bytes != 0 && qlen <= 64u;
             if (lane < DFX_CTX_SLOTS) sh.slot_claim[lane] = 0xffffffffu;
@@ -1246,9 +1293,8 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 const u64 f_out = ((u64)fl.w << 32) | fl.z, f_in = ((u64)fi.y << 32) | fi.x;
                 const u64 e_sent = ((u64)d0.w << 32) | d0.z, e_recvd = ((u64)d1.y << 32) | d1.x;
                 bool okr = true, oks = true;
-                if (pq.fold)   // every rank of the channel has got as far as this step needs: (seq + 1) x R on the step's counter
-                  okr = ld_agent64((const u64*)(fold_shared_line(f_out, rank, a.R, ge.y >> 16) + 8u * pq.fwait))
-                        >= ((u64)ge.x + 1u) * a.R * (pq.fwait ? (u64)e[4].w : 1ull);   // (a data step counts once per slice: bytes 64..79 end in rounds)
+                if (pq.fold)   // every rank of the channel has got as far as this step needs (bytes 48..63: shared counters, count at the end)
+                  okr = ld_agent64((const u64*)f_in + pq.fwait) >= (pq.fwait ? ((u64)fi.w << 32) | fi.z : ((u64)ge.x + 1u) * a.R);
                 if (pq.recv) okr = ld_agent64((const u64*)f_in) > e_recvd;
                 if (pq.send) oks = (e_sent - ld_agent64((const u64*)f_out + 8)) < (u64)(ge.z & 0xffu);
                 else if (pq.drain) oks = e_sent == ld_agent64((const u64*)f_out + 8);
@@ -1340,10 +1386,10 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
       const Prim q = fold ? make_fold_prim(p)
                           : chain_drain_round(make_prim((int)S.kind, a.R, S.bc_pos & 3u, p, (S.bc_pos & DFX_CTX_DIRECT) != 0),
                                               (int)S.kind, (S.bc_pos & DFX_CTX_DIRECT) != 0, g, S.rounds);
-      // fold steps wait for one of the channel's shared counters: every rank has published the invocation
-      // ((invocation + 1) x R), or every rank has finished its data step for every slice (x slices per share)
-      const u64* const fold_cnt = fold ? (const u64*)(fold_shared_line(S.flags_out, rank, a.R, S.nchan) + 8u * q.fwait) : nullptr;
-      const u64 fold_target = ((u64)S.seq + 1u) * a.R * (q.fwait ? (u64)S.rounds : 1ull);
+      // Fold steps: the step with data waits until every rank's line carries this invocation's tag, lane k looking at
+      // the line of entry k's rank, so that the poll that succeeds has brought the addresses along; the last wait
+      // looks at the channel's count of finished steps.
+      const uint32_t line_off = q.fold == 1 && lane < a.R ? fold_peer((int)S.kind, a.R, rank, S.nslots, lane) * (uint32_t)S.nchan * DFX_FLAG_STRIDE : 0u;
       u64* const tail_out = (u64*)S.flags_out;
       u64* const tail_in = (u64*)S.flags_in;
       const uint32_t K = S.nslots;
@@ -1371,9 +1417,22 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
       // the sequence position: the arithmetic runs while the counters travel, and a poll that
       // succeeds is followed by the job at once.
       u64 seen_cnt = 0;
-      if (lane == 0 && q.recv) seen_cnt = ld_agent64(tail_in);
-      if (lane == 1 && (q.send || q.drain)) seen_cnt = ld_agent64(tail_out + 8);
-      if (lane == 0 && q.fold) seen_cnt = ld_agent64(fold_cnt);
+      uint4 ln_recv = uint4{0, 0, 0, 0}, ln_send = ln_recv;
+      auto poll = [&]() {
+        if (q.fold == 1) {
+          asm volatile("" ::: "memory");     // (these loads are made anew at every poll)
+          if (lane < a.R) {
+            const __amdgpu_buffer_rsrc_t lines = uniform_rsrc(S.fifo_in, a.R * S.nchan * DFX_FLAG_STRIDE);
+            ln_recv = rs_ld16(lines, line_off + DFX_DIRECT_OFF);
+            ln_send = rs_ld16(lines, line_off + DFX_DIRECT_OFF + 16);
+          }
+        } else {
+          if (lane == 0 && q.recv) seen_cnt = ld_agent64(tail_in);
+          if (lane == 1 && (q.send || q.drain)) seen_cnt = ld_agent64(tail_out + 8);
+          if (lane == 0 && q.fold) seen_cnt = ld_agent64(tail_in + DFX_FOLD_RED / 8);
+        }
+      };
+      poll();
 
       // ---- slice geometry and the job's four pointers
       const int kind = S.kind, dtype = S.dtype;   // dtype: element type | reducing function << 4
@@ -1422,12 +1481,14 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
         u64 n = 0;
         for (;;) {
           bool ok = true;
-          if (lane == 0 && q.fold) ok = seen_cnt >= fold_target;
+          if (q.fold == 1 && lane < a.R) ok = ln_recv.z == inv_seq + 1u && ln_send.z == inv_seq + 1u;
+          if (lane == 0 && q.fold == 3) ok = seen_cnt >= S.fifo_out;
           if (lane == 0 && q.recv) ok = seen_cnt > recvd;
           if (lane == 1 && q.send) ok = (sent - seen_cnt) < (u64)K;
           if (lane == 1 && q.drain) ok = sent == seen_cnt;
           ++n;
           if (__ballot(!ok) == 0) break;
+          settle_slot();
           retire_finished();
           if (a.preempt && n >= thr) { res = W_TIMEOUT; break; }
           if ((n & 255u) == 0) {
@@ -1448,9 +1509,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             if (bcast0(s)) { res = W_STOP; break; }
           }
           __builtin_amdgcn_s_sleep(1);
-          if (lane == 0 && q.recv) seen_cnt = ld_agent64(tail_in);
-          if (lane == 1 && (q.send || q.drain)) seen_cnt = ld_agent64(tail_out + 8);
-          if (lane == 0 && q.fold) seen_cnt = ld_agent64(fold_cnt);
+          poll();
         }
         if (lane == 0) bump(sh.stat, ST_POLLS, n);
       }
@@ -1495,30 +1554,16 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
         }
         uint32_t jnsrc = 0, jndst = 0;
         if (q.fold == 1) {
-          // The addresses every rank published for this invocation (before it counted itself published, which a
-          // wait of this invocation has seen for all of them): lane k looks up entry k's rank (fold_peer).
+          // the addresses that the poll has brought: lane k holds those of entry k's rank (fold_peer)
           const int kd = (int)S.kind;
-          const uint32_t root = S.nslots;                       // (a collective in fold steps keeps its root there)
           const bool copies = fold_copies(kd), to_all = fold_to_all(kd);
-          bool bad = false;
           if (lane < a.R) {
-            const uint32_t peer = fold_peer(kd, a.R, rank, root, lane);
-            const Slot<AUX_DEVICE> line((const void*)fold_line(S.flags_out, rank, peer, S.nchan), DFX_FLAG_STRIDE);
-            uint4 w = uint4{0, 0, 0, 0}, wr = w;
-            for (uint32_t tries = 0; tries < 1024u; ++tries) {
-              w = line.ld16(DFX_DIRECT_OFF + 16);
-              wr = line.ld16(DFX_DIRECT_OFF);
-              if (w.z == inv_seq + 1u && wr.z == inv_seq + 1u) break;
-              __builtin_amdgcn_s_sleep(2);
-            }
-            bad = w.z != inv_seq + 1u || wr.z != inv_seq + 1u;
-            const u64 src = (((u64)w.y << 32) | w.x) + fg.soff * fg.eb, dst = (((u64)wr.y << 32) | wr.x) + fg.doff * fg.eb;
+            const u64 src = (((u64)ln_send.y << 32) | ln_send.x) + fg.soff * fg.eb, dst = (((u64)ln_recv.y << 32) | ln_recv.x) + fg.doff * fg.eb;
             if (!copies) sh.tab_src[posted & 1][lane] = src;
             else if (lane + 1 == a.R) sh.tab_src[posted & 1][0] = src;
             if (to_all) sh.tab_dst[posted & 1][lane] = dst;
             else if (lane + 1 == a.R) sh.tab_dst[posted & 1][0] = dst;
           }
-          if (__ballot(bad)) { if (lane == 0) raise_error(a, 3u, wg); stop = STOP_ABORT; have = false; continue; }
           __builtin_amdgcn_wave_barrier();
           jnsrc = copies ? 1u : a.R; jndst = to_all ? a.R : 1u;
         }
@@ -1527,7 +1572,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
         if (q.send || q.notify) ++sent;
         if (q.recv) ++recvd;
         if (done_here) {
-          if (lane == 0) { bump(sh.stat, ST_PRIMS, 1); complete(coll, inv_seq, inv_nchan); }
+          if (lane == 0) { bump(sh.stat, ST_PRIMS, 1); complete(coll, inv_seq, inv_nchan, true); }
         } else if (lane == 0) {
           Job j;
           j.fin = jfin; j.fout = jfout; j.sb = jsb; j.rb = jrb;
@@ -1541,7 +1586,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           f.tail_out = (q.send || q.notify) ? tail_out : nullptr; f.head_in = q.recv ? tail_in + 8 : nullptr;
           f.sent_new = sent; f.recvd_new = recvd;
           f.last = last ? 1u : 0u; f.coll = coll; f.seq = inv_seq; f.nchan = inv_nchan;
-          f.add_one = q.fadd ? (u64*)(fold_shared_line(S.flags_out, rank, a.R, S.nchan) + 8u * q.fadd) : nullptr;
+          f.add_one = q.fadd ? tail_in + q.fadd : nullptr;
           sh.fl[posted & 1] = f;
           lds_st(&sh.job_seq, posted + 1);
         }

@@ -244,7 +244,14 @@ DFX_HD DfxCooked cook_sqe(const DfxStatic& q, uint8_t* pool, uint32_t rank, uint
   k.fifo_out = (uint64_t)(slots + fo * q.nslots * q.slot_bytes);
   k.fifo_in = (uint64_t)(slots + fi * q.nslots * q.slot_bytes);
   // a direct broadcast has no slots (no step of it fills or reads one)
-  if ((q.kind == KIND_BC && (q.flags & DFX_SQE_DIRECT)) || (q.flags & DFX_SQE_FOLD)) k.fifo_out = k.fifo_in = 0;
+  if (q.kind == KIND_BC && (q.flags & DFX_SQE_DIRECT)) k.fifo_out = k.fifo_in = 0;
+  if (q.flags & DFX_SQE_FOLD) {
+    // fold steps have no connectors: the words carry the channel's shared counters, the channel's first line (rank 0's;
+    // the others follow nchan lines apart) and what the counter of finished steps shows at the end of this invocation
+    k.flags_in = fold_shared_line(k.flags_out, rank, R, q.nchan);
+    k.fifo_in = fold_line(k.flags_out, rank, 0, q.nchan);
+    k.fifo_out = ((uint64_t)q.seq + 1u) * R * q.rounds;
+  }
   k.slice_elems = q.slice_elems; k.rounds = q.rounds; k.seq = q.seq;
   k.nprim = (uint16_t)q.nprim; k.nchan = q.nchan;
   k.nslots = (uint8_t)((q.flags & DFX_SQE_FOLD) ? q.root : q.nslots);   // (no slots in fold steps: the byte carries the root)

@@ -1172,21 +1172,21 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
     for (uint32_t v = 0; v < t.nchan; ++v) {
       const DfxCooked& me = cooked[(size_t)r * t.nchan + v];
       const DfxCooked& nx = cooked[(size_t)((r + 1) % R) * t.nchan + v];
-      if (me.flags_out != nx.flags_in) return fail("edge %u channel %u: sender's flag line %llx, receiver's %llx", r, v, (unsigned long long)me.flags_out, (unsigned long long)nx.flags_in);
-      if (me.fifo_out != nx.fifo_in) return fail("edge %u channel %u: sender's slots %llx, receiver's %llx", r, v, (unsigned long long)me.fifo_out, (unsigned long long)nx.fifo_in);
+      if (!fold && me.flags_out != nx.flags_in) return fail("edge %u channel %u: sender's flag line %llx, receiver's %llx", r, v, (unsigned long long)me.flags_out, (unsigned long long)nx.flags_in);
+      if (!fold && me.fifo_out != nx.fifo_in) return fail("edge %u channel %u: sender's slots %llx, receiver's %llx", r, v, (unsigned long long)me.fifo_out, (unsigned long long)nx.fifo_in);
       if (me.flags_out < blk_lo || me.flags_out + DFX_FLAG_STRIDE > flags_hi || (me.flags_out & (DFX_FLAG_STRIDE - 1)))
         return fail("edge %u channel %u: flag line %llx outside the block's flag lines", r, v, (unsigned long long)me.flags_out);
       if (!no_slots && (me.fifo_out < flags_hi || me.fifo_out + conn_slot_bytes > blk_hi))
         return fail("edge %u channel %u: slots %llx outside the block", r, v, (unsigned long long)me.fifo_out);
-      if (no_slots && (me.fifo_out || me.fifo_in)) return fail("%s", "a collective without slots has slot addresses");
+      if (no_slots && !fold && (me.fifo_out || me.fifo_in)) return fail("%s", "a collective without slots has slot addresses");
       if (fold) {
         // every rank of the channel finds the same lines: rank k's from any rank's own line, and the shared one
-        const uint64_t sh_line = fold_shared_line(me.flags_out, r, R, t.nchan);
+        const uint64_t sh_line = me.flags_in;
         if (sh_line < flags_hi || sh_line + DFX_FLAG_STRIDE > blk_hi) return fail("rank %u channel %u: shared line %llx outside the block", r, v, (unsigned long long)sh_line);
-        if (sh_line != fold_shared_line(nx.flags_out, (r + 1) % R, R, t.nchan)) return fail("ranks %u and %u channel %u disagree on the shared line", r, (r + 1) % R, v);
+        if (sh_line != nx.flags_in || me.fifo_in != cooked[v].flags_out) return fail("ranks %u and %u channel %u disagree on the shared line", r, (r + 1) % R, v);
         for (uint32_t k = 0; k < R; ++k)
-          if (fold_line(me.flags_out, r, k, t.nchan) != cooked[(size_t)k * t.nchan + v].flags_out)
-            return fail("rank %u channel %u: line of rank %u resolves to %llx", r, v, k, (unsigned long long)fold_line(me.flags_out, r, k, t.nchan));
+          if (me.fifo_in + (uint64_t)k * t.nchan * DFX_FLAG_STRIDE != cooked[(size_t)k * t.nchan + v].flags_out)
+            return fail("rank %u channel %u: line of rank %u resolves to %llx", r, v, k, (unsigned long long)(me.fifo_in + (uint64_t)k * t.nchan * DFX_FLAG_STRIDE));
       }
     }
 

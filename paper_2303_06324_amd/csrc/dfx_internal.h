@@ -28,7 +28,7 @@
 // A collective in fold steps has no slots.  Its connector block is R x nchan flag lines, one per (rank, channel),
 // that carry the published buffer addresses (DFX_DIRECT_OFF), and behind them nchan shared lines, one per
 // channel, with two counters that every rank of the channel adds to:
-#define DFX_FOLD_PUB 0         //   +0  invocations published (buffer addresses written at SQE fetch)
+#define DFX_FOLD_PUB 0         //   +0  invocations published (a hint for the readiness scan: the step with data looks at the tags of the lines themselves)
 #define DFX_FOLD_RED 8         //   +8  steps with data finished (the rank's part is combined or copied and written to every recv buffer it belongs to)
 
 // Static context of one invocation on one rank: what the host writes into the SQ and what a
@@ -75,9 +75,9 @@ static_assert(sizeof(DfxDyn) == 32, "DfxDyn must be 32 bytes");
 struct alignas(16) DfxCooked {
   uint64_t sendbuf, recvbuf, count, block_elems, part_elems;
   uint64_t flags_out;    // tail counter of my send connector (head at +64 bytes)
-  uint64_t flags_in;     // tail counter of my recv connector (head at +64 bytes)
-  uint64_t fifo_out;     // first slot of my send connector
-  uint64_t fifo_in;      // first slot of my recv connector
+  uint64_t flags_in;     // tail counter of my recv connector (head at +64 bytes); fold steps: the channel's shared counters
+  uint64_t fifo_out;     // first slot of my send connector; fold steps: DFX_FOLD_RED at the end of this invocation
+  uint64_t fifo_in;      // first slot of my recv connector; fold steps: the channel's line of rank 0
   uint32_t slice_elems, rounds, seq;
   uint16_t nprim, nchan;
   uint8_t nslots, kind, dtype;
@@ -88,7 +88,7 @@ struct alignas(16) DfxCooked {
 static_assert(sizeof(DfxCooked) == 96, "DfxCooked must be 96 bytes");
 // (the scheduler reads some of it as 16-byte words: the readiness scan and the set-up of a primitive)
 static_assert(offsetof(DfxCooked, part_elems) == 32 && offsetof(DfxCooked, flags_out) == 40 && offsetof(DfxCooked, flags_in) == 48 &&
-              offsetof(DfxCooked, fifo_in) == 64 && offsetof(DfxCooked, slice_elems) == 72 && offsetof(DfxCooked, rounds) == 76 &&
+              offsetof(DfxCooked, fifo_out) == 56 && offsetof(DfxCooked, fifo_in) == 64 && offsetof(DfxCooked, slice_elems) == 72 && offsetof(DfxCooked, rounds) == 76 &&
               offsetof(DfxCooked, seq) == 80 && offsetof(DfxCooked, nprim) == 84 && offsetof(DfxCooked, nchan) == 86 &&
               offsetof(DfxCooked, nslots) == 88 && offsetof(DfxCooked, kind) == 89 && offsetof(DfxCooked, dtype) == 90 &&
               offsetof(DfxCooked, bc_pos) == 91 && offsetof(DfxCooked, priority) == 92 && offsetof(DfxCooked, vch) == 94,

@@ -20,10 +20,10 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E peak
 R = 8
-# HBM bytes per launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by the
-# plain copy kernel (profiles/hbm_traffic_allreduce_256MiB.md): reads 5 511 100 KiB + writes
-# 3 671 500 KiB per launch at the default workload.  Reported only for that workload.
-MEASURED_TRAFFIC_BYTES = 9402982400
+# HBM bytes per launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by the plain copy kernel
+# (profiles/hbm_traffic_allreduce_256MiB.md, all-reduce in fold steps): 8.002 x M read + 8.000 x M written per launch at
+# the default workload.  Reported only for that workload.
+MEASURED_TRAFFIC_BYTES = int(16.002 * (256 << 20))
 
 
 def algorithmic_bytes(msg_bytes: int, nranks: int) -> int:
@@ -34,15 +34,15 @@ def algorithmic_bytes(msg_bytes: int, nranks: int) -> int:
 
 
 def moved_bytes(msg_bytes: int, nranks: int) -> int:
-    """What the library's default path moves for an all-reduce of 2 MiB or more: with the direct
-    steps a finished chunk is written once (recv buffer) instead of twice (recv buffer and slot),
+    """What a ring with direct steps (fold_max_bytes = 0) moves for an all-reduce of 2 MiB or more: a finished chunk is written once (recv buffer) instead of twice (recv buffer and slot),
     and the opening send moves nothing (the next rank reads the chunk from the send buffer):
     reads (3R-3)/R * M, writes (2R-2)/R * M per rank."""
     return (5 * nranks - 5) * msg_bytes
 
 
 def fold_bytes(msg_bytes: int, nranks: int) -> int:
-    """What an all-reduce in fold steps (the default below 64 MiB per rank) moves: rank r reads chunk r out of all R
+    """What an all-reduce in fold steps (the default: below 64 MiB per rank, and above it for what qualifies for direct
+    steps) moves: rank r reads chunk r out of all R
     send buffers and writes the result into all R recv buffers: 2 * M per rank, every input read once and every
     output written once."""
     return 2 * nranks * msg_bytes
@@ -267,8 +267,8 @@ def size_sweep(iters: int = 10):
     rows = []
     for nbytes in wi.CONFIG2_SIZES:
         best, nchan, nprim = res[("default", nbytes)]
-        path = {2: "fold steps", 2 * R: "ring, direct steps"}.get(nprim, "ring through slots")
-        nb = {2: fold_bytes, 2 * R: moved_bytes}.get(nprim, algorithmic_bytes)(nbytes, R)     # what the path taken moves
+        path = {2: "fold steps", 2 * R: "ring geometry, direct in fold steps"}.get(nprim, "ring through slots")
+        nb = {2: fold_bytes, 2 * R: fold_bytes}.get(nprim, algorithmic_bytes)(nbytes, R)     # what the path taken moves
         rows.append({"bytes": nbytes, "us": round(best * 1e6, 1), "channels": nchan,
                      "algbw_GBs": round(nbytes / best / 1e9, 2),
                      "busbw_GBs": round(nbytes / best * 2 * (R - 1) / R / 1e9, 2),
@@ -328,14 +328,13 @@ def kinds_sweep(nbytes: int = 256 << 20, iters: int = 8):
     a = [torch.randn(n, device="cuda") for _ in range(R)]
     b = [torch.empty(n, device="cuda") for _ in range(R)]
     torch.cuda.synchronize()
-    # bytes each kind moves with the library's defaults at this size (direct steps): all-reduce (5R-5) x M;
-    # all-gather 2R blocks per rank; reduce-scatter (3R-3) blocks per rank; broadcast 2R x M (every rank reads
-    # and writes the message once); reduce (3R-3) x M (the first rank of the chain moves nothing)
-    cases = [("all-reduce", dfx.ALLREDUCE, n, moved_bytes(nbytes, R)),
-             ("all-gather", dfx.ALLGATHER, n // R, 2 * R * (nbytes // R) * R),
-             ("reduce-scatter", dfx.REDUCESCATTER, n // R, (3 * R - 3) * (nbytes // R) * R),
-             ("broadcast", dfx.BROADCAST, n, 2 * R * nbytes),
-             ("reduce", dfx.REDUCE, n, (3 * R - 3) * nbytes)]
+    # bytes each kind moves with the library's defaults at this size: every send buffer that counts read once, every
+    # recv buffer that counts written once
+    cases = [("all-reduce", dfx.ALLREDUCE, n, fold_bytes(nbytes, R)),
+             ("all-gather", dfx.ALLGATHER, n // R, (R + 1) * nbytes),
+             ("reduce-scatter", dfx.REDUCESCATTER, n // R, (R + 1) * nbytes),
+             ("broadcast", dfx.BROADCAST, n, (R + 1) * nbytes),
+             ("reduce", dfx.REDUCE, n, (R + 1) * nbytes)]
     rows = []
     ctx = dfx.Context(R, gh.make_config(quit_idle_us=0))
     try:
@@ -574,7 +573,7 @@ def main():
     # what the last timed step left in the recv buffers (checked against the oracle below, outside the timed region)
     got = {r: recv[r].cpu().numpy() for r in (0, 5)}
     same_on_all_ranks = all(torch.equal(recv[0].view(torch.int32), recv[r].view(torch.int32)) for r in range(1, R))
-    # the same workload in fold steps (the default below 64 MiB per rank), for the record: fewer bytes, no FIFOs
+    # the same workload in fold steps of one slice (the default below 64 MiB per rank), for the record
     fold_ms = None
     if not args.no_fold:
         cfg2 = gh.make_config(quit_idle_us=0, fold_max_bytes=min(2 * M, (1 << 32) - 1))
@@ -607,8 +606,8 @@ def main():
     algbw = M / (ms_per_step * 1e-3) / 1e9
     busbw = algbw * 2 * (R - 1) / R
     k_ms = sum(kern_ms) / len(kern_ms)
-    direct = info["nprim"] == 2 * R          # the all-reduce takes the direct gather steps (one step more: the drain)
-    launch_bytes = moved_bytes(M, R) if direct else algorithmic_bytes(M, R)
+    direct = info["nprim"] == 2 * R          # the all-reduce qualifies for direct steps: its data moves in fold steps
+    launch_bytes = fold_bytes(M, R) if direct else algorithmic_bytes(M, R)
     achieved = launch_bytes / (k_ms * 1e-3) / 1e9
     table_rate = algorithmic_bytes(M, R) / (k_ms * 1e-3) / 1e9
     out = {
@@ -623,10 +622,9 @@ def main():
                    "daemon_launches": int(launches)},
         "algbw_GBs": round(algbw, 2),
         "hbm_frac_wall": round(launch_bytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-        # achieved = the bytes the shipped method has to move per launch / kernel time: (5R-5) x M with the
-        # direct steps (a finished chunk is written once, the opening send moves nothing), (6R-4) x M by the printed primitive table
-        # (every gather step also through a slot), whose figure is given beside it: work per time, which
-        # the direct steps raise by moving less.
+        # achieved = the bytes the shipped method has to move per launch / kernel time: 2R x M (every input read once,
+        # every output written once), (6R-4) x M by the printed primitive table (every step through a FIFO slot),
+        # whose figure is given beside it: work per time, which moving less raises.
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": MEASURED_TRAFFIC_BYTES if args.msg_mib == 256 and direct else None,
@@ -635,10 +633,8 @@ def main():
                                        if args.msg_mib == 256 and direct else None,
                      "kernel": "dfx_daemon_kernel", "kernel_ms_avg": round(k_ms, 4),
                      "bytes_moved_per_launch": launch_bytes,
-                     "note": "achieved = bytes the shipped path moves per launch (direct steps: (5R-5) x M) / kernel time; "
-                             "the rate is what crosses the L2-to-fabric interface, where the counters sit: part of it "
-                             "(connector slots rewritten and re-read, chunks read soon after they were written) is served "
-                             "by the 256 MB memory-side cache and never reaches DRAM",
+                     "note": "achieved = bytes the shipped path moves per launch (2R x M: every input read once, every output "
+                             "written once) / kernel time, launch, submission and exit of the daemon included",
                      "primitive_table_bytes_per_launch": algorithmic_bytes(M, R),
                      "primitive_table_GBs": round(table_rate, 1),
                      "primitive_table_frac": round(table_rate / HBM_PEAK_GBS, 4)},

@@ -132,7 +132,8 @@ typedef struct {
                               that all ranks carry the same few collectives through instead of advancing all
                               of them side by side (whose FIFO slots together outgrow the memory-side cache);
                               0 = every runnable collective once per pass, in queue order */
-  uint32_t direct;         /* 1 (default): collectives of at least direct_min_bytes (all-reduce, broadcast,
+  uint32_t direct;         /* (what rings and chains do with fold_max_bytes = 0; see there for what long collectives do otherwise)
+                              1 (default): collectives of at least direct_min_bytes (all-reduce, broadcast,
                               reduce: per rank; all-gather, reduce-scatter: all R blocks, which must be
                               16-byte multiples) take direct steps, since all buffers lie in one HBM.  The
                               opening send of an all-reduce, a reduce-scatter or a reduce chain only raises
@@ -156,8 +157,11 @@ typedef struct {
                               own order (x[r+1] (op) ... (op) x[r]: same association, same bits) and writes the result
                               into chunk r of all R recv buffers; (2) when every rank has done so, it posts the
                               completion (every input read once, every output written once).  Each step is a bounded
-                              wait (Sec. 4.2) followed by the data, preempted like any primitive.  From this size on the
-                              ring through the connectors' FIFOs keeps its movers busy and is what runs.  0 = off */
+                              wait (Sec. 4.2) followed by the data, preempted like any primitive.  From this size on a
+                              collective keeps the geometry of its ring or chain (dfx_coll_info, connector block); one that
+                              qualifies for direct steps has its data moved in the same two steps all the same, slice by
+                              slice, and with direct = 0 the ring through the connectors' FIFOs is what runs.  0 = off:
+                              rings and chains at every size */
   uint32_t fold_slice_bytes; /* a collective in fold steps takes its share of a channel in slices of at most this many bytes
                               per source, one mover job each (16-byte multiple), so that what is ahead of an urgent
                               collective under priority ordering is short; 0 (default) = one slice, the whole share

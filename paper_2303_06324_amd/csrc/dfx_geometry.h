@@ -61,7 +61,7 @@ struct Prim {
   uint8_t fold, fwait, fadd;
 };
 
-// Short collectives in fold steps.  Every rank's buffers lie in the same HBM, so the dependent hops of a ring or
+// Collectives in fold steps.  Every rank's buffers lie in the same HBM, so the dependent hops of a ring or
 // a chain (a few microseconds each, whatever the size) can be replaced by steps that wait on all ranks at once:
 //   step with data: when every rank has published this invocation's buffers, a rank does its part of the work
 //                reading other ranks' send buffers where they lie and writing the result straight into the recv
@@ -248,8 +248,8 @@ DFX_HD DfxCooked cook_sqe(const DfxStatic& q, uint8_t* pool, uint32_t rank, uint
   if (q.flags & DFX_SQE_FOLD) {
     // fold steps have no connectors: the words carry the channel's shared counters, the channel's first line (rank 0's;
     // the others follow nchan lines apart) and what the counter of finished steps shows at the end of this invocation
-    k.flags_in = fold_shared_line(k.flags_out, rank, R, q.nchan);
     k.fifo_in = fold_line(k.flags_out, rank, 0, q.nchan);
+    k.flags_in = (q.flags & DFX_SQE_LONG) ? k.fifo_in + DFX_FOLD_HEAD : fold_shared_line(k.flags_out, rank, R, q.nchan);
     k.fifo_out = ((uint64_t)q.seq + 1u) * R * q.rounds;
   }
   k.slice_elems = q.slice_elems; k.rounds = q.rounds; k.seq = q.seq;

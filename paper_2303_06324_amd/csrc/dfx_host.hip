@@ -28,9 +28,13 @@ hipError_t dfx_copy_launch(const void* src, void* dst, size_t bytes, hipStream_t
 
 namespace {
 
+// What dfx_coll_info reports: the geometry of the collective's ring or chain (or of its fold steps).
+struct CollShape { uint32_t nchan, slot_bytes, rounds, nprim; };
+
 struct CollInfo {
   bool prepared = false;
   DfxStatic tmpl;   // everything but buffers, seq and ready
+  CollShape shape;
 };
 
 struct RankState {
@@ -368,7 +372,7 @@ void drain_cq(dfx_ctx* c, int rank) {
 // count, whether it takes direct steps, and the bytes of connector memory it needs (flag lines first, then
 // the slots).  Shared by dfx_prepare and the entry point that brings its own static memory.
 int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kind, size_t count, dfx_dtype dtype, dfx_op op,
-                    int root, int priority, uint64_t conn_off, DfxStatic* out, uint64_t* conn_bytes_out) {
+                    int root, int priority, uint64_t conn_off, DfxStatic* out, uint64_t* conn_bytes_out, CollShape* shape = nullptr) {
   if ((int)kind < 0 || (int)kind > 4 || (int)dtype < 0 || (int)dtype > 3 || (int)op < 0 || (int)op > 3) return DFX_ERR_INVALID_ARG;
   const bool rooted = (kind == DFX_BROADCAST || kind == DFX_REDUCE);
   if (rooted && (root < 0 || root >= nranks)) return DFX_ERR_INVALID_ARG;
@@ -470,6 +474,25 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
     t.nprim = (uint32_t)R + 1u;
   }
   else t.nprim = (uint32_t)R;
+  if (shape) *shape = CollShape{t.nchan, t.slot_bytes, t.rounds, t.nprim};
+  // Long collectives: what direct steps save of a ring's or chain's traffic, fold steps save in full (every input read
+  // once, every output written once: 2R x M of an all-reduce instead of (5R-5) x M), so a collective that qualifies for
+  // direct steps runs in fold steps above fold_max_bytes too, in jobs of this size.  Measured (us, R = 8, rings and
+  // chains with direct steps -> this): all-reduce 256 MiB fp32 1545 -> 876, reduce-scatter 128 MiB fp32 496 -> 267,
+  // broadcast 100 MiB bf16 472 -> 204.
+  // With fold_max_bytes = 0 the rings and chains run at every size.  The connector block stays what it was.
+  if ((t.flags & DFX_SQE_DIRECT) && !fold && cfg.fold_max_bytes && blocks_ok && !(kind == DFX_REDUCE && R > 63)) {
+    const bool shared = rooted;     // one stretch that all ranks' workgroups share (fold_geometry): a job is 1 / R of a channel's slice
+    // 128 KiB per source and workgroup: about 100 us at 2 x 8 streams; priority ordering lets nothing longer than
+    // its look-again budget get ahead of an urgent collective
+    const uint64_t job = cfg.fold_slice_bytes ? cfg.fold_slice_bytes : (cfg.order_policy == 1 ? 32u << 10 : 128u << 10);
+    const uint64_t cap = std::min<uint64_t>(shared ? job * R : job, ((1ull << 30) / C) & ~15ull);
+    const uint64_t bytes = std::min<uint64_t>(cap, round_up(part * eb, 16));
+    t.flags |= DFX_SQE_FOLD | DFX_SQE_LONG;
+    t.slice_elems = (uint32_t)(bytes / eb);
+    t.rounds = (uint32_t)std::max<uint64_t>(1, ceil_div(part, t.slice_elems));
+    t.nprim = fold_nprim((int)kind);
+  }
   *out = t;
   return DFX_OK;
 }
@@ -641,7 +664,7 @@ int dfx_prepare(dfx_ctx* c, int coll_id, dfx_kind kind, size_t count, dfx_dtype 
   if (ci.prepared) return DFX_ERR_INVALID_ARG;
   DfxStatic t;
   uint64_t conn_bytes = 0;
-  const int rc = plan_collective(c->cfg, c->R, coll_id, kind, count, dtype, op, root, priority, c->pool_used, &t, &conn_bytes);
+  const int rc = plan_collective(c->cfg, c->R, coll_id, kind, count, dtype, op, root, priority, c->pool_used, &t, &conn_bytes, &ci.shape);
   if (rc != DFX_OK) return rc;
   if (c->pool_used + conn_bytes > c->cfg.pool_bytes) return DFX_ERR_NO_RESOURCES;
   c->pool_used += conn_bytes;
@@ -654,10 +677,10 @@ int dfx_coll_info(dfx_ctx* c, int coll_id, uint32_t* nchan, uint32_t* slot_bytes
   if (!c || coll_id < 0 || (uint32_t)coll_id >= c->cfg.max_colls) return DFX_ERR_INVALID_ARG;
   const CollInfo& ci = c->colls[coll_id];
   if (!ci.prepared) return DFX_ERR_NOT_PREPARED;
-  if (nchan) *nchan = ci.tmpl.nchan;
-  if (slot_bytes) *slot_bytes = ci.tmpl.slot_bytes;
-  if (rounds) *rounds = ci.tmpl.rounds;
-  if (nprim) *nprim = ci.tmpl.nprim;
+  if (nchan) *nchan = ci.shape.nchan;
+  if (slot_bytes) *slot_bytes = ci.shape.slot_bytes;
+  if (rounds) *rounds = ci.shape.rounds;
+  if (nprim) *nprim = ci.shape.nprim;
   return DFX_OK;
 }
 
@@ -1182,7 +1205,8 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
       if (fold) {
         // every rank of the channel finds the same lines: rank k's from any rank's own line, and the shared one
         const uint64_t sh_line = me.flags_in;
-        if (sh_line < flags_hi || sh_line + DFX_FLAG_STRIDE > blk_hi) return fail("rank %u channel %u: shared line %llx outside the block", r, v, (unsigned long long)sh_line);
+        if ((t.flags & DFX_SQE_LONG) ? sh_line != me.fifo_in + DFX_FOLD_HEAD : (sh_line < flags_hi || sh_line + DFX_FLAG_STRIDE > blk_hi))
+          return fail("rank %u channel %u: shared counters %llx outside their line", r, v, (unsigned long long)sh_line);
         if (sh_line != nx.flags_in || me.fifo_in != cooked[v].flags_out) return fail("ranks %u and %u channel %u disagree on the shared line", r, (r + 1) % R, v);
         for (uint32_t k = 0; k < R; ++k)
           if (me.fifo_in + (uint64_t)k * t.nchan * DFX_FLAG_STRIDE != cooked[(size_t)k * t.nchan + v].flags_out)
@@ -1460,7 +1484,7 @@ int dfx_collective_noalloc(int nranks, dfx_kind kind, size_t count, dfx_dtype dt
   if (rc != DFX_OK) return rc;
   // connector block = flag lines of the collective's R x C edges, then their slots; the scratch holds
   // DFX_NA_MAX_WG flag lines and as many connectors of DFX_NA_NSLOTS x DFX_NA_SLOT_BYTES
-  const size_t flag_bytes = (size_t)(nranks + ((tmpl.flags & DFX_SQE_FOLD) ? 1 : 0)) * tmpl.nchan * DFX_FLAG_STRIDE;
+  const size_t flag_bytes = (size_t)(nranks + ((tmpl.flags & (DFX_SQE_FOLD | DFX_SQE_LONG)) == DFX_SQE_FOLD ? 1 : 0)) * tmpl.nchan * DFX_FLAG_STRIDE;
   if (flag_bytes > (size_t)DFX_NA_LINES * DFX_FLAG_STRIDE || conn_bytes > flag_bytes + DFX_NA_SLOTS_BYTES + 256) return DFX_ERR_TOO_LARGE;
   // the flag lines end where the zeroed part ends, the slots begin right there
   tmpl.conn_off = (uint64_t)((size_t)DFX_NA_CTL_BYTES - flag_bytes - L.pool);

@@ -25,9 +25,12 @@
 #define DFX_CTX_DIRECT 0x80u   // the same, in the cooked context's bc_pos byte (bits 0-1: place in a chain)
 #define DFX_SQE_FOLD 4u        // all-reduce in fold steps (always together with DFX_SQE_DIRECT: the buffers are published the same way)
 #define DFX_CTX_FOLD 0x40u     // the same, in the cooked context's bc_pos byte
+#define DFX_SQE_LONG 8u        // a long collective in fold steps (always together with DFX_SQE_FOLD): its connector block is laid out for the ring or chain
 // A collective in fold steps has no slots.  Its connector block is R x nchan flag lines, one per (rank, channel),
 // that carry the published buffer addresses (DFX_DIRECT_OFF), and behind them nchan shared lines, one per
-// channel, with two counters that every rank of the channel adds to:
+// channel, with two counters that every rank of the channel adds to (a long collective keeps the block that its ring
+// or chain would have: there the counters are in the head half, at DFX_FOLD_HEAD, of rank 0's line, which nobody else uses):
+#define DFX_FOLD_HEAD 64
 #define DFX_FOLD_PUB 0         //   +0  invocations published (a hint for the readiness scan: the step with data looks at the tags of the lines themselves)
 #define DFX_FOLD_RED 8         //   +8  steps with data finished (the rank's part is combined or copied and written to every recv buffer it belongs to)
 

@@ -1300,7 +1300,10 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 else if (pq.drain) oks = e_sent == ld_agent64((const u64*)f_out + 8);
                 rdy = okr && oks;
                 if (rdy) {
-                  u64 done = (u64)d0.x * (ge.y & 0xffffu) + d0.y;
+                  // primitives done so far, in the order of the walk: a ring takes its slices in windows (next_position),
+                  // so primitive p of the window's second slice comes right behind primitive p of its first
+                  const uint32_t wmask = e_fold ? 0u : a.window - 1u;
+                  u64 done = (u64)(d0.x & ~wmask) * (ge.y & 0xffffu) + (u64)d0.y * (wmask + 1u) + (d0.x & wmask);
                   if (a.order_policy == 1) {
                     // priority ordering (Sec. 4.3): the user's priority decides first, progress and
                     // queue position only among equals

@@ -59,11 +59,23 @@ enum { STOP_NONE = 0, STOP_ABORT = 1, STOP_QUIT = 2, STOP_EXIT = 3 };
 #define SCOPE_AGENT __HIP_MEMORY_SCOPE_AGENT
 #define SCOPE_SYSTEM __HIP_MEMORY_SCOPE_SYSTEM
 
-__device__ __forceinline__ u64 ld_agent64(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, SCOPE_AGENT); }
-__device__ __forceinline__ void st_agent64(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, SCOPE_AGENT); }
-__device__ __forceinline__ uint32_t ld_agent32(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, SCOPE_AGENT); }
-__device__ __forceinline__ u64 ld_sys64(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, SCOPE_SYSTEM); }
-__device__ __forceinline__ uint32_t ld_sys32(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, SCOPE_SYSTEM); }
+// A pointer that is known to be one to device or host memory, never to LDS: what is accessed through it takes global
+// instructions instead of flat ones (pointers that came out of LDS or were put together from integers look like
+// either to the compiler, and a flat access is waited for on both counters).
+#define GLOBAL_AS __attribute__((address_space(1)))
+template <class T>
+__device__ __forceinline__ GLOBAL_AS T* global_ptr(T* p) { return (GLOBAL_AS T*)p; }
+template <class T>
+__device__ __forceinline__ T* known_global(T* p) {
+  __builtin_assume(!__builtin_amdgcn_is_shared((const __attribute__((address_space(0))) void*)p) &&
+                   !__builtin_amdgcn_is_private((const __attribute__((address_space(0))) void*)p));
+  return p;
+}
+
+__device__ __forceinline__ u64 ld_agent64(const u64* p) { return __hip_atomic_load(global_ptr(p), __ATOMIC_RELAXED, SCOPE_AGENT); }
+__device__ __forceinline__ uint32_t ld_agent32(const uint32_t* p) { return __hip_atomic_load(global_ptr(p), __ATOMIC_RELAXED, SCOPE_AGENT); }
+__device__ __forceinline__ u64 ld_sys64(const u64* p) { return __hip_atomic_load(global_ptr(p), __ATOMIC_RELAXED, SCOPE_SYSTEM); }
+__device__ __forceinline__ uint32_t ld_sys32(const uint32_t* p) { return __hip_atomic_load(global_ptr(p), __ATOMIC_RELAXED, SCOPE_SYSTEM); }
 
 // Release fences end with an explicit wait: the L2 write-back they issue must have completed
 // before the flag store that follows.  The compiler's own wait is dropped when it believes no
@@ -239,10 +251,10 @@ typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 // slower).
 typedef v4u v4u_user __attribute__((aligned(2)));
 __device__ __forceinline__ uint4 ld_user(const v4u_user* p) {
-  return __builtin_bit_cast(uint4, __builtin_nontemporal_load(p));
+  return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const GLOBAL_AS v4u_user*)p));
 }
 __device__ __forceinline__ void st_user(v4u_user* p, uint4 v) {
-  __builtin_nontemporal_store(__builtin_bit_cast(v4u, v), p);
+  __builtin_nontemporal_store(__builtin_bit_cast(v4u, v), (GLOBAL_AS v4u_user*)p);
 }
 
 // cache-policy operand of the buffer instructions (gfx940+): bit 0 = sc0, bit 4 = sc1
@@ -726,7 +738,20 @@ __device__ __forceinline__ void bump(u64* stat, int i, u64 v) {
   (void)__hip_atomic_fetch_add(&stat[i], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// saved contexts in memory, in 16-byte words
+__device__ __forceinline__ uint4 ld_ctx(const uint4* p) { return __builtin_bit_cast(uint4, *(const GLOBAL_AS v4u*)p); }
+__device__ __forceinline__ void st_ctx(uint4* p, uint4 v) { *(GLOBAL_AS v4u*)p = __builtin_bit_cast(v4u, v); }
+template <class T>
+__device__ __forceinline__ void st_ctx(T* p, const T& v) {
+  struct Words { uint4 w[sizeof(T) / 16]; };
+  const Words x = __builtin_bit_cast(Words, v);
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(T) / 16); ++i) st_ctx((uint4*)p + i, x.w[i]);
+}
+
 __device__ __forceinline__ uint32_t bcast0(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+// two words that every lane holds alike -> one scalar
+__device__ __forceinline__ u64 bcast64(uint32_t lo, uint32_t hi) { return ((u64)bcast0(hi) << 32) | (u64)bcast0(lo); }
 
 // LDS slot of a collective's context: a multiplicative hash, because the ids that share a workgroup's
 // queue are far from random (with single-channel collectives spread over the channels they are all
@@ -741,7 +766,7 @@ __device__ __forceinline__ void lds_st(uint32_t* p, uint32_t v) { __hip_atomic_s
 // Raise a connector counter.  A maximum instead of a store: the waves that publish two
 // consecutive jobs are different ones, and their updates may reach memory in either order.
 __device__ __forceinline__ void raise_counter(u64* p, u64 v) {
-  (void)__hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, SCOPE_AGENT);
+  (void)__hip_atomic_fetch_max(global_ptr(p), v, __ATOMIC_RELAXED, SCOPE_AGENT);
 }
 
 // one trace sample; the index comes from an LDS counter that both kinds of wave use
@@ -791,12 +816,12 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
   const uint32_t D = a.sq_depth;
   const bool coh = a.fifo_coherent != 0;
 
-  DfxWgState* ws = &a.wgstate[wg];
-  DfxCtxEntry* myctx = a.ctxbuf + (size_t)wg * a.max_colls;
-  uint16_t* qstore = a.taskq_store + (size_t)wg * a.max_colls;
-  DfxSqSlot* sqbase = a.sq + (size_t)rank * D;
-  u64* cqbase = a.cq + (size_t)rank * a.cq_slots;
-  u64* trace = a.trace ? a.trace + (size_t)wg * DFX_TRACE_N : nullptr;
+  DfxWgState* ws = known_global(&a.wgstate[wg]);
+  DfxCtxEntry* myctx = known_global(a.ctxbuf + (size_t)wg * a.max_colls);
+  uint16_t* qstore = known_global(a.taskq_store + (size_t)wg * a.max_colls);
+  DfxSqSlot* sqbase = known_global(a.sq + (size_t)rank * D);
+  u64* cqbase = known_global(a.cq + (size_t)rank * a.cq_slots);
+  u64* trace = a.trace ? known_global(a.trace + (size_t)wg * DFX_TRACE_N) : nullptr;
 
   // ---- restore the workgroup state left by the previous launch (Sec. 4.5)
   u64 ri = ws->read_index;
@@ -877,7 +902,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           if (!coh) fence_release_agent();
           if (f.tail_out) raise_counter(f.tail_out, f.sent_new);
           if (f.head_in) raise_counter(f.head_in, f.recvd_new);
-          if (f.add_one) (void)__hip_atomic_fetch_add(f.add_one, 1ull, __ATOMIC_RELAXED, SCOPE_AGENT);
+          if (f.add_one) (void)__hip_atomic_fetch_add(global_ptr(f.add_one), 1ull, __ATOMIC_RELAXED, SCOPE_AGENT);
           __hip_atomic_store(&sh.wave_done[seen & 1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           if (a.trace_on > 1) bump(sh.stat, ST_T_PUB, wall_clock64() - t1);
           lds_st(&sh.jobs_done, seen + 1);
@@ -889,8 +914,14 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
     // =====================================================================================
     // scheduler wave
     // =====================================================================================
+    // What the scheduler reads all the time is made scalar once: a read of the LDS copy is a round trip of a hundred
+    // cycles in a chain of dependent instructions, a scalar that has overflowed into a vector register's lanes one instruction.
+    const uint32_t R = bcast0(a.R);
+    const struct { uint32_t cmax, max_colls, sq_shift, cq_slots, spin_init, spin_min, spin_max, spin_boost, preempt, order_policy, trace_on, fetch_batch, cq_mode, sq_eager, window, sq_local, focus_bytes, scan_min, oneshot, nwg, epoch; u64 watchdog_ticks, quit_ticks; } hot = {
+      bcast0(a.cmax), bcast0(a.max_colls), bcast0(a.sq_shift), bcast0(a.cq_slots), bcast0(a.spin_init), bcast0(a.spin_min), bcast0(a.spin_max), bcast0(a.spin_boost), bcast0(a.preempt), bcast0(a.order_policy), bcast0(a.trace_on), bcast0(a.fetch_batch), bcast0(a.cq_mode), bcast0(a.sq_eager), bcast0(a.window), bcast0(a.sq_local), bcast0(a.focus_bytes), bcast0(a.scan_min), bcast0(a.oneshot), bcast0(a.nwg), bcast0(a.epoch),
+      bcast64((uint32_t)a.watchdog_ticks, (uint32_t)(a.watchdog_ticks >> 32)), bcast64((uint32_t)a.quit_ticks, (uint32_t)(a.quit_ticks >> 32))};
     u64 last_act = wall_clock64();
-    if (a.trace_on && a.trace_on < 3) {
+    if (hot.trace_on && hot.trace_on < 3) {
       // what one clock read costs (the switch samples contain two of them, the split samples five): 16 in a row
       u64 tc = last_act;
 #pragma unroll
@@ -927,7 +958,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
     // disordered 25 MiB buckets from 1794 to 1422 us and one 8 KiB all-reduce from 25 to 20.7 us.
     auto complete = [&](uint32_t c_coll, uint32_t c_seq, uint32_t c_nchan, bool in_memory) {
       if (!in_memory) fence_release_system();   // results in the recv buffer are visible to host and later kernels
-      uint32_t* dc = &a.done_cnt[(size_t)rank * a.max_colls + c_coll];
+      GLOBAL_AS uint32_t* dc = global_ptr(&a.done_cnt[(size_t)rank * hot.max_colls + c_coll]);
       // (a collective on one channel has nobody to count with: no round trip for the counter)
       uint32_t old = 0;
       if (c_nchan > 1) old = in_memory ? __hip_atomic_fetch_add(dc, 1u, __ATOMIC_RELAXED, SCOPE_AGENT)
@@ -935,7 +966,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
       // (the counter runs on from invocation to invocation, modulo 2^32: no reset that the next one's counts could overtake)
       if (c_nchan == 1 || old + 1 == (c_seq + 1u) * c_nchan) {
         const u64 tq0 = wall_clock64();
-        if (a.cq_mode == 0) {
+        if (hot.cq_mode == 0) {
           // optimized CQ (Sec. 5): one CAS of the id into a writable slot, no ring semantics
           const u64 v = (1ull << 63) | ((u64)(c_seq & 0x7fffffffu) << 32) | c_coll;
           // where to try first: spread by id and invocation, no shared ticket to fetch (the CAS decides)
@@ -944,11 +975,11 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           for (;;) {
             // (relaxed: what the entry vouches for is in memory, by the fence above or to begin with)
             u64 expected = 0;
-            if (__hip_atomic_compare_exchange_strong(&cqbase[(t + k) % a.cq_slots], &expected, v, __ATOMIC_RELAXED,
+            if (__hip_atomic_compare_exchange_strong(global_ptr(&cqbase[(t + k) % hot.cq_slots]), &expected, v, __ATOMIC_RELAXED,
                                                      __ATOMIC_RELAXED, SCOPE_SYSTEM))
               break;
             ++k;
-            if ((k % a.cq_slots) == 0) {
+            if ((k % hot.cq_slots) == 0) {
               if (ld_agent32(&a.dev_ctl[DC_ABORT]) || ld_sys32(&a.host_ctl[HC_ABORT])) break;
               __builtin_amdgcn_s_sleep(50);
             }
@@ -961,14 +992,14 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           const u64 t = __hip_atomic_fetch_add(&ctl[0], 1ull, __ATOMIC_RELAXED, SCOPE_SYSTEM);
           bool give_up = false;
           uint32_t k = 0;
-          while (t - __hip_atomic_load(&ctl[16], __ATOMIC_RELAXED, SCOPE_SYSTEM) >= (u64)a.cq_slots) {
+          while (t - __hip_atomic_load(&ctl[16], __ATOMIC_RELAXED, SCOPE_SYSTEM) >= (u64)hot.cq_slots) {
             if ((++k & 63u) == 0 && (ld_agent32(&a.dev_ctl[DC_ABORT]) || ld_sys32(&a.host_ctl[HC_ABORT]))) { give_up = true; break; }
             __builtin_amdgcn_s_sleep(20);
           }
-          if (!give_up && a.cq_mode == 1) {
+          if (!give_up && hot.cq_mode == 1) {
             // vanilla ring: entry, fence, then the shared tail, which moves in position order
             const u64 v = ((u64)(c_seq & 0x7fffffffu) << 32) | c_coll;
-            __hip_atomic_store(&cqbase[t % a.cq_slots], v, __ATOMIC_RELAXED, SCOPE_SYSTEM);
+            __hip_atomic_store(&cqbase[t % hot.cq_slots], v, __ATOMIC_RELAXED, SCOPE_SYSTEM);
             fence_release_system();
             while (__hip_atomic_load(&ctl[8], __ATOMIC_RELAXED, SCOPE_SYSTEM) != t) {
               if ((++k & 63u) == 0 && (ld_agent32(&a.dev_ctl[DC_ABORT]) || ld_sys32(&a.host_ctl[HC_ABORT]))) { give_up = true; break; }
@@ -979,7 +1010,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             // optimized ring: id and position travel in one 64-bit atomic write, no tail, no fence;
             // the poller accepts the entry at its head when the position in it says head + 1
             const u64 v = (((t + 1) & 0xffffffffull) << 32) | ((u64)(c_seq & 0xffffu) << 16) | (c_coll & 0xffffu);
-            __hip_atomic_store(&cqbase[t % a.cq_slots], v, __ATOMIC_RELEASE, SCOPE_SYSTEM);
+            __hip_atomic_store(&cqbase[t % hot.cq_slots], v, __ATOMIC_RELEASE, SCOPE_SYSTEM);
           }
         }
         bump(sh.stat, ST_T_CQE, wall_clock64() - tq0);
@@ -1009,9 +1040,9 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
     bool ctx_open = false;     // the stores of a lone collective's context may still be under way
     auto free_slot = [&](uint32_t readers_before, u64 idx) {
       // (the counter runs on from generation to generation, modulo 2^32: no reset to wait for before the slot is used again)
-      const uint32_t gen = (uint32_t)(idx >> a.sq_shift) + 1u;
-      if (readers_before + 1 == gen * a.cmax)
-        __hip_atomic_store(&a.sq_freed[(size_t)rank * D + (idx & (D - 1))], gen, __ATOMIC_RELAXED, SCOPE_SYSTEM);
+      const uint32_t gen = (uint32_t)(idx >> hot.sq_shift) + 1u;
+      if (readers_before + 1 == gen * hot.cmax)
+        __hip_atomic_store(global_ptr(&a.sq_freed[(size_t)rank * D + (idx & (D - 1))]), gen, __ATOMIC_RELAXED, SCOPE_SYSTEM);
     };
     auto settle_slot = [&]() {
       if (rd_open) { if (lane == 0) free_slot(rd_old, rd_idx); rd_open = false; }
@@ -1051,8 +1082,8 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           // and a workgroup that kept working without reading the SQ held back its rank's SQ slots
           // -- every workgroup must read every SQE -- and with them the submitter and the rest of
           // the grid.)  A fetch is followed by further fetches, up to fetch_batch in a row.
-          const bool want = (a.sq_eager && burst < a.fetch_batch) || (qlen == 0) || !pass_progress || a.order_policy == 1 || (burst > 0 && burst < a.fetch_batch);
-          const bool probe = want && qlen < a.max_colls;
+          const bool want = (hot.sq_eager && burst < hot.fetch_batch) || (qlen == 0) || !pass_progress || hot.order_policy == 1 || (burst > 0 && burst < hot.fetch_batch);
+          const bool probe = want && qlen < hot.max_colls;
           const bool slow = ((iter & 31u) == 0) || qlen == 0 || !pass_progress;
           const bool host_look = ((iter & 31u) == 0) || qlen == 0;
           // the three control words live in different memories; three lanes fetch them at once
@@ -1061,7 +1092,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             const u64 c2 = ld_agent64((const u64*)&a.dev_ctl[DC_ABORT]);   // abort | quit
             w0 = (uint32_t)c2; w1 = (uint32_t)(c2 >> 32);
           } else if (lane == 1) {
-            if (probe) w0 = __hip_atomic_load(&sqbase[ri & (D - 1)].e.ready, __ATOMIC_RELAXED, SCOPE_SYSTEM);
+            if (probe) w0 = ld_sys32(&sqbase[ri & (D - 1)].e.ready);
           } else if (lane == 2) {
             if (host_look) w0 = ld_sys32(&a.host_ctl[HC_ABORT]);
           }
@@ -1073,30 +1104,30 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             if (!s && slow) {
               const u64 now = wall_clock64();
               if (acted) { last_act = now; acted = false; }
-              if (a.watchdog_ticks && qlen > 0 && now - last_act > a.watchdog_ticks) {
+              if (hot.watchdog_ticks && qlen > 0 && now - last_act > hot.watchdog_ticks) {
                 ws->dbg[0] = ((u64)sh.taskq[0] << 32) | qlen; ws->dbg[1] = ri; ws->dbg[2] = now - last_act;
                 raise_error(a, 1u, wg);
                 s = STOP_ABORT;
-              } else if (a.oneshot) {
+              } else if (hot.oneshot) {
                 // A launch that brings all of its work with it: this workgroup is through when it has read every
                 // entry of its rank's SQ, its queue is empty and its jobs are retired (completions posted).
-                if (!voted && qlen == 0 && ri >= (u64)a.oneshot && retired == posted) {
+                if (!voted && qlen == 0 && ri >= (u64)hot.oneshot && retired == posted) {
                   voted = true;
-                  if (__hip_atomic_fetch_add(&a.dev_ctl[DC_VOTES], 1u, __ATOMIC_ACQ_REL, SCOPE_AGENT) + 1 == a.nwg) {
+                  if (__hip_atomic_fetch_add(&a.dev_ctl[DC_VOTES], 1u, __ATOMIC_ACQ_REL, SCOPE_AGENT) + 1 == hot.nwg) {
                     __hip_atomic_store(&a.dev_ctl[DC_QUIT], 1u, __ATOMIC_RELEASE, SCOPE_AGENT);
                     s = STOP_QUIT;
                   }
                 }
-              } else if (a.quit_ticks) {
+              } else if (hot.quit_ticks) {
                 // Voluntary quit (Sec. 4.4).  Every workgroup has duties towards the others (each
                 // must read every SQE of its rank before the slot is reusable), so the grid leaves
                 // as a whole: a workgroup that has been idle or stuck for the quit period casts a
                 // vote and keeps running; it withdraws the vote when it becomes active again; the
                 // vote that completes the set raises the quit flag, which everybody obeys.
-                const bool tired = now - last_act > a.quit_ticks;
+                const bool tired = now - last_act > hot.quit_ticks;
                 if (tired && !voted) {
                   voted = true;
-                  if (__hip_atomic_fetch_add(&a.dev_ctl[DC_VOTES], 1u, __ATOMIC_ACQ_REL, SCOPE_AGENT) + 1 == a.nwg) {
+                  if (__hip_atomic_fetch_add(&a.dev_ctl[DC_VOTES], 1u, __ATOMIC_ACQ_REL, SCOPE_AGENT) + 1 == hot.nwg) {
                     __hip_atomic_store(&a.dev_ctl[DC_QUIT], 1u, __ATOMIC_RELEASE, SCOPE_AGENT);
                     s = STOP_QUIT;
                   }
@@ -1107,7 +1138,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
               }
             }
             if (!s && probe) {
-              const uint32_t gen = (uint32_t)(ri >> a.sq_shift) + 1u;
+              const uint32_t gen = (uint32_t)(ri >> hot.sq_shift) + 1u;
               if (c_ready == gen) got = 1;
             }
           }
@@ -1123,11 +1154,11 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           if (got) {
             const u64 tf0 = wall_clock64();
             // how many consecutive entries from the read index on are there?
-            uint32_t room = a.max_colls - qlen;
+            uint32_t room = hot.max_colls - qlen;
             if (room > 64) room = 64;
-            const uint32_t left = burst < a.fetch_batch ? a.fetch_batch - burst : 1u;
+            const uint32_t left = burst < hot.fetch_batch ? hot.fetch_batch - burst : 1u;
             if (left < room) room = left;
-            if (a.order_policy == 1) room = 1;       // the sorted insert below is written for one entry
+            if (hot.order_policy == 1) room = 1;       // the sorted insert below is written for one entry
             // Lane 0's entry has been seen by the control check: its words are loaded while the lanes behind it look
             // whether theirs are there.  System scope throughout: nothing of an SQ slot is ever taken from a cache.
             bool here = lane == 0;
@@ -1140,7 +1171,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             if (lane == 0) load_entry();
             else if (lane < room) {
               const u64 idx = ri + lane;
-              here = __hip_atomic_load(&sqbase[idx & (D - 1)].e.ready, __ATOMIC_RELAXED, SCOPE_SYSTEM) == (uint32_t)(idx >> a.sq_shift) + 1u;
+              here = ld_sys32(&sqbase[idx & (D - 1)].e.ready) == (uint32_t)(idx >> hot.sq_shift) + 1u;
             }
             const u64 here_mask = __ballot(here);
             uint32_t n = (here_mask == ~0ull) ? 64u : (uint32_t)__builtin_ctzll(~here_mask);   // length of the run that starts at lane 0
@@ -1152,7 +1183,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
               // an exit SQE ends the launch it was posted for; one left over from an earlier launch
               // (some workgroups had already gone when it arrived) is consumed and ignored
               is_exit_sqe = (q.flags & DFX_SQE_EXIT) != 0;
-              is_exit = is_exit_sqe && q.seq == a.epoch;
+              is_exit = is_exit_sqe && q.seq == hot.epoch;
             }
             const u64 exit_mask = __ballot(is_exit);
             if (exit_mask) n = (uint32_t)__builtin_ctzll(exit_mask) + 1;   // nothing behind an exit SQE is touched
@@ -1160,8 +1191,8 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             uint32_t c_id = 0, my_vch = 0;
             if (lane < n) {
               c_id = q.coll_id;
-              my_vch = is_exit_sqe ? ch : serving_channel(a.chan_spread != 0, ch, a.cmax, c_id, q.nchan);
-              mine = !is_exit_sqe && my_vch < q.nchan && c_id < a.max_colls;
+              my_vch = is_exit_sqe ? ch : serving_channel(ch, hot.cmax, q.start);
+              mine = !is_exit_sqe && my_vch < q.nchan && c_id < hot.max_colls;
             }
             const bool q_fold = (q.flags & DFX_SQE_FOLD) != 0;
             // the submitter wrote the send buffers before the SQEs: drop what this CU / XCD cached (fold steps read
@@ -1174,7 +1205,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             if (mine) {
               // cook the static context of this invocation into the context buffer (addresses
               // resolved once, here); restart the sequence, keep the monotone connector counters
-              const DfxCooked k = cook_sqe(q, a.pool, rank, a.R, my_vch);
+              const DfxCooked k = cook_sqe(q, a.pool, rank, R, my_vch);
               // direct and fold steps: other ranks read this rank's send buffer and read or write its recv buffer; their
               // addresses and the invocation they belong to go into the rank's line (two 16-byte device-coherent
               // stores, each with its tag; complete before any job of an invocation with direct steps is posted)
@@ -1185,22 +1216,22 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 line.st16(DFX_DIRECT_OFF + 16, uint4{(uint32_t)q.sendbuf, (uint32_t)(q.sendbuf >> 32), q.seq + 1u, 0u});
               }
               // fold steps: the channel's count of published invocations, a hint for the readiness scans
-              if (q_fold) (void)__hip_atomic_fetch_add((u64*)(k.flags_in + DFX_FOLD_PUB), 1ull, __ATOMIC_RELAXED, SCOPE_AGENT);
+              if (q_fold) (void)__hip_atomic_fetch_add(global_ptr((u64*)(k.flags_in + DFX_FOLD_PUB)), 1ull, __ATOMIC_RELAXED, SCOPE_AGENT);
               const uint32_t csl = ctx_slot(c_id);
               if (lone) {
                 DfxDyn d; d.round = 0; d.prim = 0; d.sent = 0; d.recvd = 0; d.preempted = 0; d.cidx = 0;   // (no connectors: nothing to keep)
                 sh.slot[csl].st = k; sh.slot[csl].dyn = d;
                 sh.slot_tag[csl] = c_id;
               } else if (sh.slot_tag[csl] == c_id) sh.slot_tag[csl] = 0xffffffffu;
-              myctx[c_id].st = k;
-              DfxDyn* dy = &myctx[c_id].dyn;
+              st_ctx(&myctx[c_id].st, k);
+              GLOBAL_AS DfxDyn* dy = global_ptr(&myctx[c_id].dyn);
               dy->round = 0; dy->prim = 0; dy->preempted = 0;
-              dy->cidx = first_chunk(q.kind, rank, a.R);
+              dy->cidx = first_chunk(q.kind, rank, R);
             }
             // every workgroup of the rank reads every SQE; the last reader frees the slot (relaxed: the entries have been
             // read, and nothing else hangs on the counter)
             if (lane < n) {
-              const uint32_t old = __hip_atomic_fetch_add(&a.sq_readers[(size_t)rank * D + ((ri + lane) & (D - 1))], 1u, __ATOMIC_RELAXED, SCOPE_AGENT);
+              const uint32_t old = __hip_atomic_fetch_add(global_ptr(&a.sq_readers[(size_t)rank * D + ((ri + lane) & (D - 1))]), 1u, __ATOMIC_RELAXED, SCOPE_AGENT);
               if (n == 1) rd_old = old;
               else free_slot(old, ri + lane);
             }
@@ -1210,7 +1241,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             else __builtin_amdgcn_s_waitcnt(0);
             // the entries that are this workgroup's join the task queue in SQ order
             if (mine) {
-              if (a.order_policy == 1) {
+              if (hot.order_policy == 1) {
                 // priority ordering: keep the queue sorted (stable); one entry per fetch in this mode
                 uint32_t at = qlen;
                 const int16_t pr = q.priority;
@@ -1246,7 +1277,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             // idle: back off the SQ probe (an SQ in host memory is probed across PCIe: back off further)
             ++idle;
             if (idle < 64) __builtin_amdgcn_s_sleep(8);
-            else if (a.sq_local || idle < 4096) __builtin_amdgcn_s_sleep(32);
+            else if (hot.sq_local || idle < 4096) __builtin_amdgcn_s_sleep(32);
             else __builtin_amdgcn_s_sleep(127);
             continue;
           }
@@ -1263,11 +1294,11 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           // monotone: only this workgroup consumes its recv side and fills its send side, so
           // "ready" stays true until it acts.  A queue of a thousand stuck collectives costs
           // sixteen memory round trips instead of a thousand context loads and bounded spins.
-          scanned = a.scan_min && qlen >= a.scan_min;
+          scanned = hot.scan_min && qlen >= hot.scan_min;
           if (scanned) {
             settle_slot();     // (the scan reads the contexts in memory)
             nready = 0; rk = 0; pass_bytes = 0;
-            focus = a.focus_bytes != 0 && qlen <= 64u;
+            focus = hot.focus_bytes != 0 && qlen <= 64u;
             if (lane < DFX_CTX_SLOTS) sh.slot_claim[lane] = 0xffffffffu;
             for (uint32_t base = 0; base < qlen; base += 64) {
               const uint32_t i = base + lane;
@@ -1278,23 +1309,23 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
               if (i < qlen) {
                 cid = sh.taskq[i];
                 const uint4* e = (const uint4*)&myctx[cid];
-                e0 = e[0]; e1 = e[1]; e4 = e[4];   // not needed for the vote, but for the deposit below
-                const uint4 fl = e[2];    // bytes 32..47: part_elems | flags_out
-                const uint4 fi = e[3];    // bytes 48..63: flags_in | fifo_out
-                const uint4 ge = e[5];    // bytes 80..95: seq | nprim,nchan | nslots,kind,dtype,bc_pos | priority,vch
-                const uint4 d0 = e[6];    // dyn: round | prim | sent
-                const uint4 d1 = e[7];    // dyn: recvd | preempted | cidx
+                e0 = ld_ctx(e); e1 = ld_ctx(e + 1); e4 = ld_ctx(e + 4);   // not needed for the vote, but for the deposit below
+                const uint4 fl = ld_ctx(e + 2);    // bytes 32..47: part_elems | flags_out
+                const uint4 fi = ld_ctx(e + 3);    // bytes 48..63: flags_in | fifo_out
+                const uint4 ge = ld_ctx(e + 5);    // bytes 80..95: seq | nprim,nchan | nslots,kind,dtype,bc_pos | priority,vch
+                const uint4 d0 = ld_ctx(e + 6);    // dyn: round | prim | sent
+                const uint4 d1 = ld_ctx(e + 7);    // dyn: recvd | preempted | cidx
                 e2c = fl; e3c = fi; e5c = ge; e6c = d0; e7c = d1;
                 const bool e_fold = ((ge.z >> 24) & DFX_CTX_FOLD) != 0;
                 Prim pq = e_fold ? make_fold_prim(d0.y)
-                                 : make_prim((int)((ge.z >> 8) & 0xffu), a.R, (ge.z >> 24) & 3u, d0.y, ((ge.z >> 24) & DFX_CTX_DIRECT) != 0);
+                                 : make_prim((int)((ge.z >> 8) & 0xffu), R, (ge.z >> 24) & 3u, d0.y, ((ge.z >> 24) & DFX_CTX_DIRECT) != 0);
                 if (!e_fold && ((ge.z >> 24) & DFX_CTX_DIRECT))
-                  pq = chain_drain_round(pq, (int)((ge.z >> 8) & 0xffu), true, d0.x, e[4].w);   // bytes 64..79: fifo_in | slice_elems | rounds
+                  pq = chain_drain_round(pq, (int)((ge.z >> 8) & 0xffu), true, d0.x, e4.w);   // bytes 64..79: fifo_in | slice_elems | rounds
                 const u64 f_out = ((u64)fl.w << 32) | fl.z, f_in = ((u64)fi.y << 32) | fi.x;
                 const u64 e_sent = ((u64)d0.w << 32) | d0.z, e_recvd = ((u64)d1.y << 32) | d1.x;
                 bool okr = true, oks = true;
                 if (pq.fold)   // every rank of the channel has got as far as this step needs (bytes 48..63: shared counters, count at the end)
-                  okr = ld_agent64((const u64*)f_in + pq.fwait) >= (pq.fwait ? ((u64)fi.w << 32) | fi.z : ((u64)ge.x + 1u) * a.R);
+                  okr = ld_agent64((const u64*)f_in + pq.fwait) >= (pq.fwait ? ((u64)fi.w << 32) | fi.z : ((u64)ge.x + 1u) * R);
                 if (pq.recv) okr = ld_agent64((const u64*)f_in) > e_recvd;
                 if (pq.send) oks = (e_sent - ld_agent64((const u64*)f_out + 8)) < (u64)(ge.z & 0xffu);
                 else if (pq.drain) oks = e_sent == ld_agent64((const u64*)f_out + 8);
@@ -1302,9 +1333,9 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 if (rdy) {
                   // primitives done so far, in the order of the walk: a ring takes its slices in windows (next_position),
                   // so primitive p of the window's second slice comes right behind primitive p of its first
-                  const uint32_t wmask = e_fold ? 0u : a.window - 1u;
+                  const uint32_t wmask = e_fold ? 0u : hot.window - 1u;
                   u64 done = (u64)(d0.x & ~wmask) * (ge.y & 0xffffu) + (u64)d0.y * (wmask + 1u) + (d0.x & wmask);
-                  if (a.order_policy == 1) {
+                  if (hot.order_policy == 1) {
                     // priority ordering (Sec. 4.3): the user's priority decides first, progress and
                     // queue position only among equals
                     if (done > 0xffu) done = 0xffu;
@@ -1354,55 +1385,54 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           // (a pass that ends is not a switch between two collectives: the latency sample is dropped)
           // A focused pass also ends once it has handed the movers its share of bytes: the next scan
           // looks again at which collectives are furthest along.
-          if (rk >= nready || (focus && pass_bytes >= a.focus_bytes)) { in_pass = false; sw_pending = false; continue; }
-          pos = (uint32_t)sh.rlist[rk];
+          if (rk >= nready || (focus && pass_bytes >= hot.focus_bytes)) { in_pass = false; sw_pending = false; continue; }
+          pos = bcast0((uint32_t)sh.rlist[rk]);
         } else if (pos >= qlen) { in_pass = false; sw_pending = false; continue; }
 
         // ---- LoadCollectiveContext: HBM context buffer -> LDS slot, 8 lanes x 16 bytes
-        coll = sh.taskq[pos];
+        coll = bcast0(sh.taskq[pos]);
         sl = ctx_slot(coll);
-        if (sw_pending && a.trace_on > 1) sw_lb = wall_clock64();
+        if (sw_pending && hot.trace_on > 1) sw_lb = wall_clock64();
         if (sh.slot_tag[sl] != coll) {
-          if (lane < 8) ((uint4*)&sh.slot[sl])[lane] = ((const uint4*)&myctx[coll])[lane];
+          if (lane < 8) ((uint4*)&sh.slot[sl])[lane] = ld_ctx((const uint4*)&myctx[coll] + lane);
           if (lane == 0) { sh.slot_tag[sl] = coll; bump(sh.stat, ST_LOAD, 1); }
           __builtin_amdgcn_wave_barrier();
         } else if (lane == 0) bump(sh.stat, ST_HIT, 1);
-        if (sw_pending && a.trace_on > 1) sw_le = wall_clock64();
+        if (sw_pending && hot.trace_on > 1) sw_le = wall_clock64();
         {
-          const DfxDyn& Y = sh.slot[sl].dyn;
-          g = Y.round; p = Y.prim; sent = Y.sent; recvd = Y.recvd; cidx = Y.cidx;
+          // (every lane reads the same words: into scalar registers, so that what follows branches and counts there)
+          const uint4* const y = (const uint4*)&sh.slot[sl].dyn;
+          const uint4 y0 = y[0], y1 = y[1];   // round | prim | sent, recvd | preempted | cidx
+          g = bcast0(y0.x); p = bcast0(y0.y); sent = bcast64(y0.z, y0.w); recvd = bcast64(y1.x, y1.y); cidx = bcast0(y1.w);
         }
         // SetInitialSpinThreshold (Alg. 1 line 3): largest at the front, halving per position.
         // In a scanned pass every entry visited was seen runnable, and the rest of the list is
         // known work: waiting on one collective would only keep the movers idle, so the
         // threshold stays at its minimum there.
-        thr = a.spin_init >> (pos < 31 ? pos : 31);
-        if (thr < a.spin_min || scanned) thr = a.spin_min;
+        thr = hot.spin_init >> (pos < 31 ? pos : 31);
+        if (thr < hot.spin_min || scanned) thr = hot.spin_min;
         progressed = false;
         prev_recv = 0;
         have = true;
       }
 
       // ================= next primitive of the collective in hand =================
+      // The static context stays in the LDS slot; the words that every step needs are read at once and made scalar.
       const DfxCooked& S = sh.slot[sl].st;
-      const bool fold = (S.bc_pos & DFX_CTX_FOLD) != 0;
-      const Prim q = fold ? make_fold_prim(p)
-                          : chain_drain_round(make_prim((int)S.kind, a.R, S.bc_pos & 3u, p, (S.bc_pos & DFX_CTX_DIRECT) != 0),
-                                              (int)S.kind, (S.bc_pos & DFX_CTX_DIRECT) != 0, g, S.rounds);
-      // Fold steps: the step with data waits until every rank's line carries this invocation's tag, lane k looking at
-      // the line of entry k's rank, so that the poll that succeeds has brought the addresses along; the last wait
-      // looks at the channel's count of finished steps.
-      const uint32_t line_off = q.fold == 1 && lane < a.R ? fold_peer((int)S.kind, a.R, rank, S.nslots, lane) * (uint32_t)S.nchan * DFX_FLAG_STRIDE : 0u;
-      u64* const tail_out = (u64*)S.flags_out;
-      u64* const tail_in = (u64*)S.flags_in;
-      const uint32_t K = S.nslots;
+      const uint4* const sv = (const uint4*)&S;
+      const uint4 v3 = sv[3], v4 = sv[4], v5 = sv[5];   // flags_in | fifo_out, fifo_in | slice_elems | rounds, seq | nprim,nchan | nslots,kind,dtype,bc_pos | ..
+      const u64 s_in = bcast64(v3.x, v3.y), s_fout = bcast64(v3.z, v3.w), s_fin = bcast64(v4.x, v4.y);
+      const uint32_t s_slice = bcast0(v4.z), s_rounds = bcast0(v4.w), inv_seq = bcast0(v5.x);
+      const uint32_t s_n = bcast0(v5.y), s_k = bcast0(v5.z), inv_nchan = s_n >> 16, K = s_k & 0xffu, bcp = s_k >> 24;   // (K: the root in fold steps)
+      const int kind = (int)(s_k >> 8 & 0xffu), dtype = (int)(s_k >> 16 & 0xffu);   // dtype: element type | reducing function << 4
+      const bool fold = (bcp & DFX_CTX_FOLD) != 0;
 
       if (sw_pending) {   // the first poll of the next collective ends the context switch
         const u64 t1 = wall_clock64();
-        if (trace && a.trace_on < 3 && lane == 0) {
+        if (trace && hot.trace_on < 3 && lane == 0) {
           // total | save | queue advance (save done -> context load begins) | load | set-up of the primitive (load done -> here)
           u64 tot = t1 - sw_t0, sv = sw_ts - sw_t0, adv = sw_lb - sw_ts, ldt = sw_le - sw_lb, su = t1 - sw_le;
-          if (a.trace_on < 2) { sv = 0; adv = 0; ldt = 0; su = 0; }
+          if (hot.trace_on < 2) { sv = 0; adv = 0; ldt = 0; su = 0; }
           if (tot > 0xffffu) tot = 0xffffu;
           if (sv > 0xfffu) sv = 0xfffu;
           if (adv > 0xfffu) adv = 0xfffu;
@@ -1413,55 +1443,8 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
         sw_pending = false;
       }
       u64 tm0 = 0;
-      if (a.trace_on > 1) tm0 = wall_clock64();
+      if (hot.trace_on > 1) tm0 = wall_clock64();
 
-      // ---- wait phase: lane 0 polls the recv side, lane 1 the send side (Sec. 4.2 (3)).
-      // The first poll is sent off before the slice's geometry is worked out, which depends only on
-      // the sequence position: the arithmetic runs while the counters travel, and a poll that
-      // succeeds is followed by the job at once.
-      u64 seen_cnt = 0;
-      uint4 ln_recv = uint4{0, 0, 0, 0}, ln_send = ln_recv;
-      auto poll = [&]() {
-        if (q.fold == 1) {
-          asm volatile("" ::: "memory");     // (these loads are made anew at every poll)
-          if (lane < a.R) {
-            const __amdgpu_buffer_rsrc_t lines = uniform_rsrc(S.fifo_in, a.R * S.nchan * DFX_FLAG_STRIDE);
-            ln_recv = rs_ld16(lines, line_off + DFX_DIRECT_OFF);
-            ln_send = rs_ld16(lines, line_off + DFX_DIRECT_OFF + 16);
-          }
-        } else {
-          if (lane == 0 && q.recv) seen_cnt = ld_agent64(tail_in);
-          if (lane == 1 && (q.send || q.drain)) seen_cnt = ld_agent64(tail_out + 8);
-          if (lane == 0 && q.fold) seen_cnt = ld_agent64(tail_in + DFX_FOLD_RED / 8);
-        }
-      };
-      poll();
-
-      // ---- slice geometry and the job's four pointers
-      const int kind = S.kind, dtype = S.dtype;   // dtype: element type | reducing function << 4
-      FoldGeom fg = {};
-      SliceGeom geo = {};
-      if (fold) { fg = fold_geometry(S, a.R, rank, g); geo.eb = fg.eb; geo.bytes = S.slice_elems * fg.eb; }
-      else geo = slice_geometry(S, a.R, g, cidx);
-      const uint32_t eb = geo.eb, bytes = geo.bytes;
-      const u64 soff = geo.soff, doff = geo.doff;
-      const size_t slot_bytes = (size_t)S.slice_elems * eb;
-      const void* jfin = q.recv ? (const void*)((const uint8_t*)S.fifo_in + (size_t)(recvd & (K - 1)) * slot_bytes) : nullptr;
-      void* jfout = q.send ? (void*)((uint8_t*)S.fifo_out + (size_t)(sent & (K - 1)) * slot_bytes) : nullptr;
-      const char* jsb = q.from_send ? (const char*)S.sendbuf + soff * eb : nullptr;
-      char* jrb = q.to_recv ? (char*)S.recvbuf + doff * eb : nullptr;
-      // a notified result goes to the recv buffer through the coherent path of a slot
-      if (q.notify) { jfout = jrb; jrb = nullptr; }
-
-      // the position after this primitive (slices in windows, the chunk index stepping down the ring)
-      const SeqPos nx = fold ? next_fold_position(S.rounds, g, p, cidx)
-                             : next_position(kind, a.R, rank, a.window, S.rounds, S.nprim, g, p, cidx);
-      const uint32_t g_next = nx.g, p_next = nx.p, cidx_next = nx.cidx;
-      const bool last = (g_next >= S.rounds);
-      const uint32_t inv_seq = S.seq, inv_nchan = S.nchan;
-
-      // The movers may be busy with earlier slices meanwhile; finished ones are retired between polls.
-      uint32_t res = W_OK;
       // While the first poll travels: which entry would the pass visit next, and is its context in its LDS slot?
       // If not, its load from the context buffer sets off now.  Should this wait be given up, the switch finds
       // the answer in registers (nothing below changes the queue, the list, another collective's slot or its
@@ -1470,148 +1453,241 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
       uint32_t nx_pos = 0, nx_coll = 0, nx_sl = 0;
       DfxDyn nx_dyn = {};
       uint4 nx_ctx = uint4{0, 0, 0, 0};
-      if (q.recv || q.send || q.drain || q.fold) {
+      auto look_ahead = [&]() {
         const uint32_t ni = scanned ? rk + 1u : pos + 1u;
-        if (scanned ? (ni < nready && !(focus && pass_bytes >= a.focus_bytes)) : (ni < qlen)) {
+        if (scanned ? (ni < nready && !(focus && pass_bytes >= hot.focus_bytes)) : (ni < qlen)) {
           nx_pos = scanned ? (uint32_t)sh.rlist[ni] : ni;
           nx_coll = sh.taskq[nx_pos];
           nx_sl = ctx_slot(nx_coll);
           nx_ok = true;
           nx_hit = sh.slot_tag[nx_sl] == nx_coll;
           if (nx_hit) nx_dyn = sh.slot[nx_sl].dyn;
-          else if (lane < 8) nx_ctx = ((const uint4*)&myctx[nx_coll])[lane];
+          else if (lane < 8) nx_ctx = ld_ctx((const uint4*)&myctx[nx_coll] + lane);
         }
+      };
+      // The wait phase (Sec. 4.2 (3)), with the first poll on its way already: ready() looks at what poll() has brought.
+      // The movers may be busy with earlier slices meanwhile; finished ones are retired between polls.
+      auto wait_until = [&](auto&& poll, auto&& ready) -> uint32_t {
         u64 n = 0;
+        uint32_t r = W_OK;
         for (;;) {
-          bool ok = true;
-          if (q.fold == 1 && lane < a.R) ok = ln_recv.z == inv_seq + 1u && ln_send.z == inv_seq + 1u;
-          if (lane == 0 && q.fold == 3) ok = seen_cnt >= S.fifo_out;
-          if (lane == 0 && q.recv) ok = seen_cnt > recvd;
-          if (lane == 1 && q.send) ok = (sent - seen_cnt) < (u64)K;
-          if (lane == 1 && q.drain) ok = sent == seen_cnt;
+          const bool ok = ready();
           ++n;
           if (__ballot(!ok) == 0) break;
           settle_slot();
           retire_finished();
-          if (a.preempt && n >= thr) { res = W_TIMEOUT; break; }
+          if (hot.preempt && n >= thr) { r = W_TIMEOUT; break; }
           if ((n & 255u) == 0) {
             uint32_t s = 0;
             if (lane == 0) {
               if (ld_agent32(&a.dev_ctl[DC_ABORT]) || ld_sys32(&a.host_ctl[HC_ABORT])) s = 1;
-              else if (a.watchdog_ticks) {
+              else if (hot.watchdog_ticks) {
                 const u64 now = wall_clock64();
                 if (acted) { last_act = now; acted = false; }
-                if (now - last_act > a.watchdog_ticks) {
+                if (now - last_act > hot.watchdog_ticks) {
                   ws->dbg[0] = ((u64)coll << 32) | qlen; ws->dbg[1] = ((u64)g << 32) | p; ws->dbg[2] = sent; ws->dbg[3] = recvd;
-                  ws->dbg[4] = ld_agent64(tail_in); ws->dbg[5] = ld_agent64(tail_out + 8); ws->dbg[6] = ri; ws->dbg[7] = now - last_act;
+                  ws->dbg[4] = ld_agent64((const u64*)s_in); ws->dbg[5] = ld_agent64((const u64*)S.flags_out + 8); ws->dbg[6] = ri; ws->dbg[7] = now - last_act;
                   raise_error(a, 2u, wg);
                   s = 1;
                 }
               }
             }
-            if (bcast0(s)) { res = W_STOP; break; }
+            if (bcast0(s)) { r = W_STOP; break; }
           }
           __builtin_amdgcn_s_sleep(1);
           poll();
         }
         if (lane == 0) bump(sh.stat, ST_POLLS, n);
-      }
-
-      if (res == W_OK) {
-        u64 tm1 = 0;
-        if (a.trace_on > 1) { tm1 = wall_clock64(); if (lane == 0) bump(sh.stat, ST_T_WAIT, tm1 - tm0); }
-        // The last wait of a collective in fold steps moves nothing, and the counter it has just seen says that every
-        // rank's data step of this channel -- this workgroup's own job included -- is in memory: the completion is
-        // posted here and now instead of queueing as an empty job behind the data jobs of other collectives.
-        const bool done_here = q.fold == 3;
-        // a flight slot: at most two jobs are posted and not yet retired (under priority ordering a step of a
-        // collective in fold steps, which is one long job, waits until the movers have nothing else: what is
-        // posted cannot be overtaken by a more urgent collective that arrives)
-        const uint32_t depth = (a.order_policy == 1 && q.fold) ? 1u : 2u;
-        bool given_up = false;
-        while (!done_here && posted - retired >= depth) {
+        return r;
+      };
+      // a flight slot: at most two jobs are posted and not yet retired
+      auto flight_free = [&](uint32_t depth) -> bool {
+        while (posted - retired >= depth) {
           retire_finished();
           if (posted - retired >= depth) {
-            if ((++spins & 0xffffu) == 0 && abort_seen()) { given_up = true; break; }
+            if ((++spins & 0xffffu) == 0 && abort_seen()) return false;
             __builtin_amdgcn_s_sleep(1);
           }
         }
-        if (given_up) { stop = STOP_ABORT; have = false; continue; }
-        if (q.din || q.din_send) {
-          // The previous rank published its buffers for this invocation before it notified anything
-          // (the counter just seen).  Read once per stay of the collective in hand.
-          if (prev_recv == 0) {
-            const Slot<AUX_DEVICE> line((const void*)tail_in, DFX_FLAG_STRIDE);
-            uint4 w = uint4{0, 0, 0, 0}, w2 = w;
-            for (uint32_t tries = 0; tries < 1024u; ++tries) {
-              w = line.ld16(DFX_DIRECT_OFF);
-              w2 = line.ld16(DFX_DIRECT_OFF + 16);
-              if (w.z == inv_seq + 1u && w2.z == inv_seq + 1u) break;
-              __builtin_amdgcn_s_sleep(2);
+        return true;
+      };
+      auto wait_traced = [&]() {
+        if (hot.trace_on > 1) { const u64 tm1 = wall_clock64(); if (lane == 0) bump(sh.stat, ST_T_WAIT, tm1 - tm0); }
+      };
+
+      uint32_t res = W_OK, bytes = 0;
+      SeqPos nx;
+      bool last;
+      if (fold) {
+        // ================= fold steps =================
+        nx = next_fold_position(s_rounds, g, p, cidx);
+        last = nx.g >= s_rounds;
+        if (p == 0) {
+          // The step with data waits until every rank's line carries this invocation's tag, lane k looking at the line of
+          // entry k's rank, so that the poll that succeeds has brought the addresses along.  (Lanes without an entry
+          // look at the first line: no branch around the loads, and none of their registers meets another path's.)
+          const uint32_t line_off = lane < R ? fold_peer(kind, R, rank, K, lane) * inv_nchan * DFX_FLAG_STRIDE : 0u;
+          const __amdgpu_buffer_rsrc_t lines = __builtin_amdgcn_make_buffer_rsrc((void*)s_fin, 0, (int)(R * inv_nchan * DFX_FLAG_STRIDE), 0x00020000);
+          uint4 ln_recv, ln_send;
+          auto poll = [&]() {
+            asm volatile("" ::: "memory");     // (these loads are made anew at every poll)
+            ln_recv = rs_ld16(lines, line_off + DFX_DIRECT_OFF);
+            ln_send = rs_ld16(lines, line_off + DFX_DIRECT_OFF + 16);
+          };
+          poll();
+          const uint4 v0 = sv[0], v1 = sv[1], v2 = sv[2];   // pieces' begin, stride | share, length | source offset, destination offset
+          const FoldGeom fg = fold_geometry(bcast64(v1.x, v1.y), bcast64(v1.z, v1.w), bcast64(v2.x, v2.y), s_slice, bcast0(v0.x), bcast0(v0.y), g);
+          bytes = bcast0(v0.z);
+          look_ahead();
+          res = wait_until(poll, [&]() { return lane >= R || (ln_recv.z == inv_seq + 1u && ln_send.z == inv_seq + 1u); });
+          if (res == W_OK) {
+            wait_traced();
+            // (under priority ordering a step with data, which is one long job, waits until the movers have nothing
+            // else: what is posted cannot be overtaken by a more urgent collective that arrives)
+            if (!flight_free(hot.order_policy == 1 ? 1u : 2u)) { stop = STOP_ABORT; have = false; continue; }
+            const bool copies = fold_copies(kind), to_all = fold_to_all(kind);
+            const uint32_t fs = posted & 1;
+            if (lane < R) {
+              const u64 src = (((u64)ln_send.y << 32) | ln_send.x) + fg.src, dst = (((u64)ln_recv.y << 32) | ln_recv.x) + fg.dst;
+              if (!copies) sh.tab_src[fs][lane] = src;
+              else if (lane + 1 == R) sh.tab_src[fs][0] = src;
+              if (to_all) sh.tab_dst[fs][lane] = dst;
+              else if (lane + 1 == R) sh.tab_dst[fs][0] = dst;
             }
-            if (w.z != inv_seq + 1u || w2.z != inv_seq + 1u) { raise_error(a, 3u, wg); stop = STOP_ABORT; have = false; continue; }
-            prev_recv = ((u64)w.y << 32) | w.x;
-            prev_send = ((u64)w2.y << 32) | w2.x;
+            __builtin_amdgcn_wave_barrier();
+            if (lane == 0) {
+              Job j;
+              j.fin = nullptr; j.fout = nullptr; j.sb = nullptr; j.rb = nullptr;
+              j.bytes = fg.bytes; j.first = fg.first; j.stride = fg.stride;
+              j.nsrc = copies ? 1u : R; j.ndst = to_all ? R : 1u;
+              j.dtype = dtype; j.coll = coll; j.prim = 0;
+              sh.job[fs] = j;
+              Flight f;
+              f.tail_out = nullptr; f.head_in = nullptr; f.sent_new = 0; f.recvd_new = 0;
+              f.last = 0; f.coll = coll; f.seq = inv_seq; f.nchan = inv_nchan;
+              f.add_one = (u64*)s_in + DFX_FOLD_RED / 8;
+              sh.fl[fs] = f;
+              lds_st(&sh.job_seq, posted + 1);
+            }
+            ++posted;
           }
-          jfin = q.din_send ? (const void*)((const char*)prev_send + soff * eb) : (const void*)((const char*)prev_recv + doff * eb);
-        }
-        uint32_t jnsrc = 0, jndst = 0;
-        if (q.fold == 1) {
-          // the addresses that the poll has brought: lane k holds those of entry k's rank (fold_peer)
-          const int kd = (int)S.kind;
-          const bool copies = fold_copies(kd), to_all = fold_to_all(kd);
-          if (lane < a.R) {
-            const u64 src = (((u64)ln_send.y << 32) | ln_send.x) + fg.soff * fg.eb, dst = (((u64)ln_recv.y << 32) | ln_recv.x) + fg.doff * fg.eb;
-            if (!copies) sh.tab_src[posted & 1][lane] = src;
-            else if (lane + 1 == a.R) sh.tab_src[posted & 1][0] = src;
-            if (to_all) sh.tab_dst[posted & 1][lane] = dst;
-            else if (lane + 1 == a.R) sh.tab_dst[posted & 1][0] = dst;
+        } else {
+          // The last wait moves nothing, and the counter it has seen says that every rank's data step of this channel
+          // -- this workgroup's own job included -- is in memory: the completion is posted here and now instead of
+          // queueing as an empty job behind the data jobs of other collectives.
+          u64 seen_cnt;
+          auto poll = [&]() { seen_cnt = ld_agent64((const u64*)s_in + DFX_FOLD_RED / 8); };
+          poll();
+          look_ahead();
+          res = wait_until(poll, [&]() { return seen_cnt >= s_fout; });
+          if (res == W_OK) {
+            wait_traced();
+            if (lane == 0) { bump(sh.stat, ST_PRIMS, 1); complete(coll, inv_seq, inv_nchan, true); }
           }
-          __builtin_amdgcn_wave_barrier();
-          jnsrc = copies ? 1u : a.R; jndst = to_all ? a.R : 1u;
         }
-        // ---- post the slice (an empty one is only a handshake: the movers just raise the counters);
-        // this claims the slots: the data follows, the counters after it
-        if (q.send || q.notify) ++sent;
-        if (q.recv) ++recvd;
-        if (done_here) {
-          if (lane == 0) { bump(sh.stat, ST_PRIMS, 1); complete(coll, inv_seq, inv_nchan, true); }
-        } else if (lane == 0) {
-          Job j;
-          j.fin = jfin; j.fout = jfout; j.sb = jsb; j.rb = jrb;
-          j.bytes = (q.drain || (!q.recv && !q.from_send)) ? 0u : bytes;   // drain and notify-only steps move nothing
-          if (q.fold) { j.bytes = fg.bytes; j.first = fg.first; j.stride = fg.stride; }
-          else j.first = j.stride = 0;
-          j.nsrc = jnsrc; j.ndst = jndst;
-          j.dtype = dtype; j.coll = coll; j.prim = (q.drain || q.fold == 3) ? 0xffu : p;   // (prim: for the timeline only)
-          sh.job[posted & 1] = j;
-          Flight f;
-          f.tail_out = (q.send || q.notify) ? tail_out : nullptr; f.head_in = q.recv ? tail_in + 8 : nullptr;
-          f.sent_new = sent; f.recvd_new = recvd;
-          f.last = last ? 1u : 0u; f.coll = coll; f.seq = inv_seq; f.nchan = inv_nchan;
-          f.add_one = q.fadd ? tail_in + q.fadd : nullptr;
-          sh.fl[posted & 1] = f;
-          lds_st(&sh.job_seq, posted + 1);
+      } else {
+        // ================= rings and chains =================
+        const Prim q = chain_drain_round(make_prim(kind, R, bcp & 3u, p, (bcp & DFX_CTX_DIRECT) != 0), kind, (bcp & DFX_CTX_DIRECT) != 0, g, s_rounds);
+        u64* const tail_out = (u64*)S.flags_out;
+        u64* const tail_in = (u64*)s_in;
+        // Lane 0 polls the recv side, lane 1 the send side.  The first poll is sent off before the slice's geometry is
+        // worked out, which depends only on the sequence position: the arithmetic runs while the counters travel, and
+        // a poll that succeeds is followed by the job at once.
+        u64 seen_cnt = 0;
+        auto poll = [&]() {
+          if (lane == 0 && q.recv) seen_cnt = ld_agent64(tail_in);
+          if (lane == 1 && (q.send || q.drain)) seen_cnt = ld_agent64(tail_out + 8);
+        };
+        poll();
+
+        // ---- slice geometry and the job's four pointers, and the position after this primitive
+        const SliceGeom geo = slice_geometry(S, R, g, cidx);
+        const uint32_t eb = geo.eb;
+        const u64 soff = geo.soff, doff = geo.doff;
+        bytes = geo.bytes;
+        const size_t slot_bytes = (size_t)s_slice * eb;
+        const void* jfin = q.recv ? (const void*)((const uint8_t*)s_fin + (size_t)(recvd & (K - 1)) * slot_bytes) : nullptr;
+        void* jfout = q.send ? (void*)((uint8_t*)s_fout + (size_t)(sent & (K - 1)) * slot_bytes) : nullptr;
+        const char* jsb = q.from_send ? (const char*)S.sendbuf + soff * eb : nullptr;
+        char* jrb = q.to_recv ? (char*)S.recvbuf + doff * eb : nullptr;
+        // a notified result goes to the recv buffer through the coherent path of a slot
+        if (q.notify) { jfout = jrb; jrb = nullptr; }
+        // (slices in windows, the chunk index stepping down the ring)
+        nx = next_position(kind, R, rank, hot.window, s_rounds, s_n & 0xffffu, g, p, cidx);
+        last = nx.g >= s_rounds;
+        if (q.recv || q.send || q.drain) {
+          look_ahead();
+          res = wait_until(poll, [&]() {
+            bool ok = true;
+            if (lane == 0 && q.recv) ok = seen_cnt > recvd;
+            if (lane == 1 && q.send) ok = (sent - seen_cnt) < (u64)K;
+            if (lane == 1 && q.drain) ok = sent == seen_cnt;
+            return ok;
+          });
         }
-        g = g_next; p = p_next; cidx = cidx_next;
+        if (res == W_OK) {
+          wait_traced();
+          if (!flight_free(2u)) { stop = STOP_ABORT; have = false; continue; }
+          if (q.din || q.din_send) {
+            // The previous rank published its buffers for this invocation before it notified anything
+            // (the counter just seen).  Read once per stay of the collective in hand.
+            if (prev_recv == 0) {
+              const Slot<AUX_DEVICE> line((const void*)tail_in, DFX_FLAG_STRIDE);
+              uint4 w = uint4{0, 0, 0, 0}, w2 = w;
+              for (uint32_t tries = 0; tries < 1024u; ++tries) {
+                w = line.ld16(DFX_DIRECT_OFF);
+                w2 = line.ld16(DFX_DIRECT_OFF + 16);
+                if (w.z == inv_seq + 1u && w2.z == inv_seq + 1u) break;
+                __builtin_amdgcn_s_sleep(2);
+              }
+              if (w.z != inv_seq + 1u || w2.z != inv_seq + 1u) { raise_error(a, 3u, wg); stop = STOP_ABORT; have = false; continue; }
+              prev_recv = ((u64)w.y << 32) | w.x;
+              prev_send = ((u64)w2.y << 32) | w2.x;
+            }
+            jfin = q.din_send ? (const void*)((const char*)prev_send + soff * eb) : (const void*)((const char*)prev_recv + doff * eb);
+          }
+          // ---- post the slice (an empty one is only a handshake: the movers just raise the counters);
+          // this claims the slots: the data follows, the counters after it
+          if (q.send || q.notify) ++sent;
+          if (q.recv) ++recvd;
+          if (lane == 0) {
+            Job j;
+            j.fin = jfin; j.fout = jfout; j.sb = jsb; j.rb = jrb;
+            j.bytes = (q.drain || (!q.recv && !q.from_send)) ? 0u : bytes;   // drain and notify-only steps move nothing
+            j.first = j.stride = 0;
+            j.nsrc = 0; j.ndst = 0;
+            j.dtype = dtype; j.coll = coll; j.prim = q.drain ? 0xffu : p;   // (prim: for the timeline only)
+            sh.job[posted & 1] = j;
+            Flight f;
+            f.tail_out = (q.send || q.notify) ? tail_out : nullptr; f.head_in = q.recv ? tail_in + 8 : nullptr;
+            f.sent_new = sent; f.recvd_new = recvd;
+            f.last = last ? 1u : 0u; f.coll = coll; f.seq = inv_seq; f.nchan = inv_nchan;
+            f.add_one = nullptr;
+            sh.fl[posted & 1] = f;
+            lds_st(&sh.job_seq, posted + 1);
+          }
+          ++posted;
+        }
+      }
+
+      if (res == W_OK) {
+        g = nx.g; p = nx.p; cidx = nx.cidx;
         pass_bytes += bytes;
         progressed = true;
         pass_progress = true;
         acted = true;
         // AdaptivelyAdjustSpinThreshold (Alg. 1 line 9)
         if (!scanned) {
-          thr *= a.spin_boost;
-          if (thr > a.spin_max) thr = a.spin_max;
+          thr *= hot.spin_boost;
+          if (thr > hot.spin_max) thr = hot.spin_max;
         }
-        if (!done_here) ++posted;
-
         if (last) {
           // ---- CollectiveSuccess: the entry leaves the queue now; the completion counter and the
           // CQE follow at retirement, when the data is in memory
           if (lane == 0) {
             DfxDyn d; d.round = 0; d.prim = 0; d.sent = sent; d.recvd = recvd; d.preempted = 0; d.cidx = 0;
             sh.slot[sl].dyn = d;
-            myctx[coll].dyn = d;
+            st_ctx(&myctx[coll].dyn, d);
           }
           // later entries move up, the position stays (Sec. 4.3)
           --qlen;
@@ -1637,9 +1713,9 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
         }
       } else {
         // ---- PreemptCollective + SaveCollectiveContext (lazy: only if it progressed)
-        if (a.trace_on == 3 && trace && lane == 0)   // timeline sample of a wait that ended without the primitive: index 15
+        if (hot.trace_on == 3 && trace && lane == 0)   // timeline sample of a wait that ended without the primitive: index 15
           trace_put(trace, &sh.trace_n, timeline_sample(tm0, wall_clock64(), coll, 15));
-        const bool tr = a.trace_on && res == W_TIMEOUT && pos + 1 < qlen;
+        const bool tr = hot.trace_on && res == W_TIMEOUT && pos + 1 < qlen;
         if (tr) sw_t0 = wall_clock64();
         if (lane == 0) {
           if (res == W_TIMEOUT) bump(sh.stat, ST_PREEMPT, 1);
@@ -1647,11 +1723,11 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             DfxDyn d; d.round = g; d.prim = p; d.sent = sent; d.recvd = recvd;
             d.preempted = sh.slot[sl].dyn.preempted + 1; d.cidx = cidx;
             sh.slot[sl].dyn = d;
-            myctx[coll].dyn = d;
+            st_ctx(&myctx[coll].dyn, d);
             bump(sh.stat, ST_SAVE, 1);
           } else if (res == W_TIMEOUT) bump(sh.stat, ST_LAZY, 1);
         }
-        if (tr) { if (a.trace_on > 1) sw_ts = wall_clock64(); sw_pending = true; }
+        if (tr) { if (hot.trace_on > 1) sw_ts = wall_clock64(); sw_pending = true; }
         have = false;
         if (res == W_STOP) { stop = STOP_ABORT; continue; }
         if (scanned) ++rk; else ++pos;
@@ -1659,7 +1735,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           // LoadCollectiveContext of the entry looked up during the wait (the same steps as at the head of the
           // loop): its context is in its slot and the dynamic part in registers, or the load is under way and
           // goes into the slot now
-          pos = nx_pos; coll = nx_coll; sl = nx_sl;
+          pos = bcast0(nx_pos); coll = bcast0(nx_coll); sl = bcast0(nx_sl);
           if (nx_hit) {
             if (lane == 0) bump(sh.stat, ST_HIT, 1);
           } else {
@@ -1668,13 +1744,14 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             __builtin_amdgcn_wave_barrier();
             nx_dyn = sh.slot[sl].dyn;
           }
-          g = nx_dyn.round; p = nx_dyn.prim; sent = nx_dyn.sent; recvd = nx_dyn.recvd; cidx = nx_dyn.cidx;
-          thr = a.spin_init >> (pos < 31 ? pos : 31);
-          if (thr < a.spin_min || scanned) thr = a.spin_min;
+          g = bcast0(nx_dyn.round); p = bcast0(nx_dyn.prim); cidx = bcast0(nx_dyn.cidx);
+          sent = bcast64((uint32_t)nx_dyn.sent, (uint32_t)(nx_dyn.sent >> 32)); recvd = bcast64((uint32_t)nx_dyn.recvd, (uint32_t)(nx_dyn.recvd >> 32));
+          thr = hot.spin_init >> (pos < 31 ? pos : 31);
+          if (thr < hot.spin_min || scanned) thr = hot.spin_min;
           progressed = false;
           prev_recv = 0;
           have = true;
-          if (sw_pending && a.trace_on > 1) { sw_lb = wall_clock64(); sw_le = sw_lb; }
+          if (sw_pending && hot.trace_on > 1) { sw_lb = wall_clock64(); sw_le = sw_lb; }
         }
       }
     }

@@ -37,10 +37,12 @@ DFX_HD WgPlace wg_place(uint32_t wg_map, uint32_t wg, uint32_t R, uint32_t cmax)
 // cmax, so that many small collectives spread over the rank's workgroups instead of queueing on the
 // first ones; every rank derives the same start from the id, which keeps both ends of a connector on
 // the same channel.
-DFX_HD uint32_t serving_channel(bool spread, uint32_t ch, uint32_t cmax, uint32_t coll_id, uint32_t nchan) {
-  if (spread && nchan < cmax) return (ch + cmax - (coll_id * nchan) % cmax) % cmax;
-  return ch;
+// The start is worked out where the collective is planned and travels in its entries (DfxStatic::start): a workgroup
+// that reads an entry only subtracts.
+DFX_HD uint32_t start_channel(bool spread, uint32_t cmax, uint32_t coll_id, uint32_t nchan) {
+  return spread && nchan < cmax ? (coll_id * nchan) % cmax : 0u;
 }
+DFX_HD uint32_t serving_channel(uint32_t ch, uint32_t cmax, uint32_t start) { return ch >= start ? ch - start : ch + cmax - start; }
 
 // primitive descriptor for (kind, position p in the sequence); the ring-chunk index travels in
 // the dynamic context and is stepped by next_cidx, so nothing here divides
@@ -108,12 +110,19 @@ DFX_HD bool fold_to_all(int kind) { return kind != KIND_RS && kind != KIND_RD; }
 // per rank and 22.5 us for 8 MiB, in pieces 78 and 20 us (fp32, R = 8; 256 MiB 845 -> 830 us).
 // The bytes behind the last whole 16 of a span belong to the workgroup whose pieces begin at 0.
 constexpr uint32_t DFX_FOLD_PIECE = DFX_MOVERS * 16u;
-struct FoldGeom { uint64_t soff, doff; uint32_t bytes, first, stride, eb; };
-DFX_HD FoldGeom fold_geometry(const DfxCooked& S, uint32_t R, uint32_t rank, uint32_t g) {
-  const int kind = S.kind, dt = S.dtype & 15;
-  FoldGeom o;
-  o.eb = (dt == DT_F32 || dt == DT_I32) ? 4u : 2u;
-  const uint64_t count = S.count, block = S.block_elems, span = (uint64_t)S.nchan * S.slice_elems;
+
+// The entry (SQE) of a collective in fold steps for one rank, from its plan in elements: everything about the rank's
+// part that does not depend on the channel, in bytes, so that the workgroups that read the entry multiply nothing.
+//   count       length of the rank's region (its chunk or block, or the stretch that all ranks share)
+//   block_elems where the region begins in the send buffers it is read from
+//   part_elems  where it begins in the recv buffers it is written to
+//   slice_elems span of one slice, all channels together (at most 1 GiB)
+//   slot_bytes  stride of a workgroup's pieces
+//   share       one channel's part of a slice
+DFX_HD void fold_entry(DfxStatic& e, uint32_t R, uint32_t rank) {
+  const int kind = e.kind;
+  const uint64_t eb = (e.dtype == DT_F32 || e.dtype == DT_I32) ? 4u : 2u;
+  const uint64_t count = e.count, block = e.block_elems;
   // a chunk or block of its own for every rank, or one stretch that all ranks' workgroups share
   const bool chunks = kind == KIND_AR || (kind == KIND_RD && block != count);
   const bool shared = kind == KIND_BC || (kind == KIND_RD && !chunks);
@@ -122,16 +131,25 @@ DFX_HD FoldGeom fold_geometry(const DfxCooked& S, uint32_t R, uint32_t rank, uin
     start = (uint64_t)rank * block;
     len = start >= count ? 0 : (count - start < block ? count - start : block);
   }
-  const uint64_t lo = (uint64_t)g * span < len ? (uint64_t)g * span : len;
-  const uint64_t n = len - lo < span ? len - lo : span;
-  o.soff = o.doff = start + lo;
-  if (kind == KIND_RS) o.soff += (uint64_t)rank * count;
-  if (kind == KIND_AG) o.doff += (uint64_t)rank * count;
-  o.bytes = (uint32_t)n * o.eb;
-  const uint32_t sharers = shared ? S.nchan * R : S.nchan;
-  o.first = (shared ? S.vch * R + rank : (uint32_t)S.vch) * DFX_FOLD_PIECE;
-  o.stride = sharers * DFX_FOLD_PIECE;
+  e.count = len * eb;
+  e.block_elems = (start + (kind == KIND_RS ? (uint64_t)rank * count : 0u)) * eb;
+  e.part_elems = (start + (kind == KIND_AG ? (uint64_t)rank * count : 0u)) * eb;
+  e.share = (uint32_t)(e.slice_elems * eb);
+  e.slice_elems = (uint32_t)(e.nchan * (e.slice_elems * eb));
+  e.slot_bytes = (shared ? e.nchan * R : e.nchan) * DFX_FOLD_PIECE;
+}
+
+struct FoldGeom { uint64_t src, dst; uint32_t bytes, first, stride; };   // byte offsets in the buffers; span, pieces
+DFX_HD FoldGeom fold_geometry(uint64_t len, uint64_t src, uint64_t dst, uint32_t span, uint32_t first, uint32_t stride, uint32_t g) {
+  FoldGeom o;
+  const uint64_t at = (uint64_t)g * span, lo = at < len ? at : len, n = len - lo;
+  o.src = src + lo; o.dst = dst + lo;
+  o.bytes = n < span ? (uint32_t)n : span;
+  o.first = first; o.stride = stride;
   return o;
+}
+DFX_HD FoldGeom fold_geometry(const DfxCooked& S, uint32_t g) {
+  return fold_geometry(S.count, S.block_elems, S.part_elems, S.slice_elems, (uint32_t)S.sendbuf, (uint32_t)(S.sendbuf >> 32), g);
 }
 
 // Where a fold collective's lines are, from a workgroup's own line: the line of rank r on the same channel,
@@ -250,7 +268,12 @@ DFX_HD DfxCooked cook_sqe(const DfxStatic& q, uint8_t* pool, uint32_t rank, uint
     // the others follow nchan lines apart) and what the counter of finished steps shows at the end of this invocation
     k.fifo_in = fold_line(k.flags_out, rank, 0, q.nchan);
     k.flags_in = (q.flags & DFX_SQE_LONG) ? k.fifo_in + DFX_FOLD_HEAD : fold_shared_line(k.flags_out, rank, R, q.nchan);
-    k.fifo_out = ((uint64_t)q.seq + 1u) * R * q.rounds;
+    k.fifo_out = ((uint64_t)q.seq + 1u) * (R * q.rounds);
+    // the buffers' addresses travel through the lines: the words carry where the workgroup's pieces begin and their
+    // stride, and a channel's part of a slice
+    const uint32_t first = (q.slot_bytes != q.nchan * DFX_FOLD_PIECE ? vch * R + rank : vch) * DFX_FOLD_PIECE;
+    k.sendbuf = (uint64_t)q.slot_bytes << 32 | first;
+    k.recvbuf = q.share;
   }
   k.slice_elems = q.slice_elems; k.rounds = q.rounds; k.seq = q.seq;
   k.nprim = (uint16_t)q.nprim; k.nchan = q.nchan;

@@ -441,6 +441,7 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   t.nchan = (uint16_t)C;
   t.kind = (uint8_t)kind; t.dtype = (uint8_t)dtype; t.op = (uint8_t)op; t.root = (uint8_t)(rooted ? root : 0);
   t.priority = (int16_t)priority;
+  t.start = start_channel(cfg.chan_spread != 0, cfg.max_channels, (uint32_t)coll_id, (uint32_t)C);
   if (R == 1) t.nprim = 1;
   else if (fold) {
     t.flags |= DFX_SQE_DIRECT | DFX_SQE_FOLD;   // (buffers are published as for the direct steps)
@@ -703,6 +704,7 @@ int stage_one(dfx_ctx* c, int rank, uint32_t ahead, int coll_id, const void* sen
   }
   if (!sqe_slot_free(c, rank, ahead)) return DFX_ERR_SQ_FULL;
   DfxStatic e = ci.tmpl;
+  if (e.flags & DFX_SQE_FOLD) fold_entry(e, (uint32_t)c->R, (uint32_t)rank);
   e.seq = rs->sub[coll_id];
   e.sendbuf = (uint64_t)(uintptr_t)sendbuf;
   e.recvbuf = (uint64_t)(uintptr_t)recvbuf;
@@ -1177,13 +1179,14 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
     int& o = owner[(size_t)w.rank * cmax + w.ch];
     if (o >= 0) return fail("workgroups %d and %u both map to rank %u channel %u", o, wg, w.rank, w.ch);
     o = (int)wg;
-    const uint32_t vch = serving_channel(cfg.chan_spread != 0, w.ch, cmax, (uint32_t)coll_id, t.nchan);
+    const uint32_t vch = serving_channel(w.ch, cmax, t.start);
     if (vch >= t.nchan) continue;
     int& sv = serves[(size_t)w.rank * t.nchan + vch];
     if (sv >= 0) return fail("rank %u channel %u of the collective is served by workgroups %d and %u", w.rank, vch, sv, wg);
     sv = (int)wg;
     DfxStatic q = t;
     q.sendbuf = sendbase(w.rank); q.recvbuf = recvbase(w.rank);
+    if (fold) fold_entry(q, R, w.rank);
     cooked[(size_t)w.rank * t.nchan + vch] = cook_sqe(q, (uint8_t*)(uintptr_t)pool, w.rank, R, vch);
   }
   for (size_t i = 0; i < serves.size(); ++i)
@@ -1232,9 +1235,9 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
           const Prim fq = make_fold_prim(p);
           if (fq.fold == 1) {
             const uint32_t rt = S.nslots;      // the root
-            const FoldGeom fg = fold_geometry(S, R, r, g);
+            const FoldGeom fg = fold_geometry(S, g);
             const bool copies = fold_copies(kind), to_all = fold_to_all(kind);
-            const uint64_t src = fg.soff * fg.eb, dst = fg.doff * fg.eb;
+            const uint64_t src = fg.src, dst = fg.dst;
             if (R > 64) return fail("%u table entries for 64 lanes", R);
             if (fg.bytes > (1u << 30) || fg.first % 16 || fg.stride % 16 || !fg.stride) return fail("rank %u channel %u: a span of %u bytes, pieces from %u every %u", r, v, fg.bytes, fg.first, fg.stride);
             if (fg.bytes && ((src | dst) & 15u)) return fail("rank %u channel %u step %u: 16-byte accesses at offsets %llu, %llu", r, v, p, (unsigned long long)src, (unsigned long long)dst);
@@ -1387,6 +1390,7 @@ __global__ void __launch_bounds__(64) dfx_na_seed_kernel(DfxSqSlot* sq, NaSeed s
   const uint32_t r = threadIdx.x;
   if (r >= sd.nranks) return;
   DfxStatic e = sd.tmpl;
+  if (e.flags & DFX_SQE_FOLD) fold_entry(e, sd.nranks, r);
   e.seq = 0;
   e.sendbuf = sd.sendbuf[r];
   e.recvbuf = sd.recvbuf[r];

@@ -55,8 +55,8 @@ struct alignas(16) DfxStatic {
   uint16_t flags;
   int16_t priority;
   uint32_t nprim;        // primitives per round on every rank
-  uint32_t reserved;
-  uint32_t reserved2;
+  uint32_t start;        // channel of the grid that serves channel 0 (start_channel)
+  uint32_t share;        // fold steps only (fold_entry, which also gives other words a meaning in bytes)
   uint32_t ready;        // SQ only, written last: generation of the entry
 };
 static_assert(sizeof(DfxStatic) == 96, "DfxStatic must be 96 bytes");
@@ -76,7 +76,7 @@ static_assert(sizeof(DfxDyn) == 32, "DfxDyn must be 32 bytes");
 // What a workgroup keeps of an invocation (device-private): the SQE "cooked" once at fetch time
 // into ready-to-use addresses, so that a context load needs no address arithmetic.  96 bytes.
 struct alignas(16) DfxCooked {
-  uint64_t sendbuf, recvbuf, count, block_elems, part_elems;
+  uint64_t sendbuf, recvbuf, count, block_elems, part_elems;   // fold steps: pieces' begin and stride, share, and the byte offsets of fold_entry
   uint64_t flags_out;    // tail counter of my send connector (head at +64 bytes)
   uint64_t flags_in;     // tail counter of my recv connector (head at +64 bytes); fold steps: the channel's shared counters
   uint64_t fifo_out;     // first slot of my send connector; fold steps: DFX_FOLD_RED at the end of this invocation
@@ -90,7 +90,7 @@ struct alignas(16) DfxCooked {
 };
 static_assert(sizeof(DfxCooked) == 96, "DfxCooked must be 96 bytes");
 // (the scheduler reads some of it as 16-byte words: the readiness scan and the set-up of a primitive)
-static_assert(offsetof(DfxCooked, part_elems) == 32 && offsetof(DfxCooked, flags_out) == 40 && offsetof(DfxCooked, flags_in) == 48 &&
+static_assert(offsetof(DfxCooked, count) == 16 && offsetof(DfxCooked, block_elems) == 24 && offsetof(DfxCooked, part_elems) == 32 && offsetof(DfxCooked, flags_out) == 40 && offsetof(DfxCooked, flags_in) == 48 &&
               offsetof(DfxCooked, fifo_out) == 56 && offsetof(DfxCooked, fifo_in) == 64 && offsetof(DfxCooked, slice_elems) == 72 && offsetof(DfxCooked, rounds) == 76 &&
               offsetof(DfxCooked, seq) == 80 && offsetof(DfxCooked, nprim) == 84 && offsetof(DfxCooked, nchan) == 86 &&
               offsetof(DfxCooked, nslots) == 88 && offsetof(DfxCooked, kind) == 89 && offsetof(DfxCooked, dtype) == 90 &&

@@ -518,52 +518,84 @@ __device__ __forceinline__ void rs_st16(__amdgpu_buffer_rsrc_t r, uint32_t off, 
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, (int)off, 0, AUX_DEVICE);        // out of range stores are dropped
 }
 
+// The rows of a job that one mover wave takes (see fold_row_bytes): dealt (ctr null) or drawn.
+struct Rows {
+  GLOBAL_AS uint32_t* ctr;   // the region's row counter
+  uint32_t waves;            // mover waves of all the region's workgroups
+  uint32_t row;              // the row in hand
+  uint32_t left;             // rows this wave may still take in the job, the one in hand included (0xffffffff = no limit)
+  uint32_t drawn;            // lane 0: the answer to the last draw
+  // Begin: the first job of a share starts with the wave's own row, later ones draw theirs.
+  __device__ __forceinline__ void begin(bool fresh, uint32_t wave_index) {
+    if (fresh) row = wave_index;
+    else { draw(); row = waves + (uint32_t)__builtin_amdgcn_readfirstlane(drawn); }
+  }
+  __device__ __forceinline__ void draw() {
+    if ((threadIdx.x & 63u) == 0) drawn = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, SCOPE_AGENT);
+  }
+  // Ahead of the row's loads: the next draw sets off (its answer arrives before the data does).
+  __device__ __forceinline__ void prefetch() { if (ctr && left > 1) draw(); }
+  // Behind the row: on to the next; false = the job is over for this wave.
+  __device__ __forceinline__ bool next() {
+    if (left == 1) return false;
+    if (left != 0xffffffffu) --left;
+    row = ctr ? waves + (uint32_t)__builtin_amdgcn_readfirstlane(drawn) : row + waves;
+    return true;
+  }
+};
+
 // dst[d][i] = src[0][i] (op) src[1][i] (op) ... (op) src[nsrc-1][i], left to right, for every destination d: the
-// source table lists the ranks in the ring's order of combination.  The workgroup's pieces of the span (FoldGeom):
-// `first`, `first + stride`, ... up to `bytes`.  Sources are other ranks' send buffers: device-coherent loads; the
-// destinations are recv buffers of this and of other ranks, whose workgroups post the completion: device-coherent
-// stores, which are in memory when the step counts itself done.
+// source table lists the ranks in the ring's order of combination.  Sources are other ranks' send buffers:
+// device-coherent loads; the destinations are recv buffers of this and of other ranks, whose workgroups post the
+// completion: device-coherent stores, which are in memory when the step counts itself done.
 //
 // What bounds it is HBM (2R streams, every byte once).  About sixteen 16-byte loads are in flight per thread whatever
 // the number of sources; with 2, 4 or 8 of them (and as many destinations, or one) all buffer resources stay in
 // scalar registers over the whole job (looked up for every round they cost 0.4 us per round and side: the one job of
-// an 8 KiB all-reduce took 3.4 us, now 1.7; a 25 MiB bf16 bucket, with the pieces below, 92 -> 75 us).  A buffer's resource ends with the last whole 16 bytes of the span: loads
-// behind it return 0 and stores behind it are dropped, so the last round needs no predicates.
+// an 8 KiB all-reduce took 3.4 us, now 1.8; a 25 MiB bf16 bucket, with the rows, 92 -> 75 us).  A buffer's
+// resource ends with the last whole 16 bytes of the span: loads behind it return 0 and stores behind it are dropped, so
+// the last row needs no predicates.
 // Next round's loads before this round's combine, 512 movers, non-temporal or plain cached accesses measured the
 // same (838-845 us for 256 MiB per rank, fp32, R = 8) or, non-temporal below the size of the memory-side cache,
 // worse (8 MiB: 25 against 20.5 us).
-template <int DT, int NS, bool ALL, int NTH>
-__device__ __forceinline__ void fold_fixed(const u64* src_tab, const u64* dst_tab, uint32_t whole, uint32_t first, uint32_t stride,
-                                           uint32_t tid, int op) {
-  constexpr int U = 16 / NS, ND = ALL ? NS : 1;
+template <int DT, int NS, bool ALL>
+__device__ __forceinline__ void fold_fixed(const u64* src_tab, const u64* dst_tab, uint32_t whole, Rows& rows, uint32_t lane, int op) {
+  constexpr int U = 16 / NS, ND = ALL ? NS : 1;      // (fold_row_bytes)
   __amdgpu_buffer_rsrc_t S[NS], D[ND];
 #pragma unroll
   for (int k = 0; k < NS; ++k) S[k] = uniform_rsrc(src_tab[k], whole);
 #pragma unroll
   for (int k = 0; k < ND; ++k) D[k] = uniform_rsrc(dst_tab[k], whole);
-  for (uint32_t at = first; at < whole; at += U * stride) {
-    const uint32_t o = at + tid * 16u;
+  for (;;) {
+    const uint32_t at = rows.row * (U * 1024u);
+    if (at >= whole) break;
+    rows.prefetch();
+    const uint32_t o = at + lane * 16u;
     uint4 w[NS][U];
 #pragma unroll
     for (int k = 0; k < NS; ++k)
 #pragma unroll
-      for (int u = 0; u < U; ++u) w[k][u] = rs_ld16(S[k], o + u * stride);
+      for (int u = 0; u < U; ++u) w[k][u] = rs_ld16(S[k], o + u * 1024u);
 #pragma unroll
     for (int k = 1; k < NS; ++k) op_batch<DT, U>(w[0], w[k], op);
 #pragma unroll
     for (int k = 0; k < ND; ++k)
 #pragma unroll
-      for (int u = 0; u < U; ++u) rs_st16(D[k], o + u * stride, w[0][u]);
+      for (int u = 0; u < U; ++u) rs_st16(D[k], o + u * 1024u, w[0][u]);
+    if (!rows.next()) break;
   }
 }
 
 // the same for any number of sources and destinations: addresses out of the tables as they are needed
-template <int DT, int NTH>
+template <int DT>
 __device__ __forceinline__ void fold_any(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, uint32_t whole,
-                                         uint32_t first, uint32_t stride, uint32_t tid, int op) {
-  constexpr int U = 2, NS = 8;      // vectors per source and sources in flight
-  for (uint32_t at = first; at < whole; at += U * stride) {
-    const uint32_t o = at + tid * 16u;
+                                         Rows& rows, uint32_t lane, int op) {
+  constexpr int U = 2, NS = 8;      // vectors per source (fold_row_bytes) and sources in flight
+  for (;;) {
+    const uint32_t at = rows.row * (U * 1024u);
+    if (at >= whole) break;
+    rows.prefetch();
+    const uint32_t o = at + lane * 16u;
     uint4 acc[U];
     for (uint32_t base = 0; base < nsrc; base += NS) {
       uint4 w[NS][U];
@@ -572,7 +604,7 @@ __device__ __forceinline__ void fold_any(const u64* src_tab, uint32_t nsrc, cons
         if (base + k < nsrc) {
           const __amdgpu_buffer_rsrc_t r = uniform_rsrc(src_tab[base + k], whole);
 #pragma unroll
-          for (int u = 0; u < U; ++u) w[k][u] = rs_ld16(r, o + u * stride);
+          for (int u = 0; u < U; ++u) w[k][u] = rs_ld16(r, o + u * 1024u);
         }
       }
 #pragma unroll
@@ -588,48 +620,52 @@ __device__ __forceinline__ void fold_any(const u64* src_tab, uint32_t nsrc, cons
     for (uint32_t d = 0; d < ndst; ++d) {
       const __amdgpu_buffer_rsrc_t r = uniform_rsrc(dst_tab[d], whole);
 #pragma unroll
-      for (int u = 0; u < U; ++u) rs_st16(r, o + u * stride, acc[u]);
+      for (int u = 0; u < U; ++u) rs_st16(r, o + u * 1024u, acc[u]);
     }
+    if (!rows.next()) break;
   }
 }
 
 // One source handed out to every destination (all-gather, broadcast): ND destinations, or any number (ND = 0).
 // What bounds it is the writes (R per byte read).  Reading once instead of every rank reading everything (R reads and R
 // writes per byte): host to host, bf16, R = 8, broadcast of 100 MiB 270 -> 208 us, all-gather of 32 MiB 104 -> 80 us.
-template <int ND, int NTH>
-__device__ __forceinline__ void fold_copy(const u64* src_tab, const u64* dst_tab, uint32_t ndst, uint32_t whole, uint32_t first,
-                                          uint32_t stride, uint32_t tid) {
-  constexpr int U = 4;
+template <int ND>
+__device__ __forceinline__ void fold_copy(const u64* src_tab, const u64* dst_tab, uint32_t ndst, uint32_t whole, Rows& rows, uint32_t lane) {
+  constexpr int U = 4;              // (fold_row_bytes)
   const __amdgpu_buffer_rsrc_t S = uniform_rsrc(src_tab[0], whole);
   __amdgpu_buffer_rsrc_t D[ND ? ND : 1];
 #pragma unroll
   for (int k = 0; k < ND; ++k) D[k] = uniform_rsrc(dst_tab[k], whole);
-  for (uint32_t at = first; at < whole; at += U * stride) {
-    const uint32_t o = at + tid * 16u;
+  for (;;) {
+    const uint32_t at = rows.row * (U * 1024u);
+    if (at >= whole) break;
+    rows.prefetch();
+    const uint32_t o = at + lane * 16u;
     uint4 w[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) w[u] = rs_ld16(S, o + u * stride);
+    for (int u = 0; u < U; ++u) w[u] = rs_ld16(S, o + u * 1024u);
     if (ND) {
 #pragma unroll
       for (int k = 0; k < ND; ++k)
 #pragma unroll
-        for (int u = 0; u < U; ++u) rs_st16(D[k], o + u * stride, w[u]);
+        for (int u = 0; u < U; ++u) rs_st16(D[k], o + u * 1024u, w[u]);
     } else {
       for (uint32_t d = 0; d < ndst; ++d) {
         const __amdgpu_buffer_rsrc_t r = uniform_rsrc(dst_tab[d], whole);
 #pragma unroll
-        for (int u = 0; u < U; ++u) rs_st16(r, o + u * stride, w[u]);
+        for (int u = 0; u < U; ++u) rs_st16(r, o + u * 1024u, w[u]);
       }
     }
+    if (!rows.next()) break;
   }
 }
 
 // the bytes behind the last whole 16 of a span, element by element (fold or copy)
-template <int DT, int NTH>
+template <int DT>
 __device__ __forceinline__ void fold_tail(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, uint32_t whole,
-                                          uint32_t bytes, uint32_t tid, int op) {
+                                          uint32_t bytes, uint32_t lane, int op) {
   constexpr uint32_t EB = (DT == DT_F32 || DT == DT_I32) ? 4u : 2u;
-  const uint32_t o = whole + tid * EB;
+  const uint32_t o = whole + lane * EB;
   if (o >= bytes) return;
   uint32_t v = 0;
   for (uint32_t k = 0; k < nsrc; ++k) {
@@ -646,39 +682,39 @@ __device__ __forceinline__ void fold_tail(const u64* src_tab, uint32_t nsrc, con
 }
 
 // A reduction has one source per rank and one destination, or as many destinations as sources.
-template <int DT, int NTH>
+template <int DT>
 __device__ __forceinline__ void fold_reduce(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, uint32_t bytes,
-                                            uint32_t first, uint32_t stride, uint32_t tid, int op) {
+                                            bool tail, Rows& rows, uint32_t lane, int op) {
   const uint32_t whole = bytes & ~15u;
   const bool all = ndst > 1;
-  if (nsrc == 8 && all) fold_fixed<DT, 8, true, NTH>(src_tab, dst_tab, whole, first, stride, tid, op);
-  else if (nsrc == 8) fold_fixed<DT, 8, false, NTH>(src_tab, dst_tab, whole, first, stride, tid, op);
-  else if (nsrc == 4 && all) fold_fixed<DT, 4, true, NTH>(src_tab, dst_tab, whole, first, stride, tid, op);
-  else if (nsrc == 4) fold_fixed<DT, 4, false, NTH>(src_tab, dst_tab, whole, first, stride, tid, op);
-  else if (nsrc == 2 && all) fold_fixed<DT, 2, true, NTH>(src_tab, dst_tab, whole, first, stride, tid, op);
-  else if (nsrc == 2) fold_fixed<DT, 2, false, NTH>(src_tab, dst_tab, whole, first, stride, tid, op);
-  else fold_any<DT, NTH>(src_tab, nsrc, dst_tab, ndst, whole, first, stride, tid, op);
-  if (whole < bytes && first == 0) fold_tail<DT, NTH>(src_tab, nsrc, dst_tab, ndst, whole, bytes, tid, op);
+  if (nsrc == 8 && all) fold_fixed<DT, 8, true>(src_tab, dst_tab, whole, rows, lane, op);
+  else if (nsrc == 8) fold_fixed<DT, 8, false>(src_tab, dst_tab, whole, rows, lane, op);
+  else if (nsrc == 4 && all) fold_fixed<DT, 4, true>(src_tab, dst_tab, whole, rows, lane, op);
+  else if (nsrc == 4) fold_fixed<DT, 4, false>(src_tab, dst_tab, whole, rows, lane, op);
+  else if (nsrc == 2 && all) fold_fixed<DT, 2, true>(src_tab, dst_tab, whole, rows, lane, op);
+  else if (nsrc == 2) fold_fixed<DT, 2, false>(src_tab, dst_tab, whole, rows, lane, op);
+  else fold_any<DT>(src_tab, nsrc, dst_tab, ndst, whole, rows, lane, op);
+  if (tail) fold_tail<DT>(src_tab, nsrc, dst_tab, ndst, whole, bytes, lane, op);
 }
 
-template <int NTH>
+// tail: this wave does the bytes behind the last whole 16 (exactly one of the region's waves, once)
 __device__ __forceinline__ void fold_dispatch(int dtype, const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst,
-                                              uint32_t bytes, uint32_t first, uint32_t stride, uint32_t tid) {
+                                              uint32_t bytes, bool tail, Rows& rows, uint32_t lane) {
   if (nsrc == 1) {
     const uint32_t whole = bytes & ~15u;
-    if (ndst == 8) fold_copy<8, NTH>(src_tab, dst_tab, ndst, whole, first, stride, tid);
-    else if (ndst == 4) fold_copy<4, NTH>(src_tab, dst_tab, ndst, whole, first, stride, tid);
-    else fold_copy<0, NTH>(src_tab, dst_tab, ndst, whole, first, stride, tid);
+    if (ndst == 8) fold_copy<8>(src_tab, dst_tab, ndst, whole, rows, lane);
+    else if (ndst == 4) fold_copy<4>(src_tab, dst_tab, ndst, whole, rows, lane);
+    else fold_copy<0>(src_tab, dst_tab, ndst, whole, rows, lane);
     // (every element type is a multiple of 2 bytes)
-    if (whole < bytes && first == 0) fold_tail<DT_F16, NTH>(src_tab, 1, dst_tab, ndst, whole, bytes, tid, OP_SUM);
+    if (tail) fold_tail<DT_F16>(src_tab, 1, dst_tab, ndst, whole, bytes, lane, OP_SUM);
     return;
   }
   const int op = dtype >> 4;
   switch (dtype & 15) {
-    case DT_F32: fold_reduce<DT_F32, NTH>(src_tab, nsrc, dst_tab, ndst, bytes, first, stride, tid, op); break;
-    case DT_BF16: fold_reduce<DT_BF16, NTH>(src_tab, nsrc, dst_tab, ndst, bytes, first, stride, tid, op); break;
-    case DT_F16: fold_reduce<DT_F16, NTH>(src_tab, nsrc, dst_tab, ndst, bytes, first, stride, tid, op); break;
-    default: fold_reduce<DT_I32, NTH>(src_tab, nsrc, dst_tab, ndst, bytes, first, stride, tid, op); break;
+    case DT_F32: fold_reduce<DT_F32>(src_tab, nsrc, dst_tab, ndst, bytes, tail, rows, lane, op); break;
+    case DT_BF16: fold_reduce<DT_BF16>(src_tab, nsrc, dst_tab, ndst, bytes, tail, rows, lane, op); break;
+    case DT_F16: fold_reduce<DT_F16>(src_tab, nsrc, dst_tab, ndst, bytes, tail, rows, lane, op); break;
+    default: fold_reduce<DT_I32>(src_tab, nsrc, dst_tab, ndst, bytes, tail, rows, lane, op); break;
   }
 }
 
@@ -690,7 +726,9 @@ struct Job {                         // what the scheduler wave hands to the mov
   uint32_t bytes; int dtype;
   uint32_t coll, prim;               // for the timeline trace only
   uint32_t nsrc, ndst;               // not 0: step with data of a collective in fold steps (that many sources and destinations in the job's tables)
-  uint32_t first, stride;            // ... the workgroup's pieces of the span of `bytes` (FoldGeom)
+  uint32_t index, sharers;           // ... which of the region's workgroups this is, and how many there are
+  uint32_t limit, fresh;             // ... rows per wave (0 = no limit); first job of the share
+  u64 draw;                          // ... the region's row counter (0 = rows are dealt)
 };
 
 // What publishing and retiring a posted job needs.  Written by the scheduler when it posts the
@@ -873,8 +911,18 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
         }
       } else
 #endif
-      if (j.nsrc) fold_dispatch<GTHREADS>(j.dtype, sh.tab_src[seen & 1], bcast0(j.nsrc), sh.tab_dst[seen & 1], bcast0(j.ndst), bcast0(j.bytes),
-                                          bcast0(j.first), bcast0(j.stride), mtid);
+      if (j.nsrc) {
+        const uint32_t wave = bcast0(mtid >> 6), sharers = bcast0(j.sharers), index = bcast0(j.index), limit = bcast0(j.limit), jbytes = bcast0(j.bytes);
+        const bool fresh = bcast0(j.fresh) != 0;
+        Rows rows;
+        rows.ctr = (GLOBAL_AS uint32_t*)(uint32_t*)bcast64((uint32_t)j.draw, (uint32_t)(j.draw >> 32));
+        rows.waves = sharers * (GTHREADS / 64);
+        rows.left = limit ? limit : 0xffffffffu;
+        rows.drawn = 0;
+        rows.begin(fresh, wave * sharers + index);
+        fold_dispatch((int)bcast0((uint32_t)j.dtype), sh.tab_src[seen & 1], bcast0(j.nsrc), sh.tab_dst[seen & 1], bcast0(j.ndst), jbytes,
+                      (jbytes & 15u) && fresh && index == 0 && wave == 0, rows, lane);
+      }
       else if (coh) run_prim<AUX_DEVICE, GTHREADS>(j.dtype, j.fin, j.sb, j.rb, j.fout, j.bytes, mtid);
       else run_prim<AUX_CACHED, GTHREADS>(j.dtype, j.fin, j.sb, j.rb, j.fout, j.bytes, mtid);
       // this wave's stores (and loads) have been performed before it counts itself done
@@ -1215,6 +1263,10 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 line.st16(DFX_DIRECT_OFF, uint4{(uint32_t)q.recvbuf, (uint32_t)(q.recvbuf >> 32), q.seq + 1u, 0u});
                 line.st16(DFX_DIRECT_OFF + 16, uint4{(uint32_t)q.sendbuf, (uint32_t)(q.sendbuf >> 32), q.seq + 1u, 0u});
               }
+              // rows to be drawn: the counter of the next invocation starts over (nobody draws from it: every rank has
+              // finished the invocation before this one, or this rank would not have been given this one)
+              if ((q.flags & DFX_SQE_DRAWN) && my_vch == 0)
+                __hip_atomic_store(global_ptr((uint32_t*)(k.flags_out + DFX_FOLD_DRAW + 8u * ((q.seq + 1u) & 1u))), 0u, __ATOMIC_RELAXED, SCOPE_AGENT);
               // fold steps: the channel's count of published invocations, a hint for the readiness scans
               if (q_fold) (void)__hip_atomic_fetch_add(global_ptr((u64*)(k.flags_in + DFX_FOLD_PUB)), 1ull, __ATOMIC_RELAXED, SCOPE_AGENT);
               const uint32_t csl = ctx_slot(c_id);
@@ -1535,8 +1587,10 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             ln_send = rs_ld16(lines, line_off + DFX_DIRECT_OFF + 16);
           };
           poll();
-          const uint4 v0 = sv[0], v1 = sv[1], v2 = sv[2];   // pieces' begin, stride | share, length | source offset, destination offset
-          const FoldGeom fg = fold_geometry(bcast64(v1.x, v1.y), bcast64(v1.z, v1.w), bcast64(v2.x, v2.y), s_slice, bcast0(v0.x), bcast0(v0.y), g);
+          const uint4 v0 = sv[0], v1 = sv[1], v2 = sv[2];   // row limit | share, length | source offset, destination offset
+          const bool drawn = (bcp & DFX_CTX_DRAWN) != 0;
+          const uint32_t row_limit = bcast0(v0.x), vch = bcast0(v5.w) >> 16;
+          const FoldGeom fg = fold_geometry(bcast64(v1.x, v1.y), bcast64(v1.z, v1.w), bcast64(v2.x, v2.y), s_slice, drawn, g);
           bytes = bcast0(v0.z);
           look_ahead();
           res = wait_until(poll, [&]() { return lane >= R || (ln_recv.z == inv_seq + 1u && ln_send.z == inv_seq + 1u); });
@@ -1558,7 +1612,10 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             if (lane == 0) {
               Job j;
               j.fin = nullptr; j.fout = nullptr; j.sb = nullptr; j.rb = nullptr;
-              j.bytes = fg.bytes; j.first = fg.first; j.stride = fg.stride;
+              j.bytes = fg.bytes; j.index = vch; j.sharers = inv_nchan;
+              j.limit = nx.p ? 0u : row_limit;                        // (the last job takes all the rows there are)
+              j.fresh = !drawn || g == 0;
+              j.draw = drawn ? fold_draw_word(s_fin, rank, vch, inv_nchan, inv_seq) : 0;
               j.nsrc = copies ? 1u : R; j.ndst = to_all ? R : 1u;
               j.dtype = dtype; j.coll = coll; j.prim = 0;
               sh.job[fs] = j;
@@ -1654,8 +1711,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             Job j;
             j.fin = jfin; j.fout = jfout; j.sb = jsb; j.rb = jrb;
             j.bytes = (q.drain || (!q.recv && !q.from_send)) ? 0u : bytes;   // drain and notify-only steps move nothing
-            j.first = j.stride = 0;
-            j.nsrc = 0; j.ndst = 0;
+            j.nsrc = 0; j.ndst = 0; j.index = j.sharers = j.limit = j.fresh = 0; j.draw = 0;
             j.dtype = dtype; j.coll = coll; j.prim = q.drain ? 0xffu : p;   // (prim: for the timeline only)
             sh.job[posted & 1] = j;
             Flight f;

@@ -76,7 +76,7 @@ struct Prim {
 //   reduce-scatter:  block r out of all R send buffers, in the same order             -> the own recv buffer
 //   reduce:          chunk r out of all R send buffers, x[root+1] (op) ... (op) x[root] -> chunk r of the root's recv buffer
 //   all-gather:      the own send buffer, once                                        -> block r of all R recv buffers
-//   broadcast:       every R-th piece of the root's send buffer                       -> the same of all R recv buffers
+//   broadcast:       the r-th of R parts of the root's send buffer                    -> the same of all R recv buffers
 // So every input is read once and every output written once, whatever the kind.  (All-gather and broadcast hand
 // their data out instead of every rank fetching all of it: one read per byte instead of R.)
 // Each step is a bounded wait followed by the data, like any primitive: nothing is touched before the wait has
@@ -102,60 +102,81 @@ DFX_HD uint32_t fold_peer(int kind, uint32_t R, uint32_t rank, uint32_t root, ui
 DFX_HD bool fold_copies(int kind) { return kind == KIND_AG || kind == KIND_BC; }
 DFX_HD bool fold_to_all(int kind) { return kind != KIND_RS && kind != KIND_RD; }
 
-// Where slice g of a collective in fold steps lies: a span of the chunk (block, message) that the workgroups which
-// share it take piece by piece in turn, DFX_FOLD_PIECE bytes each: this workgroup's pieces begin `first` bytes into the
-// span and follow each other `stride` bytes apart, the last one cut off at `bytes`.  The workgroups that share a
-// span advance through it side by side, so that together they sweep one compact stretch of every buffer: with
-// one contiguous part per workgroup (256 x 16 streams megabytes apart) the same kernel loop took 85-87 us for 24 MiB
-// per rank and 22.5 us for 8 MiB, in pieces 78 and 20 us (fp32, R = 8; 256 MiB 845 -> 830 us).
-// The bytes behind the last whole 16 of a span belong to the workgroup whose pieces begin at 0.
-constexpr uint32_t DFX_FOLD_PIECE = DFX_MOVERS * 16u;
+// The part of a rank -- its region: a chunk, a block, its R-th of a broadcast -- is worked through in rows: a mover wave
+// takes 64 lanes x 16 bytes x as many vectors as keep about sixteen loads in flight per lane, out of every source, and
+// goes on to another row.  Row t begins at t * fold_row_bytes.  The first rows go to the waves of the region's
+// workgroups in turn (workgroup by workgroup, so that a short region spreads over them).
+//   dealt rows: the next ones in turn as well;
+//   drawn rows: whoever is through draws the next from a counter.
+// Either way the waves advance side by side and sweep one compact stretch of every buffer: with one contiguous part per
+// workgroup (256 x 16 streams megabytes apart) the same loop took 85-87 us for 24 MiB per rank and 22.5 us for 8 MiB,
+// side by side 78 and 20 us (fp32, R = 8).  Drawing them pays where a wave has several rows: the memory system
+// does not serve workgroups alike, and the workgroups of one rank were through with equal parts after 15 to 50 us
+// (all-gather of 32 MiB); drawn, after 46 to 53.  Host to host: 25 MiB bf16 bucket 107 -> 101 us, sixteen of them 1405 -> 1315,
+// all-reduce of 256 MiB 876 -> 857.
+// A job is a span of the region with its rows dealt (a slice; all of it where there is one slice), or so and so many
+// drawn rows per wave of the whole region, the last job of a share as many as there are.
+constexpr uint32_t DFX_FOLD_WAVES = DFX_MOVERS / 64;      // mover waves of a workgroup
+DFX_HD uint32_t fold_row_bytes(bool copies, uint32_t R) { return 1024u * (copies ? 4u : R == 4 ? 4u : R == 2 ? 8u : 2u); }
+
+// A rank's region in elements: where it begins in the message and how long it is.  chunk: what one rank has, in elements.
+DFX_HD uint64_t fold_chunk_elems(int kind, uint64_t count, uint64_t block, uint32_t R, uint32_t eb) {
+  if (kind == KIND_AR || (kind == KIND_RD && block != count)) return block;      // (planned as chunks)
+  if (kind == KIND_RD || kind == KIND_BC) return ((count + R - 1) / R + 16 / eb - 1) / (16 / eb) * (16 / eb);
+  return count;                                                                 // (a block per rank)
+}
 
 // The entry (SQE) of a collective in fold steps for one rank, from its plan in elements: everything about the rank's
 // part that does not depend on the channel, in bytes, so that the workgroups that read the entry multiply nothing.
-//   count       length of the rank's region (its chunk or block, or the stretch that all ranks share)
+//   count       length of the rank's region
 //   block_elems where the region begins in the send buffers it is read from
 //   part_elems  where it begins in the recv buffers it is written to
-//   slice_elems span of one slice, all channels together (at most 1 GiB)
-//   slot_bytes  stride of a workgroup's pieces
-//   share       one channel's part of a slice
+//   slice_elems span of one slice, all channels together (at most 1 GiB); rows are drawn: the longest region, all of it
+//   slot_bytes  rows are drawn: rows per wave and job (0 = no limit)
+//   share       one channel's part of a slice or job
 DFX_HD void fold_entry(DfxStatic& e, uint32_t R, uint32_t rank) {
   const int kind = e.kind;
-  const uint64_t eb = (e.dtype == DT_F32 || e.dtype == DT_I32) ? 4u : 2u;
-  const uint64_t count = e.count, block = e.block_elems;
-  // a chunk or block of its own for every rank, or one stretch that all ranks' workgroups share
-  const bool chunks = kind == KIND_AR || (kind == KIND_RD && block != count);
-  const bool shared = kind == KIND_BC || (kind == KIND_RD && !chunks);
+  const uint32_t eb = (e.dtype == DT_F32 || e.dtype == DT_I32) ? 4u : 2u;
+  const uint64_t count = e.count, chunk = fold_chunk_elems(kind, count, e.block_elems, R, eb);
   uint64_t start = 0, len = count;
-  if (chunks) {
-    start = (uint64_t)rank * block;
-    len = start >= count ? 0 : (count - start < block ? count - start : block);
+  if (kind == KIND_AR || kind == KIND_RD || kind == KIND_BC) {
+    start = (uint64_t)rank * chunk;
+    len = start >= count ? 0 : (count - start < chunk ? count - start : chunk);
   }
   e.count = len * eb;
   e.block_elems = (start + (kind == KIND_RS ? (uint64_t)rank * count : 0u)) * eb;
   e.part_elems = (start + (kind == KIND_AG ? (uint64_t)rank * count : 0u)) * eb;
-  e.share = (uint32_t)(e.slice_elems * eb);
-  e.slice_elems = (uint32_t)(e.nchan * (e.slice_elems * eb));
-  e.slot_bytes = (shared ? e.nchan * R : e.nchan) * DFX_FOLD_PIECE;
+  e.share = e.slice_elems * eb;
+  if (e.flags & DFX_SQE_DRAWN) {
+    const uint32_t row = fold_row_bytes(kind == KIND_AG || kind == KIND_BC, R);
+    e.slice_elems = (uint32_t)(chunk * eb);
+    e.slot_bytes = e.rounds > 1 ? e.share / (DFX_FOLD_WAVES * row) : 0u;
+  } else {
+    e.slice_elems = (uint32_t)(e.nchan * (uint64_t)e.share);
+    e.slot_bytes = 0;
+  }
 }
 
-struct FoldGeom { uint64_t src, dst; uint32_t bytes, first, stride; };   // byte offsets in the buffers; span, pieces
-DFX_HD FoldGeom fold_geometry(uint64_t len, uint64_t src, uint64_t dst, uint32_t span, uint32_t first, uint32_t stride, uint32_t g) {
+struct FoldGeom { uint64_t src, dst; uint32_t bytes; };   // byte offsets of the job's span in the buffers, its length
+DFX_HD FoldGeom fold_geometry(uint64_t len, uint64_t src, uint64_t dst, uint32_t span, bool drawn, uint32_t g) {
   FoldGeom o;
-  const uint64_t at = (uint64_t)g * span, lo = at < len ? at : len, n = len - lo;
+  const uint64_t at = drawn ? 0u : (uint64_t)g * span, lo = at < len ? at : len, n = len - lo;
   o.src = src + lo; o.dst = dst + lo;
   o.bytes = n < span ? (uint32_t)n : span;
-  o.first = first; o.stride = stride;
   return o;
 }
 DFX_HD FoldGeom fold_geometry(const DfxCooked& S, uint32_t g) {
-  return fold_geometry(S.count, S.block_elems, S.part_elems, S.slice_elems, (uint32_t)S.sendbuf, (uint32_t)(S.sendbuf >> 32), g);
+  return fold_geometry(S.count, S.block_elems, S.part_elems, S.slice_elems, (S.bc_pos & DFX_CTX_DRAWN) != 0, g);
 }
 
 // Where a fold collective's lines are, from a workgroup's own line: the line of rank r on the same channel,
 // and the channel's shared line.
 DFX_HD uint64_t fold_line(uint64_t own_line, uint32_t rank, uint32_t r, uint32_t nchan) {
   return own_line + ((uint64_t)r - (uint64_t)rank) * nchan * DFX_FLAG_STRIDE;
+}
+// the row counter of the region of `rank`, for invocation seq, from the channel's line of rank 0
+DFX_HD uint64_t fold_draw_word(uint64_t line0, uint32_t rank, uint32_t vch, uint32_t nchan, uint32_t seq) {
+  return line0 + (uint64_t)rank * nchan * DFX_FLAG_STRIDE - (uint64_t)vch * DFX_FLAG_STRIDE + DFX_FOLD_DRAW + 8u * (seq & 1u);
 }
 DFX_HD uint64_t fold_shared_line(uint64_t own_line, uint32_t rank, uint32_t R, uint32_t nchan) {
   return own_line + ((uint64_t)R - (uint64_t)rank) * nchan * DFX_FLAG_STRIDE;
@@ -269,10 +290,8 @@ DFX_HD DfxCooked cook_sqe(const DfxStatic& q, uint8_t* pool, uint32_t rank, uint
     k.fifo_in = fold_line(k.flags_out, rank, 0, q.nchan);
     k.flags_in = (q.flags & DFX_SQE_LONG) ? k.fifo_in + DFX_FOLD_HEAD : fold_shared_line(k.flags_out, rank, R, q.nchan);
     k.fifo_out = ((uint64_t)q.seq + 1u) * (R * q.rounds);
-    // the buffers' addresses travel through the lines: the words carry where the workgroup's pieces begin and their
-    // stride, and a channel's part of a slice
-    const uint32_t first = (q.slot_bytes != q.nchan * DFX_FOLD_PIECE ? vch * R + rank : vch) * DFX_FOLD_PIECE;
-    k.sendbuf = (uint64_t)q.slot_bytes << 32 | first;
+    // the buffers' addresses travel through the lines: the words carry the jobs' row limit and a channel's part of a slice
+    k.sendbuf = q.slot_bytes;
     k.recvbuf = q.share;
   }
   k.slice_elems = q.slice_elems; k.rounds = q.rounds; k.seq = q.seq;
@@ -284,7 +303,8 @@ DFX_HD DfxCooked cook_sqe(const DfxStatic& q, uint8_t* pool, uint32_t rank, uint
   k.bc_pos = bpos == 0 ? 0 : (bpos == R - 1 ? 2 : 1);
   if (q.kind == KIND_RD && (q.flags & DFX_SQE_DIRECT) && bpos == 1 && R > 2) k.bc_pos = 3;   // reads the first rank's send buffer
   if (q.flags & DFX_SQE_DIRECT) k.bc_pos |= DFX_CTX_DIRECT;   // a collective with direct steps
-  if (q.flags & DFX_SQE_FOLD) k.bc_pos |= DFX_CTX_FOLD;       // an all-reduce in fold steps
+  if (q.flags & DFX_SQE_FOLD) k.bc_pos |= DFX_CTX_FOLD;       // a collective in fold steps
+  if (q.flags & DFX_SQE_DRAWN) k.bc_pos |= DFX_CTX_DRAWN;     // ... whose rows are drawn
   k.priority = q.priority; k.vch = (uint16_t)vch;
   return k;
 }

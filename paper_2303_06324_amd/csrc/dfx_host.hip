@@ -483,16 +483,24 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   // broadcast 100 MiB bf16 472 -> 204.
   // With fold_max_bytes = 0 the rings and chains run at every size.  The connector block stays what it was.
   if ((t.flags & DFX_SQE_DIRECT) && !fold && cfg.fold_max_bytes && blocks_ok && !(kind == DFX_REDUCE && R > 63)) {
-    const bool shared = rooted;     // one stretch that all ranks' workgroups share (fold_geometry): a job is 1 / R of a channel's slice
     // 128 KiB per source and workgroup: about 100 us at 2 x 8 streams; priority ordering lets nothing longer than
     // its look-again budget get ahead of an urgent collective
     const uint64_t job = cfg.fold_slice_bytes ? cfg.fold_slice_bytes : (cfg.order_policy == 1 ? 32u << 10 : 128u << 10);
-    const uint64_t cap = std::min<uint64_t>(shared ? job * R : job, ((1ull << 30) / C) & ~15ull);
-    const uint64_t bytes = std::min<uint64_t>(cap, round_up(part * eb, 16));
+    const uint64_t chunk = fold_chunk_elems((int)kind, count, block, (uint32_t)R, eb);     // a rank's region; a channel's part of it
+    const uint64_t share = std::max<uint64_t>(round_up(ceil_div(chunk, C), per16), per16);
+    const uint64_t bytes = std::min<uint64_t>(std::min<uint64_t>(job, ((1ull << 30) / C) & ~15ull), share * eb);
     t.flags |= DFX_SQE_FOLD | DFX_SQE_LONG;
     t.slice_elems = (uint32_t)(bytes / eb);
-    t.rounds = (uint32_t)std::max<uint64_t>(1, ceil_div(part, t.slice_elems));
+    t.rounds = (uint32_t)std::max<uint64_t>(1, ceil_div(share, t.slice_elems));
     t.nprim = fold_nprim((int)kind);
+  }
+  // Rows are drawn where a wave has at least four of them (with fewer the last ones are as uneven as equal parts) and
+  // the region's offsets fit 32 bits; a job size that the caller asked for keeps its slices, whose rows are dealt.
+  if ((t.flags & DFX_SQE_FOLD) && !cfg.fold_slice_bytes) {
+    const uint64_t region = fold_chunk_elems((int)kind, count, t.block_elems, (uint32_t)R, eb) * eb;
+    const uint64_t row = fold_row_bytes(kind == DFX_ALLGATHER || kind == DFX_BROADCAST, (uint32_t)R);
+    if (region >= 4 * row * DFX_FOLD_WAVES * C && region <= (1ull << 30) && (t.rounds == 1 || t.slice_elems * (uint64_t)eb >= DFX_FOLD_WAVES * row))
+      t.flags |= DFX_SQE_DRAWN;
   }
   *out = t;
   return DFX_OK;
@@ -1210,6 +1218,9 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
         const uint64_t sh_line = me.flags_in;
         if ((t.flags & DFX_SQE_LONG) ? sh_line != me.fifo_in + DFX_FOLD_HEAD : (sh_line < flags_hi || sh_line + DFX_FLAG_STRIDE > blk_hi))
           return fail("rank %u channel %u: shared counters %llx outside their line", r, v, (unsigned long long)sh_line);
+        for (uint32_t sq = 0; sq < 2; ++sq)
+          if (fold_draw_word(me.fifo_in, r, v, t.nchan, sq) != cooked[(size_t)r * t.nchan].flags_out + DFX_FOLD_DRAW + 8u * sq)
+            return fail("rank %u channel %u: the row counter is not in the rank's line of channel 0", r, v);
         if (sh_line != nx.flags_in || me.fifo_in != cooked[v].flags_out) return fail("ranks %u and %u channel %u disagree on the shared line", r, (r + 1) % R, v);
         for (uint32_t k = 0; k < R; ++k)
           if (me.fifo_in + (uint64_t)k * t.nchan * DFX_FLAG_STRIDE != cooked[(size_t)k * t.nchan + v].flags_out)
@@ -1239,7 +1250,10 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
             const bool copies = fold_copies(kind), to_all = fold_to_all(kind);
             const uint64_t src = fg.src, dst = fg.dst;
             if (R > 64) return fail("%u table entries for 64 lanes", R);
-            if (fg.bytes > (1u << 30) || fg.first % 16 || fg.stride % 16 || !fg.stride) return fail("rank %u channel %u: a span of %u bytes, pieces from %u every %u", r, v, fg.bytes, fg.first, fg.stride);
+            const uint32_t row = fold_row_bytes(copies, R), waves = t.nchan * DFX_FOLD_WAVES;
+            if (fg.bytes > (1u << 30)) return fail("rank %u channel %u: a span of %u bytes", r, v, fg.bytes);
+            // (drawn rows: any wave may take any row behind the first ones; walked here as if they were dealt, once)
+            const bool walk = !(t.flags & DFX_SQE_DRAWN) || g == 0;
             if (fg.bytes && ((src | dst) & 15u)) return fail("rank %u channel %u step %u: 16-byte accesses at offsets %llu, %llu", r, v, p, (unsigned long long)src, (unsigned long long)dst);
             if (fg.bytes && src + fg.bytes > send_bytes) return fail("rank %u channel %u: read of send buffers %llu+%u of %llu", r, v, (unsigned long long)src, fg.bytes, (unsigned long long)send_bytes);
             if (fg.bytes && dst + fg.bytes > recv_bytes) return fail("rank %u channel %u: write of recv buffers %llu+%u of %llu", r, v, (unsigned long long)dst, fg.bytes, (unsigned long long)recv_bytes);
@@ -1250,11 +1264,12 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
               const uint32_t peer = fold_peer(kind, R, r, rt, k);
               if (peer >= R || (seen >> peer & 1u)) return fail("rank %u channel %u: entry %u names rank %u", r, v, k, peer);
               seen |= 1ull << peer;
-              if (!to_all && k + 1 < R) continue;
+              if ((!to_all && k + 1 < R) || !walk) continue;
               const uint32_t whole = fg.bytes & ~15u;
-              for (uint64_t at = fg.first; at < whole; at += fg.stride)
-                written[peer].push_back({dst + at, dst + std::min<uint64_t>(at + DFX_FOLD_PIECE, whole)});
-              if (whole < fg.bytes && fg.first == 0) written[peer].push_back({dst + whole, dst + fg.bytes});
+              for (uint32_t wv = 0; wv < DFX_FOLD_WAVES; ++wv)
+                for (uint64_t at = (uint64_t)(wv * t.nchan + v) * row; at < whole; at += (uint64_t)waves * row)
+                  written[peer].push_back({dst + at, dst + std::min<uint64_t>(at + row, whole)});
+              if (whole < fg.bytes && v == 0) written[peer].push_back({dst + whole, dst + fg.bytes});
             }
             const uint32_t lastp = fold_peer(kind, R, r, rt, R - 1);
             if ((copies || !to_all) && lastp != ((kind == KIND_BC || kind == KIND_RD) ? rt : r)) return fail("rank %u channel %u: the last entry is rank %u", r, v, lastp);

@@ -26,11 +26,16 @@
 #define DFX_SQE_FOLD 4u        // all-reduce in fold steps (always together with DFX_SQE_DIRECT: the buffers are published the same way)
 #define DFX_CTX_FOLD 0x40u     // the same, in the cooked context's bc_pos byte
 #define DFX_SQE_LONG 8u        // a long collective in fold steps (always together with DFX_SQE_FOLD): its connector block is laid out for the ring or chain
+#define DFX_SQE_DRAWN 16u      // fold steps: the rows of a rank's region are drawn from a counter (fold_entry)
+#define DFX_CTX_DRAWN 0x20u    // the same, in the cooked context's bc_pos byte
 // A collective in fold steps has no slots.  Its connector block is R x nchan flag lines, one per (rank, channel),
 // that carry the published buffer addresses (DFX_DIRECT_OFF), and behind them nchan shared lines, one per
 // channel, with two counters that every rank of the channel adds to (a long collective keeps the block that its ring
 // or chain would have: there the counters are in the head half, at DFX_FOLD_HEAD, of rank 0's line, which nobody else uses):
 #define DFX_FOLD_HEAD 64
+// Row counters of a rank's region: two words in the head half of the rank's line of channel 0, for even and odd
+// invocations; the other one starts over when an invocation is fetched.
+#define DFX_FOLD_DRAW 96
 #define DFX_FOLD_PUB 0         //   +0  invocations published (a hint for the readiness scan: the step with data looks at the tags of the lines themselves)
 #define DFX_FOLD_RED 8         //   +8  steps with data finished (the rank's part is combined or copied and written to every recv buffer it belongs to)
 
@@ -76,7 +81,7 @@ static_assert(sizeof(DfxDyn) == 32, "DfxDyn must be 32 bytes");
 // What a workgroup keeps of an invocation (device-private): the SQE "cooked" once at fetch time
 // into ready-to-use addresses, so that a context load needs no address arithmetic.  96 bytes.
 struct alignas(16) DfxCooked {
-  uint64_t sendbuf, recvbuf, count, block_elems, part_elems;   // fold steps: pieces' begin and stride, share, and the byte offsets of fold_entry
+  uint64_t sendbuf, recvbuf, count, block_elems, part_elems;   // fold steps: jobs' row limit, share, and the byte offsets of fold_entry
   uint64_t flags_out;    // tail counter of my send connector (head at +64 bytes)
   uint64_t flags_in;     // tail counter of my recv connector (head at +64 bytes); fold steps: the channel's shared counters
   uint64_t fifo_out;     // first slot of my send connector; fold steps: DFX_FOLD_RED at the end of this invocation

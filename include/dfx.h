@@ -386,9 +386,9 @@ int dfx_check_geometry(int nranks, const dfx_config* cfg, dfx_kind kind, size_t 
  * counters, saved contexts, connector flag lines and slots) in a static device array of the library:
  * 32.5 MiB per GPU the library runs on, held until the process ends.  The call allocates nothing (no hipMalloc,
  * hipFree, stream, event or host allocation) and only enqueues work on hip_stream (NULL = the null stream): a
- * kernel that clears the array's control part, one that writes the submission entries, the daemon kernel
- * (nranks x min(32, 256 / nranks) workgroups, which leaves by itself when every vrank's completion is posted)
- * and one that writes the outcome.  It returns when the work is enqueued; the results are in recvbufs once the
+ * kernel that clears the array's control part and writes the submission entries, and the daemon kernel (at most
+ * nranks x min(32, 256 / nranks) workgroups, as many as the collective has channels), which leaves by itself when
+ * every vrank's completion is posted and writes the outcome.  It returns when the work is enqueued; the results are in recvbufs once the
  * stream has reached the end of that work.
  * nranks: 1 .. 64.  kind / count / dtype / op / root: as for dfx_prepare; same values, bit for bit, as the
  * context path.  sendbufs / recvbufs: host arrays of nranks device pointers (read during the call), the buffers

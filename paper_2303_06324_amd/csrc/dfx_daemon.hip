@@ -768,7 +768,10 @@ struct Shared {
 __device__ __forceinline__ void raise_error(const DfxDaemonArgs& a, uint32_t code, uint32_t wg) {
   uint32_t expected = 0;
   if (__hip_atomic_compare_exchange_strong(&a.dev_ctl[DC_ERR], &expected, code, __ATOMIC_RELAXED, __ATOMIC_RELAXED, SCOPE_AGENT))
+  {
     __hip_atomic_store(&a.dev_ctl[DC_ERR_WG], wg, __ATOMIC_RELAXED, SCOPE_AGENT);
+    if (a.status) __hip_atomic_store(a.status, 0x100u | code, __ATOMIC_RELAXED, SCOPE_AGENT);
+  }
   __hip_atomic_store(&a.dev_ctl[DC_ABORT], 1u, __ATOMIC_RELEASE, SCOPE_AGENT);
 }
 
@@ -1158,13 +1161,17 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 s = STOP_ABORT;
               } else if (hot.oneshot) {
                 // A launch that brings all of its work with it: this workgroup is through when it has read every
-                // entry of its rank's SQ, its queue is empty and its jobs are retired (completions posted).
-                if (!voted && qlen == 0 && ri >= (u64)hot.oneshot && retired == posted) {
-                  voted = true;
-                  if (__hip_atomic_fetch_add(&a.dev_ctl[DC_VOTES], 1u, __ATOMIC_ACQ_REL, SCOPE_AGENT) + 1 == hot.nwg) {
-                    __hip_atomic_store(&a.dev_ctl[DC_QUIT], 1u, __ATOMIC_RELEASE, SCOPE_AGENT);
-                    s = STOP_QUIT;
+                // entry of its rank's SQ, its queue is empty and its jobs are retired (completions posted).  Nobody waits
+                // for it any more, so it leaves on its own; the last one to count itself out knows that everybody is
+                // through and writes the outcome (an error has been written by the workgroup that raised it, which
+                // does not count itself out).
+                if (qlen == 0 && ri >= (u64)hot.oneshot && retired == posted) {
+                  if (__hip_atomic_fetch_add(&a.dev_ctl[DC_VOTES], 1u, __ATOMIC_RELAXED, SCOPE_AGENT) + 1 == hot.nwg && a.status) {
+                    uint32_t n = 0;
+                    for (uint32_t i = 0; i < R * hot.cq_slots; ++i) n += (uint32_t)(ld_sys64(&a.cq[i]) >> 63);
+                    __hip_atomic_store(a.status, n == R ? 0u : 0x200u, __ATOMIC_RELAXED, SCOPE_AGENT);
                   }
+                  s = STOP_EXIT;
                 }
               } else if (hot.quit_ticks) {
                 // Voluntary quit (Sec. 4.4).  Every workgroup has duties towards the others (each

@@ -1395,35 +1395,30 @@ struct NaSeed {                       // what the seeding kernel writes into the
   uint32_t nranks;
 };
 
-// clears the part of the scratch that must start at zero (a fill kernel, not a memset node: the call may be captured)
-__global__ void __launch_bounds__(256) dfx_na_zero_kernel(uint4* p, uint32_t nvec) {
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nvec; i += gridDim.x * blockDim.x) p[i] = uint4{0, 0, 0, 0};
-}
-
-// writes the SQEs the host would have written: entry 0 of every rank's SQ, generation word included
-__global__ void __launch_bounds__(64) dfx_na_seed_kernel(DfxSqSlot* sq, NaSeed sd) {
-  const uint32_t r = threadIdx.x;
-  if (r >= sd.nranks) return;
-  DfxStatic e = sd.tmpl;
-  if (e.flags & DFX_SQE_FOLD) fold_entry(e, sd.nranks, r);
-  e.seq = 0;
-  e.sendbuf = sd.sendbuf[r];
-  e.recvbuf = sd.recvbuf[r];
-  e.ready = 1;                        // generation of the first lap
-  sq[(size_t)r * DFX_NA_SQ_DEPTH].e = e;
-}
-
-// after the daemon: 0 = every rank's completion is in its CQ and no error was raised
-__global__ void dfx_na_status_kernel(const uint32_t* dev_ctl, const uint64_t* cq, uint32_t nranks, uint32_t* status) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  uint32_t st = 0;
-  if (dev_ctl[DC_ERR]) st = 0x100u | dev_ctl[DC_ERR];
-  else {
-    uint32_t n = 0;
-    for (uint32_t i = 0; i < nranks * DFX_NA_CQ_SLOTS; ++i) n += (uint32_t)(cq[i] >> 63);
-    if (n != nranks) st = 0x200u;
+// Prepares the scratch for one launch: clears what must start at zero -- the control structures and the collective's flag
+// lines, two ranges -- and writes the SQEs the host would have written: entry 0 of every rank's SQ, generation word included.
+// (A kernel and no memset node: the call may be captured.  One launch for both, and no other one behind the daemon,
+// which writes the outcome itself, and only the daemon's workgroups that serve a channel: an all-reduce of 64 KiB
+// takes 26.9 us, with a fill, a seed and a status kernel and 256 workgroups 32.5.)
+__global__ void __launch_bounds__(256) dfx_na_prepare_kernel(unsigned char* base, uint32_t ctl_vec, uint32_t lines_at, uint32_t lines_vec, uint32_t sq_at, NaSeed sd) {
+  constexpr uint32_t kSqVec = DFX_NA_MAX_RANKS * DFX_NA_SQ_DEPTH * (uint32_t)sizeof(DfxSqSlot) / 16u;
+  uint4* const p = (uint4*)base;
+  const uint32_t sq0 = sq_at / 16u, me = blockIdx.x * blockDim.x + threadIdx.x, all = gridDim.x * blockDim.x;
+  for (uint32_t i = me; i < ctl_vec; i += all)
+    if (i < sq0 || i >= sq0 + kSqVec) p[i] = uint4{0, 0, 0, 0};
+  for (uint32_t i = me; i < lines_vec; i += all) p[lines_at / 16u + i] = uint4{0, 0, 0, 0};
+  if (blockIdx.x != 0 || threadIdx.x >= DFX_NA_MAX_RANKS * DFX_NA_SQ_DEPTH) return;
+  const uint32_t slot = threadIdx.x, r = slot / DFX_NA_SQ_DEPTH;
+  DfxSqSlot e = {};
+  if (slot % DFX_NA_SQ_DEPTH == 0 && r < sd.nranks) {
+    e.e = sd.tmpl;
+    if (e.e.flags & DFX_SQE_FOLD) fold_entry(e.e, sd.nranks, r);
+    e.e.seq = 0;
+    e.e.sendbuf = sd.sendbuf[r];
+    e.e.recvbuf = sd.recvbuf[r];
+    e.e.ready = 1;                      // generation of the first lap
   }
-  *status = st;
+  ((DfxSqSlot*)(base + sq_at))[slot] = e;
 }
 
 struct NaDevice {
@@ -1517,14 +1512,16 @@ int dfx_collective_noalloc(int nranks, dfx_kind kind, size_t count, dfx_dtype dt
   a.dev_ctl = (uint32_t*)(base + L.dev_ctl); a.pool = base + L.pool;
   a.ctxbuf = (DfxCtxEntry*)(base + L.ctxbuf); a.wgstate = (DfxWgState*)(base + L.wgstate);
   a.taskq_store = (uint16_t*)(base + L.taskq); a.trace = nullptr;
-  a.nwg = nwg; a.scan_min = cfg.scan_min; a.epoch = 1;
-  a.R = (uint32_t)nranks; a.cmax = cfg.max_channels; a.max_colls = 1; a.sq_depth = DFX_NA_SQ_DEPTH; a.sq_shift = 1; a.cq_slots = DFX_NA_CQ_SLOTS;
+  a.nwg = (uint32_t)nranks * tmpl.nchan;      // (no workgroup without a channel to serve)
+  a.scan_min = cfg.scan_min; a.epoch = 1;
+  a.R = (uint32_t)nranks; a.cmax = tmpl.nchan; a.max_colls = 1; a.sq_depth = DFX_NA_SQ_DEPTH; a.sq_shift = 1; a.cq_slots = DFX_NA_CQ_SLOTS;
   a.spin_init = cfg.spin_init; a.spin_min = cfg.spin_min; a.spin_max = cfg.spin_max; a.spin_boost = cfg.spin_boost; a.preempt = 1;
   a.wg_map = 0; a.order_policy = 0; a.trace_on = 0; a.fetch_batch = 0xffffffffu; a.fifo_coherent = 1; a.chan_spread = 1;
   a.cq_mode = 0; a.sq_eager = 1; a.window = cfg.window; a.sq_local = 1; a.focus_bytes = cfg.focus_bytes;
   a.watchdog_ticks = (uint64_t)((double)cfg.watchdog_ms * 1000.0 / nd->tick_us);
   a.quit_ticks = 0;
   a.oneshot = 1;
+  a.status = status_dev;
 
   NaSeed sd;
   memset(&sd, 0, sizeof(sd));
@@ -1533,12 +1530,11 @@ int dfx_collective_noalloc(int nranks, dfx_kind kind, size_t count, dfx_dtype dt
   for (int r = 0; r < nranks; ++r) { sd.sendbuf[r] = (uint64_t)(uintptr_t)sendbufs[r]; sd.recvbuf[r] = (uint64_t)(uintptr_t)recvbufs[r]; }
 
   hipStream_t st = (hipStream_t)hip_stream;
-  hipLaunchKernelGGL(dfx_na_zero_kernel, dim3(64), dim3(256), 0, st, (uint4*)base, (uint32_t)(DFX_NA_CTL_BYTES / 16));
-  hipLaunchKernelGGL(dfx_na_seed_kernel, dim3(1), dim3(64), 0, st, a.sq, sd);
+  const size_t lines_at = (size_t)DFX_NA_CTL_BYTES - na_up(flag_bytes);
+  hipLaunchKernelGGL(dfx_na_prepare_kernel, dim3(32), dim3(256), 0, st, base, (uint32_t)(L.end_of_zeroed / 16), (uint32_t)lines_at,
+                     (uint32_t)(na_up(flag_bytes) / 16), (uint32_t)L.sq, sd);
   if (hipGetLastError() != hipSuccess) return DFX_ERR_HIP;
-  if (dfx_daemon_launch(nwg, st, a) != hipSuccess) return DFX_ERR_HIP;
-  if (status_dev) hipLaunchKernelGGL(dfx_na_status_kernel, dim3(1), dim3(64), 0, st, a.dev_ctl, a.cq, (uint32_t)nranks, status_dev);
-  return hipGetLastError() == hipSuccess ? DFX_OK : DFX_ERR_HIP;
+  return dfx_daemon_launch(a.nwg, st, a) == hipSuccess ? DFX_OK : DFX_ERR_HIP;
 }
 
 // Calibration helper for the profiler's HBM byte counters: copies `bytes` (multiple of 16)

@@ -160,8 +160,9 @@ struct DfxDaemonArgs {
   uint64_t watchdog_ticks;  // wall-clock ticks; 0 = off
   uint64_t quit_ticks;      // wall-clock ticks; 0 = off
   uint32_t oneshot;         // not 0: the SQs were filled before the launch with this many entries per rank and nobody
-                            // will submit more: a workgroup that has read them all and finished its share votes to
-                            // leave (and never withdraws the vote); the last vote ends the grid
+                            // will submit more: a workgroup that has read them all and finished its share counts itself
+                            // out and leaves; the last one writes the outcome to `status`
+  uint32_t* status;         // one-shot launches: outcome (0, 0x100 | error, 0x200 = a completion is missing), or null
 };
 
 #endif

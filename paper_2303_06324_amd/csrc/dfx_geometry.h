@@ -117,7 +117,7 @@ DFX_HD bool fold_to_all(int kind) { return kind != KIND_RS && kind != KIND_RD; }
 // A job is a span of the region with its rows dealt (a slice; all of it where there is one slice), or so and so many
 // drawn rows per wave of the whole region, the last job of a share as many as there are.
 constexpr uint32_t DFX_FOLD_WAVES = DFX_MOVERS / 64;      // mover waves of a workgroup
-DFX_HD uint32_t fold_row_bytes(bool copies, uint32_t R) { return 1024u * (copies ? 4u : R == 4 ? 4u : R == 2 ? 8u : 2u); }
+DFX_HD uint32_t fold_row_bytes(bool copies, uint32_t R) { return 1024u * (R == 2 ? 8u : copies || R == 4 ? 4u : 2u); }
 
 // A rank's region in elements: where it begins in the message and how long it is.  chunk: what one rank has, in elements.
 DFX_HD uint64_t fold_chunk_elems(int kind, uint64_t count, uint64_t block, uint32_t R, uint32_t eb) {

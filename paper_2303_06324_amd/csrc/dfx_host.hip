@@ -506,8 +506,11 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
     t.nprim = fold_nprim((int)kind);
   }
   // Rows are drawn where a wave has at least four of them (with fewer the last ones are as uneven as equal parts) and
-  // the region's offsets fit 32 bits; a job size that the caller asked for keeps its slices, whose rows are dealt.
-  if ((t.flags & DFX_SQE_FOLD) && !cfg.fold_slice_bytes) {
+  // the region's offsets fit 32 bits; a job size that the caller asked for keeps its slices, whose rows are dealt, and so
+  // does priority ordering: its workgroups may be at different collectives, and one that is first at a region would
+  // draw all of it in a job that a more urgent collective has to wait for (sixteen staggered buckets: urgent one
+  // after 0.93 ms with drawn rows, 0.43-0.62 with dealt ones).
+  if ((t.flags & DFX_SQE_FOLD) && !cfg.fold_slice_bytes && cfg.order_policy != 1) {
     const uint64_t region = fold_chunk_elems((int)kind, count, t.block_elems, (uint32_t)R, eb) * eb;
     const uint64_t row = fold_row_bytes(kind == DFX_ALLGATHER || kind == DFX_BROADCAST, (uint32_t)R);
     if (region >= 4 * row * DFX_FOLD_WAVES * C && region <= (1ull << 30) && (t.rounds == 1 || t.slice_elems * (uint64_t)eb >= DFX_FOLD_WAVES * row))

@@ -20,10 +20,11 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E peak
 R = 8
-# HBM bytes per launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by the plain copy kernel
-# (profiles/hbm_traffic_allreduce_256MiB.md, all-reduce in fold steps): 8.002 x M read + 8.000 x M written per launch at
-# the default workload.  Reported only for that workload.
-MEASURED_TRAFFIC_BYTES = int(16.002 * (256 << 20))
+# HBM bytes per launch at the default workload, measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE and scaled by the plain
+# copy kernel (profiles/hbm_traffic_allreduce_256MiB.md): with the library's defaults (data in fold steps) 2 100 025 KiB read +
+# 2 101 305 KiB written; as a ring with direct steps (fold_max_bytes = 0) 5 511 100 KiB + 3 671 500 KiB.
+FOLD_TRAFFIC_BYTES = 4302161920
+MEASURED_TRAFFIC_BYTES = 9402982400
 
 
 def algorithmic_bytes(msg_bytes: int, nranks: int) -> int:
@@ -34,8 +35,8 @@ def algorithmic_bytes(msg_bytes: int, nranks: int) -> int:
 
 
 def moved_bytes(msg_bytes: int, nranks: int) -> int:
-    """What a ring with direct steps (fold_max_bytes = 0) moves for an all-reduce of 2 MiB or more: a finished chunk is written once (recv buffer) instead of twice (recv buffer and slot),
-    and the opening send moves nothing (the next rank reads the chunk from the send buffer):
+    """What a ring with direct steps (fold_max_bytes = 0) moves for an all-reduce of 2 MiB or more: a finished chunk is
+    written once (recv buffer) instead of twice (recv buffer and slot), and the opening send moves nothing (the next rank reads the chunk from the send buffer):
     reads (3R-3)/R * M, writes (2R-2)/R * M per rank."""
     return (5 * nranks - 5) * msg_bytes
 
@@ -627,7 +628,7 @@ def main():
         # whose figure is given beside it: work per time, which moving less raises.
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": MEASURED_TRAFFIC_BYTES if args.msg_mib == 256 and direct else None,
+                     "traffic": FOLD_TRAFFIC_BYTES if args.msg_mib == 256 and direct else None,
                      "traffic_source": "profiles/hbm_traffic_allreduce_256MiB.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE scaled "
                                        "by the copy kernel; a constant from that profile, not measured in this run)"
                                        if args.msg_mib == 256 and direct else None,

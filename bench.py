@@ -268,8 +268,8 @@ def size_sweep(iters: int = 10):
     rows = []
     for nbytes in wi.CONFIG2_SIZES:
         best, nchan, nprim = res[("default", nbytes)]
-        path = {2: "fold steps", 2 * R: "ring geometry, direct in fold steps"}.get(nprim, "ring through slots")
-        nb = {2: fold_bytes, 2 * R: fold_bytes}.get(nprim, algorithmic_bytes)(nbytes, R)     # what the path taken moves
+        path = {2: "fold steps", 2 * R: "ring with direct steps"}.get(nprim, "ring through slots")
+        nb = {2: fold_bytes, 2 * R: moved_bytes}.get(nprim, algorithmic_bytes)(nbytes, R)     # what the path taken moves
         rows.append({"bytes": nbytes, "us": round(best * 1e6, 1), "channels": nchan,
                      "algbw_GBs": round(nbytes / best / 1e9, 2),
                      "busbw_GBs": round(nbytes / best * 2 * (R - 1) / R / 1e9, 2),
@@ -574,7 +574,7 @@ def main():
     # what the last timed step left in the recv buffers (checked against the oracle below, outside the timed region)
     got = {r: recv[r].cpu().numpy() for r in (0, 5)}
     same_on_all_ranks = all(torch.equal(recv[0].view(torch.int32), recv[r].view(torch.int32)) for r in range(1, R))
-    # the same workload in fold steps of one slice (the default below 64 MiB per rank), for the record
+    # the same workload in fold steps of one job (as messages below 64 MiB per rank run), inside a resident daemon, for the record
     fold_ms = None
     if not args.no_fold:
         cfg2 = gh.make_config(quit_idle_us=0, fold_max_bytes=min(2 * M, (1 << 32) - 1))
@@ -607,8 +607,8 @@ def main():
     algbw = M / (ms_per_step * 1e-3) / 1e9
     busbw = algbw * 2 * (R - 1) / R
     k_ms = sum(kern_ms) / len(kern_ms)
-    direct = info["nprim"] == 2 * R          # the all-reduce qualifies for direct steps: its data moves in fold steps
-    launch_bytes = fold_bytes(M, R) if direct else algorithmic_bytes(M, R)
+    fold = info["nprim"] == 2                # what runs: fold steps (else the ring, with direct steps or through slots)
+    launch_bytes = (fold_bytes if fold else moved_bytes if info["nprim"] == 2 * R else algorithmic_bytes)(M, R)
     achieved = launch_bytes / (k_ms * 1e-3) / 1e9
     table_rate = algorithmic_bytes(M, R) / (k_ms * 1e-3) / 1e9
     out = {
@@ -619,7 +619,8 @@ def main():
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": f"config 2: R=8 virtual ranks, one all-reduce(sum) fp32, {args.msg_mib} MiB per rank, "
                                f"ring chunk = size/8, N(0,1) inputs resident in HBM",
-                   "channels_per_rank": info["nchan"], "slot_bytes": info["slot_bytes"], "rounds": info["rounds"],
+                   "path": "fold steps" if fold else "ring", "channels_per_rank": info["nchan"], "slice_bytes": info["slot_bytes"],
+                   "slices": info["rounds"],
                    "daemon_launches": int(launches)},
         "algbw_GBs": round(algbw, 2),
         "hbm_frac_wall": round(launch_bytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
@@ -628,13 +629,13 @@ def main():
         # whose figure is given beside it: work per time, which moving less raises.
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": FOLD_TRAFFIC_BYTES if args.msg_mib == 256 and direct else None,
+                     "traffic": FOLD_TRAFFIC_BYTES if args.msg_mib == 256 and fold else None,
                      "traffic_source": "profiles/hbm_traffic_allreduce_256MiB.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE scaled "
                                        "by the copy kernel; a constant from that profile, not measured in this run)"
-                                       if args.msg_mib == 256 and direct else None,
+                                       if args.msg_mib == 256 and fold else None,
                      "kernel": "dfx_daemon_kernel", "kernel_ms_avg": round(k_ms, 4),
                      "bytes_moved_per_launch": launch_bytes,
-                     "note": "achieved = bytes the shipped path moves per launch (2R x M: every input read once, every output "
+                     "note": "achieved = bytes the shipped path moves per launch (fold steps: 2R x M, every input read once, every output "
                              "written once) / kernel time, launch, submission and exit of the daemon included",
                      "primitive_table_bytes_per_launch": algorithmic_bytes(M, R),
                      "primitive_table_GBs": round(table_rate, 1),
@@ -643,8 +644,8 @@ def main():
     }
     if fold_ms is not None:
         out["fold_steps_same_workload"] = {
-            "note": "the same all-reduce in fold steps (library default below 64 MiB per rank; here forced): resident daemon, "
-                    "submit -> last CQE, best of 6; moves 2R x M (every input read once, every output written once) instead of (5R-5) x M and uses no FIFO slots",
+            "note": "the same all-reduce with its share in one job instead of several (as below 64 MiB per rank): resident daemon, "
+                    "submit -> last CQE, best of 6; moves what the headline moves",
             "ms": round(fold_ms, 4), "busbw_GBs": round(M / (fold_ms * 1e-3) / 1e9 * 2 * (R - 1) / R, 2),
             "bytes_moved": fold_bytes(M, R), "hbm_frac": round(fold_bytes(M, R) / (fold_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
     del send, recv

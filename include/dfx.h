@@ -149,19 +149,20 @@ typedef struct {
                               quarter of it per rank); 0 = every
                               all-reduce, broadcast and reduce, every all-gather and reduce-scatter of
                               16-byte-multiple blocks */
-  uint32_t fold_max_bytes; /* default 64 MiB: an all-reduce of fewer bytes per rank runs in fold steps instead of ring steps.
-                              The 2R-1 ring steps depend on one another and cost a few microseconds each whatever the
-                              size, and a short message gives a channel one slice, so nothing hides them; with all
-                              buffers in one HBM two steps that wait on all ranks at once do the same work: (1) when
-                              every rank has submitted, rank r combines chunk r out of all R send buffers in the ring's
-                              own order (x[r+1] (op) ... (op) x[r]: same association, same bits) and writes the result
-                              into chunk r of all R recv buffers; (2) when every rank has done so, it posts the
-                              completion (every input read once, every output written once).  Each step is a bounded
-                              wait (Sec. 4.2) followed by the data, preempted like any primitive.  From this size on a
-                              collective keeps the geometry of its ring or chain (dfx_coll_info, connector block); one that
-                              qualifies for direct steps has its data moved in the same two steps all the same, slice by
-                              slice, and with direct = 0 the ring through the connectors' FIFOs is what runs.  0 = off:
-                              rings and chains at every size */
+  uint32_t fold_max_bytes; /* default 64 MiB; 0 = off: rings and chains at every size.  A collective whose largest buffer per
+                              rank is smaller runs in fold steps instead of the steps of its ring or chain (an all-gather
+                              or reduce-scatter: if its blocks are 16-byte multiples).  Ring steps depend on one another
+                              and cost a few microseconds each whatever the size, and a short message gives a channel
+                              one slice, so nothing hides them; with all buffers in one HBM two steps that wait on all
+                              ranks at once do the same work: (1) when every rank has submitted, each rank does its part
+                              straight from send buffers to recv buffers (all-reduce: rank r combines chunk r out of all
+                              R send buffers in the ring's own order, x[r+1] (op) ... (op) x[r] -- same association, same
+                              bits -- and writes the result into chunk r of all R recv buffers); (2) when every rank has
+                              done so, it posts the completion (every input read once, every output written once).  Each
+                              step is a bounded wait (Sec. 4.2) followed by the data, preempted like any primitive.
+                              From this size on the collectives that qualify for direct steps run in fold steps too, in
+                              several jobs; the others (direct = 0, or below direct_min_bytes) as rings and chains
+                              through the connectors' FIFOs.  dfx_coll_info tells what runs */
   uint32_t fold_slice_bytes; /* a collective in fold steps takes its share of a channel in slices of at most this many bytes
                               per source, one mover job each (16-byte multiple), so that what is ahead of an urgent
                               collective under priority ordering is short; 0 (default) = one slice, the whole share
@@ -321,7 +322,10 @@ int dfx_stop(dfx_ctx* ctx);
 /* Counters of one vrank; out: host. Safe while the daemon runs (values may lag). */
 int dfx_stats(dfx_ctx* ctx, int rank, dfx_stats_t* out);
 
-/* Geometry the library chose for a prepared collective (for tests and the bench). */
+/* Geometry of what runs for a prepared collective (for tests and the bench): channels; bytes of one slice (of one mover
+   job's part of every source, where the collective runs in fold steps); slices (jobs) of a channel's share; primitives per
+   slice.  nprim = 2 on more than one rank says fold steps, except for an all-gather or reduce-scatter of two ranks, whose
+   ring through slots has two as well; chains have 1 and one round more than slices where they take direct steps. */
 int dfx_coll_info(dfx_ctx* ctx, int coll_id, uint32_t* nchan, uint32_t* slot_bytes, uint32_t* rounds,
                   uint32_t* nprim);
 

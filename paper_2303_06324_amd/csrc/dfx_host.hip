@@ -28,7 +28,7 @@ hipError_t dfx_copy_launch(const void* src, void* dst, size_t bytes, hipStream_t
 
 namespace {
 
-// What dfx_coll_info reports: the geometry of the collective's ring or chain (or of its fold steps).
+// What dfx_coll_info reports: the geometry of what runs (ring or chain, or fold steps).
 struct CollShape { uint32_t nchan, slot_bytes, rounds, nprim; };
 
 struct CollInfo {
@@ -486,7 +486,7 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
     t.nprim = (uint32_t)R + 1u;
   }
   else t.nprim = (uint32_t)R;
-  if (shape) *shape = CollShape{t.nchan, t.slot_bytes, t.rounds, t.nprim};
+  CollShape runs{t.nchan, t.slot_bytes, t.rounds, t.nprim};
   // Long collectives: what direct steps save of a ring's or chain's traffic, fold steps save in full (every input read
   // once, every output written once: 2R x M of an all-reduce instead of (5R-5) x M), so a collective that qualifies for
   // direct steps runs in fold steps above fold_max_bytes too, in jobs of this size.  Measured (us, R = 8, rings and
@@ -504,7 +504,9 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
     t.slice_elems = (uint32_t)(bytes / eb);
     t.rounds = (uint32_t)std::max<uint64_t>(1, ceil_div(share, t.slice_elems));
     t.nprim = fold_nprim((int)kind);
+    runs = CollShape{t.nchan, (uint32_t)bytes, t.rounds, t.nprim};
   }
+  if (shape) *shape = runs;
   // Rows are drawn where a wave has at least four of them (with fewer the last ones are as uneven as equal parts) and
   // the region's offsets fit 32 bits; a job size that the caller asked for keeps its slices, whose rows are dealt, and so
   // does priority ordering: its workgroups may be at different collectives, and one that is first at a region would

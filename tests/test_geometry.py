@@ -31,6 +31,7 @@ def test_workload_of_the_faulting_run_under_every_map(wg_map):
              (dfx.BROADCAST, 1 << 21)]
     for i, (kind, count) in enumerate(cases):                       # coll ids 0 .. 9 as in that run
         assert dfx.check_geometry(R, kind, count, dfx.F32, root=3, coll_id=i, wg_map=wg_map) == "", (kind, count)
+        assert dfx.check_geometry(R, kind, count, dfx.F32, root=3, coll_id=i, wg_map=wg_map, cfg=_cfg(fold_max_bytes=0)) == "", (kind, count)
     for p in range(13, 27):                                         # the all-reduce size sweep
         assert dfx.check_geometry(R, dfx.ALLREDUCE, (1 << p) // 4, dfx.F32, wg_map=wg_map) == ""
     n3 = 25 * (1 << 20) // 2                                        # the sixteen bf16 buckets
@@ -62,9 +63,10 @@ def test_scheduler_knobs(knobs):
                 assert msg == "", (knobs, kind, count, cid, msg)
 
 
-def test_a_large_offset_case():
-    """5 GiB + a ragged tail per rank on two ranks: byte offsets beyond 2^32, thousands of slices per channel."""
-    assert dfx.check_geometry(2, dfx.ALLREDUCE, (5 << 30) // 4 + 12345, dfx.I32) == ""
+@pytest.mark.parametrize("knobs", [dict(), dict(fold_max_bytes=0), dict(direct=0)], ids=["defaults", "ring_with_direct_steps", "through_slots"])
+def test_a_large_offset_case(knobs):
+    """5 GiB + a ragged tail per rank on two ranks: byte offsets beyond 2^32, hundreds of slices per channel."""
+    assert dfx.check_geometry(2, dfx.ALLREDUCE, (5 << 30) // 4 + 12345, dfx.I32, cfg=_cfg(**knobs)) == ""
 
 
 def test_it_refuses_what_it_cannot_check():

@@ -44,12 +44,13 @@ def _equal_whole(t, want, what):
         raise AssertionError(f"{what}: {bad.size} words differ, first at element {int(bad[0])}")
 
 
-@pytest.mark.parametrize("knobs", [dict(), dict(direct=0), dict(direct=0, slot_bytes=128 << 10), dict(fold_max_bytes=512 << 20)],
-                         ids=["defaults", "every_step_through_a_slot", "slots_128KiB", "fold_steps"])
-def test_config2_largest_size_whole_buffers(big, knobs):
+@pytest.mark.parametrize("knobs,nprim,slices", [(dict(), 2, "many"), (dict(fold_max_bytes=0), 16, "many"), (dict(direct=0), 15, "many"),
+                                                (dict(direct=0, slot_bytes=128 << 10), 15, "many"), (dict(fold_max_bytes=512 << 20), 2, "one")],
+                         ids=["defaults", "ring_with_direct_steps", "every_step_through_a_slot", "slots_128KiB", "fold_steps_in_one_job"])
+def test_config2_largest_size_whole_buffers(big, knobs, nprim, slices):
     """The size the headline metric is quoted on: all 8 x 64 Mi elements compared with the oracle's fold,
-    for the library defaults (the ring with direct steps), with every step through a FIFO slot, and in fold steps
-    (which the defaults take below 64 MiB); two invocations, so
+    for the library defaults (fold steps in several jobs), for the ring with direct steps, with every step through a FIFO
+    slot, and in fold steps of one job (which the defaults take below 64 MiB); two invocations, so
     that the second one starts with the connectors' counters mid-ring."""
     import paper_2303_06324_amd as dfx
     from paper_2303_06324_amd import harness as gh
@@ -60,7 +61,8 @@ def test_config2_largest_size_whole_buffers(big, knobs):
     ctx = dfx.Context(R, gh.make_config(**knobs))
     try:
         ctx.prepare(0, dfx.ALLREDUCE, n, dfx.F32)
-        assert ctx.coll_info(0)["nprim"] == (2 if "fold_max_bytes" in knobs else 2 * R if knobs.get("direct", 1) else 2 * R - 1)
+        info = ctx.coll_info(0)                          # the path that runs: 2 steps, 2R ring steps (direct), 2R-1 ring steps
+        assert info["nprim"] == nprim and (info["rounds"] > 1) == (slices == "many"), info
         for it in range(2):
             dw.reset_recv()
             for r in range(R):
@@ -79,13 +81,15 @@ def test_config2_largest_size_whole_buffers(big, knobs):
     assert np.all(np.abs(want.astype(np.float64) - ref) <= 1e-6 * mag)
 
 
-def test_other_kinds_at_the_largest_size(big):
-    """All-gather, reduce-scatter, broadcast and reduce at 256 MiB of largest per-rank buffer, fp32, library
-    defaults (the configuration of the bench's table of kinds: direct steps, several slices per channel share,
-    512 KiB / 64 KiB slices for the chains): whole buffers against the oracle's closed forms; what a kind must
-    not write keeps its fill pattern."""
+@pytest.mark.parametrize("knobs", [dict(), dict(fold_max_bytes=0)], ids=["defaults", "rings_and_chains_with_direct_steps"])
+def test_other_kinds_at_the_largest_size(big, knobs):
+    """All-gather, reduce-scatter, broadcast and reduce at 256 MiB of largest per-rank buffer, fp32, with the library
+    defaults (the configuration of the bench's table of kinds: fold steps in several jobs) and as rings and chains (direct
+    steps, several slices per channel share, 512 KiB / 64 KiB slices for the chains): whole buffers against the oracle's
+    closed forms; what a kind must not write keeps its fill pattern."""
     import torch
     import paper_2303_06324_amd as dfx
+    from paper_2303_06324_amd import harness as gh
     w, dw = big
     R, n, root = 8, w.colls[0].count, 3
     blk = n // R
@@ -100,14 +104,15 @@ def test_other_kinds_at_the_largest_size(big):
     def untouched(t, lo_bytes):
         return bool((t[lo_bytes:] == 0xA5).all())
 
-    ctx = dfx.Context(R)
+    ctx = dfx.Context(R, gh.make_config(**knobs))
     try:
         ctx.prepare(0, dfx.ALLGATHER, blk, dfx.F32)
         ctx.prepare(1, dfx.REDUCESCATTER, blk, dfx.F32)
         ctx.prepare(2, dfx.BROADCAST, n, dfx.F32, dfx.SUM, root)
         ctx.prepare(3, dfx.REDUCE, n, dfx.F32, dfx.SUM, root)
-        assert ctx.coll_info(0)["rounds"] == 4 and ctx.coll_info(0)["nprim"] == R + 1
-        assert ctx.coll_info(1)["rounds"] == 4 and ctx.coll_info(1)["nprim"] == R + 1
+        runs = [(ctx.coll_info(i)["nprim"], ctx.coll_info(i)["rounds"]) for i in range(4)]
+        if knobs: assert runs == [(R + 1, 4), (R + 1, 4), (1, 17), (1, 129)], runs      # (the chains' last round is the drain)
+        else: assert all(p == 2 and g > 1 for p, g in runs), runs
 
         run(ctx, 0)                                  # all-gather: every rank ends with the concatenation
         want = rd.all_gather_definition([h[:blk] for h in host])
@@ -198,23 +203,25 @@ def test_config5_full_1024_small_allreduces():
     assert max(s["max_taskq"] for s in stats) <= 1024
 
 
-def test_allreduce_beyond_4GiB_offsets_sampled():
-    """R = 2, int32, 5 GiB + a ragged tail per rank: byte offsets inside one buffer pass 2^32, thousands of
-    slices per channel.  Integer sums are exact in any order, so whole-buffer checks run on the device too;
-    sampled windows (chunk boundary, both ends, around the 4 GiB mark, random) go through the oracle."""
+@pytest.mark.parametrize("knobs,nprim", [(dict(), 2), (dict(fold_max_bytes=0), 4)], ids=["defaults", "ring_with_direct_steps"])
+def test_allreduce_beyond_4GiB_offsets_sampled(knobs, nprim):
+    """R = 2, int32, 5 GiB + a ragged tail per rank: byte offsets inside one buffer pass 2^32, hundreds of
+    slices per channel, in fold steps and as a ring.  Integer sums are exact in any order, so whole-buffer checks run on the
+    device too; sampled windows (chunk boundary, both ends, around the 4 GiB mark, random) go through the oracle."""
     import torch
     import paper_2303_06324_amd as dfx
+    from paper_2303_06324_amd import harness as gh
     R, n = 2, (5 << 30) // 4 + 12345
     g = torch.Generator(device="cuda")
     g.manual_seed(99)
     send = [torch.randint(-(1 << 20), 1 << 20, (n,), device="cuda", dtype=torch.int32, generator=g) for _ in range(R)]
     recv = [torch.full((n,), -7, device="cuda", dtype=torch.int32) for _ in range(R)]
     torch.cuda.synchronize()
-    ctx = dfx.Context(R)
+    ctx = dfx.Context(R, gh.make_config(**knobs))
     try:
         ctx.prepare(0, dfx.ALLREDUCE, n, dfx.I32)
         info = ctx.coll_info(0)
-        assert info["rounds"] > 100
+        assert info["rounds"] > 100 and info["nprim"] == nprim, info
         for r in range(R):
             assert ctx.submit(r, 0, send[r].data_ptr(), recv[r].data_ptr()) == dfx.OK
         assert ctx.wait_all(60.0) == dfx.OK

@@ -40,7 +40,8 @@ def _both_paths(kind, dtype, count, R, root=0, op=wi.SUM, seed=0):
 
 
 def test_noalloc_two_calls_in_a_row_second_one_smaller():
-    _both_paths(wi.AR, wi.F32, 17 * (1 << 20) + 7, 8, seed=1)    # 68 MiB per rank: the ring, direct steps, many slices through the scratch's slots
+    _both_paths(wi.AR, wi.F32, 17 * (1 << 20) + 7, 8, seed=1)    # 68 MiB per rank: fold steps in several jobs
+    _both_paths(wi.RS, wi.I32, (2 << 20) + 1, 8, seed=4)         # blocks that are no 16-byte multiples: the ring, many slices through the scratch's slots
     _both_paths(wi.AR, wi.F32, 4099, 8, seed=2)                   # smaller: one channel, fold steps
     _both_paths(wi.AR, wi.BF16, 300007, 8, op=wi.MAX, seed=3)
 

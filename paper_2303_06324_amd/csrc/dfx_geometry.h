@@ -288,7 +288,7 @@ DFX_HD DfxCooked cook_sqe(const DfxStatic& q, uint8_t* pool, uint32_t rank, uint
     // fold steps have no connectors: the words carry the channel's shared counters, the channel's first line (rank 0's;
     // the others follow nchan lines apart) and what the counter of finished steps shows at the end of this invocation
     k.fifo_in = fold_line(k.flags_out, rank, 0, q.nchan);
-    k.flags_in = (q.flags & DFX_SQE_LONG) ? k.fifo_in + DFX_FOLD_HEAD : fold_shared_line(k.flags_out, rank, R, q.nchan);
+    k.flags_in = fold_shared_line(k.flags_out, rank, R, q.nchan);
     k.fifo_out = ((uint64_t)q.seq + 1u) * (R * q.rounds);
     // the buffers' addresses travel through the lines: the words carry the jobs' row limit and a channel's part of a slice
     k.sendbuf = q.slot_bytes;

@@ -433,10 +433,6 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   const uint64_t rounds = std::max<uint64_t>(1, ceil_div(part, slice_elems));
   if (rounds > 0xfffffffeull) return DFX_ERR_INVALID_ARG;
   const uint64_t K = cfg.nslots;
-  // (a direct broadcast fills no slot: its connectors are the flag lines alone)
-  // (a collective in fold steps has none either: R x C lines with the published addresses and C shared lines of counters)
-  *conn_bytes_out = fold ? round_up((R + 1) * C * DFX_FLAG_STRIDE, 256)
-                         : round_up(R * C * DFX_FLAG_STRIDE + (bc_direct ? 0 : R * C * K * slot_bytes), 256);
 
   DfxStatic t;
   memset(&t, 0, sizeof(t));
@@ -492,7 +488,7 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   // direct steps runs in fold steps above fold_max_bytes too, in jobs of this size.  Measured (us, R = 8, rings and
   // chains with direct steps -> this): all-reduce 256 MiB fp32 1545 -> 876, reduce-scatter 128 MiB fp32 496 -> 267,
   // broadcast 100 MiB bf16 472 -> 204.
-  // With fold_max_bytes = 0 the rings and chains run at every size.  The connector block stays what it was.
+  // With fold_max_bytes = 0 the rings and chains run at every size.
   if ((t.flags & DFX_SQE_DIRECT) && !fold && cfg.fold_max_bytes && blocks_ok && !(kind == DFX_REDUCE && R > 63)) {
     // 128 KiB per source and workgroup: about 100 us at 2 x 8 streams; priority ordering lets nothing longer than
     // its look-again budget get ahead of an urgent collective
@@ -500,13 +496,17 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
     const uint64_t chunk = fold_chunk_elems((int)kind, count, block, (uint32_t)R, eb);     // a rank's region; a channel's part of it
     const uint64_t share = std::max<uint64_t>(round_up(ceil_div(chunk, C), per16), per16);
     const uint64_t bytes = std::min<uint64_t>(std::min<uint64_t>(job, ((1ull << 30) / C) & ~15ull), share * eb);
-    t.flags |= DFX_SQE_FOLD | DFX_SQE_LONG;
+    t.flags |= DFX_SQE_FOLD;
     t.slice_elems = (uint32_t)(bytes / eb);
     t.rounds = (uint32_t)std::max<uint64_t>(1, ceil_div(share, t.slice_elems));
     t.nprim = fold_nprim((int)kind);
     runs = CollShape{t.nchan, (uint32_t)bytes, t.rounds, t.nprim};
   }
   if (shape) *shape = runs;
+  // (a collective in fold steps has no slots: R x C lines with the published addresses and C shared lines of counters; a
+  // direct broadcast fills none either: its connectors are the flag lines alone)
+  *conn_bytes_out = round_up((t.flags & DFX_SQE_FOLD) ? (R + 1) * C * DFX_FLAG_STRIDE
+                                                      : R * C * DFX_FLAG_STRIDE + (bc_direct ? 0 : R * C * K * slot_bytes), 256);
   // Rows are drawn where a wave has at least four of them (with fewer the last ones are as uneven as equal parts) and
   // the region's offsets fit 32 bits; a job size that the caller asked for keeps its slices, whose rows are dealt, and so
   // does priority ordering: its workgroups may be at different collectives, and one that is first at a region would
@@ -1232,7 +1232,7 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
       if (fold) {
         // every rank of the channel finds the same lines: rank k's from any rank's own line, and the shared one
         const uint64_t sh_line = me.flags_in;
-        if ((t.flags & DFX_SQE_LONG) ? sh_line != me.fifo_in + DFX_FOLD_HEAD : (sh_line < flags_hi || sh_line + DFX_FLAG_STRIDE > blk_hi))
+        if (sh_line < flags_hi || sh_line + DFX_FLAG_STRIDE > blk_hi)
           return fail("rank %u channel %u: shared counters %llx outside their line", r, v, (unsigned long long)sh_line);
         for (uint32_t sq = 0; sq < 2; ++sq)
           if (fold_draw_word(me.fifo_in, r, v, t.nchan, sq) != cooked[(size_t)r * t.nchan].flags_out + DFX_FOLD_DRAW + 8u * sq)
@@ -1514,7 +1514,7 @@ int dfx_collective_noalloc(int nranks, dfx_kind kind, size_t count, dfx_dtype dt
   if (rc != DFX_OK) return rc;
   // connector block = flag lines of the collective's R x C edges, then their slots; the scratch holds
   // DFX_NA_MAX_WG flag lines and as many connectors of DFX_NA_NSLOTS x DFX_NA_SLOT_BYTES
-  const size_t flag_bytes = (size_t)(nranks + ((tmpl.flags & (DFX_SQE_FOLD | DFX_SQE_LONG)) == DFX_SQE_FOLD ? 1 : 0)) * tmpl.nchan * DFX_FLAG_STRIDE;
+  const size_t flag_bytes = (size_t)(nranks + ((tmpl.flags & DFX_SQE_FOLD) ? 1 : 0)) * tmpl.nchan * DFX_FLAG_STRIDE;
   if (flag_bytes > (size_t)DFX_NA_LINES * DFX_FLAG_STRIDE || conn_bytes > flag_bytes + DFX_NA_SLOTS_BYTES + 256) return DFX_ERR_TOO_LARGE;
   // the flag lines end where the zeroed part ends, the slots begin right there
   tmpl.conn_off = (uint64_t)((size_t)DFX_NA_CTL_BYTES - flag_bytes - L.pool);

@@ -25,14 +25,11 @@
 #define DFX_CTX_DIRECT 0x80u   // the same, in the cooked context's bc_pos byte (bits 0-1: place in a chain)
 #define DFX_SQE_FOLD 4u        // all-reduce in fold steps (always together with DFX_SQE_DIRECT: the buffers are published the same way)
 #define DFX_CTX_FOLD 0x40u     // the same, in the cooked context's bc_pos byte
-#define DFX_SQE_LONG 8u        // a long collective in fold steps (always together with DFX_SQE_FOLD): its connector block is laid out for the ring or chain
 #define DFX_SQE_DRAWN 16u      // fold steps: the rows of a rank's region are drawn from a counter (fold_entry)
 #define DFX_CTX_DRAWN 0x20u    // the same, in the cooked context's bc_pos byte
-// A collective in fold steps has no slots.  Its connector block is R x nchan flag lines, one per (rank, channel),
-// that carry the published buffer addresses (DFX_DIRECT_OFF), and behind them nchan shared lines, one per
-// channel, with two counters that every rank of the channel adds to (a long collective keeps the block that its ring
-// or chain would have: there the counters are in the head half, at DFX_FOLD_HEAD, of rank 0's line, which nobody else uses):
-#define DFX_FOLD_HEAD 64
+// A collective in fold steps has no slots, whatever its size.  Its connector block is R x nchan flag lines, one per (rank,
+// channel), that carry the published buffer addresses (DFX_DIRECT_OFF), and behind them nchan shared lines, one per
+// channel, with two counters that every rank of the channel adds to.
 // Row counters of a rank's region: two words in the head half of the rank's line of channel 0, for even and odd
 // invocations; the other one starts over when an invocation is fetched.
 #define DFX_FOLD_DRAW 96

@@ -523,7 +523,7 @@ struct Rows {
   GLOBAL_AS uint32_t* ctr;   // the region's row counter
   uint32_t waves;            // mover waves of all the region's workgroups
   uint32_t row;              // the row in hand
-  uint32_t left;             // rows this wave may still take in the job, the one in hand included (0xffffffff = no limit)
+  uint32_t left;             // rows this wave may still take in the job, the one in hand included (0xffffffff = no limit: dealt)
   uint32_t drawn;            // lane 0: the answer to the last draw
   // Begin: the first job of a share starts with the wave's own row, later ones draw theirs.
   __device__ __forceinline__ void begin(bool fresh, uint32_t wave_index) {
@@ -730,7 +730,7 @@ struct Job {                         // what the scheduler wave hands to the mov
   uint32_t coll, prim;               // for the timeline trace only
   uint32_t nsrc, ndst;               // not 0: step with data of a collective in fold steps (that many sources and destinations in the job's tables)
   uint32_t index, sharers;           // ... which of the region's workgroups this is, and how many there are
-  uint32_t limit, fresh;             // ... rows per wave (0 = no limit); first job of the share
+  uint32_t limit, fresh;             // ... drawn rows per wave at most (0 = rows are dealt); first job of the share
   u64 draw;                          // ... the region's row counter (0 = rows are dealt)
 };
 
@@ -922,7 +922,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
         const bool fresh = bcast0(j.fresh) != 0;
         Rows rows;
         rows.ctr = (GLOBAL_AS uint32_t*)(uint32_t*)bcast64((uint32_t)j.draw, (uint32_t)(j.draw >> 32));
-        rows.waves = sharers * (GTHREADS / 64);
+        rows.waves = sharers * DFX_FOLD_WAVES;
         rows.left = limit ? limit : 0xffffffffu;
         rows.drawn = 0;
         rows.begin(fresh, wave * sharers + index);
@@ -1623,7 +1623,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
               Job j;
               j.fin = nullptr; j.fout = nullptr; j.sb = nullptr; j.rb = nullptr;
               j.bytes = fg.bytes; j.index = vch; j.sharers = inv_nchan;
-              j.limit = nx.p ? 0u : row_limit;                        // (the last job takes all the rows there are)
+              j.limit = row_limit;
               j.fresh = !drawn || g == 0;
               j.draw = drawn ? fold_draw_word(s_fin, rank, vch, inv_nchan, inv_seq) : 0;
               j.nsrc = copies ? 1u : R; j.ndst = to_all ? R : 1u;

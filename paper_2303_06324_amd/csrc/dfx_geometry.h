@@ -114,9 +114,11 @@ DFX_HD bool fold_to_all(int kind) { return kind != KIND_RS && kind != KIND_RD; }
 // does not serve workgroups alike, and the workgroups of one rank were through with equal parts after 15 to 50 us
 // (all-gather of 32 MiB); drawn, after 46 to 53.  Host to host: 25 MiB bf16 bucket 107 -> 101 us, sixteen of them 1405 -> 1315,
 // all-reduce of 256 MiB 876 -> 857.
-// A job is a span of the region with its rows dealt (a slice; all of it where there is one slice), or so and so many
-// drawn rows per wave of the whole region, the last job of a share as many as there are.
-constexpr uint32_t DFX_FOLD_WAVES = DFX_MOVERS / 64;      // mover waves of a workgroup
+// A job is a span of the region with its rows dealt (a slice; all of it where there is one slice), or at most so and so
+// many drawn rows per wave.  The limit holds for every job, so that a workgroup that is alone at a region -- the others of
+// its rank are still at another collective -- moves no more than twice its equal part before it looks at its queue again;
+// all jobs together may take more rows than there are, so that whoever is through early can go on.
+constexpr uint32_t DFX_FOLD_WAVES = DFX_MOVERS / 64 / DFX_MOVER_GROUPS;      // mover waves that share a job
 DFX_HD uint32_t fold_row_bytes(bool copies, uint32_t R) { return 1024u * (R == 2 ? 8u : copies || R == 4 ? 4u : 2u); }
 
 // A rank's region in elements: where it begins in the message and how long it is.  chunk: what one rank has, in elements.
@@ -132,7 +134,7 @@ DFX_HD uint64_t fold_chunk_elems(int kind, uint64_t count, uint64_t block, uint3
 //   block_elems where the region begins in the send buffers it is read from
 //   part_elems  where it begins in the recv buffers it is written to
 //   slice_elems span of one slice, all channels together (at most 1 GiB); rows are drawn: the longest region, all of it
-//   slot_bytes  rows are drawn: rows per wave and job (0 = no limit)
+//   slot_bytes  rows are drawn: rows per wave and job at most (0: rows are dealt)
 //   share       one channel's part of a slice or job
 DFX_HD void fold_entry(DfxStatic& e, uint32_t R, uint32_t rank) {
   const int kind = e.kind;
@@ -147,11 +149,8 @@ DFX_HD void fold_entry(DfxStatic& e, uint32_t R, uint32_t rank) {
   e.block_elems = (start + (kind == KIND_RS ? (uint64_t)rank * count : 0u)) * eb;
   e.part_elems = (start + (kind == KIND_AG ? (uint64_t)rank * count : 0u)) * eb;
   e.share = e.slice_elems * eb;
-  if (e.flags & DFX_SQE_DRAWN) {
-    const uint32_t row = fold_row_bytes(kind == KIND_AG || kind == KIND_BC, R);
-    e.slice_elems = (uint32_t)(chunk * eb);
-    e.slot_bytes = e.rounds > 1 ? e.share / (DFX_FOLD_WAVES * row) : 0u;
-  } else {
+  if (e.flags & DFX_SQE_DRAWN) e.slice_elems = (uint32_t)(chunk * eb);      // (slot_bytes: the plan's row limit)
+  else {
     e.slice_elems = (uint32_t)(e.nchan * (uint64_t)e.share);
     e.slot_bytes = 0;
   }

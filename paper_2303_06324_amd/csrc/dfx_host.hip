@@ -502,7 +502,6 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
     t.nprim = fold_nprim((int)kind);
     runs = CollShape{t.nchan, (uint32_t)bytes, t.rounds, t.nprim};
   }
-  if (shape) *shape = runs;
   // (a collective in fold steps has no slots: R x C lines with the published addresses and C shared lines of counters; a
   // direct broadcast fills none either: its connectors are the flag lines alone)
   *conn_bytes_out = round_up((t.flags & DFX_SQE_FOLD) ? (R + 1) * C * DFX_FLAG_STRIDE
@@ -514,10 +513,25 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   // after 0.93 ms with drawn rows, 0.43-0.62 with dealt ones).
   if ((t.flags & DFX_SQE_FOLD) && !cfg.fold_slice_bytes && cfg.order_policy != 1) {
     const uint64_t region = fold_chunk_elems((int)kind, count, t.block_elems, (uint32_t)R, eb) * eb;
-    const uint64_t row = fold_row_bytes(kind == DFX_ALLGATHER || kind == DFX_BROADCAST, (uint32_t)R);
-    if (region >= 4 * row * DFX_FOLD_WAVES * C && region <= (1ull << 30) && (t.rounds == 1 || t.slice_elems * (uint64_t)eb >= DFX_FOLD_WAVES * row))
+    const uint64_t row = fold_row_bytes(kind == DFX_ALLGATHER || kind == DFX_BROADCAST, (uint32_t)R), waves = DFX_FOLD_WAVES * C;
+    if (region >= 4 * row * waves && region <= (1ull << 30)) {
+      // Rows a wave may take in one job: twice its equal part of the region, or of a slice where there are several; then
+      // half as many jobs again as hold the region, so that fast workgroups can take half as much again as their part.
+      // (Without the limit the first workgroup at the region of a 64 MiB all-reduce could take all 8 MiB of it, from
+      // every source, in one job that nothing behind it can overtake.)
+      const uint64_t equal = ceil_div(ceil_div(region, row), waves);
+      uint64_t limit = 2 * equal;
+      if (t.rounds > 1) {
+        limit = std::max<uint64_t>(1, 2 * t.slice_elems * (uint64_t)eb / (DFX_FOLD_WAVES * row));
+        t.rounds = (uint32_t)ceil_div(3 * equal, 2 * limit);
+      }
       t.flags |= DFX_SQE_DRAWN;
+      t.slot_bytes = (uint32_t)limit;
+      runs.slot_bytes = (uint32_t)std::min<uint64_t>(limit * row * DFX_FOLD_WAVES, region);
+      runs.rounds = t.rounds;
+    }
   }
+  if (shape) *shape = runs;
   *out = t;
   return DFX_OK;
 }
@@ -1268,7 +1282,8 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
             if (R > 64) return fail("%u table entries for 64 lanes", R);
             const uint32_t row = fold_row_bytes(copies, R), waves = t.nchan * DFX_FOLD_WAVES;
             if (fg.bytes > (1u << 30)) return fail("rank %u channel %u: a span of %u bytes", r, v, fg.bytes);
-            // (drawn rows: any wave may take any row behind the first ones; walked here as if they were dealt, once)
+            // (drawn rows: any wave may take any row behind the first ones; walked here as if they were dealt, once -- that
+            // every row is taken exactly once is checked below)
             const bool walk = !(t.flags & DFX_SQE_DRAWN) || g == 0;
             if (fg.bytes && ((src | dst) & 15u)) return fail("rank %u channel %u step %u: 16-byte accesses at offsets %llu, %llu", r, v, p, (unsigned long long)src, (unsigned long long)dst);
             if (fg.bytes && src + fg.bytes > send_bytes) return fail("rank %u channel %u: read of send buffers %llu+%u of %llu", r, v, (unsigned long long)src, fg.bytes, (unsigned long long)send_bytes);
@@ -1334,6 +1349,50 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
         g = nx.g; p = nx.p; cidx = nx.cidx;
         if (g >= S.rounds) break;
         if (++steps > (1ull << 26)) return fail("rank %u channel %u: the walk does not end", r, v);
+      }
+    }
+  // (iv) drawn rows: whatever the order in which the waves of a rank get on, every row is taken exactly once, in jobs of no
+  // more rows than allowed, which is at most twice a wave's equal part of the region or of a slice
+  if (t.flags & DFX_SQE_DRAWN)
+    for (uint32_t r = 0; r < R; ++r) {
+      const DfxCooked& S = cooked[(size_t)r * t.nchan];
+      const uint32_t row = fold_row_bytes(fold_copies(kind), R), waves = t.nchan * DFX_FOLD_WAVES, limit = (uint32_t)S.sendbuf;
+      const uint32_t whole = fold_geometry(S, 0).bytes & ~15u, nrows = (whole + row - 1) / row;
+      const uint64_t part = std::min<uint64_t>(S.recvbuf, ceil_div(S.slice_elems, t.nchan)), most = 2 * ceil_div(part, DFX_FOLD_WAVES * row);
+      if (!limit || limit > most) return fail("rank %u: jobs of %u rows per wave (0 = no limit), equal parts allow %llu", r, limit, (unsigned long long)most);
+      // orders: one workgroup after the other, each through all of its jobs (first to last, last to first); one row at a time in turn
+      for (int order = 0; order < 3; ++order) {
+        std::vector<uint8_t> taken(nrows, 0);
+        uint32_t ctr = 0;
+        struct Wave { uint32_t job, in_job; bool open; };
+        std::vector<Wave> w(waves, Wave{0, 0, true});
+        auto step = [&](uint32_t i) -> int {      // 0 = through, 1 = took a row or ended a job, 2 = row taken before
+          Wave& x = w[i];
+          if (!x.open) return 0;
+          const uint64_t at = (x.job == 0 && x.in_job == 0) ? (i % DFX_FOLD_WAVES) * t.nchan + i / DFX_FOLD_WAVES : (uint64_t)waves + ctr++;
+          bool job_over = at >= nrows;
+          if (!job_over) {
+            if (taken[at]++) return 2;
+            job_over = ++x.in_job == limit;
+          }
+          if (job_over) { x.in_job = 0; x.open = ++x.job < t.rounds; }
+          return 1;
+        };
+        bool any = true;
+        while (any) {
+          any = false;
+          for (uint32_t k = 0; k < waves; ++k) {
+            const uint32_t i = order == 1 ? waves - 1 - k : k;
+            int s;
+            do {
+              s = step(i);
+              if (s == 2) return fail("rank %u: a row is taken twice (order %d)", r, order);
+              any = any || s;
+            } while (s && order < 2);
+          }
+        }
+        for (uint32_t k = 0; k < nrows; ++k)
+          if (!taken[k]) return fail("rank %u: row %u of %u is taken by nobody (order %d, %u jobs of %u rows, %u waves)", r, k, nrows, order, t.rounds, limit, waves);
       }
     }
   for (uint32_t r = 0; r < R; ++r)

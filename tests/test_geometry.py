@@ -63,6 +63,25 @@ def test_scheduler_knobs(knobs):
                 assert msg == "", (knobs, kind, count, cid, msg)
 
 
+@pytest.mark.parametrize("R", [2, 3, 4, 5, 8, 16])
+@pytest.mark.parametrize("kind", KINDS)
+def test_drawn_rows_are_taken_once_in_bounded_jobs(kind, R):
+    """From the shortest region whose rows are drawn to shares of several jobs, with edges in between: the check lets the
+    waves of a rank get on in three orders and holds every job to twice an equal part."""
+    for C, long in itertools.product([1, 3, 256 // R if R > 8 else 32], [False, True]):
+        cfg = _cfg(max_channels=C, **(dict(fold_max_bytes=4096, direct_min_bytes=0) if long else {}))
+        for rows in (16, 17, 31, 64, 65, 100, 301):                         # per wave and channel, rows of 2 KiB
+            for extra in (0, 16, 2048, 2064):
+                region = rows * 2048 * 4 * C // 4 + extra
+                n = region // 4 if kind in (dfx.ALLGATHER, dfx.REDUCESCATTER) else R * region // 4 - 3
+                msg = dfx.check_geometry(R, kind, n, dfx.F32, root=R - 1, cfg=cfg)
+                assert msg == "", (kind, R, C, long, rows, extra, msg)
+    for mib in (32, 63, 64, 256, 1024):                                     # the defaults
+        n = (mib << 20) // 4 // (R if kind in (dfx.ALLGATHER, dfx.REDUCESCATTER) else 1) // 4 * 4
+        msg = dfx.check_geometry(R, kind, n, dfx.F32, root=1, cfg=_cfg(max_channels=min(32, 256 // R)))
+        assert msg == "", (kind, R, mib, msg)
+
+
 @pytest.mark.parametrize("knobs", [dict(), dict(fold_max_bytes=0), dict(direct=0)], ids=["defaults", "ring_with_direct_steps", "through_slots"])
 def test_a_large_offset_case(knobs):
     """5 GiB + a ragged tail per rank on two ranks: byte offsets beyond 2^32, hundreds of slices per channel."""

@@ -1,7 +1,89 @@
-"""Collectives in fold steps whose share takes several jobs: what they hold of the connector pool."""
+"""Collectives in fold steps whose share takes several jobs: what they hold of the connector pool, and the jobs' edges --
+rows drawn behind the first job, a wave that has used up its rows, jobs that find none left, regions that end inside a row and
+inside 16 bytes -- for every kind and for rank counts with a data mover of their own (2, 4, 8) and without (3, 5); with the
+usual waits, with waits given up at once, with dealt rows (priority ordering), and with the daemon stopped between jobs.
+Bit-exact against the oracle (same order of combination, one rounding per hop: no tolerance), guard zones around the recv
+buffers."""
+import numpy as np
 import pytest
 
+import workload_inputs as wi
+from oracle import ring_data as rd
+
 pytestmark = pytest.mark.gpu
+
+LONG = dict(fold_max_bytes=65536, direct_min_bytes=0, chan_spread=0)     # from 64 KiB on in several jobs
+
+
+def _workload(kind, R, regions, seed):
+    colls = []
+    for i, nbytes in enumerate(regions):
+        dtype = (wi.BF16, wi.F32, wi.I32, wi.F16)[(i + R) % 4]
+        eb = wi.ELEM_BYTES[dtype]
+        count = nbytes // eb if kind in (wi.AG, wi.RS) else R * nbytes // eb - (1, 3)[i % 2]     # blocks are 16-byte multiples
+        colls.append(wi.CollSpec(i, kind, dtype, count, R - 1 if kind in (wi.BC, wi.RD) else 0,
+                                 (wi.SUM, wi.MAX)[i % 2] if kind in (wi.AR, wi.RS, wi.RD) else wi.SUM))
+    return wi.Workload(f"jobs_{kind}_{R}", R, colls, [list(range(len(colls)))] * R, seed=seed, cfg=93)
+
+
+def _check(w, dw):
+    for ci, c in enumerate(w.colls):
+        want, got = rd.run_closed_form(c.kind, dw.send_host[ci], c.dtype, c.root, c.op), dw.results(ci)
+        for r in range(w.R):
+            if c.kind == wi.RD and r != c.root:
+                assert np.all(got[r].view(np.uint8) == 0xA5), (ci, r)
+            else:
+                assert np.array_equal(got[r].view(np.uint8), want[r].view(np.uint8)), (ci, c, r)
+    dw.check_untouched()
+
+
+@pytest.mark.parametrize("knobs", [dict(), dict(scan_min=0, spin_init=1, spin_min=1, spin_max=1, spin_boost=1), dict(order_policy=1)],
+                         ids=["defaults", "give_up_at_once", "dealt_rows"])
+@pytest.mark.parametrize("R", [2, 3, 4, 5, 8])
+@pytest.mark.parametrize("kind", [wi.AR, wi.AG, wi.RS, wi.BC, wi.RD])
+def test_shares_of_several_jobs(kind, R, knobs):
+    from paper_2303_06324_amd import harness as gh
+    import paper_2303_06324_amd as dfx
+    C, job = 2, 128 << 10
+    w = _workload(kind, R, [C * 4 * job, C * 5 * job + 48, C * 9 * job + 3 * 2048 + 16, C * 3 * job - 16], seed=kind * 10 + R)
+    dw = gh.DeviceWorkload(w)
+    ctx = dfx.Context(R, gh.make_config(max_channels=C, **LONG, **knobs))
+    try:
+        gh.prepare_all(ctx, w)
+        for ci in range(len(w.colls)):
+            assert ctx.coll_info(ci)["nprim"] == 2 and ctx.coll_info(ci)["rounds"] > 1, ctx.coll_info(ci)
+        for _ in range(3):                           # row counters of both parities, the first one's again
+            dw.reset_recv()
+            gh.submit_round_robin(ctx, dw)
+            assert ctx.wait_all(30.0) == dfx.OK
+        assert ctx.stop() == dfx.OK
+    finally:
+        ctx.finalize()
+    _check(w, dw)
+
+
+@pytest.mark.parametrize("kind", [wi.AR, wi.AG, wi.RS])
+def test_daemon_stopped_between_jobs(kind):
+    """One channel per rank and regions of 4 MiB: a few milliseconds of some twenty to thirty jobs.  The exit entry arrives behind the
+    submissions, posted jobs run to their end, and the next launch goes on from the saved contexts."""
+    from paper_2303_06324_amd import harness as gh
+    import paper_2303_06324_amd as dfx
+    R = 8
+    w = _workload(kind, R, [(4 << 20) + 48, (4 << 20) + 16], seed=70 + kind)
+    dw = gh.DeviceWorkload(w)
+    ctx = dfx.Context(R, gh.make_config(max_channels=1, **LONG))
+    try:
+        gh.prepare_all(ctx, w)
+        for _ in range(3):
+            dw.reset_recv()
+            gh.submit_round_robin(ctx, dw)
+            assert ctx.stop() == dfx.OK
+            assert ctx.wait_all(30.0) == dfx.OK
+        assert ctx.stop() == dfx.OK
+        assert ctx.stats(0)["launches"] >= 4, ctx.stats(0)["launches"]     # (at least one stop came before the end)
+    finally:
+        ctx.finalize()
+    _check(w, dw)
 
 
 def test_long_collectives_hold_no_slots():

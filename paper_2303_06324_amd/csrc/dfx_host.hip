@@ -506,12 +506,15 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   // direct broadcast fills none either: its connectors are the flag lines alone)
   *conn_bytes_out = round_up((t.flags & DFX_SQE_FOLD) ? (R + 1) * C * DFX_FLAG_STRIDE
                                                       : R * C * DFX_FLAG_STRIDE + (bc_direct ? 0 : R * C * K * slot_bytes), 256);
-  // Rows are drawn where a wave has at least four of them (with fewer the last ones are as uneven as equal parts) and
-  // the region's offsets fit 32 bits; a job size that the caller asked for keeps its slices, whose rows are dealt, and so
+  // Rows are drawn where a wave has at least four of them (with fewer the last ones are as uneven as equal parts), the
+  // region's offsets fit 32 bits and the results go to every rank.  Kinds with one destination (reduce-scatter, reduce) are
+  // bound by their reads, which workgroups get alike, and there the draws only cost: drawn -> dealt, us per call, fp32,
+  // reduce-scatter of 25 MiB 54 -> 45.5, 128 MiB 316 -> 257 (R = 8), 48 MiB 52 -> 39 (R = 2), 54 -> 44 (R = 4), 200 MiB 480 -> 310 (R = 3,
+  // 415 as a ring).  A job size that the caller asked for keeps its slices, whose rows are dealt, and so
   // does priority ordering: its workgroups may be at different collectives, and one that is first at a region would
-  // draw all of it in a job that a more urgent collective has to wait for (sixteen staggered buckets: urgent one
-  // after 0.93 ms with drawn rows, 0.43-0.62 with dealt ones).
-  if ((t.flags & DFX_SQE_FOLD) && !cfg.fold_slice_bytes && cfg.order_policy != 1) {
+  // draw twice its part in a job that a more urgent collective has to wait for (sixteen staggered buckets, jobs without a
+  // limit: urgent one after 0.93 ms with drawn rows, 0.43-0.62 with dealt ones).
+  if ((t.flags & DFX_SQE_FOLD) && !cfg.fold_slice_bytes && cfg.order_policy != 1 && fold_to_all((int)kind)) {
     const uint64_t region = fold_chunk_elems((int)kind, count, t.block_elems, (uint32_t)R, eb) * eb;
     const uint64_t row = fold_row_bytes(kind == DFX_ALLGATHER || kind == DFX_BROADCAST, (uint32_t)R), waves = DFX_FOLD_WAVES * C;
     if (region >= 4 * row * waves && region <= (1ull << 30)) {

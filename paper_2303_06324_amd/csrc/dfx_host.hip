@@ -496,11 +496,14 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
     const uint64_t chunk = fold_chunk_elems((int)kind, count, block, (uint32_t)R, eb);     // a rank's region; a channel's part of it
     const uint64_t share = std::max<uint64_t>(round_up(ceil_div(chunk, C), per16), per16);
     const uint64_t bytes = std::min<uint64_t>(std::min<uint64_t>(job, ((1ull << 30) / C) & ~15ull), share * eb);
-    t.flags |= DFX_SQE_FOLD;
-    t.slice_elems = (uint32_t)(bytes / eb);
-    t.rounds = (uint32_t)std::max<uint64_t>(1, ceil_div(share, t.slice_elems));
-    t.nprim = fold_nprim((int)kind);
-    runs = CollShape{t.nchan, (uint32_t)bytes, t.rounds, t.nprim};
+    const uint64_t jobs = std::max<uint64_t>(1, ceil_div(share, bytes / eb));
+    if (jobs <= 0xfffffffeull) {       // (more than the walk counts, with slices of a few bytes: the ring or chain runs)
+      t.flags |= DFX_SQE_FOLD;
+      t.slice_elems = (uint32_t)(bytes / eb);
+      t.rounds = (uint32_t)jobs;
+      t.nprim = fold_nprim((int)kind);
+      runs = CollShape{t.nchan, (uint32_t)bytes, t.rounds, t.nprim};
+    }
   }
   // (a collective in fold steps has no slots: R x C lines with the published addresses and C shared lines of counters; a
   // direct broadcast fills none either: its connectors are the flag lines alone)
@@ -509,8 +512,8 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   // Rows are drawn where a wave has at least four of them (with fewer the last ones are as uneven as equal parts), the
   // region's offsets fit 32 bits and the results go to every rank.  Kinds with one destination (reduce-scatter, reduce) are
   // bound by their reads, which workgroups get alike, and there the draws only cost: drawn -> dealt, us per call, fp32,
-  // reduce-scatter of 25 MiB 54 -> 45.5, 128 MiB 316 -> 257 (R = 8), 48 MiB 52 -> 39 (R = 2), 54 -> 44 (R = 4), 200 MiB 480 -> 310 (R = 3,
-  // 415 as a ring).  A job size that the caller asked for keeps its slices, whose rows are dealt, and so
+  // reduce-scatter of 25 MiB 54 -> 45.5, 128 MiB 316 -> 257 (R = 8), 48 MiB 52 -> 39 (R = 2), 54 -> 44 (R = 4), 200 MiB 482 -> 406 (R = 3,
+  // 416 as a ring).  A job size that the caller asked for keeps its slices, whose rows are dealt, and so
   // does priority ordering: its workgroups may be at different collectives, and one that is first at a region would
   // draw twice its part in a job that a more urgent collective has to wait for (sixteen staggered buckets, jobs without a
   // limit: urgent one after 0.93 ms with drawn rows, 0.43-0.62 with dealt ones).

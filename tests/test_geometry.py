@@ -88,6 +88,12 @@ def test_a_large_offset_case(knobs):
     assert dfx.check_geometry(2, dfx.ALLREDUCE, (5 << 30) // 4 + 12345, dfx.I32, cfg=_cfg(**knobs)) == ""
 
 
+def test_more_jobs_than_the_walk_counts():
+    """128 GiB on two ranks with one channel: 2^32 slices of 16 bytes do not fit the walk's 32-bit count, so it stays a ring."""
+    cfg = _cfg(max_channels=1, fold_slice_bytes=16, slot_bytes=1 << 30)
+    assert dfx.check_geometry(2, dfx.ALLREDUCE, (128 << 30) // 4, dfx.F32, cfg=cfg) == ""
+
+
 def test_it_refuses_what_it_cannot_check():
     assert dfx.check_geometry(8, dfx.BROADCAST, 1024, dfx.F32, root=9) != ""
     assert dfx.check_geometry(8, dfx.ALLREDUCE, 1024, dfx.F32, wg_map=3) != ""

@@ -533,6 +533,8 @@ struct Rows {
   __device__ __forceinline__ void draw() {
     if ((threadIdx.x & 63u) == 0) drawn = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, SCOPE_AGENT);
   }
+  // that row and no other
+  __device__ __forceinline__ void only(uint32_t r) { ctr = nullptr; row = r; left = 1; }
   // Ahead of the row's loads: the next draw sets off (its answer arrives before the data does).
   __device__ __forceinline__ void prefetch() { if (ctr && left > 1) draw(); }
   // Behind the row: on to the next; false = the job is over for this wave.
@@ -553,22 +555,22 @@ struct Rows {
 // the number of sources; with 2, 4 or 8 of them (and as many destinations, or one) all buffer resources stay in
 // scalar registers over the whole job (looked up for every round they cost 0.4 us per round and side: the one job of
 // an 8 KiB all-reduce took 3.4 us, now 1.8; a 25 MiB bf16 bucket, with the rows, 92 -> 75 us).  A buffer's
-// resource ends with the last whole 16 bytes of the span: loads behind it return 0 and stores behind it are dropped, so
+// resource ends with the last row's last whole 16 bytes: loads behind it return 0 and stores behind it are dropped, so
 // the last row needs no predicates.
 // Next round's loads before this round's combine, 512 movers, non-temporal or plain cached accesses measured the
 // same (838-845 us for 256 MiB per rank, fp32, R = 8) or, non-temporal below the size of the memory-side cache,
 // worse (8 MiB: 25 against 20.5 us).
 template <int DT, int NS, bool ALL>
-__device__ __forceinline__ void fold_fixed(const u64* src_tab, const u64* dst_tab, uint32_t whole, Rows& rows, uint32_t lane, int op) {
+__device__ __forceinline__ void fold_fixed(const u64* src_tab, const u64* dst_tab, uint32_t from, uint32_t end, Rows& rows, uint32_t lane, int op) {
   constexpr int U = 16 / NS, ND = ALL ? NS : 1;      // (fold_row_bytes)
   __amdgpu_buffer_rsrc_t S[NS], D[ND];
 #pragma unroll
-  for (int k = 0; k < NS; ++k) S[k] = uniform_rsrc(src_tab[k], whole);
+  for (int k = 0; k < NS; ++k) S[k] = uniform_rsrc(src_tab[k], end);
 #pragma unroll
-  for (int k = 0; k < ND; ++k) D[k] = uniform_rsrc(dst_tab[k], whole);
+  for (int k = 0; k < ND; ++k) D[k] = uniform_rsrc(dst_tab[k], end);
   for (;;) {
-    const uint32_t at = rows.row * (U * 1024u);
-    if (at >= whole) break;
+    const uint32_t at = from + rows.row * (U * 1024u);
+    if (at >= end) break;
     rows.prefetch();
     const uint32_t o = at + lane * 16u;
     uint4 w[NS][U];
@@ -603,13 +605,13 @@ struct LaneTable {
 
 // the same for any number of sources and destinations
 template <int DT>
-__device__ __forceinline__ void fold_any(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, uint32_t whole,
+__device__ __forceinline__ void fold_any(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, uint32_t from, uint32_t end,
                                          Rows& rows, uint32_t lane, int op) {
   constexpr int U = 2, NS = 8;      // vectors per source (fold_row_bytes) and sources in flight
   const LaneTable S(src_tab, nsrc, lane), D(dst_tab, ndst, lane);
   for (;;) {
-    const uint32_t at = rows.row * (U * 1024u);
-    if (at >= whole) break;
+    const uint32_t at = from + rows.row * (U * 1024u);
+    if (at >= end) break;
     rows.prefetch();
     const uint32_t o = at + lane * 16u;
     uint4 acc[U];
@@ -618,7 +620,7 @@ __device__ __forceinline__ void fold_any(const u64* src_tab, uint32_t nsrc, cons
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
         if (base + k < nsrc) {
-          const __amdgpu_buffer_rsrc_t r = S.rsrc(base + k, whole);
+          const __amdgpu_buffer_rsrc_t r = S.rsrc(base + k, end);
 #pragma unroll
           for (int u = 0; u < U; ++u) w[k][u] = rs_ld16(r, o + u * 1024u);
         }
@@ -634,7 +636,7 @@ __device__ __forceinline__ void fold_any(const u64* src_tab, uint32_t nsrc, cons
       }
     }
     for (uint32_t d = 0; d < ndst; ++d) {
-      const __amdgpu_buffer_rsrc_t r = D.rsrc(d, whole);
+      const __amdgpu_buffer_rsrc_t r = D.rsrc(d, end);
 #pragma unroll
       for (int u = 0; u < U; ++u) rs_st16(r, o + u * 1024u, acc[u]);
     }
@@ -648,16 +650,16 @@ __device__ __forceinline__ void fold_any(const u64* src_tab, uint32_t nsrc, cons
 // Two ranks have 64 workgroups in all and take twice the vectors per row: broadcast of 32 MiB 62 -> 38.5 us,
 // all-gather of 128 MiB 233 -> 171.
 template <int ND, int U>
-__device__ __forceinline__ void fold_copy(const u64* src_tab, const u64* dst_tab, uint32_t ndst, uint32_t whole, Rows& rows, uint32_t lane) {
+__device__ __forceinline__ void fold_copy(const u64* src_tab, const u64* dst_tab, uint32_t ndst, uint32_t from, uint32_t end, Rows& rows, uint32_t lane) {
   // (U: fold_row_bytes)
-  const __amdgpu_buffer_rsrc_t S = uniform_rsrc(src_tab[0], whole);
+  const __amdgpu_buffer_rsrc_t S = uniform_rsrc(src_tab[0], end);
   __amdgpu_buffer_rsrc_t D[ND ? ND : 1];
 #pragma unroll
-  for (int k = 0; k < ND; ++k) D[k] = uniform_rsrc(dst_tab[k], whole);
+  for (int k = 0; k < ND; ++k) D[k] = uniform_rsrc(dst_tab[k], end);
   const LaneTable T(dst_tab, ndst, lane);      // (any number of them)
   for (;;) {
-    const uint32_t at = rows.row * (U * 1024u);
-    if (at >= whole) break;
+    const uint32_t at = from + rows.row * (U * 1024u);
+    if (at >= end) break;
     rows.prefetch();
     const uint32_t o = at + lane * 16u;
     uint4 w[U];
@@ -670,7 +672,7 @@ __device__ __forceinline__ void fold_copy(const u64* src_tab, const u64* dst_tab
         for (int u = 0; u < U; ++u) rs_st16(D[k], o + u * 1024u, w[u]);
     } else {
       for (uint32_t d = 0; d < ndst; ++d) {
-        const __amdgpu_buffer_rsrc_t r = T.rsrc(d, whole);
+        const __amdgpu_buffer_rsrc_t r = T.rsrc(d, end);
 #pragma unroll
         for (int u = 0; u < U; ++u) rs_st16(r, o + u * 1024u, w[u]);
       }
@@ -681,10 +683,10 @@ __device__ __forceinline__ void fold_copy(const u64* src_tab, const u64* dst_tab
 
 // the bytes behind the last whole 16 of a span, element by element (fold or copy)
 template <int DT>
-__device__ __forceinline__ void fold_tail(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, uint32_t whole,
+__device__ __forceinline__ void fold_tail(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, uint32_t end,
                                           uint32_t bytes, uint32_t lane, int op) {
   constexpr uint32_t EB = (DT == DT_F32 || DT == DT_I32) ? 4u : 2u;
-  const uint32_t o = whole + lane * EB;
+  const uint32_t o = end + lane * EB;
   if (o >= bytes) return;
   uint32_t v = 0;
   for (uint32_t k = 0; k < nsrc; ++k) {
@@ -700,41 +702,46 @@ __device__ __forceinline__ void fold_tail(const u64* src_tab, uint32_t nsrc, con
   }
 }
 
+// A span: `head` bytes (fold_head), rows, and the bytes behind the last whole 16.  front, tail: this wave takes the bytes before
+// and behind the rows (exactly one of the region's waves each, once).
+struct Span { uint32_t head, end, bytes; bool front, tail; };
+
 // A reduction has one source per rank and one destination, or as many destinations as sources.
 template <int DT>
-__device__ __forceinline__ void fold_reduce(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, uint32_t bytes,
-                                            bool tail, Rows& rows, uint32_t lane, int op) {
-  const uint32_t whole = bytes & ~15u;
+__device__ __forceinline__ void fold_reduce(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, const Span& sp,
+                                            Rows& rows, uint32_t lane, int op) {
+  const uint32_t from = sp.head, end = sp.end;
   const bool all = ndst > 1;
-  if (nsrc == 8 && all) fold_fixed<DT, 8, true>(src_tab, dst_tab, whole, rows, lane, op);
-  else if (nsrc == 8) fold_fixed<DT, 8, false>(src_tab, dst_tab, whole, rows, lane, op);
-  else if (nsrc == 4 && all) fold_fixed<DT, 4, true>(src_tab, dst_tab, whole, rows, lane, op);
-  else if (nsrc == 4) fold_fixed<DT, 4, false>(src_tab, dst_tab, whole, rows, lane, op);
-  else if (nsrc == 2 && all) fold_fixed<DT, 2, true>(src_tab, dst_tab, whole, rows, lane, op);
-  else if (nsrc == 2) fold_fixed<DT, 2, false>(src_tab, dst_tab, whole, rows, lane, op);
-  else fold_any<DT>(src_tab, nsrc, dst_tab, ndst, whole, rows, lane, op);
-  if (tail) fold_tail<DT>(src_tab, nsrc, dst_tab, ndst, whole, bytes, lane, op);
+  if (nsrc == 8 && all) fold_fixed<DT, 8, true>(src_tab, dst_tab, from, end, rows, lane, op);
+  else if (nsrc == 8) fold_fixed<DT, 8, false>(src_tab, dst_tab, from, end, rows, lane, op);
+  else if (nsrc == 4 && all) fold_fixed<DT, 4, true>(src_tab, dst_tab, from, end, rows, lane, op);
+  else if (nsrc == 4) fold_fixed<DT, 4, false>(src_tab, dst_tab, from, end, rows, lane, op);
+  else if (nsrc == 2 && all) fold_fixed<DT, 2, true>(src_tab, dst_tab, from, end, rows, lane, op);
+  else if (nsrc == 2) fold_fixed<DT, 2, false>(src_tab, dst_tab, from, end, rows, lane, op);
+  else fold_any<DT>(src_tab, nsrc, dst_tab, ndst, from, end, rows, lane, op);
+  if (sp.front) { Rows one = rows; one.only(0); fold_any<DT>(src_tab, nsrc, dst_tab, ndst, 0, from, one, lane, op); }
+  if (sp.tail) fold_tail<DT>(src_tab, nsrc, dst_tab, ndst, end, sp.bytes, lane, op);
 }
 
-// tail: this wave does the bytes behind the last whole 16 (exactly one of the region's waves, once)
-__device__ __forceinline__ void fold_dispatch(int dtype, const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst,
-                                              uint32_t bytes, bool tail, Rows& rows, uint32_t lane) {
+__device__ __forceinline__ void fold_dispatch(int dtype, const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, const Span& sp,
+                                              Rows& rows, uint32_t lane) {
   if (nsrc == 1) {
-    const uint32_t whole = bytes & ~15u;
-    if (ndst == 8) fold_copy<8, 4>(src_tab, dst_tab, ndst, whole, rows, lane);
-    else if (ndst == 4) fold_copy<4, 4>(src_tab, dst_tab, ndst, whole, rows, lane);
-    else if (ndst == 2) fold_copy<2, 8>(src_tab, dst_tab, ndst, whole, rows, lane);
-    else fold_copy<0, 4>(src_tab, dst_tab, ndst, whole, rows, lane);
+    const uint32_t from = sp.head, end = sp.end;
+    if (ndst == 8) fold_copy<8, 4>(src_tab, dst_tab, ndst, from, end, rows, lane);
+    else if (ndst == 4) fold_copy<4, 4>(src_tab, dst_tab, ndst, from, end, rows, lane);
+    else if (ndst == 2) fold_copy<2, 8>(src_tab, dst_tab, ndst, from, end, rows, lane);
+    else fold_copy<0, 4>(src_tab, dst_tab, ndst, from, end, rows, lane);
     // (every element type is a multiple of 2 bytes)
-    if (tail) fold_tail<DT_F16>(src_tab, 1, dst_tab, ndst, whole, bytes, lane, OP_SUM);
+    if (sp.front) { Rows one = rows; one.only(0); fold_copy<0, 1>(src_tab, dst_tab, ndst, 0, from, one, lane); }
+    if (sp.tail) fold_tail<DT_F16>(src_tab, 1, dst_tab, ndst, end, sp.bytes, lane, OP_SUM);
     return;
   }
   const int op = dtype >> 4;
   switch (dtype & 15) {
-    case DT_F32: fold_reduce<DT_F32>(src_tab, nsrc, dst_tab, ndst, bytes, tail, rows, lane, op); break;
-    case DT_BF16: fold_reduce<DT_BF16>(src_tab, nsrc, dst_tab, ndst, bytes, tail, rows, lane, op); break;
-    case DT_F16: fold_reduce<DT_F16>(src_tab, nsrc, dst_tab, ndst, bytes, tail, rows, lane, op); break;
-    default: fold_reduce<DT_I32>(src_tab, nsrc, dst_tab, ndst, bytes, tail, rows, lane, op); break;
+    case DT_F32: fold_reduce<DT_F32>(src_tab, nsrc, dst_tab, ndst, sp, rows, lane, op); break;
+    case DT_BF16: fold_reduce<DT_BF16>(src_tab, nsrc, dst_tab, ndst, sp, rows, lane, op); break;
+    case DT_F16: fold_reduce<DT_F16>(src_tab, nsrc, dst_tab, ndst, sp, rows, lane, op); break;
+    default: fold_reduce<DT_I32>(src_tab, nsrc, dst_tab, ndst, sp, rows, lane, op); break;
   }
 }
 
@@ -747,6 +754,7 @@ struct Job {                         // what the scheduler wave hands to the mov
   uint32_t coll, prim;               // for the timeline trace only
   uint32_t nsrc, ndst;               // not 0: step with data of a collective in fold steps (that many sources and destinations in the job's tables)
   uint32_t index, sharers;           // ... which of the region's workgroups this is, and how many there are
+  uint32_t head;                     // ... bytes before the first row (fold_head)
   uint32_t limit, fresh;             // ... drawn rows per wave at most (0 = rows are dealt); first job of the share
   u64 draw;                          // ... the region's row counter (0 = rows are dealt)
 };
@@ -943,8 +951,11 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
         rows.left = limit ? limit : 0xffffffffu;
         rows.drawn = 0;
         rows.begin(fresh, wave * sharers + index);
-        fold_dispatch((int)bcast0((uint32_t)j.dtype), sh.tab_src[seen & 1], bcast0(j.nsrc), sh.tab_dst[seen & 1], bcast0(j.ndst), jbytes,
-                      (jbytes & 15u) && fresh && index == 0 && wave == 0, rows, lane);
+        Span sp;
+        sp.head = bcast0(j.head); sp.end = sp.head + ((jbytes - sp.head) & ~15u); sp.bytes = jbytes;
+        sp.front = sp.head && fresh && index + 1 == sharers && wave + 1 == DFX_FOLD_WAVES;
+        sp.tail = (jbytes & 15u) && fresh && index == 0 && wave == 0;
+        fold_dispatch((int)bcast0((uint32_t)j.dtype), sh.tab_src[seen & 1], bcast0(j.nsrc), sh.tab_dst[seen & 1], bcast0(j.ndst), sp, rows, lane);
       }
       else if (coh) run_prim<AUX_DEVICE, GTHREADS>(j.dtype, j.fin, j.sb, j.rb, j.fout, j.bytes, mtid);
       else run_prim<AUX_CACHED, GTHREADS>(j.dtype, j.fin, j.sb, j.rb, j.fout, j.bytes, mtid);
@@ -1639,7 +1650,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             if (lane == 0) {
               Job j;
               j.fin = nullptr; j.fout = nullptr; j.sb = nullptr; j.rb = nullptr;
-              j.bytes = fg.bytes; j.index = vch; j.sharers = inv_nchan;
+              j.bytes = fg.bytes; j.head = fold_head(fg.dst, fg.bytes, inv_nchan); j.index = vch; j.sharers = inv_nchan;
               j.limit = row_limit;
               j.fresh = !drawn || g == 0;
               j.draw = drawn ? fold_draw_word(s_fin, rank, vch, inv_nchan, inv_seq) : 0;
@@ -1738,7 +1749,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             Job j;
             j.fin = jfin; j.fout = jfout; j.sb = jsb; j.rb = jrb;
             j.bytes = (q.drain || (!q.recv && !q.from_send)) ? 0u : bytes;   // drain and notify-only steps move nothing
-            j.nsrc = 0; j.ndst = 0; j.index = j.sharers = j.limit = j.fresh = 0; j.draw = 0;
+            j.nsrc = 0; j.ndst = 0; j.index = j.sharers = j.head = j.limit = j.fresh = 0; j.draw = 0;
             j.dtype = dtype; j.coll = coll; j.prim = q.drain ? 0xffu : p;   // (prim: for the timeline only)
             sh.job[posted & 1] = j;
             Flight f;

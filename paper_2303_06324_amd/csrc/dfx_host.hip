@@ -1303,11 +1303,13 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
               if (peer >= R || (seen >> peer & 1u)) return fail("rank %u channel %u: entry %u names rank %u", r, v, k, peer);
               seen |= 1ull << peer;
               if ((!to_all && k + 1 < R) || !walk) continue;
-              const uint32_t whole = fg.bytes & ~15u;
+              const uint32_t head = fold_head(dst, fg.bytes, t.nchan), end = head + ((fg.bytes - head) & ~15u);
+              if (fg.bytes / t.nchan >= (32u << 10) && (dst + head) % 128) return fail("rank %u channel %u step %u: rows from offset %llu of the recv buffers, no 128-byte line", r, v, p, (unsigned long long)(dst + head));
+              if (head && v + 1 == t.nchan) written[peer].push_back({dst, dst + head});
               for (uint32_t wv = 0; wv < DFX_FOLD_WAVES; ++wv)
-                for (uint64_t at = (uint64_t)(wv * t.nchan + v) * row; at < whole; at += (uint64_t)waves * row)
-                  written[peer].push_back({dst + at, dst + std::min<uint64_t>(at + row, whole)});
-              if (whole < fg.bytes && v == 0) written[peer].push_back({dst + whole, dst + fg.bytes});
+                for (uint64_t at = head + (uint64_t)(wv * t.nchan + v) * row; at < end; at += (uint64_t)waves * row)
+                  written[peer].push_back({dst + at, dst + std::min<uint64_t>(at + row, end)});
+              if (end < fg.bytes && v == 0) written[peer].push_back({dst + end, dst + fg.bytes});
             }
             const uint32_t lastp = fold_peer(kind, R, r, rt, R - 1);
             if ((copies || !to_all) && lastp != ((kind == KIND_BC || kind == KIND_RD) ? rt : r)) return fail("rank %u channel %u: the last entry is rank %u", r, v, lastp);
@@ -1364,7 +1366,8 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
     for (uint32_t r = 0; r < R; ++r) {
       const DfxCooked& S = cooked[(size_t)r * t.nchan];
       const uint32_t row = fold_row_bytes(fold_copies(kind), R), waves = t.nchan * DFX_FOLD_WAVES, limit = (uint32_t)S.sendbuf;
-      const uint32_t whole = fold_geometry(S, 0).bytes & ~15u, nrows = (whole + row - 1) / row;
+      const FoldGeom fg = fold_geometry(S, 0);
+      const uint32_t rest = (fg.bytes - fold_head(fg.dst, fg.bytes, t.nchan)) & ~15u, nrows = (rest + row - 1) / row;
       const uint64_t part = std::min<uint64_t>(S.recvbuf, ceil_div(S.slice_elems, t.nchan)), most = 2 * ceil_div(part, DFX_FOLD_WAVES * row);
       if (!limit || limit > most) return fail("rank %u: jobs of %u rows per wave (0 = no limit), equal parts allow %llu", r, limit, (unsigned long long)most);
       // orders: one workgroup after the other, each through all of its jobs (first to last, last to first); one row at a time in turn

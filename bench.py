@@ -1,8 +1,8 @@
 #!/usr/bin/env python3
-"""Headline benchmark: 8-virtual-rank ring all-reduce through the preemptive daemon kernel.
+"""Headline benchmark: 8-virtual-rank all-reduce (the values of a ring) through the preemptive daemon kernel.
 
 One "step" = one pass of the whole hot path over one batch: launch the daemon, every vrank
-submits its SQE, primitives run through the HBM connectors, CQEs are posted and polled, the exit
+submits its SQE, its steps run, CQEs are posted and polled, the exit
 SQE drains the grid.  Workload = the large-message point of the size sweep (R = 8, fp32 sum,
 256 MiB per rank, inputs resident in HBM before the timed region).
 
@@ -21,10 +21,9 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E peak
 R = 8
 # HBM bytes per launch at the default workload, measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE and scaled by the plain
-# copy kernel (profiles/hbm_traffic_allreduce_256MiB.md): with the library's defaults (data in fold steps) 2 100 025 KiB read +
+# copy kernel (profiles/hbm_traffic_allreduce_256MiB.md): in fold steps (the library's defaults) 2 100 025 KiB read +
 # 2 101 305 KiB written; as a ring with direct steps (fold_max_bytes = 0) 5 511 100 KiB + 3 671 500 KiB.
-FOLD_TRAFFIC_BYTES = 4302161920
-MEASURED_TRAFFIC_BYTES = 9402982400
+MEASURED_TRAFFIC_BYTES = {"fold steps": 4302161920, "ring with direct steps": 9402982400}
 
 
 def algorithmic_bytes(msg_bytes: int, nranks: int) -> int:
@@ -47,6 +46,15 @@ def fold_bytes(msg_bytes: int, nranks: int) -> int:
     send buffers and writes the result into all R recv buffers: 2 * M per rank, every input read once and every
     output written once."""
     return 2 * nranks * msg_bytes
+
+
+def path_of(nprim: int) -> str:
+    """What an all-reduce of R ranks runs, from the steps that dfx_coll_info reports."""
+    return {2: "fold steps", 2 * R: "ring with direct steps"}.get(nprim, "ring through slots")
+
+
+def path_bytes(path: str, msg_bytes: int) -> int:
+    return {"fold steps": fold_bytes, "ring with direct steps": moved_bytes}.get(path, algorithmic_bytes)(msg_bytes, R)
 
 
 def cpu_baseline(sends, min_seconds: float = 10.0, max_reps: int = 40):
@@ -238,7 +246,7 @@ def deadlock_prone():
 def size_sweep(iters: int = 10):
     """All-reduce latency / bandwidth over the sweep's sizes inside one resident daemon (submit of the first
     vrank -> last CQE seen by the host; best of `iters`) with the library's defaults, and beside it the same
-    sizes as rings only (`fold_max_bytes = 0`) and in fold steps only (the limit raised above every size)."""
+    sizes as rings only (`fold_max_bytes = 0`) and in fold steps of one job (the limit raised above every size)."""
     import torch
     import paper_2303_06324_amd as dfx
     from paper_2303_06324_amd import harness as gh
@@ -268,8 +276,8 @@ def size_sweep(iters: int = 10):
     rows = []
     for nbytes in wi.CONFIG2_SIZES:
         best, nchan, nprim = res[("default", nbytes)]
-        path = {2: "fold steps", 2 * R: "ring with direct steps"}.get(nprim, "ring through slots")
-        nb = {2: fold_bytes, 2 * R: moved_bytes}.get(nprim, algorithmic_bytes)(nbytes, R)     # what the path taken moves
+        path = path_of(nprim)
+        nb = path_bytes(path, nbytes)     # what the path taken moves
         rows.append({"bytes": nbytes, "us": round(best * 1e6, 1), "channels": nchan,
                      "algbw_GBs": round(nbytes / best / 1e9, 2),
                      "busbw_GBs": round(nbytes / best * 2 * (R - 1) / R / 1e9, 2),
@@ -283,8 +291,8 @@ def size_sweep(iters: int = 10):
 
 def kinds_by_size(sizes=(8 << 10, 1 << 20, 8 << 20, 32 << 20, 256 << 20), iters: int = 8):
     """The four other kinds over sizes (largest per-rank buffer; fp32, sum, root 3): rings / chains
-    (`fold_max_bytes = 0`) against fold steps at every size; the library's default takes the fold steps
-    below 64 MiB."""
+    (`fold_max_bytes = 0`) against fold steps of one job at every size; the library's default takes fold steps too, from
+    64 MiB on in several jobs."""
     import torch
     import paper_2303_06324_amd as dfx
     from paper_2303_06324_amd import harness as gh
@@ -607,8 +615,9 @@ def main():
     algbw = M / (ms_per_step * 1e-3) / 1e9
     busbw = algbw * 2 * (R - 1) / R
     k_ms = sum(kern_ms) / len(kern_ms)
-    fold = info["nprim"] == 2                # what runs: fold steps (else the ring, with direct steps or through slots)
-    launch_bytes = (fold_bytes if fold else moved_bytes if info["nprim"] == 2 * R else algorithmic_bytes)(M, R)
+    path = path_of(info["nprim"])
+    launch_bytes = path_bytes(path, M)
+    traffic = MEASURED_TRAFFIC_BYTES.get(path) if args.msg_mib == 256 else None
     achieved = launch_bytes / (k_ms * 1e-3) / 1e9
     table_rate = algorithmic_bytes(M, R) / (k_ms * 1e-3) / 1e9
     out = {
@@ -619,27 +628,26 @@ def main():
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": f"config 2: R=8 virtual ranks, one all-reduce(sum) fp32, {args.msg_mib} MiB per rank, "
                                f"ring chunk = size/8, N(0,1) inputs resident in HBM",
-                   "path": "fold steps" if fold else "ring", "channels_per_rank": info["nchan"], "slice_bytes": info["slot_bytes"],
+                   "path": path, "channels_per_rank": info["nchan"], "slice_bytes": info["slot_bytes"],
                    "slices": info["rounds"],
                    "daemon_launches": int(launches)},
         "algbw_GBs": round(algbw, 2),
         "hbm_frac_wall": round(launch_bytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-        # achieved = the bytes the shipped method has to move per launch / kernel time: 2R x M (every input read once,
-        # every output written once), (6R-4) x M by the printed primitive table (every step through a FIFO slot),
-        # whose figure is given beside it: work per time, which moving less raises.
+        # achieved = the bytes the path that runs has to move per launch / kernel time (fold steps: 2R x M, every input read
+        # once, every output written once).  Beside it the (6R-4) x M of the printed primitive table (every step through a
+        # FIFO slot) per time: a rate of work, no rate of the memory, which moves less.
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": FOLD_TRAFFIC_BYTES if args.msg_mib == 256 and fold else None,
+                     "traffic": traffic,
                      "traffic_source": "profiles/hbm_traffic_allreduce_256MiB.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE scaled "
                                        "by the copy kernel; a constant from that profile, not measured in this run)"
-                                       if args.msg_mib == 256 and fold else None,
+                                       if traffic else None,
                      "kernel": "dfx_daemon_kernel", "kernel_ms_avg": round(k_ms, 4),
                      "bytes_moved_per_launch": launch_bytes,
                      "note": "achieved = bytes the shipped path moves per launch (fold steps: 2R x M, every input read once, every output "
                              "written once) / kernel time, launch, submission and exit of the daemon included",
                      "primitive_table_bytes_per_launch": algorithmic_bytes(M, R),
-                     "primitive_table_GBs": round(table_rate, 1),
-                     "primitive_table_frac": round(table_rate / HBM_PEAK_GBS, 4)},
+                     "primitive_table_GBs": round(table_rate, 1)},
         "copy_kernel_GBs": round(copy_gbs, 1),
     }
     if fold_ms is not None:

@@ -132,7 +132,7 @@ typedef struct {
                               that all ranks carry the same few collectives through instead of advancing all
                               of them side by side (whose FIFO slots together outgrow the memory-side cache);
                               0 = every runnable collective once per pass, in queue order */
-  uint32_t direct;         /* (what rings and chains do with fold_max_bytes = 0; see there for what long collectives do otherwise)
+  uint32_t direct;         /* (steps of rings and chains, which run with fold_max_bytes = 0; a long collective that would take them runs in fold steps otherwise)
                               1 (default): collectives of at least direct_min_bytes (all-reduce, broadcast,
                               reduce: per rank; all-gather, reduce-scatter: all R blocks, which must be
                               16-byte multiples) take direct steps, since all buffers lie in one HBM.  The
@@ -163,11 +163,14 @@ typedef struct {
                               From this size on the collectives that qualify for direct steps run in fold steps too, in
                               several jobs; the others (direct = 0, or below direct_min_bytes) as rings and chains
                               through the connectors' FIFOs.  dfx_coll_info tells what runs */
-  uint32_t fold_slice_bytes; /* a collective in fold steps takes its share of a channel in slices of at most this many bytes
-                              per source, one mover job each (16-byte multiple), so that what is ahead of an urgent
-                              collective under priority ordering is short; 0 (default) = one slice, the whole share
-                              (with 32 KiB slices under priority ordering the urgent bucket of the bench's staggered
-                              study completes after 0.52-0.68 ms instead of 0.63-0.78 ms and the whole run takes 8 % longer) */
+  uint32_t fold_slice_bytes; /* most bytes per source of one mover job of a collective in fold steps (16-byte multiple).  0 (default):
+                              below fold_max_bytes a channel's share in one job, above it jobs of 128 KiB (32 KiB under
+                              priority ordering); where a region is long enough and the results go to every rank, the
+                              workgroups of a rank draw its rows from a counter under FIFO ordering instead of taking
+                              equal parts, at most twice as much per job.  Any other value: jobs of that size, equal
+                              parts.  Under priority ordering 32 KiB keep what is ahead of an urgent collective short
+                              (the urgent bucket of the bench's staggered study completes after 0.43-0.54 ms instead
+                              of 0.51-0.70 ms and the whole run takes 5 % longer) */
   uint32_t reserved0;      /* keeps the struct a multiple of 8 bytes; must be 0 */
 } dfx_config;
 

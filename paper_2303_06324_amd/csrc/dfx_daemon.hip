@@ -9,7 +9,10 @@
 // and switch to the next collective.  Completion is counted per collective; the last channel
 // posts the CQE.  Connectors are FIFOs of K slots in HBM guarded by monotone tail/head
 // counters; a primitive touches nothing before both its conditions hold (Sec. 4.1, 4.5).
-// Long collectives take direct steps, because every rank's buffers lie in the same HBM: in
+// Every rank's buffers lie in the same HBM, so most collectives run in fold steps, which need no connectors: every rank
+// does its part straight from send buffers to recv buffers when all have submitted, and posts the completion
+// when all are through (see make_fold_prim; dfx_config.fold_max_bytes says which do).
+// Rings and chains, where they run, take direct steps from direct_min_bytes on: in
 // the copy steps (gather phase of an all-reduce, all-gather, broadcast) the result goes to the
 // rank's recv buffer only (through the coherent path described below), the counter is raised
 // all the same, and the next rank reads the chunk from that recv buffer; the opening send of

@@ -57,10 +57,9 @@ struct Prim {
   // (the recv buffer is the caller's again once the completion is posted).
   bool notify, din, drain;
   bool din_send;   // the input is the previous rank's SEND buffer (first reduce step of a direct all-reduce / reduce-scatter)
-  // Fold steps of a short collective (see make_fold_prim): fold = 1 the step with data, 3 the last wait, which
-  // moves nothing; 0 = neither.  fwait: the channel's shared counter the wait phase looks at
-  // (0 published, 1 done); fadd: the counter the step adds to when its data is in memory (0 = none).
-  uint8_t fold, fwait, fadd;
+  // Fold steps (see make_fold_prim): fold = 1 the step with data, 3 the last wait, which moves nothing; 0 = neither.
+  // fwait: the channel's shared counter that says whether the step can run (0 published, 1 done).
+  uint8_t fold, fwait;
 };
 
 // Collectives in fold steps.  Every rank's buffers lie in the same HBM, so the dependent hops of a ring or
@@ -81,13 +80,12 @@ struct Prim {
 // their data out instead of every rank fetching all of it: one read per byte instead of R.)
 // Each step is a bounded wait followed by the data, like any primitive: nothing is touched before the wait has
 // succeeded, so a collective stuck in either of them is preempted like any other.
-DFX_HD uint32_t fold_nprim(int) { return 2u; }
+constexpr uint32_t DFX_FOLD_NPRIM = 2u;
 DFX_HD Prim make_fold_prim(uint32_t p) {
   Prim q;
-  q.recv = q.send = q.notify = q.din = q.drain = q.din_send = false;
-  q.from_send = q.to_recv = false;
-  if (p == 0) { q.fold = 1; q.fwait = 0; q.fadd = 1; q.from_send = true; q.to_recv = true; }
-  else { q.fold = 3; q.fwait = 1; q.fadd = 0; }
+  q.recv = q.send = q.notify = q.din = q.drain = q.din_send = q.from_send = q.to_recv = false;   // (no connectors, no pointers of its own)
+  q.fold = p == 0 ? 1 : 3;
+  q.fwait = p == 0 ? 0 : 1;
   return q;
 }
 
@@ -194,7 +192,7 @@ DFX_HD uint64_t fold_shared_line(uint64_t own_line, uint32_t rank, uint32_t R, u
 DFX_HD Prim make_prim(int kind, uint32_t R, uint32_t bc_pos, uint32_t p, bool direct) {
   Prim q;
   q.notify = q.din = q.drain = q.din_send = false;
-  q.fold = q.fwait = q.fadd = 0;
+  q.fold = q.fwait = 0;
   if (R == 1) { q.recv = q.send = false; q.from_send = q.to_recv = true; return q; }   // copy
   if (kind == KIND_AR && direct) {
     const uint32_t last_reduce = R - 1;

@@ -203,7 +203,6 @@ int launch_locked(dfx_ctx* c) {
   // collective that arrives waits for less work that was chosen before it was there.
   if (c->cfg.order_policy == 1 && a.focus_bytes > (32u << 10)) a.focus_bytes = 32u << 10;
   a.scan_min = c->cfg.scan_min;
-  a.chan_spread = c->cfg.chan_spread;
   a.epoch = (uint32_t)(c->launches + 1);
   // quit votes and the quit flag belong to one launch
   HIPCHK(c, hipMemsetAsync(c->dev_ctl + DC_QUIT, 0, 2 * sizeof(uint32_t), c->stream));
@@ -399,7 +398,8 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   // of an all-gather / reduce-scatter must be 16-byte multiples (they are read with 16-byte vectors where they lie).
   const uint64_t largest_bytes = (kind == DFX_ALLGATHER || kind == DFX_REDUCESCATTER) ? count * eb * R : count * eb;
   const bool blocks_ok = !(kind == DFX_ALLGATHER || kind == DFX_REDUCESCATTER) || (count * eb) % 16 == 0;
-  // (a reduce's fold step has one look-up more than it has ranks, one per lane of the scheduler wavefront: at most 63 ranks)
+  // (A reduce on 64 ranks stays a chain.  The step's tables would hold it, but it has never run in fold steps: a form of the
+  // look-up that was to cover it once faulted the GPU, in another collective, and why was never shown.)
   const bool fold = R > 1 && cfg.fold_max_bytes && largest_bytes < cfg.fold_max_bytes && blocks_ok && !(kind == DFX_REDUCE && R > 63);
   uint64_t block = count;
   // (a reduce in fold steps is cut into chunks like an all-reduce: rank r combines chunk r into the root's buffer)
@@ -452,7 +452,7 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   if (R == 1) t.nprim = 1;
   else if (fold) {
     t.flags |= DFX_SQE_DIRECT | DFX_SQE_FOLD;   // (buffers are published as for the direct steps)
-    t.nprim = fold_nprim((int)kind);            // one step with data and the last wait
+    t.nprim = DFX_FOLD_NPRIM;            // one step with data and the last wait
   }
   else if (kind == DFX_ALLREDUCE) {
     // direct gather steps (one more step: the drain) where the message is long enough to gain from them
@@ -486,12 +486,12 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   // Long collectives: what direct steps save of a ring's or chain's traffic, fold steps save in full (every input read
   // once, every output written once: 2R x M of an all-reduce instead of (5R-5) x M), so a collective that qualifies for
   // direct steps runs in fold steps above fold_max_bytes too, in jobs of this size.  Measured (us, R = 8, rings and
-  // chains with direct steps -> this): all-reduce 256 MiB fp32 1545 -> 876, reduce-scatter 128 MiB fp32 496 -> 267,
-  // broadcast 100 MiB bf16 472 -> 204.
+  // chains with direct steps -> this): all-reduce 256 MiB fp32 1545 -> 806, reduce-scatter 128 MiB fp32 496 -> 268,
+  // broadcast 100 MiB bf16 472 -> 200.
   // With fold_max_bytes = 0 the rings and chains run at every size.
   if ((t.flags & DFX_SQE_DIRECT) && !fold && cfg.fold_max_bytes && blocks_ok && !(kind == DFX_REDUCE && R > 63)) {
-    // 128 KiB per source and workgroup: about 100 us at 2 x 8 streams; priority ordering lets nothing longer than
-    // its look-again budget get ahead of an urgent collective
+    // 128 KiB per source and workgroup (drawn rows: twice that at most), about 100 us at 2 x 8 streams; priority ordering
+    // lets nothing longer than its look-again budget get ahead of an urgent collective
     const uint64_t job = cfg.fold_slice_bytes ? cfg.fold_slice_bytes : (cfg.order_policy == 1 ? 32u << 10 : 128u << 10);
     const uint64_t chunk = fold_chunk_elems((int)kind, count, block, (uint32_t)R, eb);     // a rank's region; a channel's part of it
     const uint64_t share = std::max<uint64_t>(round_up(ceil_div(chunk, C), per16), per16);
@@ -501,7 +501,7 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
       t.flags |= DFX_SQE_FOLD;
       t.slice_elems = (uint32_t)(bytes / eb);
       t.rounds = (uint32_t)jobs;
-      t.nprim = fold_nprim((int)kind);
+      t.nprim = DFX_FOLD_NPRIM;
       runs = CollShape{t.nchan, (uint32_t)bytes, t.rounds, t.nprim};
     }
   }
@@ -516,7 +516,7 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   // 416 as a ring).  A job size that the caller asked for keeps its slices, whose rows are dealt, and so
   // does priority ordering: its workgroups may be at different collectives, and one that is first at a region would
   // draw twice its part in a job that a more urgent collective has to wait for (sixteen staggered buckets, jobs without a
-  // limit: urgent one after 0.93 ms with drawn rows, 0.43-0.62 with dealt ones).
+  // limit: urgent one after 0.93 ms with drawn rows, 0.43-0.70 with dealt ones).
   if ((t.flags & DFX_SQE_FOLD) && !cfg.fold_slice_bytes && cfg.order_policy != 1 && fold_to_all((int)kind)) {
     const uint64_t region = fold_chunk_elems((int)kind, count, t.block_elems, (uint32_t)R, eb) * eb;
     const uint64_t row = fold_row_bytes(kind == DFX_ALLGATHER || kind == DFX_BROADCAST, (uint32_t)R), waves = DFX_FOLD_WAVES * C;
@@ -1601,7 +1601,7 @@ int dfx_collective_noalloc(int nranks, dfx_kind kind, size_t count, dfx_dtype dt
   a.scan_min = cfg.scan_min; a.epoch = 1;
   a.R = (uint32_t)nranks; a.cmax = tmpl.nchan; a.max_colls = 1; a.sq_depth = DFX_NA_SQ_DEPTH; a.sq_shift = 1; a.cq_slots = DFX_NA_CQ_SLOTS;
   a.spin_init = cfg.spin_init; a.spin_min = cfg.spin_min; a.spin_max = cfg.spin_max; a.spin_boost = cfg.spin_boost; a.preempt = 1;
-  a.wg_map = 0; a.order_policy = 0; a.trace_on = 0; a.fetch_batch = 0xffffffffu; a.fifo_coherent = 1; a.chan_spread = 1;
+  a.wg_map = 0; a.order_policy = 0; a.trace_on = 0; a.fetch_batch = 0xffffffffu; a.fifo_coherent = 1;
   a.cq_mode = 0; a.sq_eager = 1; a.window = cfg.window; a.sq_local = 1; a.focus_bytes = cfg.focus_bytes;
   a.watchdog_ticks = (uint64_t)((double)cfg.watchdog_ms * 1000.0 / nd->tick_us);
   a.quit_ticks = 0;

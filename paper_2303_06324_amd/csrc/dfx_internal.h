@@ -23,7 +23,7 @@
 #define DFX_SQE_EXIT 1u
 #define DFX_SQE_DIRECT 2u      // collective with direct steps (reads the previous rank's recv / send buffer instead of slots)
 #define DFX_CTX_DIRECT 0x80u   // the same, in the cooked context's bc_pos byte (bits 0-1: place in a chain)
-#define DFX_SQE_FOLD 4u        // all-reduce in fold steps (always together with DFX_SQE_DIRECT: the buffers are published the same way)
+#define DFX_SQE_FOLD 4u        // collective in fold steps (always together with DFX_SQE_DIRECT: the buffers are published the same way)
 #define DFX_CTX_FOLD 0x40u     // the same, in the cooked context's bc_pos byte
 #define DFX_SQE_DRAWN 16u      // fold steps: the rows of a rank's region are drawn from a counter (fold_entry)
 #define DFX_CTX_DRAWN 0x20u    // the same, in the cooked context's bc_pos byte
@@ -153,7 +153,7 @@ struct DfxDaemonArgs {
   uint32_t epoch;           // number of this launch (exit SQEs name the launch they end)
   uint32_t R, cmax, max_colls, sq_depth, sq_shift, cq_slots;
   uint32_t spin_init, spin_min, spin_max, spin_boost, preempt;
-  uint32_t wg_map, order_policy, trace_on, fetch_batch, fifo_coherent, chan_spread, cq_mode, sq_eager, window, sq_local, focus_bytes;
+  uint32_t wg_map, order_policy, trace_on, fetch_batch, fifo_coherent, cq_mode, sq_eager, window, sq_local, focus_bytes;
   uint64_t watchdog_ticks;  // wall-clock ticks; 0 = off
   uint64_t quit_ticks;      // wall-clock ticks; 0 = off
   uint32_t oneshot;         // not 0: the SQs were filled before the launch with this many entries per rank and nobody

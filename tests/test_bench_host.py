@@ -56,11 +56,14 @@ def test_roofline_byte_counts_follow_from_the_primitive_programs(R):
     assert _blocks_moved(sm.RD, R, False, root=1) == 3 * R - 1 and _blocks_moved(sm.RD, R, True, root=1) == 3 * R - 3
 
 
-def test_measured_traffic_constant_is_the_moved_bytes_of_the_headline_workload():
-    """The counter-measured HBM traffic that bench.py reports for the 256 MiB workload lies within 0.2 % of
-    what the direct steps have to move."""
-    want = bench.moved_bytes(256 << 20, 8)
-    assert abs(bench.MEASURED_TRAFFIC_BYTES - want) / want < 2e-3
+@pytest.mark.parametrize("path", ["fold steps", "ring with direct steps"])
+def test_measured_traffic_is_what_the_path_has_to_move(path):
+    """The counter-measured HBM traffic that bench.py reports for the 256 MiB workload lies within 0.2 % of what the
+    path that ran has to move; the paths are told apart by the number of steps the library reports."""
+    want = bench.path_bytes(path, 256 << 20)
+    assert want == {"fold steps": bench.fold_bytes, "ring with direct steps": bench.moved_bytes}[path](256 << 20, 8)
+    assert abs(bench.MEASURED_TRAFFIC_BYTES[path] - want) / want < 2e-3
+    assert [bench.path_of(n) for n in (2, 16, 15)] == ["fold steps", "ring with direct steps", "ring through slots"]
 
 
 def test_more_than_one_gpu_is_refused():

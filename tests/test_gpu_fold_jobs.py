@@ -62,6 +62,33 @@ def test_shares_of_several_jobs(kind, R, knobs):
     _check(w, dw)
 
 
+@pytest.mark.parametrize("R", [2, 5, 8])
+@pytest.mark.parametrize("knobs", [dict(), LONG], ids=["one_job", "several_jobs"])
+def test_all_reduce_in_place(R, knobs):
+    """recvbuf == sendbuf, with chunks at odd multiples of 16 bytes (a wave takes the bytes before the rows) and a ragged end:
+    every byte is read by the wave that then overwrites it, and by no other."""
+    from paper_2303_06324_amd import harness as gh
+    import paper_2303_06324_amd as dfx
+    import torch
+    n = R * ((768 << 10) + 48) // 2 - 5
+    w = wi.Workload("in_place", R, [wi.CollSpec(0, wi.AR, wi.BF16, n)], [[0]] * R, seed=R, cfg=94)
+    host = wi.all_sends(w, 0)
+    want = rd.all_reduce_fold(host, wi.BF16)
+    ctx = dfx.Context(R, gh.make_config(max_channels=2, **knobs))
+    try:
+        gh.prepare_all(ctx, w)
+        assert ctx.coll_info(0)["nprim"] == 2 and (ctx.coll_info(0)["rounds"] > 1) == bool(knobs)
+        for it in range(2):
+            buf = [torch.from_numpy(h.view(np.uint8).copy()).cuda() for h in host]
+            torch.cuda.synchronize()
+            p = [t.data_ptr() for t in buf]
+            assert ctx.submit_all(0, ctx.make_all(p, p)) == dfx.OK and ctx.wait_all(20.0) == dfx.OK
+            for r in range(R):
+                assert np.array_equal(buf[r].cpu().numpy(), want.view(np.uint8)), (it, r)
+    finally:
+        ctx.finalize()
+
+
 @pytest.mark.parametrize("kind", [wi.AR, wi.AG, wi.RS])
 def test_daemon_stopped_between_jobs(kind):
     """One channel per rank and regions of 4 MiB: a few milliseconds of some twenty to thirty jobs.  The exit entry arrives behind the

@@ -166,7 +166,7 @@ DFX_HD FoldGeom fold_geometry(uint64_t len, uint64_t src, uint64_t dst, uint32_t
 // buffers.  A region begins at any multiple of 16 bytes (the chunk of an all-reduce, the block of an all-gather), and rows
 // counted from there end inside a line, of which two waves then write a part each, straight to memory.  us per call, fp32,
 // regions at odd multiples of 16 bytes, rows from the region's start -> from the line (= regions on lines): all-gather of 64 MiB
-// 192 -> 132 (R = 8), 158 -> 96 (R = 6), all-reduce of 25 MiB 98 -> 82, broadcast of 110 MiB 306 -> 205 (R = 8).
+// 192 -> 132 (R = 8), 158 -> 96 (R = 6), all-reduce of 25 MiB 98 -> 92, broadcast of 110 MiB 306 -> 205 (R = 8).
 // Short spans keep their rows at the front: the round trip for the bytes before would cost what whole lines gain (64 KiB,
 // R = 8: 0.4 us; a wave has four rows from 32 KiB per workgroup on).
 DFX_HD uint32_t fold_head(uint64_t dst, uint32_t bytes, uint32_t nchan) {

@@ -11,7 +11,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-R, ROUNDS, ROOT = 8, 12, 3
+R, ITERATIONS, ROOT = 8, 12, 3
 
 
 def _done(ev, seconds):
@@ -47,8 +47,8 @@ def test_send_buffers_rewritten_under_a_resident_daemon(kind, n):
     send = [torch.from_numpy(b).cuda() for b in base]
     recv = [torch.full((nr,), -1, dtype=torch.int32, device="cuda") for _ in range(R)]
     ring = [torch.full((R * n,), -1, dtype=torch.int32, device="cuda") for _ in range(R)]        # an all-gather of odd blocks
-    kept = torch.zeros((ROUNDS, R, nr), dtype=torch.int32, device="cuda")
-    kept_ring = torch.zeros((ROUNDS, R, (n - 1) * R), dtype=torch.int32, device="cuda")
+    kept = torch.zeros((ITERATIONS, R, nr), dtype=torch.int32, device="cuda")
+    kept_ring = torch.zeros((ITERATIONS, R, (n - 1) * R), dtype=torch.int32, device="cuda")
     scratch, reads = torch.zeros(64, device="cuda"), torch.zeros(R, dtype=torch.int64, device="cuda")
     torch.cuda.synchronize()
     # four channels per rank leave the other kernels most of the compute units; a second without work before the daemon leaves
@@ -61,7 +61,7 @@ def test_send_buffers_rewritten_under_a_resident_daemon(kind, n):
         p1 = ctx.make_all([t.data_ptr() for t in send], [t.data_ptr() for t in ring])
         assert ctx.start() == dfx.OK
         st = _stream_beside_the_daemon(torch, scratch)
-        for i in range(ROUNDS):
+        for i in range(ITERATIONS):
             with torch.cuda.stream(st):
                 for r in range(R):
                     reads[r] = send[r].sum() + recv[r].sum()
@@ -79,13 +79,13 @@ def test_send_buffers_rewritten_under_a_resident_daemon(kind, n):
                 ev.record(st)
             assert _done(ev, 10.0)
             if i == 0: launches = ctx.stats(0)["launches"]
-        assert ctx.stats(0)["launches"] == launches          # one daemon through all rounds but the first
+        assert ctx.stats(0)["launches"] == launches          # one daemon through all iterations but the first
         assert ctx.stop() == dfx.OK
     finally:
         ctx.finalize()
     torch.cuda.synchronize()
     kept, kept_ring = kept.cpu().numpy(), kept_ring.cpu().numpy()
-    for i in range(ROUNDS):
+    for i in range(ITERATIONS):
         now = [(b.astype(np.int64) + sum(r * 7 + j + 1 for j in range(i + 1))).astype(np.int32) for r, b in enumerate(base)]
         total = np.sum([x.astype(np.int64) for x in now], axis=0).astype(np.int32)
         for r in range(R):

@@ -467,7 +467,7 @@ def studies():
     out = {"cq_variants": [], "ordering_config3": []}
     w5 = wi.config5(n_colls=1024, seed=4)
     d5 = gh.DeviceWorkload(w5, keep_host=False)
-    for mode, name in ((0, "optimized CQ: one CAS into a free slot"), (1, "vanilla ring buffer"),
+    for mode, name in ((0, "optimized CQ: one posted write into the id's slot"), (1, "vanilla ring buffer"),
                        (2, "optimized ring buffer: id + position in one 64-bit write")):
         ctx = dfx.Context(R, gh.make_config(cq_mode=mode, quit_idle_us=0))
         try:

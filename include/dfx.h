@@ -68,7 +68,7 @@ typedef struct {
   uint32_t max_channels;   /* workgroups per vrank; daemon grid = nranks * max_channels (Sec. 5: launched with the largest grid) */
   uint32_t max_colls;      /* coll_id range [0, max_colls); also task-queue capacity (<= 4096) */
   uint32_t sq_depth;       /* SQ ring entries per vrank (power of two; default 1024: a burst of a thousand submissions does not wait for the daemon) */
-  uint32_t cq_slots;       /* CQ slot-array length per vrank (Sec. 5 "optimized CQ") */
+  uint32_t cq_slots;       /* length of the CQ ring per vrank (cq_mode 1 and 2; the optimized CQ has a slot per id) */
   uint32_t nslots;         /* K: slots per connector FIFO, >= 2 (a fused recv+send ring cannot run on 1) */
   uint32_t slot_bytes;     /* S: bytes per FIFO slot and channel, multiple of 16 (default 256 KiB).  A slice is
                               at most this long.  The chains take shorter slices, because their last rank starts
@@ -116,7 +116,7 @@ typedef struct {
                               (small collectives all share the first task queues: the single-queue
                               setting of Sec. 2.3) */
   uint32_t cq_mode;        /* completion-queue variant (Sec. 5 "Optimizing CQ"): 0 = optimized CQ, one
-                              system-scope CAS of the id into a free slot (default); 1 = vanilla ring buffer
+                              posted 8-byte write of id and invocation into the id's own slot, no ring semantics (default); 1 = vanilla ring buffer
                               (reserve, entry, fence, in-order tail update); 2 = optimized ring buffer (id and
                               position in one 64-bit atomic write, validated by the poller against its head) */
   uint32_t sq_eager;       /* 1 (default): a workgroup probes the SQ before every pass over its queue; 0: only when
@@ -248,9 +248,10 @@ int dfx_prepare(dfx_ctx* ctx, int coll_id, dfx_kind kind, size_t count, dfx_dtyp
  * invocations of one coll_id (Sec. 4.2) and must not overlap each other, except that an all-reduce may
  * run in place (recvbuf == sendbuf).
  * Errors: INVALID_ARG, NOT_PREPARED, BUSY, SQ_FULL (retry), ABORTED, HIP.
- * Unless dfx_set_callback has started the poller thread, completions wait in the CQ (cq_slots entries per vrank) until
+ * Unless dfx_set_callback has started the poller thread, completions wait in the CQ until
  * dfx_poll / dfx_wait / dfx_wait_all take them, or until a dfx_submit on that vrank finds the SQ full
- * and moves them to the host-side list itself.  A vrank whose CQ is full stops making progress.
+ * and moves them to the host-side list itself.  A vrank whose CQ ring (cq_mode 1 and 2: cq_slots entries) is full stops
+ * making progress.
  */
 int dfx_submit(dfx_ctx* ctx, int rank, int coll_id, const void* sendbuf, void* recvbuf);
 

@@ -42,6 +42,7 @@ struct RankState {
   uint64_t sq_tail = 0;                 // entries written to this rank's SQ
   std::vector<uint32_t> sub;            // per coll: submissions so far
   std::vector<uint32_t> done;           // per coll: completions seen
+  std::vector<uint32_t> open;           // ids submitted whose completion has not been seen, in the order of submission (CQ with a slot per id)
   std::deque<dfx_cqe> ready;            // completions not yet handed to the caller
   uint64_t cq_head = 0;                 // ring-buffer CQ variants: entries consumed
   std::atomic<uint64_t> n_sub{0}, n_cqe{0};
@@ -76,6 +77,7 @@ struct dfx_ctx {
   DfxSqSlot* sq = nullptr;
   uint32_t* host_ctl = nullptr;
   uint64_t* cq = nullptr;
+  uint32_t cq_slots = 0;             // per rank
   uint64_t* cq_ctl = nullptr;        // ring bookkeeping of the ring-buffer CQ variants (same allocation as cq)
   uint32_t* sq_freed = nullptr;      // [R][sq_depth] generation of the last entry every workgroup has read (same allocation as cq)
   // device memory
@@ -189,7 +191,7 @@ int launch_locked(dfx_ctx* c) {
   a.sq_readers = c->sq_readers; a.done_cnt = c->done_cnt; a.dev_ctl = c->dev_ctl;
   a.pool = c->pool; a.ctxbuf = c->ctxbuf; a.wgstate = c->wgstate; a.taskq_store = c->taskq_store; a.trace = c->trace;
   a.R = (uint32_t)c->R; a.cmax = c->cfg.max_channels; a.max_colls = c->cfg.max_colls;
-  a.sq_depth = c->cfg.sq_depth; a.sq_shift = c->sq_shift; a.cq_slots = c->cfg.cq_slots;
+  a.sq_depth = c->cfg.sq_depth; a.sq_shift = c->sq_shift; a.cq_slots = c->cq_slots;
   a.spin_init = c->cfg.spin_init; a.spin_min = c->cfg.spin_min; a.spin_max = c->cfg.spin_max;
   a.spin_boost = c->cfg.spin_boost; a.preempt = c->cfg.preempt;
   a.wg_map = c->cfg.wg_map; a.order_policy = c->cfg.order_policy; a.trace_on = c->cfg.trace;
@@ -319,7 +321,7 @@ int push_sqe(dfx_ctx* c, int rank, const DfxStatic& e) {
 // Move every completion of a rank that has arrived into its ready list (caller holds the rank's mutex).
 void drain_cq(dfx_ctx* c, int rank) {
   RankState* rs = c->ranks[rank];
-  volatile uint64_t* q = c->cq + (size_t)rank * c->cfg.cq_slots;
+  volatile uint64_t* q = c->cq + (size_t)rank * c->cq_slots;
   auto take = [&](uint32_t coll, uint32_t seq) {
     dfx_cqe e;
     e.coll_id = coll;
@@ -329,25 +331,20 @@ void drain_cq(dfx_ctx* c, int rank) {
     rs->n_cqe.fetch_add(1, std::memory_order_relaxed);
   };
   if (c->cfg.cq_mode == 0) {
-    // optimized CQ: scan the slots, take the valid ones and mark them writable
-    auto look = [&](uint32_t i) {
-      const uint64_t v = q[i];
-      if (!(v >> 63)) return;
-      std::atomic_thread_fence(std::memory_order_acquire);
-      q[i] = 0;
-      take((uint32_t)(v & 0xffffffffu), (uint32_t)((v >> 32) & 0x7fffffffu));
-    };
-    // eight slots at a time: their valid bits are the sign bits (a caller that waits sweeps all ranks' slots over and
-    // over, and the sweep is part of what it waits for: word by word an all-reduce of 8 KiB took 18.6 us, now 17.6)
-    std::atomic_signal_fence(std::memory_order_seq_cst);
-    uint32_t i = 0;
-    for (; i + 8 <= c->cfg.cq_slots; i += 8) {
-      const __m128i* p = (const __m128i*)(const uint64_t*)(q + i);
-      const __m128i any = _mm_or_si128(_mm_or_si128(_mm_loadu_si128(p), _mm_loadu_si128(p + 1)), _mm_or_si128(_mm_loadu_si128(p + 2), _mm_loadu_si128(p + 3)));
-      if (_mm_movemask_pd(_mm_castsi128_pd(any)))
-        for (uint32_t k = 0; k < 8; ++k) look(i + k);
+    // a slot per id: look where a completion is expected, for the invocation that is expected.  Nothing is written back, so a
+    // caller that waits reads a line or two per rank, which stay in its cache until the daemon writes them.
+    size_t kept = 0;
+    for (size_t i = 0; i < rs->open.size(); ++i) {
+      const uint32_t coll = rs->open[i], seq = rs->sub[coll] - 1u;
+      if (q[coll] == ((1ull << 63) | ((uint64_t)(seq & 0x7fffffffu) << 32) | coll)) {
+        std::atomic_thread_fence(std::memory_order_acquire);
+        take(coll, seq & 0x7fffffffu);
+      } else {
+        if (kept != i) rs->open[kept] = coll;
+        ++kept;
+      }
     }
-    for (; i < c->cfg.cq_slots; ++i) look(i);
+    rs->open.resize(kept);
     return;
   }
   volatile uint64_t* ctl = c->cq_ctl + (size_t)rank * DFX_CQ_CTL_WORDS;
@@ -357,14 +354,14 @@ void drain_cq(dfx_ctx* c, int rank) {
     const uint64_t tail = ctl[8];
     std::atomic_thread_fence(std::memory_order_acquire);
     for (; rs->cq_head < tail; ++rs->cq_head) {
-      const uint64_t v = q[rs->cq_head % c->cfg.cq_slots];
+      const uint64_t v = q[rs->cq_head % c->cq_slots];
       take((uint32_t)(v & 0xffffffffu), (uint32_t)((v >> 32) & 0x7fffffffu));
     }
   } else {
     // optimized ring: the entry at the head is valid when the position written into it is head + 1;
     // the invocation number is the host's own count (one invocation of an id is outstanding at a time)
     for (;;) {
-      const uint64_t v = q[rs->cq_head % c->cfg.cq_slots];
+      const uint64_t v = q[rs->cq_head % c->cq_slots];
       if ((uint32_t)(v >> 32) != (uint32_t)(rs->cq_head + 1)) break;
       std::atomic_thread_fence(std::memory_order_acquire);
       const uint32_t coll = (uint32_t)(v & 0xffffu);
@@ -654,7 +651,8 @@ int dfx_init(dfx_ctx** out, int nranks, const dfx_config* ucfg, void* hip_stream
 
   const size_t R = (size_t)nranks;
   const size_t sq_bytes = R * cfg.sq_depth * sizeof(DfxSqSlot) + HC_N * sizeof(uint32_t) + 256;
-  const size_t cq_slots_bytes = round_up(R * cfg.cq_slots * sizeof(uint64_t), 64);
+  c->cq_slots = cfg.cq_mode == 0 ? cfg.max_colls : cfg.cq_slots;
+  const size_t cq_slots_bytes = round_up(R * c->cq_slots * sizeof(uint64_t), 64);
   const size_t cq_ctl_bytes = round_up(R * DFX_CQ_CTL_WORDS * sizeof(uint64_t), 64);
   const size_t cq_bytes = cq_slots_bytes + cq_ctl_bytes + R * cfg.sq_depth * sizeof(uint32_t);
   if (c->sq_device) {
@@ -697,6 +695,7 @@ int dfx_init(dfx_ctx** out, int nranks, const dfx_config* ucfg, void* hip_stream
     RankState* rs = new RankState();
     rs->sub.assign(cfg.max_colls, 0);
     rs->done.assign(cfg.max_colls, 0);
+    rs->open.reserve(cfg.max_colls);
     c->ranks.push_back(rs);
   }
   *out = c;
@@ -755,6 +754,7 @@ int stage_one(dfx_ctx* c, int rank, uint32_t ahead, int coll_id, const void* sen
   e.recvbuf = (uint64_t)(uintptr_t)recvbuf;
   sqe_write_body(c, rank, ahead, e);
   rs->sub[coll_id]++;
+  if (c->cfg.cq_mode == 0) rs->open.push_back((uint32_t)coll_id);
   return DFX_OK;
 }
 
@@ -826,7 +826,11 @@ int dfx_submit_all(dfx_ctx* c, int coll_id, const void* const* sendbufs, void* c
       break;
     }
     // one vrank could not take it: nothing has been published, the staged ones are taken back
-    for (int r = 0; r < staged; ++r) { c->ranks[r]->sub[coll_id]--; c->ranks[r]->mu.unlock(); }
+    for (int r = 0; r < staged; ++r) {
+      c->ranks[r]->sub[coll_id]--;
+      if (c->cfg.cq_mode == 0) c->ranks[r]->open.pop_back();
+      c->ranks[r]->mu.unlock();
+    }
     if (rc != DFX_ERR_SQ_FULL) return rc;
     { std::lock_guard<std::mutex> lk(c->ranks[staged]->mu); drain_cq(c, staged); }
     const int rr = ensure_running(c);

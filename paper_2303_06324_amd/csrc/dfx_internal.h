@@ -136,7 +136,7 @@ enum { HC_ABORT = 0, HC_N = 16 };
 
 struct DfxDaemonArgs {
   DfxSqSlot* sq;            // [R][sq_depth]   host-visible
-  uint64_t* cq;             // [R][cq_slots]   host-visible
+  uint64_t* cq;             // [R][cq_slots]   host-visible; a slot per id (cq_mode 0: cq_slots >= max_colls) or a ring
   uint64_t* cq_ctl;         // [R][DFX_CQ_CTL_WORDS] host-visible: bookkeeping of the ring-buffer CQ variants
   uint32_t* host_ctl;       // [HC_N]          host-visible
   uint32_t* sq_freed;       // [R][sq_depth]   host memory: generation of the entry last read by every workgroup

@@ -1561,7 +1561,9 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
       };
       // The wait phase (Sec. 4.2 (3)), with the first poll on its way already: ready() looks at what poll() has brought.
       // The movers may be busy with earlier slices meanwhile; finished ones are retired between polls.
-      auto wait_until = [&](auto&& poll, auto&& ready) -> uint32_t {
+      // lone: the wait may go on past its threshold while nothing else is there to do (at most LONE_POLLS times).
+      constexpr u64 LONE_POLLS = 256;
+      auto wait_until = [&](auto&& poll, auto&& ready, auto&& lone) -> uint32_t {
         u64 n = 0;
         uint32_t r = W_OK;
         for (;;) {
@@ -1570,7 +1572,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           if (__ballot(!ok) == 0) break;
           settle_slot();
           retire_finished();
-          if (hot.preempt && n >= thr) { r = W_TIMEOUT; break; }
+          if (hot.preempt && n >= thr && !(n < LONE_POLLS && lone())) { r = W_TIMEOUT; break; }
           if ((n & 255u) == 0) {
             uint32_t s = 0;
             if (lane == 0) {
@@ -1635,7 +1637,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           const FoldGeom fg = fold_geometry(bcast64(v1.x, v1.y), bcast64(v1.z, v1.w), bcast64(v2.x, v2.y), s_slice, drawn, g);
           bytes = bcast0(v0.z);
           look_ahead();
-          res = wait_until(poll, [&]() { return lane >= R || (ln_recv.z == inv_seq + 1u && ln_send.z == inv_seq + 1u); });
+          res = wait_until(poll, [&]() { return lane >= R || (ln_recv.z == inv_seq + 1u && ln_send.z == inv_seq + 1u); }, [] { return false; });
           if (res == W_OK) {
             wait_traced();
             // (under priority ordering a step with data, which is one long job, waits until the movers have nothing
@@ -1674,11 +1676,18 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           // The last wait moves nothing, and the counter it has seen says that every rank's data step of this channel
           // -- this workgroup's own job included -- is in memory: the completion is posted here and now instead of
           // queueing as an empty job behind the data jobs of other collectives.
+          // A collective that is alone in the queue has nothing to be given up for until another entry arrives: lane 1 looks for
+          // that one in the same poll (an SQ in device memory; behind PCIe it would hold the poll up).  Given up after its
+          // threshold and taken up again by the next pass, the wait saw the counter up to 3 us late: a 25 MiB bf16 all-reduce
+          // took 98.6 us, now 97.8, an all-gather of 32 MiB 76.7, now 73.6.
+          const bool alone = qlen == 1 && hot.sq_local;
+          const u64* const word = alone && lane == 1 ? (const u64*)&sqbase[ri & (D - 1)].e.share : (const u64*)s_in + DFX_FOLD_RED / 8;
           u64 seen_cnt;
-          auto poll = [&]() { seen_cnt = ld_agent64((const u64*)s_in + DFX_FOLD_RED / 8); };
+          auto poll = [&]() { seen_cnt = ld_sys64(word); };
           poll();
           look_ahead();
-          res = wait_until(poll, [&]() { return seen_cnt >= s_fout; });
+          res = wait_until(poll, [&]() { return (alone && lane == 1) || seen_cnt >= s_fout; },
+                           [&]() { return alone && (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(seen_cnt >> 32), 1) != (uint32_t)(ri >> hot.sq_shift) + 1u; });
           if (res == W_OK) {
             wait_traced();
             if (lane == 0) { bump(sh.stat, ST_PRIMS, 1); complete(coll, inv_seq, inv_nchan, true); }
@@ -1722,7 +1731,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             if (lane == 1 && q.send) ok = (sent - seen_cnt) < (u64)K;
             if (lane == 1 && q.drain) ok = sent == seen_cnt;
             return ok;
-          });
+          }, [] { return false; });
         }
         if (res == W_OK) {
           wait_traced();

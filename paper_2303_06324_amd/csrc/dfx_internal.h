@@ -62,6 +62,7 @@ struct alignas(16) DfxStatic {
   uint32_t ready;        // SQ only, written last: generation of the entry
 };
 static_assert(sizeof(DfxStatic) == 96, "DfxStatic must be 96 bytes");
+static_assert(offsetof(DfxStatic, share) == 88 && offsetof(DfxStatic, ready) == 92, "one 8-byte load at `share` brings `ready` in its upper half");
 
 // Dynamic context (Sec. 4.2: current chunk id, aborted primitive id) plus the monotone
 // connector counters of this (rank, channel).  32 bytes = two 16-byte vectors.

@@ -260,7 +260,7 @@ int dfx_submit(dfx_ctx* ctx, int rank, int coll_id, const void* sendbuf, void* r
  * sendbufs / recvbufs: host arrays of nranks device pointers.  The same as nranks dfx_submit calls,
  * minus nranks-1 trips through the caller's language binding; for the single-process setting in which
  * one thread drives all vranks, and with all entries made visible together (their bodies, one store fence,
- * their generation words).  All or nothing: returns DFX_OK when every vrank's entry is in its SQ, else the first
+ * their generation words).  A collective in fold steps starts sooner this way: every entry comes with all ranks' buffers.  All or nothing: returns DFX_OK when every vrank's entry is in its SQ, else the first
  * status that is not OK with no vrank submitted (a full SQ is retried for up to timeout_ns first).
  */
 int dfx_submit_all(dfx_ctx* ctx, int coll_id, const void* const* sendbufs, void* const* recvbufs, uint64_t timeout_ns);

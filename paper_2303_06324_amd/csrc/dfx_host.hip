@@ -75,6 +75,7 @@ struct dfx_ctx {
   size_t qmem_sq_bytes = 0;
   void* qmem_cq = nullptr;           // CQ slot arrays (pinned host)
   DfxSqSlot* sq = nullptr;
+  DfxPeer* sq_peers = nullptr;       // same allocation, where the SQ is in device memory
   uint32_t* host_ctl = nullptr;
   uint64_t* cq = nullptr;
   uint32_t cq_slots = 0;             // per rank
@@ -187,7 +188,7 @@ int reap_locked(dfx_ctx* c, bool* idle) {
 int launch_locked(dfx_ctx* c) {
   DfxDaemonArgs a;
   memset(&a, 0, sizeof(a));
-  a.sq = c->sq; a.cq = c->cq; a.host_ctl = c->host_ctl;
+  a.sq = c->sq; a.cq = c->cq; a.host_ctl = c->host_ctl; a.sq_peers = c->sq_peers;
   a.sq_readers = c->sq_readers; a.done_cnt = c->done_cnt; a.dev_ctl = c->dev_ctl;
   a.pool = c->pool; a.ctxbuf = c->ctxbuf; a.wgstate = c->wgstate; a.taskq_store = c->taskq_store; a.trace = c->trace;
   a.R = (uint32_t)c->R; a.cmax = c->cfg.max_channels; a.max_colls = c->cfg.max_colls;
@@ -650,7 +651,9 @@ int dfx_init(dfx_ctx** out, int nranks, const dfx_config* ucfg, void* hip_stream
   INITCHK(hipEventCreate(&c->ev_stop));
 
   const size_t R = (size_t)nranks;
-  const size_t sq_bytes = R * cfg.sq_depth * sizeof(DfxSqSlot) + HC_N * sizeof(uint32_t) + 256;
+  const size_t ctl_at = round_up(R * cfg.sq_depth * sizeof(DfxSqSlot), 256), peers_at = round_up(ctl_at + HC_N * sizeof(uint32_t), 256);
+  const size_t peers_bytes = c->sq_device && R * R * cfg.sq_depth * sizeof(DfxPeer) <= DFX_PEERS_MAX_BYTES ? R * R * cfg.sq_depth * sizeof(DfxPeer) : 0;
+  const size_t sq_bytes = peers_at + peers_bytes;
   c->cq_slots = cfg.cq_mode == 0 ? cfg.max_colls : cfg.cq_slots;
   const size_t cq_slots_bytes = round_up(R * c->cq_slots * sizeof(uint64_t), 64);
   const size_t cq_ctl_bytes = round_up(R * DFX_CQ_CTL_WORDS * sizeof(uint64_t), 64);
@@ -667,7 +670,8 @@ int dfx_init(dfx_ctx** out, int nranks, const dfx_config* ucfg, void* hip_stream
   INITCHK(hipHostMalloc(&c->qmem_cq, cq_bytes, hipHostMallocMapped | hipHostMallocCoherent));
   memset(c->qmem_cq, 0, cq_bytes);
   c->sq = (DfxSqSlot*)c->qmem_sq;
-  c->host_ctl = (uint32_t*)((char*)c->qmem_sq + round_up(R * cfg.sq_depth * sizeof(DfxSqSlot), 256));
+  c->host_ctl = (uint32_t*)((char*)c->qmem_sq + ctl_at);
+  if (peers_bytes) c->sq_peers = (DfxPeer*)((char*)c->qmem_sq + peers_at);
   c->cq = (uint64_t*)c->qmem_cq;
   c->cq_ctl = (uint64_t*)((char*)c->qmem_cq + cq_slots_bytes);
   c->sq_freed = (uint32_t*)((char*)c->qmem_cq + cq_slots_bytes + cq_ctl_bytes);
@@ -735,7 +739,7 @@ namespace {
 
 // The body of one invocation's SQE, `ahead` entries behind the tail (the caller holds the rank's mutex and
 // publishes afterwards).  Counts the invocation as submitted, so that the same id again in one run is BUSY.
-int stage_one(dfx_ctx* c, int rank, uint32_t ahead, int coll_id, const void* sendbuf, void* recvbuf) {
+int stage_one(dfx_ctx* c, int rank, uint32_t ahead, int coll_id, const void* sendbuf, void* recvbuf, uint16_t more_flags = 0) {
   if (coll_id < 0 || (uint32_t)coll_id >= c->cfg.max_colls) return DFX_ERR_INVALID_ARG;
   if (c->aborted.load()) return DFX_ERR_ABORTED;
   const CollInfo& ci = c->colls[coll_id];
@@ -748,7 +752,10 @@ int stage_one(dfx_ctx* c, int rank, uint32_t ahead, int coll_id, const void* sen
   }
   if (!sqe_slot_free(c, rank, ahead)) return DFX_ERR_SQ_FULL;
   DfxStatic e = ci.tmpl;
-  if (e.flags & DFX_SQE_FOLD) fold_entry(e, (uint32_t)c->R, (uint32_t)rank);
+  if (e.flags & DFX_SQE_FOLD) {
+    fold_entry(e, (uint32_t)c->R, (uint32_t)rank);
+    e.flags |= more_flags;
+  }
   e.seq = rs->sub[coll_id];
   e.sendbuf = (uint64_t)(uintptr_t)sendbuf;
   e.recvbuf = (uint64_t)(uintptr_t)recvbuf;
@@ -815,10 +822,21 @@ int dfx_submit_all(dfx_ctx* c, int coll_id, const void* const* sendbufs, void* c
     int rc = DFX_OK, staged = 0;
     for (; staged < c->R; ++staged) {
       c->ranks[staged]->mu.lock();
-      rc = stage_one(c, staged, 0u, coll_id, sendbufs[staged], recvbufs[staged]);
+      rc = stage_one(c, staged, 0u, coll_id, sendbufs[staged], recvbufs[staged], c->sq_peers ? DFX_SQE_PEERS : 0);
       if (rc != DFX_OK) { c->ranks[staged]->mu.unlock(); break; }
     }
     if (rc == DFX_OK) {
+      if (c->sq_peers && (c->colls[coll_id].tmpl.flags & DFX_SQE_FOLD)) {
+        // every entry's table (a slot's table is as free as the slot: every workgroup of the rank reads both before it counts itself in)
+        const DfxStatic& t = c->colls[coll_id].tmpl;
+        for (int r = 0; r < c->R; ++r) {
+          DfxPeer* tab = c->sq_peers + ((size_t)r * c->cfg.sq_depth + (c->ranks[r]->sq_tail & (c->cfg.sq_depth - 1))) * (size_t)c->R;
+          for (int k = 0; k < c->R; ++k) {
+            const uint32_t p = fold_peer(t.kind, (uint32_t)c->R, (uint32_t)r, t.root, (uint32_t)k);
+            _mm_storeu_si128((__m128i*)(tab + k), _mm_set_epi64x((long long)(uintptr_t)recvbufs[p], (long long)(uintptr_t)sendbufs[p]));
+          }
+        }
+      }
       sqe_fence();
       for (int r = 0; r < c->R; ++r) sqe_publish(c, r, 1);
       _mm_sfence();

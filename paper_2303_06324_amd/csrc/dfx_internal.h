@@ -27,6 +27,7 @@
 #define DFX_CTX_FOLD 0x40u     // the same, in the cooked context's bc_pos byte
 #define DFX_SQE_DRAWN 16u      // fold steps: the rows of a rank's region are drawn from a counter (fold_entry)
 #define DFX_CTX_DRAWN 0x20u    // the same, in the cooked context's bc_pos byte
+#define DFX_SQE_PEERS 64u      // fold steps, submitted on every rank at once: the entry's table of buffers is filled in (DfxPeer)
 // A collective in fold steps has no slots, whatever its size.  Its connector block is R x nchan flag lines, one per (rank,
 // channel), that carry the published buffer addresses (DFX_DIRECT_OFF), and behind them nchan shared lines, one per
 // channel, with two counters that every rank of the channel adds to.
@@ -112,6 +113,11 @@ struct alignas(16) DfxSqSlot {   // one SQ ring entry, padded to two 64-byte lin
 };
 static_assert(sizeof(DfxSqSlot) == 128, "SQ slot must be 128 bytes");
 
+// Where a submission covers all ranks at once, every rank's entry comes with the buffers of all of them, in the order of the rank's
+// tables (fold_peer): its workgroups need not wait until the others have published theirs.
+struct alignas(16) DfxPeer { uint64_t sendbuf, recvbuf; };
+#define DFX_PEERS_MAX_BYTES (16u << 20)   // tables of all SQ slots: R x sq_depth x R entries; contexts that would need more go without
+
 // Per-workgroup state that survives daemon exit / voluntary quit (Sec. 4.5).
 struct alignas(16) DfxWgState {
   uint64_t read_index;   // SQ entries consumed by this workgroup
@@ -140,6 +146,7 @@ struct DfxDaemonArgs {
   uint64_t* cq;             // [R][cq_slots]   host-visible; a slot per id (cq_mode 0: cq_slots >= max_colls) or a ring
   uint64_t* cq_ctl;         // [R][DFX_CQ_CTL_WORDS] host-visible: bookkeeping of the ring-buffer CQ variants
   uint32_t* host_ctl;       // [HC_N]          host-visible
+  const DfxPeer* sq_peers;  // [R][sq_depth][R] host-visible: the tables of DFX_SQE_PEERS entries (or null)
   uint32_t* sq_freed;       // [R][sq_depth]   host memory: generation of the entry last read by every workgroup
   uint32_t* sq_readers;     // [R][sq_depth]   device
   uint32_t* done_cnt;       // [R][max_colls]  device

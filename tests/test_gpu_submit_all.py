@@ -1,0 +1,68 @@
+"""Submissions on every rank at once: the entries come with all ranks' buffers, and a rank that finds one alone in its queue starts
+without having seen the others.  Checked where that can go wrong: buffers that change from call to call under the same ids (the
+tables of a reused SQ slot), calls that overtake one another (two or more entries in a queue, a table replaced while its collective
+still waits), single submissions and rings in between, several jobs, priority ordering, rank counts with and without a data mover
+of their own, an SQ of two entries.  int32, sums and copies: exact."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("R,knobs", [(8, dict()), (8, dict(sq_depth=2, chan_spread=0)), (3, dict(order_policy=1)), (4, dict(scan_min=0, spin_init=1, spin_min=1, spin_max=1, spin_boost=1)),
+                                     (16, dict(max_channels=4)), (8, dict(fold_max_bytes=1 << 16, direct_min_bytes=0, max_channels=2)), (2, dict(sq_in_device=0))],
+                         ids=["defaults", "two_entries", "priority", "give_up_at_once", "sixteen", "several_jobs", "sq_on_host"])
+def test_buffers_change_from_call_to_call(R, knobs):
+    import torch
+    import paper_2303_06324_amd as dfx
+    from paper_2303_06324_amd import harness as gh
+    kinds = [dfx.ALLREDUCE, dfx.ALLGATHER, dfx.REDUCESCATTER, dfx.BROADCAST, dfx.REDUCE, dfx.ALLREDUCE, dfx.ALLGATHER]
+    counts = [1001, 4096, 2052, 70003, 33333, 200004, 255]                   # (the last one: a ring of odd blocks)
+    roots = [0, 0, 0, R - 1, R // 2, 0, 0]
+    g = torch.Generator(device="cuda").manual_seed(R)
+    sets, want = [], []
+    for s in range(3):
+        rows = []
+        for k, n, root in zip(kinds, counts, roots):
+            ns, nr = n * (R if k == dfx.REDUCESCATTER else 1), n * (R if k == dfx.ALLGATHER else 1)
+            send = [torch.randint(-1000, 1000, (ns,), generator=g, device="cuda", dtype=torch.int32) for _ in range(R)]
+            recv = [torch.full((nr,), -7, device="cuda", dtype=torch.int32) for _ in range(R)]
+            total = torch.stack(send).sum(0).to(torch.int32)
+            out = [torch.cat(send) if k == dfx.ALLGATHER else total[r * n:(r + 1) * n] if k == dfx.REDUCESCATTER else send[root] if k == dfx.BROADCAST
+                   else total if k == dfx.ALLREDUCE or r == root else recv[r].clone() for r in range(R)]
+            rows.append((send, recv))
+            want.append((recv, out))
+        sets.append(rows)
+    torch.cuda.synchronize()
+    ctx = dfx.Context(R, gh.make_config(**{**dict(max_channels=min(8, 256 // R)), **knobs}))
+    try:
+        for i, (k, n, root) in enumerate(zip(kinds, counts, roots)):
+            ctx.prepare(i, k, n, dfx.I32, dfx.SUM, root, priority=i % 3)
+        ptrs = [[ctx.make_all([t.data_ptr() for t in send], [t.data_ptr() for t in recv]) for send, recv in rows] for rows in sets]
+        rng = np.random.default_rng(R)
+        for it in range(60):
+            s = int(rng.integers(3))
+            ids = [int(i) for i in rng.permutation(len(kinds))[:int(rng.integers(1, 5))]]
+            for i in ids:
+                if rng.random() < 0.25:                                    # rank by rank, in another order
+                    send, recv = sets[s][i]
+                    for r in rng.permutation(R):
+                        while ctx.submit(int(r), i, send[r].data_ptr(), recv[r].data_ptr()) == dfx.ERR_SQ_FULL:
+                            pass
+                else:
+                    assert ctx.submit_all(i, ptrs[s][i]) == dfx.OK
+            assert ctx.wait_all(20.0) == dfx.OK, (it, ids)
+        for s in range(3):                                                 # every set once more, one call at a time
+            for i in range(len(kinds)):
+                for t in sets[s][i][1]:
+                    t.fill_(-7)
+        torch.cuda.synchronize()
+        for s in range(3):
+            for i in range(len(kinds)):
+                assert ctx.submit_all(i, ptrs[s][i]) == dfx.OK and ctx.wait_all(20.0) == dfx.OK
+        assert ctx.stop() == dfx.OK
+    finally:
+        assert ctx.finalize() == dfx.OK
+    for n, (recv, out) in enumerate(want):
+        for r in range(R):
+            assert torch.equal(recv[r], out[r]), (n // len(kinds), n % len(kinds), r)

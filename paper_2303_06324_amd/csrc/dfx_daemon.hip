@@ -80,6 +80,10 @@ __device__ __forceinline__ uint32_t ld_agent32(const uint32_t* p) { return __hip
 __device__ __forceinline__ u64 ld_sys64(const u64* p) { return __hip_atomic_load(global_ptr(p), __ATOMIC_RELAXED, SCOPE_SYSTEM); }
 __device__ __forceinline__ uint32_t ld_sys32(const uint32_t* p) { return __hip_atomic_load(global_ptr(p), __ATOMIC_RELAXED, SCOPE_SYSTEM); }
 
+__device__ __forceinline__ uint32_t bcast0(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+// two words that every lane holds alike -> one scalar
+__device__ __forceinline__ u64 bcast64(uint32_t lo, uint32_t hi) { return ((u64)bcast0(hi) << 32) | (u64)bcast0(lo); }
+
 // Release fences end with an explicit wait: the L2 write-back they issue must have completed
 // before the flag store that follows.  The compiler's own wait is dropped when it believes no
 // memory operation is pending (the wave's own stores were drained earlier), and the write-back
@@ -263,6 +267,7 @@ __device__ __forceinline__ void st_user(v4u_user* p, uint4 v) {
 // cache-policy operand of the buffer instructions (gfx940+): bit 0 = sc0, bit 4 = sc1
 constexpr int AUX_CACHED = 0;    // ordinary cached access (per-CU cache, write-back in this XCD's L2)
 constexpr int AUX_DEVICE = 16;   // sc1: device scope, coherent across the XCDs' L2s
+constexpr int AUX_STREAM = 18;   // sc1 | nt: the same for what is read once: the caches on the way need not keep it
 
 template <int AUX>
 struct Slot {   // one connector slot seen through a buffer resource
@@ -517,6 +522,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(u64 addr, uint32_
 __device__ __forceinline__ uint4 rs_ld16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, AUX_DEVICE));   // out of range reads return 0
 }
+__device__ __forceinline__ uint4 rs_ld16_stream(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, AUX_STREAM));
+}
 __device__ __forceinline__ void rs_st16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint4 v) {
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, (int)off, 0, AUX_DEVICE);        // out of range stores are dropped
 }
@@ -594,8 +602,10 @@ __device__ __forceinline__ void fold_fixed(const u64* src_tab, const u64* dst_ta
 // with drawn rows and 406 with dealt ones, 416 as the ring it once was.)
 struct LaneTable {
   uint32_t lo, hi;
-  __device__ __forceinline__ LaneTable(const u64* tab, uint32_t n, uint32_t lane) {
-    const u64 a = tab[lane < n ? lane : 0u];
+  __device__ __forceinline__ LaneTable(const u64* tab, uint32_t n, uint32_t lane, u64 off = 0, uint32_t first = 0) {
+    uint32_t e = lane < n ? first + lane : 0u;       // (entry k: the one `first` + k of n, all of them `off` bytes on)
+    if (e >= n) e -= n;
+    const u64 a = tab[e] + off;
     lo = (uint32_t)a; hi = (uint32_t)(a >> 32);
   }
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(uint32_t k, uint32_t bytes) const {
@@ -686,10 +696,10 @@ __device__ __forceinline__ void fold_copy(const u64* src_tab, const u64* dst_tab
 // other they took as long as a short span's rows (all-reduce of 1 MiB bf16 with an odd end 23.6 us, now 22.8).
 template <int DT>
 __device__ __forceinline__ void fold_ends(const u64* src_tab, uint32_t nsrc, const u64* dst_tab, uint32_t ndst, uint32_t at, uint32_t end,
-                                          uint32_t lane, int op) {
+                                          uint32_t lane, int op, u64 src_off = 0, u64 dst_off = 0) {
   constexpr uint32_t EB = (DT == DT_F32 || DT == DT_I32) ? 4u : 2u;
   constexpr int NS = 8;
-  const LaneTable S(src_tab, nsrc, lane), D(dst_tab, ndst, lane);
+  const LaneTable S(src_tab, nsrc, lane, src_off), D(dst_tab, ndst, lane, dst_off);
   const uint32_t o = at + lane * EB;       // (elements behind the end: loads return 0, stores are dropped)
   uint32_t v = 0;
   for (uint32_t base = 0; base < nsrc; base += NS) {
@@ -756,6 +766,174 @@ __device__ __forceinline__ void fold_dispatch(int dtype, const u64* src_tab, uin
   }
 }
 
+// ---- sweeps (sweep_region): the same movers over all regions of the message.  Their tables hold whole buffers, every rank's.
+// What bounds them is HBM: in a kernel of its own the same loop (eight sources and destinations, dealt rows) moves 256 MiB per rank in
+// 750 - 765 us, reads alone go at 6.7 - 7 TB/s, writes alone at 5.5, so 710 us is the floor of the all-reduce, which takes 746.  Deeper
+// pipelines (next row's loads ahead, 32 in flight per lane), 512 or 1024 movers and non-temporal stores measured the same.
+struct Sweep {
+  uint32_t kind, R, rank, nreg;
+  uint32_t rows, all;                      // rows of a region, of the message
+  uint32_t waves, base, skip;              // sweep_row
+  uint32_t longest;
+  u64 total;
+  uint32_t lo, hi;                         // rows of the region in hand
+  uint32_t first;                          // ... where its order of combination begins in the tables
+  FoldRegion f;
+  u64 own_src, own_dst;                    // the rank's own region
+  uint32_t ends_at, ends;                  // ... bytes before or behind its rows that this wave takes
+  __device__ __forceinline__ void enter(uint32_t t) {
+    const uint32_t c = t / rows;
+    lo = c * rows; hi = lo + rows;
+    f = sweep_region((int)kind, longest, total, c);
+    first = sweep_first(nreg, c, rank, R);
+  }
+  // Bytes at which the row in hand begins; the region's address tables are to be looked up where `moved` says so.  False: no row left.
+  __device__ __forceinline__ bool row(uint32_t n, uint32_t row_bytes, uint32_t& at, bool& moved) {
+    const uint32_t t = bcast0(sweep_row(n, waves, base, skip));
+    if (t >= all) return false;
+    moved = t >= hi;
+    if (moved) enter(t);
+    at = f.head + (t - lo) * row_bytes;
+    return true;
+  }
+};
+
+template <int DT, int NS, bool ALL>
+__device__ __forceinline__ void sweep_fixed(const u64* src_tab, const u64* dst_tab, Sweep& w, Rows& rows, uint32_t lane, int op) {
+  constexpr int U = 16 / NS, ND = ALL ? NS : 1;      // (sweep_row_bytes)
+  __amdgpu_buffer_rsrc_t S[NS], D[ND];
+  uint32_t at;
+  bool moved;
+  while (w.row(rows.row, U * 1024u, at, moved)) {
+    if (moved) {
+      const LaneTable a(src_tab, NS, lane, w.f.src, w.first), b(dst_tab, NS, lane, w.f.dst, w.first);
+#pragma unroll
+      for (int k = 0; k < NS; ++k) S[k] = a.rsrc(k, w.f.end);
+#pragma unroll
+      for (int k = 0; k < ND; ++k) D[k] = b.rsrc(ALL ? k : NS - 1, w.f.end);
+    }
+    rows.prefetch();
+    if (at < w.f.end) {      // (a short last region has rows without bytes)
+      const uint32_t o = at + lane * 16u;
+      uint4 v[NS][U];
+#pragma unroll
+      for (int k = 0; k < NS; ++k)
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[k][u] = rs_ld16_stream(S[k], o + u * 1024u);
+#pragma unroll
+      for (int k = 1; k < NS; ++k) op_batch<DT, U>(v[0], v[k], op);
+#pragma unroll
+      for (int k = 0; k < ND; ++k)
+#pragma unroll
+        for (int u = 0; u < U; ++u) rs_st16(D[k], o + u * 1024u, v[0][u]);
+    }
+    if (!rows.next()) break;
+  }
+}
+
+template <int DT>
+__device__ __forceinline__ void sweep_any(const u64* src_tab, const u64* dst_tab, bool to_all, Sweep& w, Rows& rows, uint32_t lane, int op) {
+  constexpr int U = 2, NS = 8;      // vectors per source (sweep_row_bytes) and sources in flight
+  const uint32_t R = w.R;
+  LaneTable S(src_tab, R, lane), D(dst_tab, R, lane);
+  uint32_t at;
+  bool moved;
+  while (w.row(rows.row, U * 1024u, at, moved)) {
+    if (moved) {
+      S = LaneTable(src_tab, R, lane, w.f.src, w.first);
+      D = LaneTable(dst_tab, R, lane, w.f.dst, w.first);
+    }
+    rows.prefetch();
+    if (at < w.f.end) {
+      const uint32_t o = at + lane * 16u;
+      uint4 acc[U];
+      for (uint32_t k0 = 0; k0 < R; k0 += NS) {
+        uint4 v[NS][U];
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+          if (k0 + k < R) {
+            const __amdgpu_buffer_rsrc_t r = S.rsrc(k0 + k, w.f.end);
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[k][u] = rs_ld16_stream(r, o + u * 1024u);
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+          if (k0 + k < R) {
+            if (k0 + k == 0) {
+#pragma unroll
+              for (int u = 0; u < U; ++u) acc[u] = v[0][u];
+            } else op_batch<DT, U>(acc, v[k], op);
+          }
+        }
+      }
+      for (uint32_t d = to_all ? 0u : R - 1u; d < R; ++d) {
+        const __amdgpu_buffer_rsrc_t r = D.rsrc(d, w.f.end);
+#pragma unroll
+        for (int u = 0; u < U; ++u) rs_st16(r, o + u * 1024u, acc[u]);
+      }
+    }
+    if (!rows.next()) break;
+  }
+}
+
+// Copies store half a row at a time to every destination (R = 8; sixteen stores): 2415 MB from one buffer to eight in 420 us, a row of
+// 4 KiB at a time in 457.
+template <int ND>
+__device__ __forceinline__ void sweep_copy(const u64* src_tab, const u64* dst_tab, Sweep& w, Rows& rows, uint32_t lane) {
+  constexpr int U = 16 / ND, B = 4 / U;      // (sweep_row_bytes)
+  __amdgpu_buffer_rsrc_t S, D[ND];
+  uint32_t at;
+  bool moved;
+  while (w.row(rows.row, B * U * 1024u, at, moved)) {
+    if (moved) {
+      const LaneTable a(src_tab, ND, lane, w.f.src, w.first), b(dst_tab, ND, lane, w.f.dst, w.first);
+      S = a.rsrc(ND - 1, w.f.end);
+#pragma unroll
+      for (int k = 0; k < ND; ++k) D[k] = b.rsrc(k, w.f.end);
+    }
+    rows.prefetch();
+    const uint32_t o = at + lane * 16u;
+    uint4 v[B * U];
+#pragma unroll
+    for (int u = 0; u < B * U; ++u) v[u] = rs_ld16_stream(S, o + u * 1024u);
+#pragma unroll
+    for (int h = 0; h < B * U; h += U)
+#pragma unroll
+      for (int k = 0; k < ND; ++k)
+#pragma unroll
+        for (int u = h; u < h + U; ++u) rs_st16(D[k], o + u * 1024u, v[u]);
+    if (!rows.next()) break;
+  }
+}
+
+template <int DT>
+__device__ __forceinline__ void sweep_reduce(const u64* src_tab, const u64* dst_tab, bool to_all, Sweep& w, Rows& rows, uint32_t lane, int op) {
+  if (w.R == 8 && to_all) sweep_fixed<DT, 8, true>(src_tab, dst_tab, w, rows, lane, op);
+  else if (w.R == 8) sweep_fixed<DT, 8, false>(src_tab, dst_tab, w, rows, lane, op);
+  else if (w.R == 4 && to_all) sweep_fixed<DT, 4, true>(src_tab, dst_tab, w, rows, lane, op);
+  else if (w.R == 4) sweep_fixed<DT, 4, false>(src_tab, dst_tab, w, rows, lane, op);
+  else sweep_any<DT>(src_tab, dst_tab, to_all, w, rows, lane, op);
+  if (w.ends) fold_ends<DT>(src_tab, w.R, dst_tab + (to_all ? 0u : w.R - 1u), to_all ? w.R : 1u, w.ends_at, w.ends, lane, op, w.own_src, w.own_dst);
+}
+
+__device__ __forceinline__ void sweep_dispatch(int dtype, const u64* src_tab, const u64* dst_tab, Sweep& w, Rows& rows, uint32_t lane) {
+  if (fold_copies((int)w.kind)) {      // (on four or eight ranks)
+    if (w.R == 8) sweep_copy<8>(src_tab, dst_tab, w, rows, lane);
+    else sweep_copy<4>(src_tab, dst_tab, w, rows, lane);
+    if (w.ends) fold_ends<DT_F16>(src_tab + (w.R - 1u), 1, dst_tab, w.R, w.ends_at, w.ends, lane, OP_SUM, w.own_src, w.own_dst);
+    return;
+  }
+  const int op = dtype >> 4;
+  const bool to_all = fold_to_all((int)w.kind);
+  switch (dtype & 15) {
+    case DT_F32: sweep_reduce<DT_F32>(src_tab, dst_tab, to_all, w, rows, lane, op); break;
+    case DT_BF16: sweep_reduce<DT_BF16>(src_tab, dst_tab, to_all, w, rows, lane, op); break;
+    case DT_F16: sweep_reduce<DT_F16>(src_tab, dst_tab, to_all, w, rows, lane, op); break;
+    default: sweep_reduce<DT_I32>(src_tab, dst_tab, to_all, w, rows, lane, op); break;
+  }
+}
+
 // ------------------------------------------------------------------------------------------
 // LDS state of one workgroup
 // ------------------------------------------------------------------------------------------
@@ -769,6 +947,8 @@ struct Job {                         // what the scheduler wave hands to the mov
   uint32_t limit, fresh;             // ... drawn rows per wave at most (0 = rows are dealt); first job of the share
   u64 draw;                          // ... the region's row counter (0 = rows are dealt)
 };
+constexpr uint32_t FRESH_SWEEP = 2u;   // (fresh: all ranks sweep the message together, SweepJob says more)
+struct SweepJob { uint32_t kind, R, rank, longest, at, pad; u64 total; };   // at: rows of this wave's that earlier jobs have taken, times the rank's waves (dealt)
 
 // What publishing and retiring a posted job needs.  Written by the scheduler when it posts the
 // job; read by the mover wave that finishes the job last (counter updates) and by the scheduler
@@ -788,6 +968,7 @@ struct Shared {
   uint32_t slot_claim[DFX_CTX_SLOTS];  // readiness scan: which entry of the scan gets to fill a slot (scan step << 8 | lane)
   Job job[2];                        // posted jobs, indexed by job number & 1
   Flight fl[2];
+  SweepJob sweep[2];                 // ... of a sweep
   u64 tab_src[2][64];                // fold steps: source addresses of the job, in the order of combination
   u64 tab_dst[2][64];                // ... and where the result goes
   uint4 peer[64];                    // table of buffers that came with the lone entry in hand (DfxPeer)
@@ -830,9 +1011,6 @@ __device__ __forceinline__ void st_ctx(T* p, const T& v) {
   for (int i = 0; i < (int)(sizeof(T) / 16); ++i) st_ctx((uint4*)p + i, x.w[i]);
 }
 
-__device__ __forceinline__ uint32_t bcast0(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-// two words that every lane holds alike -> one scalar
-__device__ __forceinline__ u64 bcast64(uint32_t lo, uint32_t hi) { return ((u64)bcast0(hi) << 32) | (u64)bcast0(lo); }
 
 // LDS slot of a collective's context: a multiplicative hash, because the ids that share a workgroup's
 // queue are far from random (with single-channel collectives spread over the channels they are all
@@ -954,7 +1132,36 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
         }
       } else
 #endif
-      if (j.nsrc) {
+      if (j.nsrc && __builtin_expect(bcast0(j.fresh) >= FRESH_SWEEP, 0)) {
+        const SweepJob sj = sh.sweep[seen & 1];
+        const uint32_t wave = bcast0(mtid >> 6), sharers = bcast0(j.sharers), index = bcast0(j.index);
+        const bool fresh = (bcast0(j.fresh) & 1u) != 0;
+        Sweep w;
+        w.kind = bcast0(sj.kind); w.R = bcast0(sj.R); w.rank = bcast0(sj.rank); w.longest = bcast0(sj.longest);
+        w.total = bcast64((uint32_t)sj.total, (uint32_t)(sj.total >> 32));
+        w.nreg = sweep_regions((int)w.kind, w.R);
+        const uint32_t row = sweep_row_bytes(fold_copies((int)w.kind), w.R), mine = index * DFX_FOLD_WAVES + wave;
+        w.rows = (w.longest + row - 1u) / row; w.all = w.rows * w.nreg;
+        w.waves = sharers * DFX_FOLD_WAVES; w.base = w.rank * w.waves; w.skip = w.waves * (w.R - 1u);
+        w.lo = w.hi = 0;
+        Rows rows;
+        rows.ctr = (GLOBAL_AS uint32_t*)(uint32_t*)bcast64((uint32_t)j.draw, (uint32_t)(j.draw >> 32));
+        rows.waves = w.waves;
+        rows.left = bcast0(j.limit);
+        rows.drawn = 0;
+        if (rows.ctr) rows.begin(fresh, mine);
+        else rows.row = mine + bcast0(sj.at);
+        w.ends = 0;
+        if (fresh && w.rank < w.nreg) {
+          const FoldRegion own = sweep_region((int)w.kind, w.longest, w.total, w.rank);
+          const bool front = mine + 1 == w.waves, tail = mine == 0 && own.end < own.len;
+          w.own_src = own.src; w.own_dst = own.dst;
+          w.ends_at = front ? 0u : own.end;
+          w.ends = front ? own.head : tail ? own.len : 0u;
+        }
+        sweep_dispatch((int)bcast0((uint32_t)j.dtype), sh.tab_src[seen & 1], sh.tab_dst[seen & 1], w, rows, lane);
+      }
+      else if (j.nsrc) {
         const uint32_t wave = bcast0(mtid >> 6), sharers = bcast0(j.sharers), index = bcast0(j.index), limit = bcast0(j.limit), jbytes = bcast0(j.bytes);
         const bool fresh = bcast0(j.fresh) != 0;
         Rows rows;
@@ -1137,11 +1344,20 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
     };
 
     // ---- a step with data of a collective in fold steps goes to the movers; lane k holds the buffers of entry k's rank
-    struct FoldStep { int kind, dtype; uint32_t coll, seq, nchan, vch, limit, fresh; u64 line0, counters; bool drawn; };
+    struct FoldStep { int kind, dtype; uint32_t coll, seq, nchan, vch, limit, fresh; u64 line0, counters; bool drawn, sweep; uint32_t g, longest; u64 total; };
     auto post_fold = [&](const FoldStep& st, const FoldGeom& fg, u64 sendbuf, u64 recvbuf) {
       const bool copies = fold_copies(st.kind), to_all = fold_to_all(st.kind);
       const uint32_t fs = posted & 1;
-      if (lane < R) {
+      if (__builtin_expect(st.sweep, 0)) {      // whole buffers, every rank's
+        if (lane < R) { sh.tab_src[fs][lane] = sendbuf; sh.tab_dst[fs][lane] = recvbuf; }
+        if (lane == 0) {
+          SweepJob sj;
+          sj.kind = (uint32_t)st.kind; sj.R = R; sj.rank = rank; sj.longest = st.longest; sj.pad = 0;
+          sj.at = st.g * st.limit * st.nchan * DFX_FOLD_WAVES;
+          sj.total = st.total;
+          sh.sweep[fs] = sj;
+        }
+      } else if (lane < R) {
         const u64 src = sendbuf + fg.src, dst = recvbuf + fg.dst;
         if (!copies) sh.tab_src[fs][lane] = src;
         else if (lane + 1 == R) sh.tab_src[fs][0] = src;
@@ -1348,8 +1564,10 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 const FoldGeom fg = fold_geometry(bcast64((uint32_t)q.count, (uint32_t)(q.count >> 32)), bcast64((uint32_t)q.block_elems, (uint32_t)(q.block_elems >> 32)),
                                                   bcast64((uint32_t)q.part_elems, (uint32_t)(q.part_elems >> 32)), bcast0(q.slice_elems), e_drawn, 0);
                 const u64 line0 = (u64)(uintptr_t)a.pool + bcast64((uint32_t)q.conn_off, (uint32_t)(q.conn_off >> 32)) + (u64)e_vch * DFX_FLAG_STRIDE;
+                const bool e_sweep = (e_flags & DFX_SQE_SWEEP) != 0;
                 const FoldStep st = {(int)bcast0(q.kind), (int)bcast0((uint32_t)q.dtype | ((uint32_t)q.op << 4)), peers_of - 1u, bcast0(q.seq), e_nchan, e_vch,
-                                     bcast0(q.slot_bytes), 1u, line0, fold_line(line0, 0, R, e_nchan), e_drawn};
+                                     e_sweep ? bcast0(q.slice_elems) : bcast0(q.slot_bytes), e_sweep ? FRESH_SWEEP | 1u : 1u, line0, fold_line(line0, 0, R, e_nchan), e_drawn,
+                                     e_sweep, 0, bcast0((uint32_t)q.count), bcast64((uint32_t)q.block_elems, (uint32_t)(q.block_elems >> 32))};
                 post_fold(st, fg, ((u64)peer.y << 32) | peer.x, ((u64)peer.w << 32) | peer.z);
                 const SeqPos nx = next_fold_position(e_rounds, 0, 0, 0);
                 first_round = nx.g; first_prim = nx.p;
@@ -1688,7 +1906,9 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           const uint32_t row_limit = bcast0(v0.x), vch = bcast0(v5.w) >> 16;
           const FoldGeom fg = fold_geometry(bcast64(v1.x, v1.y), bcast64(v1.z, v1.w), bcast64(v2.x, v2.y), s_slice, drawn, g);
           bytes = bcast0(v0.z);
-          const FoldStep st = {kind, dtype, coll, inv_seq, inv_nchan, vch, row_limit, !drawn || g == 0 ? 1u : 0u, s_fin, s_in, drawn};
+          const bool sweep = (bcp & DFX_CTX_SWEEP) != 0;
+          const FoldStep st = {kind, dtype, coll, inv_seq, inv_nchan, vch, sweep ? s_slice : row_limit, sweep ? FRESH_SWEEP | (g == 0) : !drawn || g == 0,
+                               s_fin, s_in, drawn, sweep, g, bcast0(v1.x), bcast64(v1.z, v1.w)};
           if (peers_of == coll + 1u) {
             // The entry came with every rank's buffers, so every rank has submitted: there is nothing to wait for.  Without the
             // others' lines (a store and its way to memory, a load or two) a 25 MiB all-reduce takes 96.5 us instead of 97.8.

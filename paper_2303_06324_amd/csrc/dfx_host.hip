@@ -536,6 +536,31 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
       runs.rounds = t.rounds;
     }
   }
+  // Sweeps (sweep_region): where a rank's workgroups are those of whole XCDs, or as many ranks share one (R = 4, 8, 16, ..), and the
+  // message outgrows the memory-side cache: from 128 MiB of inputs where ranks combine, 256 MiB of outputs where they copy (up
+  // to eight ranks).  us per call without -> with, fp32, buffers that take turns: all-reduce R = 8 of 16 MiB 69 -> 64, 64 MiB 216 -> 199,
+  // 256 MiB 789 -> 746, R = 4 32 MiB 70 -> 65, R = 16 64 MiB 432 -> 413; reduce-scatter R = 8 of 16 MiB 46 -> 40, 128 MiB 260 -> 221,
+  // R = 16 64 MiB 243 -> 222; all-gather R = 8 of 32 MiB 71 -> 69, 128 MiB 252 -> 235, R = 4 64 MiB 106 -> 91.  Below: inputs that lie in
+  // the cache are not read any faster (all-reduce of 12 MiB, the same buffers again, 45 -> 47).  Three, five or six ranks
+  // lose (reduce-scatter R = 5 of 64 MiB 104 -> 119), and so do copies of 16 ranks (16 MiB 72 -> 75).
+  // Results for all are drawn, results for one dealt, as above: reduce-scatter of 64 MiB drawn 124, dealt 111; all-reduce 199 and 230.
+  const bool copies = fold_copies((int)kind), to_all = fold_to_all((int)kind);
+  const uint64_t region = (sweep_regions((int)kind, (uint32_t)R) == 1 ? count : fold_chunk_elems((int)kind, count, t.block_elems, (uint32_t)R, eb)) * eb;
+  if ((t.flags & DFX_SQE_FOLD) && !cfg.fold_slice_bytes && cfg.wg_map == 0 && (R == 4 || R % 8 == 0) && !(copies && R > 8) &&
+      R * largest_bytes >= (copies ? 256ull << 20 : 128ull << 20) && region <= (1ull << 30)) {
+    const uint64_t row = sweep_row_bytes(copies, (uint32_t)R), waves = DFX_FOLD_WAVES * C;
+    const uint64_t equal = ceil_div(ceil_div(region, row) * sweep_regions((int)kind, (uint32_t)R), R * waves);     // rows per wave
+    const bool draw = to_all && cfg.order_policy != 1 && equal >= 4;
+    // jobs: as without a sweep (one below fold_max_bytes, else 128 KiB per source and workgroup, 32 KiB under priority ordering)
+    const uint64_t job = std::max<uint64_t>(1, (cfg.order_policy == 1 ? 32u << 10 : 128u << 10) / (DFX_FOLD_WAVES * row));
+    const uint64_t limit = (draw ? 2 : 1) * (fold ? equal : std::min(job, equal));
+    t.flags = (uint16_t)((t.flags & ~DFX_SQE_DRAWN) | DFX_SQE_SWEEP | (draw ? DFX_SQE_DRAWN : 0u));
+    t.rounds = fold ? 1u : (uint32_t)ceil_div(draw ? 9 * equal : equal, draw ? 8 * limit : limit);
+    t.slice_elems = (uint32_t)(std::min<uint64_t>(limit / (draw ? 2 : 1) * row * DFX_FOLD_WAVES, 1ull << 30) / eb);
+    t.slot_bytes = (uint32_t)limit;
+    runs.slot_bytes = (uint32_t)std::min<uint64_t>(limit * row * DFX_FOLD_WAVES, 1ull << 30);
+    runs.rounds = t.rounds;
+  }
   if (shape) *shape = runs;
   *out = t;
   return DFX_OK;
@@ -1311,6 +1336,23 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
             if (R > 64) return fail("%u table entries for 64 lanes", R);
             const uint32_t row = fold_row_bytes(copies, R), waves = t.nchan * DFX_FOLD_WAVES;
             if (fg.bytes > (1u << 30)) return fail("rank %u channel %u: a span of %u bytes", r, v, fg.bytes);
+            if (t.flags & DFX_SQE_SWEEP) {
+              // the regions that the buffers hold, and the order of the tables' entries in each; the rows themselves: below
+              for (uint32_t c = 0; c < sweep_regions(kind, R); ++c) {
+                const FoldRegion f = sweep_region(kind, S.count, S.block_elems, c);
+                if (f.len && ((f.src | f.dst) & 15u)) return fail("region %u: 16-byte accesses at offsets %llu, %llu", c, (unsigned long long)f.src, (unsigned long long)f.dst);
+                if (f.len && (f.src + f.len > send_bytes || f.dst + f.len > recv_bytes)) return fail("region %u leaves the buffers", c);
+                const uint32_t first = sweep_first(sweep_regions(kind, R), c, r, R);
+                for (uint32_t k = 0; k < R; ++k) {
+                  const uint32_t e = first + k >= R ? first + k - R : first + k, peer = fold_peer(kind, R, r, rt, e), want = fold_peer(kind, R, c, rt, k);
+                  if (peer != want) return fail("rank %u region %u: entry %u names rank %u, the order of combination rank %u", r, c, k, peer, want);
+                }
+              }
+              const SeqPos nx = next_fold_position(S.rounds, g, p, cidx);
+              g = nx.g; p = nx.p; cidx = nx.cidx;
+              if (++steps > (uint64_t)S.rounds + 8) return fail("rank %u channel %u: the fold steps do not end", r, v);
+              continue;
+            }
             // (drawn rows: any wave may take any row behind the first ones; walked here as if they were dealt, once -- that
             // every row is taken exactly once is checked below)
             const bool walk = !(t.flags & DFX_SQE_DRAWN) || g == 0;
@@ -1382,9 +1424,72 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
         if (++steps > (1ull << 26)) return fail("rank %u channel %u: the walk does not end", r, v);
       }
     }
-  // (iv) drawn rows: whatever the order in which the waves of a rank get on, every row is taken exactly once, in jobs of no
+  // (iv) sweeps: every row of every region is taken exactly once, whatever the order in which the waves of a rank get on where they
+  // are drawn, and the bytes before and behind the rows by the rank whose region it is; nothing else is written
+  if (t.flags & DFX_SQE_SWEEP) {
+    const uint32_t nreg = sweep_regions(kind, R), row = sweep_row_bytes(fold_copies(kind), R), waves = t.nchan * DFX_FOLD_WAVES;
+    const uint64_t longest = cooked[0].count, total = cooked[0].block_elems;
+    const uint32_t per = (uint32_t)ceil_div(longest, row), all = per * nreg, limit = cooked[0].slice_elems;
+    std::vector<uint8_t> taken(all, 0);
+    if (!limit) return fail("%s", "jobs without rows");
+    for (uint32_t r = 0; r < R; ++r) {
+      std::vector<uint8_t> mine(all, 0);
+      auto take = [&](uint32_t n) -> bool {      // false: behind the last row
+        const uint32_t at = sweep_row(n, waves, r * waves, waves * (R - 1));
+        if (at >= all) return false;
+        if (mine[at] < 2) ++mine[at];
+        return true;
+      };
+      if (!(t.flags & DFX_SQE_DRAWN)) {
+        for (uint32_t w = 0; w < waves; ++w)
+          for (uint32_t g = 0; g < t.rounds; ++g)
+            for (uint32_t i = 0; i < limit; ++i)
+              if (!take(w + (g * limit + i) * waves)) break;
+      } else {
+        if ((uint32_t)cooked[0].sendbuf != limit) return fail("%s", "drawn rows without their limit");
+        for (int order = 0; order < 3; ++order) {       // one wave after the other, first to last, last to first; a row at a time in turn
+          std::fill(mine.begin(), mine.end(), (uint8_t)0);
+          uint32_t ctr = 0;
+          struct Wave { uint32_t job, in_job; };
+          std::vector<Wave> w(waves, Wave{0, 0});
+          auto step = [&](uint32_t i) -> bool {
+            Wave& x = w[i];
+            if (x.job >= t.rounds) return false;
+            const bool ok = take(x.job == 0 && x.in_job == 0 ? i : waves + ctr++);
+            if (!ok || ++x.in_job == limit) { x.in_job = 0; ++x.job; }
+            return true;
+          };
+          bool any = true;
+          while (any) {
+            any = false;
+            for (uint32_t k = 0; k < waves; ++k) {
+              bool s;
+              do { s = step(order == 1 ? waves - 1 - k : k); any = any || s; } while (s && order < 2);
+            }
+          }
+          if (order < 2)
+            for (uint32_t i = 0; i < all; ++i)
+              if (mine[i] != (i / waves % R == r)) return fail("rank %u: row %u is taken %u times (order %d)", r, i, (unsigned)mine[i], order);
+        }
+      }
+      for (uint32_t i = 0; i < all; ++i) taken[i] = (uint8_t)std::min(2, taken[i] + mine[i]);
+    }
+    for (uint32_t i = 0; i < all; ++i)
+      if (taken[i] != 1) return fail("row %u of %u is taken %s", i, all, taken[i] ? "twice" : "by nobody");
+    for (uint32_t c = 0; c < nreg; ++c) {
+      const FoldRegion f = sweep_region(kind, longest, total, c);
+      for (uint32_t r = 0; r < R; ++r) {
+        if (!fold_to_all(kind) && r != (kind == KIND_RD ? (uint32_t)root : c)) continue;
+        if (f.head) written[r].push_back({f.dst, f.dst + f.head});
+        for (uint64_t at = f.head; at < f.end; at += row) written[r].push_back({f.dst + at, f.dst + std::min<uint64_t>(at + row, f.end)});
+        if (f.end < f.len) written[r].push_back({f.dst + f.end, f.dst + f.len});
+        if ((uint64_t)per * row < f.end - f.head) return fail("region %u: %u rows for %u bytes", c, per, f.end - f.head);
+      }
+    }
+  }
+  // (v) drawn rows of a region: whatever the order in which the waves of a rank get on, every row is taken exactly once, in jobs of no
   // more rows than allowed, which is at most twice a wave's equal part of the region or of a slice
-  if (t.flags & DFX_SQE_DRAWN)
+  if ((t.flags & DFX_SQE_DRAWN) && !(t.flags & DFX_SQE_SWEEP))
     for (uint32_t r = 0; r < R; ++r) {
       const DfxCooked& S = cooked[(size_t)r * t.nchan];
       const uint32_t row = fold_row_bytes(fold_copies(kind), R), waves = t.nchan * DFX_FOLD_WAVES, limit = (uint32_t)S.sendbuf;

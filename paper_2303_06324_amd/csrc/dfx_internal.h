@@ -27,6 +27,8 @@
 #define DFX_CTX_FOLD 0x40u     // the same, in the cooked context's bc_pos byte
 #define DFX_SQE_DRAWN 16u      // fold steps: the rows of a rank's region are drawn from a counter (fold_entry)
 #define DFX_CTX_DRAWN 0x20u    // the same, in the cooked context's bc_pos byte
+#define DFX_SQE_SWEEP 32u      // fold steps: all ranks sweep the message together (sweep_region)
+#define DFX_CTX_SWEEP 0x10u    // the same, in the cooked context's bc_pos byte
 #define DFX_SQE_PEERS 64u      // fold steps, submitted on every rank at once: the entry's table of buffers is filled in (DfxPeer)
 // A collective in fold steps has no slots, whatever its size.  Its connector block is R x nchan flag lines, one per (rank,
 // channel), that carry the published buffer addresses (DFX_DIRECT_OFF), and behind them nchan shared lines, one per
@@ -80,7 +82,7 @@ static_assert(sizeof(DfxDyn) == 32, "DfxDyn must be 32 bytes");
 // What a workgroup keeps of an invocation (device-private): the SQE "cooked" once at fetch time
 // into ready-to-use addresses, so that a context load needs no address arithmetic.  96 bytes.
 struct alignas(16) DfxCooked {
-  uint64_t sendbuf, recvbuf, count, block_elems, part_elems;   // fold steps: jobs' row limit, share, and the byte offsets of fold_entry
+  uint64_t sendbuf, recvbuf, count, block_elems, part_elems;   // fold steps: jobs' row limit, share, and the bytes of fold_entry
   uint64_t flags_out;    // tail counter of my send connector (head at +64 bytes)
   uint64_t flags_in;     // tail counter of my recv connector (head at +64 bytes); fold steps: the channel's shared counters
   uint64_t fifo_out;     // first slot of my send connector; fold steps: DFX_FOLD_RED at the end of this invocation

@@ -3,13 +3,14 @@ import os
 import shutil
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdfx.so")
-SOURCES = ["dfx_daemon.hip", "dfx_host.hip"]
+SOURCES = ["dfx_daemon.hip", "dfx_host.hip"]      # compiled side by side, then linked
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # never emit packed-fp32 instructions (hipcc flag; the host pass warns that it does not know it)
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-ffp-contract=off", "-Wall", "-Wno-unused-function", "-Wno-unused-command-line-argument",
@@ -57,12 +58,24 @@ def build(verbose: bool = False) -> str:
     extra = os.environ.get("DFX_EXTRA_DEFS", "").split()      # e.g. "-DDFX_UNROLL=4" for experiments
     extra = extra + ['-DDFX_BUILD_ID_STR="' + source_id() + '"']
     out = os.environ.get("DFX_BUILD_OUT", LIB)
-    cmd = [hipcc] + FLAGS + extra + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", out + ".tmp", "-lpthread"]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    noise = "is not a recognized feature for this target"
-    err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + err)
+    noise, errs = "is not a recognized feature for this target", []
+
+    def finish(cmd, proc):
+        err = "\n".join(l for l in proc.communicate()[1].splitlines() if noise not in l)
+        if proc.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + err)
+        errs.append(err)
+
+    def start(cmd):
+        return cmd, subprocess.Popen(cmd, stdout=subprocess.DEVNULL, stderr=subprocess.PIPE, text=True)
+
+    with tempfile.TemporaryDirectory() as tmp:
+        objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
+        jobs = [start([hipcc] + FLAGS + extra + ["-c", os.path.join(CSRC, s), "-o", o]) for s, o in zip(SOURCES, objs)]
+        for job in jobs:
+            finish(*job)
+        finish(*start([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", out + ".tmp", "-lpthread"]))
+    err = "\n".join(e for e in errs if e.strip())
     os.replace(out + ".tmp", out)
     if verbose and err.strip():
         print(err, file=sys.stderr)

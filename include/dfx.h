@@ -393,11 +393,12 @@ int dfx_check_geometry(int nranks, const dfx_config* cfg, dfx_kind kind, size_t 
  * with memory they allocate -- with everything the daemon kernel needs beyond the caller's buffers (SQ, CQ,
  * counters, saved contexts, connector flag lines and slots) in a static device array of the library:
  * 32.5 MiB per GPU the library runs on, held until the process ends.  The call allocates nothing (no hipMalloc,
- * hipFree, stream, event or host allocation) and only enqueues work on hip_stream (NULL = the null stream): a
- * kernel that clears the array's control part and writes the submission entries, and the daemon kernel (at most
- * nranks x min(32, 256 / nranks) workgroups, as many as the collective has channels), which leaves by itself when
- * every vrank's completion is posted and writes the outcome.  It returns when the work is enqueued; the results are in recvbufs once the
- * stream has reached the end of that work.
+ * hipFree, stream, event or host allocation) and only enqueues work on hip_stream (NULL = the null stream).  A collective in
+ * fold steps is one kernel, whose workgroups do every rank's part.  The others (one rank; an all-gather or reduce-scatter
+ * whose blocks are no 16-byte multiples; a reduce on 64 ranks) are two: one that clears the array's control part and writes
+ * the submission entries, and the daemon kernel (at most nranks x min(32, 256 / nranks) workgroups, as many as the collective
+ * has channels), which leaves by itself when every vrank's completion is posted and writes the outcome.  It returns when the
+ * work is enqueued; the results are in recvbufs once the stream has reached the end of that work.
  * nranks: 1 .. 64.  kind / count / dtype / op / root: as for dfx_prepare; same values, bit for bit, as the
  * context path.  sendbufs / recvbufs: host arrays of nranks device pointers (read during the call), the buffers
  * under the rules of dfx_submit.  status_dev: device, 4 bytes, may be NULL; written at the end: 0 = completed,

@@ -8,7 +8,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdfx.so")
-SOURCES = ["dfx_daemon.hip", "dfx_host.hip"]      # compiled side by side, then linked
+SOURCES = ["dfx_daemon.hip", "dfx_once.hip", "dfx_host.hip"]      # compiled side by side, then linked
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # never emit packed-fp32 instructions (hipcc flag; the host pass warns that it does not know it)

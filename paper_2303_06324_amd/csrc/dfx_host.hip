@@ -24,6 +24,7 @@
 // defined next to the kernels
 hipError_t dfx_daemon_occupancy(int* blocks_per_cu);
 hipError_t dfx_daemon_launch(uint32_t nwg, hipStream_t stream, const DfxDaemonArgs& a);
+hipError_t dfx_fold_once_launch(const DfxFoldOnce& a, hipStream_t stream);
 hipError_t dfx_copy_launch(const void* src, void* dst, size_t bytes, hipStream_t stream);
 
 namespace {
@@ -1576,7 +1577,7 @@ namespace {
 // Offsets inside the zeroed part of the scratch.  The connector pool comes last: its flag lines are the end of
 // the zeroed part and its slots follow them directly (a collective's connector block = flag lines, then slots).
 struct NaLayout {
-  size_t dev_ctl, host_ctl, sq, sq_freed, sq_readers, cq, cq_ctl, done_cnt, wgstate, taskq, ctxbuf, pool, end_of_zeroed;
+  size_t dev_ctl, host_ctl, once, sq, sq_freed, sq_readers, cq, cq_ctl, done_cnt, wgstate, taskq, ctxbuf, pool, end_of_zeroed;
 };
 constexpr size_t na_up(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr NaLayout na_layout() {
@@ -1584,6 +1585,7 @@ constexpr NaLayout na_layout() {
   size_t o = 0;
   L.dev_ctl = o; o = na_up(o + DC_N * 4);
   L.host_ctl = o; o = na_up(o + HC_N * 4);
+  L.once = o; o = na_up(o + 4);
   L.sq = o; o = na_up(o + (size_t)DFX_NA_MAX_RANKS * DFX_NA_SQ_DEPTH * sizeof(DfxSqSlot));
   L.sq_freed = o; o = na_up(o + (size_t)DFX_NA_MAX_RANKS * DFX_NA_SQ_DEPTH * 4);
   L.sq_readers = o; o = na_up(o + (size_t)DFX_NA_MAX_RANKS * DFX_NA_SQ_DEPTH * 4);
@@ -1610,8 +1612,7 @@ struct NaSeed {                       // what the seeding kernel writes into the
 // Prepares the scratch for one launch: clears what must start at zero -- the control structures and the collective's flag
 // lines, two ranges -- and writes the SQEs the host would have written: entry 0 of every rank's SQ, generation word included.
 // (A kernel and no memset node: the call may be captured.  One launch for both, and no other one behind the daemon,
-// which writes the outcome itself, and only the daemon's workgroups that serve a channel: an all-reduce of 64 KiB
-// takes 26.9 us, with a fill, a seed and a status kernel and 256 workgroups 32.5.)
+// which writes the outcome itself, and only the daemon's workgroups that serve a channel.)
 __global__ void __launch_bounds__(256) dfx_na_prepare_kernel(unsigned char* base, uint32_t ctl_vec, uint32_t lines_at, uint32_t lines_vec, uint32_t sq_at, NaSeed sd) {
   constexpr uint32_t kSqVec = DFX_NA_MAX_RANKS * DFX_NA_SQ_DEPTH * (uint32_t)sizeof(DfxSqSlot) / 16u;
   uint4* const p = (uint4*)base;
@@ -1716,6 +1717,31 @@ int dfx_collective_noalloc(int nranks, dfx_kind kind, size_t count, dfx_dtype dt
   tmpl.conn_off = (uint64_t)((size_t)DFX_NA_CTL_BYTES - flag_bytes - L.pool);
 
   unsigned char* base = nd->ptr;
+  // In fold steps: one plain kernel (dfx_once.hip), whose launch is all the waiting there is.  By way of the daemon (a kernel that
+  // fills its queues, the daemon) -> this, us per call, fp32, R = 8: all-reduce of 64 KiB 27.2 -> 9.5, 4 MiB 40 -> 16.5, 64 MiB 234 -> 191,
+  // reduce-scatter of 16 MiB 61.5 -> 29.8.  One rank, blocks that are no 16-byte multiples and the reduce on 64 ranks take the daemon.
+  if (tmpl.flags & DFX_SQE_FOLD) {
+    static_assert(DFX_NA_MAX_RANKS == DFX_ONCE_MAX_RANKS, "buffers of every rank");
+    const bool copies = fold_copies((int)kind);
+    const uint64_t nreg = sweep_regions((int)kind, (uint32_t)nranks), n = (uint64_t)nranks;
+    const uint64_t chunk = fold_chunk_elems((int)kind, count, tmpl.block_elems, (uint32_t)nranks, (uint32_t)eb) * eb;
+    uint64_t rows;                           // of one rank
+    if (tmpl.flags & DFX_SQE_SWEEP)
+      rows = ceil_div(ceil_div((nreg == 1 ? count * eb : chunk), sweep_row_bytes(copies, (uint32_t)nranks)) * nreg, n * DFX_ONCE_STRETCH) * DFX_ONCE_STRETCH;
+    else rows = ceil_div(chunk, fold_row_bytes(copies, (uint32_t)nranks));
+    DfxFoldOnce o;
+    memset(&o, 0, sizeof(o));
+    o.e = tmpl;
+    for (int r = 0; r < nranks; ++r) { o.sendbuf[r] = (uint64_t)(uintptr_t)sendbufs[r]; o.recvbuf[r] = (uint64_t)(uintptr_t)recvbufs[r]; }
+    o.R = (uint32_t)nranks;
+    // One row per wave, two where the results go to one rank: us per call with 1 / 2 / 4 rows, fp32, R = 8: all-reduce of 64 MiB
+    // 191 / 195 / 198, all-gather of 256 MiB 457 / 486 / 493, reduce-scatter of 64 MiB 125 / 98 / 99, 256 MiB 478 / 418 / 438.
+    o.rows_per_wave = fold_to_all((int)kind) ? 1u : 2u;
+    o.groups = (uint32_t)std::max<uint64_t>(1, ceil_div(rows, (uint64_t)o.rows_per_wave * (DFX_ONCE_THREADS / 64)));
+    o.status = status_dev;
+    o.count = (uint32_t*)(base + L.once);
+    return dfx_fold_once_launch(o, (hipStream_t)hip_stream) == hipSuccess ? DFX_OK : DFX_ERR_HIP;
+  }
   DfxDaemonArgs a;
   memset(&a, 0, sizeof(a));
   a.sq = (DfxSqSlot*)(base + L.sq); a.cq = (uint64_t*)(base + L.cq); a.cq_ctl = (uint64_t*)(base + L.cq_ctl);

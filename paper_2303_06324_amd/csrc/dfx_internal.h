@@ -172,4 +172,16 @@ struct DfxDaemonArgs {
   uint32_t* status;         // one-shot launches: outcome (0, 0x100 | error, 0x200 = a completion is missing), or null
 };
 
+// One collective in fold steps as one plain kernel (dfx_once.hip): its plan, every rank's buffers, workgroups per rank.
+#define DFX_ONCE_THREADS 256
+#define DFX_ONCE_MAX_RANKS 64
+#define DFX_ONCE_STRETCH 128u      // sweeps: rows that a rank takes in a row (sweep_row's `waves`)
+struct DfxFoldOnce {
+  DfxStatic e;
+  uint64_t sendbuf[DFX_ONCE_MAX_RANKS], recvbuf[DFX_ONCE_MAX_RANKS];
+  uint32_t R, groups, rows_per_wave;
+  uint32_t* status;         // outcome, or null
+  uint32_t* count;          // workgroups through (starts and ends at 0)
+};
+
 #endif

@@ -69,7 +69,8 @@ struct Prim {
 //                buffers it belongs to; reductions combine in the ring's (the chain's) own order -- the same
 //                association as the hops would give, hence the same bits;
 //   last wait:   no data; when every rank has done its part, every byte of the own recv buffer has arrived, nobody
-//                reads this rank's send buffer any more, and the completion may be posted.
+//                reads this rank's send buffer any more, and the completion may be posted.  One workgroup per rank, channel
+//                0's, waits for all channels; the others are through when their last job is posted.
 // What rank r reads and writes in its step with data:
 //   all-reduce:      chunk r out of all R send buffers, x[r+1] (op) ... (op) x[r]     -> chunk r of all R recv buffers
 //   reduce-scatter:  block r out of all R send buffers, in the same order             -> the own recv buffer
@@ -413,15 +414,14 @@ DFX_HD SeqPos next_position(int kind, uint32_t R, uint32_t rank, uint32_t W, uin
   return n;
 }
 
-// The walk of a collective in fold steps: the step with data (p = 0) for every slice of the share, then the
-// last wait (p = 1) once.  g >= rounds afterwards: that was it.
-DFX_HD SeqPos next_fold_position(uint32_t rounds, uint32_t g, uint32_t p, uint32_t cidx) {
+// The walk of a collective in fold steps: the step with data (p = 0) for every slice of the share, then, on channel 0, the last
+// wait (p = 1) once, which is for all channels.  g >= rounds afterwards: that was it.
+DFX_HD SeqPos next_fold_position(uint32_t rounds, uint32_t vch, uint32_t g, uint32_t p, uint32_t cidx) {
   SeqPos n;
-  n.cidx = cidx;
-  if (p == 0) {
-    if (g + 1 < rounds) { n.g = g + 1; n.p = 0; }
-    else { n.g = g; n.p = 1; }
-  } else { n.g = rounds; n.p = 0; }
+  n.cidx = cidx; n.p = 0;
+  if (p == 0 && g + 1 < rounds) n.g = g + 1;
+  else if (p == 0 && vch == 0) { n.g = g; n.p = 1; }
+  else n.g = rounds;
   return n;
 }
 

@@ -1349,8 +1349,9 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
                   if (peer != want) return fail("rank %u region %u: entry %u names rank %u, the order of combination rank %u", r, c, k, peer, want);
                 }
               }
-              const SeqPos nx = next_fold_position(S.rounds, g, p, cidx);
+              const SeqPos nx = next_fold_position(S.rounds, v, g, p, cidx);
               g = nx.g; p = nx.p; cidx = nx.cidx;
+              if (g >= S.rounds) break;
               if (++steps > (uint64_t)S.rounds + 8) return fail("rank %u channel %u: the fold steps do not end", r, v);
               continue;
             }
@@ -1379,7 +1380,7 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
             const uint32_t lastp = fold_peer(kind, R, r, rt, R - 1);
             if ((copies || !to_all) && lastp != ((kind == KIND_BC || kind == KIND_RD) ? rt : r)) return fail("rank %u channel %u: the last entry is rank %u", r, v, lastp);
           }
-          const SeqPos nx = next_fold_position(S.rounds, g, p, cidx);
+          const SeqPos nx = next_fold_position(S.rounds, v, g, p, cidx);
           g = nx.g; p = nx.p; cidx = nx.cidx;
           if (g >= S.rounds) break;
           if (++steps > (uint64_t)S.rounds + 8) return fail("rank %u channel %u: the fold steps do not end", r, v);

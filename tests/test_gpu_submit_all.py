@@ -66,3 +66,34 @@ def test_buffers_change_from_call_to_call(R, knobs):
     for n, (recv, out) in enumerate(want):
         for r in range(R):
             assert torch.equal(recv[r], out[r]), (n // len(kinds), n % len(kinds), r)
+
+
+@pytest.mark.parametrize("max_channels,count", [(63, 70000), (64, 70000), (65, 70000), (128, 150001)])
+def test_more_channels_than_a_wave_has_lanes(max_channels, count):
+    """The last wait looks at a counter per channel, a lane each, and at the SQ where a lane is left for it: below, at and beyond 64 channels."""
+    import torch
+    import paper_2303_06324_amd as dfx
+    from paper_2303_06324_amd import harness as gh
+    R = 2
+    g = torch.Generator(device="cuda").manual_seed(max_channels)
+    send = [torch.randint(-1000, 1000, (count,), generator=g, device="cuda", dtype=torch.int32) for _ in range(R)]
+    recv = [torch.full((count,), -7, device="cuda", dtype=torch.int32) for _ in range(R)]
+    torch.cuda.synchronize()
+    ctx = dfx.Context(R, gh.make_config(max_channels=max_channels, chan_min_bytes=1024))
+    try:
+        ctx.prepare(0, dfx.ALLREDUCE, count, dfx.I32)
+        assert ctx.coll_info(0)["nchan"] == max_channels
+        ptrs = ctx.make_all([t.data_ptr() for t in send], [t.data_ptr() for t in recv])
+        for it in range(30):
+            if it % 3 == 2:
+                for r in range(R):
+                    assert ctx.submit(r, 0, send[r].data_ptr(), recv[r].data_ptr()) == dfx.OK
+            else:
+                assert ctx.submit_all(0, ptrs) == dfx.OK
+            assert ctx.wait_all(20.0) == dfx.OK
+        assert ctx.stop() == dfx.OK
+    finally:
+        assert ctx.finalize() == dfx.OK
+    want = send[0] + send[1]
+    for r in range(R):
+        assert torch.equal(recv[r], want), r

@@ -23,7 +23,7 @@ R = 8
 # HBM bytes per launch at the default workload, measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE and scaled by the plain
 # copy kernel (profiles/hbm_traffic_allreduce_256MiB.md): in fold steps (the library's defaults) 2 099 210 KiB read +
 # 2 101 323 KiB written; as a ring with direct steps (fold_max_bytes = 0) 5 511 100 KiB + 3 671 500 KiB.
-MEASURED_TRAFFIC_BYTES = {"fold steps": 4301345792, "ring with direct steps": 9402982400}
+MEASURED_TRAFFIC_BYTES = {"fold steps": 4301051904, "ring with direct steps": 9402982400}
 
 
 def algorithmic_bytes(msg_bytes: int, nranks: int) -> int:

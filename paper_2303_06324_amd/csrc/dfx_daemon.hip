@@ -10,8 +10,8 @@
 // posts the CQE.  Connectors are FIFOs of K slots in HBM guarded by monotone tail/head
 // counters; a primitive touches nothing before both its conditions hold (Sec. 4.1, 4.5).
 // Every rank's buffers lie in the same HBM, so most collectives run in fold steps, which need no connectors: every rank
-// does its part straight from send buffers to recv buffers when all have submitted, and posts the completion
-// when all are through (see make_fold_prim; dfx_config.fold_max_bytes says which do).
+// does its part straight from send buffers to recv buffers when all have submitted, and its workgroup on channel 0 posts the
+// completion when all are through (see make_fold_prim; dfx_config.fold_max_bytes says which do).
 // Rings and chains, where they run, take direct steps from direct_min_bytes on: in
 // the copy steps (gather phase of an all-reduce, all-gather, broadcast) the result goes to the
 // rank's recv buffer only (through the coherent path described below), the counter is raised
@@ -675,10 +675,9 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
     auto complete = [&](uint32_t c_coll, uint32_t c_seq, uint32_t c_nchan, bool in_memory) {
       if (!in_memory) fence_release_system();   // results in the recv buffer are visible to host and later kernels
       GLOBAL_AS uint32_t* dc = global_ptr(&a.done_cnt[(size_t)rank * hot.max_colls + c_coll]);
-      // (a collective on one channel has nobody to count with: no round trip for the counter)
+      // (one channel, or channel 0 for all of them in fold steps: nobody to count with, no round trip for the counter)
       uint32_t old = 0;
-      if (c_nchan > 1) old = in_memory ? __hip_atomic_fetch_add(dc, 1u, __ATOMIC_RELAXED, SCOPE_AGENT)
-                                       : __hip_atomic_fetch_add(dc, 1u, __ATOMIC_ACQ_REL, SCOPE_AGENT);
+      if (c_nchan > 1) old = __hip_atomic_fetch_add(dc, 1u, __ATOMIC_ACQ_REL, SCOPE_AGENT);
       // (the counter runs on from invocation to invocation, modulo 2^32: no reset that the next one's counts could overtake)
       if (c_nchan == 1 || old + 1 == (c_seq + 1u) * c_nchan) {
         const u64 tq0 = wall_clock64();

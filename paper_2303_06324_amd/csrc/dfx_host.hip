@@ -485,8 +485,8 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   // Long collectives: what direct steps save of a ring's or chain's traffic, fold steps save in full (every input read
   // once, every output written once: 2R x M of an all-reduce instead of (5R-5) x M), so a collective that qualifies for
   // direct steps runs in fold steps above fold_max_bytes too, in jobs of this size.  Measured (us, R = 8, rings and
-  // chains with direct steps -> this): all-reduce 256 MiB fp32 1545 -> 806, reduce-scatter 128 MiB fp32 496 -> 268,
-  // broadcast 100 MiB bf16 472 -> 200.
+  // chains with direct steps -> this, a region per rank): all-reduce 256 MiB fp32 1545 -> 806, reduce-scatter 128 MiB fp32
+  // 496 -> 268, broadcast 100 MiB bf16 472 -> 200 (as sweeps, below: 739, 232, 187).
   // With fold_max_bytes = 0 the rings and chains run at every size.
   if ((t.flags & DFX_SQE_DIRECT) && !fold && cfg.fold_max_bytes && blocks_ok && !(kind == DFX_REDUCE && R > 63)) {
     // 128 KiB per source and workgroup (drawn rows: twice that at most), about 100 us at 2 x 8 streams; priority ordering
@@ -1567,7 +1567,6 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
 #define DFX_NA_SQ_DEPTH 2u
 #define DFX_NA_CQ_SLOTS 2u
 #define DFX_NA_MAX_RANKS 64u
-#define DFX_NA_LINES (DFX_NA_MAX_WG + 64u)      // flag lines: one per connector, and a collective in fold steps has one more per channel
 #define DFX_NA_CTL_BYTES (512u << 10)           // everything but the slots: must start at zero on every call
 #define DFX_NA_SLOTS_BYTES ((size_t)DFX_NA_MAX_WG * DFX_NA_NSLOTS * DFX_NA_SLOT_BYTES)
 #define DFX_NA_SCRATCH_BYTES ((size_t)DFX_NA_CTL_BYTES + DFX_NA_SLOTS_BYTES)
@@ -1597,7 +1596,7 @@ constexpr NaLayout na_layout() {
   L.taskq = o; o = na_up(o + (size_t)DFX_NA_MAX_WG * 2);
   L.ctxbuf = o; o = na_up(o + (size_t)DFX_NA_MAX_WG * sizeof(DfxCtxEntry));
   // the pool's flag lines end exactly where the zeroed part ends
-  L.pool = DFX_NA_CTL_BYTES - (size_t)DFX_NA_LINES * DFX_FLAG_STRIDE;
+  L.pool = DFX_NA_CTL_BYTES - (size_t)DFX_NA_MAX_WG * DFX_FLAG_STRIDE;
   L.end_of_zeroed = o;
   return L;
 }
@@ -1626,7 +1625,6 @@ __global__ void __launch_bounds__(256) dfx_na_prepare_kernel(unsigned char* base
   DfxSqSlot e = {};
   if (slot % DFX_NA_SQ_DEPTH == 0 && r < sd.nranks) {
     e.e = sd.tmpl;
-    if (e.e.flags & DFX_SQE_FOLD) fold_entry(e.e, sd.nranks, r);
     e.e.seq = 0;
     e.e.sendbuf = sd.sendbuf[r];
     e.e.recvbuf = sd.recvbuf[r];
@@ -1712,8 +1710,8 @@ int dfx_collective_noalloc(int nranks, dfx_kind kind, size_t count, dfx_dtype dt
   if (rc != DFX_OK) return rc;
   // connector block = flag lines of the collective's R x C edges, then their slots; the scratch holds
   // DFX_NA_MAX_WG flag lines and as many connectors of DFX_NA_NSLOTS x DFX_NA_SLOT_BYTES
-  const size_t flag_bytes = (size_t)(nranks + ((tmpl.flags & DFX_SQE_FOLD) ? 1 : 0)) * tmpl.nchan * DFX_FLAG_STRIDE;
-  if (flag_bytes > (size_t)DFX_NA_LINES * DFX_FLAG_STRIDE || conn_bytes > flag_bytes + DFX_NA_SLOTS_BYTES + 256) return DFX_ERR_TOO_LARGE;
+  const size_t flag_bytes = (size_t)nranks * tmpl.nchan * DFX_FLAG_STRIDE;
+  if (flag_bytes > (size_t)DFX_NA_MAX_WG * DFX_FLAG_STRIDE || conn_bytes > flag_bytes + DFX_NA_SLOTS_BYTES + 256) return DFX_ERR_TOO_LARGE;
   // the flag lines end where the zeroed part ends, the slots begin right there
   tmpl.conn_off = (uint64_t)((size_t)DFX_NA_CTL_BYTES - flag_bytes - L.pool);
 

@@ -841,12 +841,16 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             const u64 c2 = ld_agent64((const u64*)&a.dev_ctl[DC_ABORT]);   // abort | quit
             w0 = (uint32_t)c2; w1 = (uint32_t)(c2 >> 32);
           } else if (lane == 1) {
-            if (probe) w0 = ld_sys32(&sqbase[ri & (D - 1)].e.ready);
+            if (probe) {
+              const u64 sr = ld_sys64((const u64*)&sqbase[ri & (D - 1)].e.share);        // share | generation
+              w0 = (uint32_t)(sr >> 32); w1 = (uint32_t)sr;
+            }
           } else if (lane == 2) {
             if (host_look) w0 = ld_sys32(&a.host_ctl[HC_ABORT]);
           }
           const uint32_t c_abort = __builtin_amdgcn_readlane(w0, 0), c_quit = __builtin_amdgcn_readlane(w1, 0);
           const uint32_t c_ready = __builtin_amdgcn_readlane(w0, 1), c_habort = __builtin_amdgcn_readlane(w0, 2);
+          const bool with_table = (__builtin_amdgcn_readlane(w1, 1) & DFX_SHARE_PEERS) != 0;      // (of an entry that is there)
           if (c_abort || c_habort) s = STOP_ABORT;
           else if (c_quit) s = STOP_QUIT;
           if (lane == 0) {
@@ -922,9 +926,9 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
 #pragma unroll
               for (int i = 0; i < (int)(sizeof(DfxStatic) / 8); ++i) qw.w[i] = ld_sys64(src + i);
             };
-            // (the table of buffers that an entry may come with, lane k its entry k: whether there is one is known when the entry is)
+            // (the table of buffers that lane 0's entry may come with, lane k its entry k)
             uint4 peer = uint4{0, 0, 0, 0};
-            if (a.sq_peers && lane < R) {
+            if (with_table && lane < R) {
               const u64* const t = (const u64*)(known_global(a.sq_peers) + ((size_t)rank * D + (ri & (D - 1))) * R + lane);
               const u64 t0 = ld_sys64(t), t1 = ld_sys64(t + 1);
               peer = uint4{(uint32_t)t0, (uint32_t)(t0 >> 32), (uint32_t)t1, (uint32_t)(t1 >> 32)};
@@ -970,7 +974,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             peers_of = 0;
             uint32_t first_round = 0, first_prim = 0;      // where the invocation's walk goes on
             bool through = false;                          // ... nowhere: it needs no place in the queue
-            if (lone && mine_mask == 1ull && __ballot(lane == 0 && (q.flags & DFX_SQE_PEERS)) != 0) {
+            if (lone && with_table && mine_mask == 1ull) {
               peers_of = bcast0(c_id) + 1u;
               if (qlen == 0 && posted == retired) {
                 const uint32_t e_rounds = bcast0(q.rounds), e_flags = bcast0(q.flags), e_nchan = bcast0(q.nchan), e_vch = bcast0(my_vch);

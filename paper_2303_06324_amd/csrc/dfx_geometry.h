@@ -341,7 +341,7 @@ DFX_HD DfxCooked cook_sqe(const DfxStatic& q, uint8_t* pool, uint32_t rank, uint
     k.fifo_out = ((uint64_t)q.seq + 1u) * (R * q.rounds);
     // the buffers' addresses travel through the lines: the words carry the jobs' row limit and a channel's part of a slice
     k.sendbuf = q.slot_bytes;
-    k.recvbuf = q.share;
+    k.recvbuf = q.share & ~DFX_SHARE_PEERS;
   }
   k.slice_elems = q.slice_elems; k.rounds = q.rounds; k.seq = q.seq;
   k.nprim = (uint16_t)q.nprim; k.nchan = q.nchan;

@@ -765,7 +765,7 @@ namespace {
 
 // The body of one invocation's SQE, `ahead` entries behind the tail (the caller holds the rank's mutex and
 // publishes afterwards).  Counts the invocation as submitted, so that the same id again in one run is BUSY.
-int stage_one(dfx_ctx* c, int rank, uint32_t ahead, int coll_id, const void* sendbuf, void* recvbuf, uint16_t more_flags = 0) {
+int stage_one(dfx_ctx* c, int rank, uint32_t ahead, int coll_id, const void* sendbuf, void* recvbuf, uint32_t share_bits = 0) {
   if (coll_id < 0 || (uint32_t)coll_id >= c->cfg.max_colls) return DFX_ERR_INVALID_ARG;
   if (c->aborted.load()) return DFX_ERR_ABORTED;
   const CollInfo& ci = c->colls[coll_id];
@@ -780,7 +780,7 @@ int stage_one(dfx_ctx* c, int rank, uint32_t ahead, int coll_id, const void* sen
   DfxStatic e = ci.tmpl;
   if (e.flags & DFX_SQE_FOLD) {
     fold_entry(e, (uint32_t)c->R, (uint32_t)rank);
-    e.flags |= more_flags;
+    e.share |= share_bits;
   }
   e.seq = rs->sub[coll_id];
   e.sendbuf = (uint64_t)(uintptr_t)sendbuf;
@@ -848,7 +848,7 @@ int dfx_submit_all(dfx_ctx* c, int coll_id, const void* const* sendbufs, void* c
     int rc = DFX_OK, staged = 0;
     for (; staged < c->R; ++staged) {
       c->ranks[staged]->mu.lock();
-      rc = stage_one(c, staged, 0u, coll_id, sendbufs[staged], recvbufs[staged], c->sq_peers ? DFX_SQE_PEERS : 0);
+      rc = stage_one(c, staged, 0u, coll_id, sendbufs[staged], recvbufs[staged], c->sq_peers ? DFX_SHARE_PEERS : 0u);
       if (rc != DFX_OK) { c->ranks[staged]->mu.unlock(); break; }
     }
     if (rc == DFX_OK) {
@@ -1279,8 +1279,15 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
     sv = (int)wg;
     DfxStatic q = t;
     q.sendbuf = sendbase(w.rank); q.recvbuf = recvbase(w.rank);
-    if (fold) fold_entry(q, R, w.rank);
-    cooked[(size_t)w.rank * t.nchan + vch] = cook_sqe(q, (uint8_t*)(uintptr_t)pool, w.rank, R, vch);
+    if (fold) {
+      fold_entry(q, R, w.rank);
+      if (q.share & DFX_SHARE_PEERS) return fail("rank %u: a channel's part of %u bytes looks like a table of buffers", w.rank, q.share);
+    }
+    DfxStatic with_table = q;                    // (as dfx_submit_all makes it)
+    if (fold) with_table.share |= DFX_SHARE_PEERS;
+    DfxCooked& k = cooked[(size_t)w.rank * t.nchan + vch];
+    k = cook_sqe(with_table, (uint8_t*)(uintptr_t)pool, w.rank, R, vch);
+    if (fold && k.recvbuf != q.share) return fail("rank %u: a channel's part is %u bytes, %llu with a table of buffers", w.rank, q.share, (unsigned long long)k.recvbuf);
   }
   for (size_t i = 0; i < serves.size(); ++i)
     if (serves[i] < 0) return fail("rank %zu channel %zu of the collective has no workgroup", i / t.nchan, i % t.nchan);

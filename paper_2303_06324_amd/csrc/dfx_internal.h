@@ -29,7 +29,9 @@
 #define DFX_CTX_DRAWN 0x20u    // the same, in the cooked context's bc_pos byte
 #define DFX_SQE_SWEEP 32u      // fold steps: all ranks sweep the message together (sweep_region)
 #define DFX_CTX_SWEEP 0x10u    // the same, in the cooked context's bc_pos byte
-#define DFX_SQE_PEERS 64u      // fold steps, submitted on every rank at once: the entry's table of buffers is filled in (DfxPeer)
+// Fold steps, submitted on every rank at once: the entry's table of buffers is filled in (DfxPeer).  A bit of DfxStatic::share, which the
+// control check reads along with the generation word: whether there is a table to load is known before the entry is.
+#define DFX_SHARE_PEERS 0x80000000u
 // A collective in fold steps has no slots, whatever its size.  Its connector block is R x nchan flag lines, one per (rank,
 // channel), that carry the published buffer addresses (DFX_DIRECT_OFF), and behind them nchan shared lines, one per
 // channel, with two counters that every rank of the channel adds to.
@@ -61,7 +63,7 @@ struct alignas(16) DfxStatic {
   int16_t priority;
   uint32_t nprim;        // primitives per round on every rank
   uint32_t start;        // channel of the grid that serves channel 0 (start_channel)
-  uint32_t share;        // fold steps only (fold_entry, which also gives other words a meaning in bytes)
+  uint32_t share;        // fold steps only (fold_entry, which also gives other words a meaning in bytes); | DFX_SHARE_PEERS
   uint32_t ready;        // SQ only, written last: generation of the entry
 };
 static_assert(sizeof(DfxStatic) == 96, "DfxStatic must be 96 bytes");
@@ -148,7 +150,7 @@ struct DfxDaemonArgs {
   uint64_t* cq;             // [R][cq_slots]   host-visible; a slot per id (cq_mode 0: cq_slots >= max_colls) or a ring
   uint64_t* cq_ctl;         // [R][DFX_CQ_CTL_WORDS] host-visible: bookkeeping of the ring-buffer CQ variants
   uint32_t* host_ctl;       // [HC_N]          host-visible
-  const DfxPeer* sq_peers;  // [R][sq_depth][R] host-visible: the tables of DFX_SQE_PEERS entries (or null)
+  const DfxPeer* sq_peers;  // [R][sq_depth][R] host-visible: the tables of DFX_SHARE_PEERS entries (or null)
   uint32_t* sq_freed;       // [R][sq_depth]   host memory: generation of the entry last read by every workgroup
   uint32_t* sq_readers;     // [R][sq_depth]   device
   uint32_t* done_cnt;       // [R][max_colls]  device

@@ -401,11 +401,12 @@ int dfx_check_geometry(int nranks, const dfx_config* cfg, dfx_kind kind, size_t 
  * work is enqueued; the results are in recvbufs once the stream has reached the end of that work.
  * nranks: 1 .. 64.  kind / count / dtype / op / root: as for dfx_prepare; same values, bit for bit, as the
  * context path.  sendbufs / recvbufs: host arrays of nranks device pointers (read during the call), the buffers
- * under the rules of dfx_submit.  status_dev: device, 4 bytes, may be NULL; written at the end: 0 = completed,
- * 0x100 | code = the in-kernel watchdog or an internal check fired, 0x200 = a completion is missing.
+ * under the rules of dfx_submit.  status_dev: device, 4 bytes, may be NULL; written at the end (in a captured stream by a kernel
+ * node of its own, where the collective runs in fold steps): 0 = completed; by way of the daemon kernel also 0x100 | code = the
+ * in-kernel watchdog or an internal check fired, 0x200 = a completion is missing.
  * Limits: no per-rank buffer (send or recv) above DFX_NOALLOC_MAX_BYTES => DFX_ERR_TOO_LARGE.
  * Every call on a GPU uses that GPU's one array: calls that overlap on one GPU race (also from different
- * streams or threads); a call is refused with DFX_ERR_BUSY while a context's daemon is in flight on the device,
+ * streams or threads; the calls after them are not affected); a call is refused with DFX_ERR_BUSY while a context's daemon is in flight on the device,
  * and no context's daemon may be started on the device before the call's work has finished.
  * Errors: INVALID_ARG, TOO_LARGE, BUSY, NO_RESOURCES (the grid cannot be co-resident on this device), HIP.
  */

@@ -1592,7 +1592,7 @@ constexpr NaLayout na_layout() {
   size_t o = 0;
   L.dev_ctl = o; o = na_up(o + DC_N * 4);
   L.host_ctl = o; o = na_up(o + HC_N * 4);
-  L.once = o; o = na_up(o + 4);
+  L.once = o; o = na_up(o + DFX_ONCE_COUNTERS * 4);
   L.sq = o; o = na_up(o + (size_t)DFX_NA_MAX_RANKS * DFX_NA_SQ_DEPTH * sizeof(DfxSqSlot));
   L.sq_freed = o; o = na_up(o + (size_t)DFX_NA_MAX_RANKS * DFX_NA_SQ_DEPTH * 4);
   L.sq_readers = o; o = na_up(o + (size_t)DFX_NA_MAX_RANKS * DFX_NA_SQ_DEPTH * 4);
@@ -1644,6 +1644,7 @@ struct NaDevice {
   unsigned char* ptr = nullptr;      // this device's copy of `scratch` (hipGetSymbolAddress), never the array's name
   double tick_us = 0.01;
   int max_wg = 0;                    // workgroups that can be resident at once
+  std::atomic<uint32_t> calls{0};    // calls in fold steps that reported an outcome through a counter
 };
 std::mutex g_na_mu;
 NaDevice g_na_dev[kMaxDevices];
@@ -1745,7 +1746,15 @@ int dfx_collective_noalloc(int nranks, dfx_kind kind, size_t count, dfx_dtype dt
     o.rows_per_wave = fold_to_all((int)kind) ? 1u : 2u;
     o.groups = (uint32_t)std::max<uint64_t>(1, ceil_div(rows, (uint64_t)o.rows_per_wave * (DFX_ONCE_THREADS / 64)));
     o.status = status_dev;
-    o.count = (uint32_t*)(base + L.once);
+    if (status_dev) {
+      hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing((hipStream_t)hip_stream, &cap) != hipSuccess) (void)hipGetLastError();      // (the launch will say so)
+      if (cap == hipStreamCaptureStatusNone) {
+        const uint32_t call = nd->calls.fetch_add(1, std::memory_order_relaxed);
+        o.count = (uint32_t*)(base + L.once) + call % DFX_ONCE_COUNTERS;
+        o.clear = (uint32_t*)(base + L.once) + (call + DFX_ONCE_COUNTERS / 2) % DFX_ONCE_COUNTERS;
+      }
+    }
     return dfx_fold_once_launch(o, (hipStream_t)hip_stream) == hipSuccess ? DFX_OK : DFX_ERR_HIP;
   }
   DfxDaemonArgs a;

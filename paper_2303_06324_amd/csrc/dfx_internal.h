@@ -183,7 +183,13 @@ struct DfxFoldOnce {
   uint64_t sendbuf[DFX_ONCE_MAX_RANKS], recvbuf[DFX_ONCE_MAX_RANKS];
   uint32_t R, groups, rows_per_wave;
   uint32_t* status;         // outcome, or null
-  uint32_t* count;          // workgroups through (starts and ends at 0)
+  uint32_t* count;          // workgroups through: this call's word of DFX_ONCE_COUNTERS (null: the outcome comes from a kernel behind this one)
+  uint32_t* clear;          // ... and the word of the call that comes half of them later
 };
+// Every call that reports an outcome counts in a word of its own, in turn: its last workgroup puts the word back to 0, and all the
+// same a call clears the word half a round ahead.  With one word for all and nobody to clear it, two calls that overlapped once (which is the caller's mistake) left a residue in it, and every later call reported too early or never.
+// A captured call is replayed with the same word, whenever: it has a kernel behind it instead.  (Which costs 3 us: 15.4 -> 18.6 us
+// per call of 64 KiB, R = 8, was every call to have one.)
+#define DFX_ONCE_COUNTERS 1024u
 
 #endif

@@ -61,16 +61,22 @@ extern "C" __global__ void __launch_bounds__(DFX_ONCE_THREADS, 2) dfx_fold_once_
     sp.ends = last ? sp.head : first && (fg.bytes & 15u) ? fg.bytes : 0u;
     fold_dispatch(dtype, tab_src, copies ? 1u : R, tab_dst, to_all ? R : 1u, sp, rows, lane);
   }
-  // the outcome, behind everybody's stores: the last workgroup writes it (the counter wraps: it is 0 again for the next call)
-  if (a.status) {
+  // the outcome, behind everybody's stores: the last workgroup writes it
+  if (a.count) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(global_ptr(a.clear), 0u, __ATOMIC_RELAXED, SCOPE_AGENT);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (threadIdx.x == 0 && atomicInc(a.count, gridDim.x - 1u) + 1u == gridDim.x)
+    if (threadIdx.x == 0 && atomicAdd(a.count, 1u) + 1u == gridDim.x) {
+      __hip_atomic_store(global_ptr(a.count), 0u, __ATOMIC_RELAXED, SCOPE_AGENT);
       __hip_atomic_store(global_ptr(a.status), 0u, __ATOMIC_RELAXED, SCOPE_AGENT);
+    }
   }
 }
 
+__global__ void dfx_once_outcome_kernel(uint32_t* status) { *status = 0u; }
+
 hipError_t dfx_fold_once_launch(const DfxFoldOnce& a, hipStream_t stream) {
   hipLaunchKernelGGL(dfx_fold_once_kernel, dim3(a.R * a.groups), dim3(DFX_ONCE_THREADS), 0, stream, a);
+  if (a.status && !a.count) hipLaunchKernelGGL(dfx_once_outcome_kernel, dim3(1), dim3(1), 0, stream, a.status);
   return hipGetLastError();
 }

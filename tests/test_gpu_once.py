@@ -77,7 +77,7 @@ def test_messages_that_are_swept(kind, R):
 
 
 def test_captured_and_replayed():
-    """One kernel node; the outcome's counter is back at its start after every replay."""
+    """Two kernel nodes, the collective's and the outcome's: every replay reports one."""
     import torch
     from paper_2303_06324_amd import harness as gh
     R, n = 8, 40008
@@ -106,4 +106,32 @@ def test_captured_and_replayed():
             assert torch.equal(got[:n], want.cpu()[:n]), (it, r)
     for r in range(R):
         dw.send[0][r].copy_(send[r])
+    dw.check_untouched()
+
+
+def test_calls_that_overlapped_leave_the_next_ones_their_outcome():
+    """Calls of different sizes on two streams at once (buffers and status words of their own), then one at a time, more of them than
+    there are counters: every one of these reports its outcome and nobody else's."""
+    import torch
+    from paper_2303_06324_amd import harness as gh
+    R = 8
+    counts = [2051, MIB + 9, 300007, 4 * MIB + 3]
+    w = wi.Workload("once_overlap", R, [wi.CollSpec(i, wi.AR, wi.I32, c) for i, c in enumerate(counts)], [list(range(4))] * R, seed=7, cfg=102)
+    dw = gh.DeviceWorkload(w)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    status = torch.full((4,), -1, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    for it in range(60):
+        for k, st in enumerate(streams):                     # stream 0: the first and third, stream 1: the others
+            ci = k + 2 * (it % 2)
+            _call(dw, w, ci, status[ci:], st.cuda_stream)
+    torch.cuda.synchronize()
+    dw.reset_recv()
+    for it in range(1100):
+        ci = it // 50 % 2 if it % 50 == 49 else 2 * (it % 2)
+        status.fill_(-1)
+        _call(dw, w, ci, status[ci:])
+        assert status.tolist() == [0 if i == ci else -1 for i in range(4)], (it, ci)
+    for ci in range(3):
+        _check(w, dw, ci)
     dw.check_untouched()

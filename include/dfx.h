@@ -388,6 +388,17 @@ int dfx_check_geometry(int nranks, const dfx_config* cfg, dfx_kind kind, size_t 
                        int root, int coll_id, uint32_t wg_map, char* msg, size_t msg_bytes);
 
 /*
+ * How a collective would run, by the arguments of dfx_prepare and a configuration (NULL = defaults), on the host, without a GPU: a sum
+ * of DFX_ROUTE_*, or a negative status.  For tests and the bench.
+ */
+#define DFX_ROUTE_DIRECT 1          /* takes direct steps, or (with FOLD) fold steps */
+#define DFX_ROUTE_FOLD 2            /* fold steps (dfx_config.fold_max_bytes) */
+#define DFX_ROUTE_DRAWN 4           /* ... whose rows are drawn from a counter */
+#define DFX_ROUTE_SWEEP 8           /* ... all ranks sweep the message together */
+#define DFX_ROUTE_SWEEP_NOALLOC 16  /* ... in dfx_collective_noalloc too */
+int dfx_plan_route(int nranks, const dfx_config* cfg, dfx_kind kind, size_t count, dfx_dtype dtype, int root);
+
+/*
  * For callers that cannot allocate: code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  One invocation of one collective on every vrank -- what dfx_init + dfx_prepare + dfx_submit_all do
  * with memory they allocate -- with everything the daemon kernel needs beyond the caller's buffers (SQ, CQ,

@@ -96,6 +96,7 @@ def _load() -> C.CDLL:
         "dfx_build_id": ([], C.c_char_p),
         "dfx_copy_calibrate": ([vp, vp, sz, vp, C.POINTER(C.c_float)], i),
         "dfx_check_geometry": ([i, C.POINTER(Config), i, sz, i, i, i, i, C.c_uint32, C.c_char_p, sz], i),
+        "dfx_plan_route": ([i, C.POINTER(Config), i, sz, i, i], i),
         "dfx_collective_noalloc": ([i, i, sz, i, i, i, C.POINTER(vp), C.POINTER(vp), vp, vp], i),
     }
     for name, (args, res) in sig.items():
@@ -279,3 +280,14 @@ def check_geometry(nranks: int, kind: int, count: int, dtype: int, op: int = SUM
     rc = _lib.dfx_check_geometry(nranks, C.byref(cfg) if cfg is not None else None, kind, count, dtype, op, root,
                                  coll_id, wg_map, buf, 512)
     return "" if rc == OK else (buf.value.decode() or strerror(rc))
+
+
+ROUTES = ("direct", "fold", "drawn", "sweep", "sweep_noalloc")
+
+
+def plan_route(nranks: int, kind: int, count: int, dtype: int, root: int = 0, cfg: Optional[Config] = None) -> set:
+    """How a collective would run: a subset of ROUTES (no GPU needed)."""
+    rc = _lib.dfx_plan_route(nranks, C.byref(cfg) if cfg is not None else None, kind, count, dtype, root)
+    if rc < 0:
+        raise DfxError(rc, "dfx_plan_route")
+    return {name for bit, name in enumerate(ROUTES) if rc >> bit & 1}

@@ -156,6 +156,17 @@ DFX_HD uint32_t sweep_first(uint32_t nreg, uint32_t c, uint32_t rank, uint32_t R
 // The n-th row of a rank, counted over all regions (base: rank x W; skip: W x (R - 1)).
 DFX_HD uint32_t sweep_row(uint32_t n, uint32_t waves, uint32_t base, uint32_t skip) { return base + n + n / waves * skip; }
 
+// As a plain kernel (DfxFoldOnce) a rank has `groups` workgroups, and a workgroup's rows lie together: its waves take them in turn.
+constexpr uint32_t DFX_ONCE_WAVES = DFX_ONCE_THREADS / 64;
+struct OnceWave { uint32_t row; bool head, tail; };   // first row (the next ones DFX_ONCE_WAVES apart); takes the bytes before or behind the region's rows
+DFX_HD OnceWave once_wave(uint32_t group, uint32_t groups, uint32_t rows_per_wave, uint32_t wave) {
+  OnceWave w;
+  w.row = group * rows_per_wave * DFX_ONCE_WAVES + wave;
+  w.head = group + 1 == groups && wave + 1 == DFX_ONCE_WAVES;
+  w.tail = group == 0 && wave == 0;
+  return w;
+}
+
 // The entry (SQE) of a collective in fold steps for one rank, from its plan in elements: everything about the rank's
 // part that does not depend on the channel, in bytes, so that the workgroups that read the entry multiply nothing.
 //   count       length of the rank's region

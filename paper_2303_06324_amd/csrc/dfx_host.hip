@@ -537,18 +537,22 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
       runs.rounds = t.rounds;
     }
   }
-  // Sweeps (sweep_region): where a rank's workgroups are those of whole XCDs, or as many ranks share one (R = 4, 8, 16, ..), and the
-  // message outgrows the memory-side cache: from 128 MiB of inputs where ranks combine, 256 MiB of outputs where they copy (up
-  // to eight ranks).  us per call without -> with, fp32, buffers that take turns: all-reduce R = 8 of 16 MiB 69 -> 64, 64 MiB 216 -> 199,
-  // 256 MiB 789 -> 746, R = 4 32 MiB 70 -> 65, R = 16 64 MiB 432 -> 413; reduce-scatter R = 8 of 16 MiB 46 -> 40, 128 MiB 260 -> 221,
-  // R = 16 64 MiB 243 -> 222; all-gather R = 8 of 32 MiB 71 -> 69, 128 MiB 252 -> 235, R = 4 64 MiB 106 -> 91.  Below: inputs that lie in
-  // the cache are not read any faster (all-reduce of 12 MiB, the same buffers again, 45 -> 47).  Three, five or six ranks
-  // lose (reduce-scatter R = 5 of 64 MiB 104 -> 119), and so do copies of 16 ranks (16 MiB 72 -> 75).
+  // Sweeps (sweep_region): where the ranks are as many as share the XCDs evenly (R = 4, 8, 16, 32, 64), and the message outgrows the
+  // memory-side cache: from 128 MiB of inputs where ranks combine, 256 MiB of outputs where they copy (up to eight ranks).  us per
+  // call without -> with, fp32, buffers that take turns: all-reduce R = 8 of 16 MiB 69 -> 64, 64 MiB 216 -> 199, 256 MiB 789 -> 746,
+  // R = 4 32 MiB 70 -> 65, R = 16 64 MiB 432 -> 413, R = 32 4 MiB 70 -> 68, 48 MiB 673 -> 630; reduce-scatter R = 8 of 16 MiB 46 -> 40,
+  // 128 MiB 260 -> 221, R = 16 64 MiB 243 -> 222, R = 32 4 MiB 42 -> 41, 48 MiB 350 -> 316; all-gather R = 8 of 32 MiB 71 -> 69, 128 MiB
+  // 252 -> 235, R = 4 64 MiB 106 -> 91.  Below: inputs that lie in the cache are not read any faster (all-reduce of 12 MiB, the same
+  // buffers again, 45 -> 47).  Three, five or six ranks lose (reduce-scatter R = 5 of 64 MiB 104 -> 119), so do copies of 16 ranks
+  // (16 MiB 72 -> 75), and 24, 40, 48 and 56 ranks lose as often as they gain (all-reduce R = 24 of 8 MiB 98 -> 102, 32 MiB 332 -> 323;
+  // reduce-scatter R = 56 of 3 MiB 61 -> 66, R = 40 of 12 MiB 126 -> 121).
+  // On 64 ranks a region may be short, and then a stretch reaches over several of them: all-reduce of 2 MiB 90 -> 95, 2.6 MiB 117 -> 114,
+  // 5 MiB 194 -> 181; reduce-scatter of 3 MiB 68 -> 72, 4.1 MiB 87 -> 91, 8 MiB 131 -> 119.
   // Results for all are drawn, results for one dealt, as above: reduce-scatter of 64 MiB drawn 124, dealt 111; all-reduce 199 and 230.
   const bool copies = fold_copies((int)kind), to_all = fold_to_all((int)kind);
   const uint64_t region = (sweep_regions((int)kind, (uint32_t)R) == 1 ? count : fold_chunk_elems((int)kind, count, t.block_elems, (uint32_t)R, eb)) * eb;
-  if ((t.flags & DFX_SQE_FOLD) && !cfg.fold_slice_bytes && cfg.wg_map == 0 && (R == 4 || R % 8 == 0) && !(copies && R > 8) &&
-      R * largest_bytes >= (copies ? 256ull << 20 : 128ull << 20) && region <= (1ull << 30)) {
+  if ((t.flags & DFX_SQE_FOLD) && !cfg.fold_slice_bytes && cfg.wg_map == 0 && R >= 4 && is_pow2((uint32_t)R) && !(copies && R > 8) &&
+      region >= (to_all ? 40u << 10 : 128u << 10) && R * largest_bytes >= (copies ? 256ull << 20 : 128ull << 20) && region <= (1ull << 30)) {
     const uint64_t row = sweep_row_bytes(copies, (uint32_t)R), waves = DFX_FOLD_WAVES * C;
     const uint64_t equal = ceil_div(ceil_div(region, row) * sweep_regions((int)kind, (uint32_t)R), R * waves);     // rows per wave
     const bool draw = to_all && cfg.order_policy != 1 && equal >= 4;
@@ -565,6 +569,30 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   if (shape) *shape = runs;
   *out = t;
   return DFX_OK;
+}
+
+// The same collective in fold steps as one plain kernel (dfx_once.hip): workgroups per rank, rows per wave, and whether it is swept.
+struct OnceShape { uint16_t flags; uint32_t groups, rows_per_wave; };
+OnceShape once_shape(const DfxStatic& t, uint32_t R) {
+  const int kind = t.kind;
+  const uint32_t eb = elem_bytes(t.dtype);
+  const bool copies = fold_copies(kind);
+  OnceShape o;
+  o.flags = t.flags;
+  // More than 16 ranks sweep from 16 MiB per rank on: the stretches of the plain kernel are the same for all, and regions shorter than a
+  // few of them come apart (us per call, fp32, without -> with: R = 32 all-reduce of 4 MiB 56 -> 65, 9.2 MiB 130 -> 144, 16 MiB 217 -> 200,
+  // reduce-scatter of 9.2 MiB 69 -> 72, 16 MiB 109 -> 100; R = 64 reduce-scatter of 4.2 MiB 59 -> 85, all-reduce of 8.8 MiB 258 -> 270, 16 MiB 444 -> 410).
+  if (R > 16 && t.count * eb * (kind == KIND_RS ? R : 1u) < (16u << 20)) o.flags &= (uint16_t)~DFX_SQE_SWEEP;
+  const uint64_t nreg = sweep_regions(kind, R), chunk = fold_chunk_elems(kind, t.count, t.block_elems, R, eb) * eb;
+  uint64_t rows;                           // of one rank
+  if (o.flags & DFX_SQE_SWEEP)
+    rows = ceil_div(ceil_div(nreg == 1 ? t.count * eb : chunk, sweep_row_bytes(copies, R)) * nreg, (uint64_t)R * DFX_ONCE_STRETCH) * DFX_ONCE_STRETCH;
+  else rows = ceil_div(chunk, fold_row_bytes(copies, R));
+  // One row per wave, two where the results go to one rank: us per call with 1 / 2 / 4 rows, fp32, R = 8: all-reduce of 64 MiB
+  // 191 / 195 / 198, all-gather of 256 MiB 457 / 486 / 493, reduce-scatter of 64 MiB 125 / 98 / 99, 256 MiB 478 / 418 / 438.
+  o.rows_per_wave = fold_to_all(kind) ? 1u : 2u;
+  o.groups = (uint32_t)std::max<uint64_t>(1, ceil_div(rows, (uint64_t)o.rows_per_wave * DFX_ONCE_WAVES));
+  return o;
 }
 
 inline void backoff(uint32_t& spins) {
@@ -1225,6 +1253,19 @@ const char* dfx_strerror(int s) {
   }
 }
 
+int dfx_plan_route(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t count, dfx_dtype dtype, int root) {
+  dfx_config cfg;
+  dfx_config_default(&cfg);
+  if (ucfg) { if (ucfg->struct_bytes != sizeof(dfx_config)) return DFX_ERR_INVALID_ARG; cfg = *ucfg; }
+  if (nranks < 1 || nranks > 64 || cfg.max_channels < 1 || cfg.chan_min_bytes < 16 || cfg.slot_bytes < 16) return DFX_ERR_INVALID_ARG;
+  DfxStatic t;
+  uint64_t conn_bytes = 0;
+  const int rc = plan_collective(cfg, nranks, 0, kind, count, dtype, DFX_SUM, root, 0, 0, &t, &conn_bytes);
+  if (rc != DFX_OK) return rc;
+  return ((t.flags & DFX_SQE_DIRECT) ? DFX_ROUTE_DIRECT : 0) | ((t.flags & DFX_SQE_FOLD) ? DFX_ROUTE_FOLD : 0) | ((t.flags & DFX_SQE_DRAWN) ? DFX_ROUTE_DRAWN : 0) |
+         ((t.flags & DFX_SQE_SWEEP) ? DFX_ROUTE_SWEEP : 0) | ((t.flags & DFX_SQE_FOLD) && (once_shape(t, (uint32_t)nranks).flags & DFX_SQE_SWEEP) ? DFX_ROUTE_SWEEP_NOALLOC : 0);
+}
+
 // ------------------------------------------------------------------------------------------
 // Geometry self-check: the kernel's index arithmetic walked on the host, without a GPU
 // ------------------------------------------------------------------------------------------
@@ -1496,6 +1537,37 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
       }
     }
   }
+  // (vi) as a plain kernel: every row of every region by one wave, the bytes before and behind a region's rows by one each, not the same
+  if (fold && std::max(send_bytes, recv_bytes) <= DFX_NOALLOC_MAX_BYTES) {
+    const OnceShape o = once_shape(t, R);
+    const bool copies = fold_copies(kind), sweep = (o.flags & DFX_SQE_SWEEP) != 0;
+    std::vector<uint8_t> taken;
+    for (uint32_t r = 0; r < R; ++r) {
+      DfxStatic q = t;
+      q.flags = o.flags;
+      fold_entry(q, R, r);
+      const FoldGeom fg = fold_geometry(q.count, q.block_elems, q.part_elems, 1u << 30, true, 0);
+      const uint32_t head = fold_head(fg.dst, fg.bytes, q.nchan), row = sweep ? sweep_row_bytes(copies, R) : fold_row_bytes(copies, R);
+      const uint32_t all = sweep ? (uint32_t)ceil_div(q.count, row) * sweep_regions(kind, R) : (uint32_t)ceil_div((fg.bytes - head) & ~15u, row);
+      if (!sweep && fg.bytes != q.count) return fail("plain kernel, rank %u: %u of %llu bytes", r, fg.bytes, (unsigned long long)q.count);
+      if (!sweep || r == 0) taken.assign(all, 0);
+      uint32_t heads = 0, tails = 0;
+      for (uint32_t gr = 0; gr < o.groups; ++gr)
+        for (uint32_t wv = 0; wv < DFX_ONCE_WAVES; ++wv) {
+          const OnceWave w = once_wave(gr, o.groups, o.rows_per_wave, wv);
+          if (w.head && w.tail) return fail("%s", "plain kernel: one wave for the bytes before and behind the rows");
+          heads += w.head; tails += w.tail;
+          for (uint32_t i = 0; i < o.rows_per_wave; ++i) {
+            const uint32_t n = w.row + i * DFX_ONCE_WAVES, at = sweep ? sweep_row(n, DFX_ONCE_STRETCH, r * DFX_ONCE_STRETCH, DFX_ONCE_STRETCH * (R - 1u)) : n;
+            if (at < all && taken[at] < 2) ++taken[at];
+          }
+        }
+      if (heads != 1 || tails != 1) return fail("plain kernel, rank %u: %u and %u waves for the bytes before and behind the rows", r, heads, tails);
+      if (!sweep || r + 1 == R)
+        for (uint32_t i = 0; i < all; ++i)
+          if (taken[i] != 1) return fail("plain kernel, rank %u: row %u of %u is taken %s", r, i, all, taken[i] ? "twice" : "by nobody");
+    }
+  }
   // (v) drawn rows of a region: whatever the order in which the waves of a rank get on, every row is taken exactly once, in jobs of no
   // more rows than allowed, which is at most twice a wave's equal part of the region or of a slice
   if ((t.flags & DFX_SQE_DRAWN) && !(t.flags & DFX_SQE_SWEEP))
@@ -1729,22 +1801,15 @@ int dfx_collective_noalloc(int nranks, dfx_kind kind, size_t count, dfx_dtype dt
   // reduce-scatter of 16 MiB 61.5 -> 29.8.  One rank, blocks that are no 16-byte multiples and the reduce on 64 ranks take the daemon.
   if (tmpl.flags & DFX_SQE_FOLD) {
     static_assert(DFX_NA_MAX_RANKS == DFX_ONCE_MAX_RANKS, "buffers of every rank");
-    const bool copies = fold_copies((int)kind);
-    const uint64_t nreg = sweep_regions((int)kind, (uint32_t)nranks), n = (uint64_t)nranks;
-    const uint64_t chunk = fold_chunk_elems((int)kind, count, tmpl.block_elems, (uint32_t)nranks, (uint32_t)eb) * eb;
-    uint64_t rows;                           // of one rank
-    if (tmpl.flags & DFX_SQE_SWEEP)
-      rows = ceil_div(ceil_div((nreg == 1 ? count * eb : chunk), sweep_row_bytes(copies, (uint32_t)nranks)) * nreg, n * DFX_ONCE_STRETCH) * DFX_ONCE_STRETCH;
-    else rows = ceil_div(chunk, fold_row_bytes(copies, (uint32_t)nranks));
     DfxFoldOnce o;
     memset(&o, 0, sizeof(o));
+    const OnceShape shape = once_shape(tmpl, (uint32_t)nranks);
     o.e = tmpl;
+    o.e.flags = shape.flags;
     for (int r = 0; r < nranks; ++r) { o.sendbuf[r] = (uint64_t)(uintptr_t)sendbufs[r]; o.recvbuf[r] = (uint64_t)(uintptr_t)recvbufs[r]; }
     o.R = (uint32_t)nranks;
-    // One row per wave, two where the results go to one rank: us per call with 1 / 2 / 4 rows, fp32, R = 8: all-reduce of 64 MiB
-    // 191 / 195 / 198, all-gather of 256 MiB 457 / 486 / 493, reduce-scatter of 64 MiB 125 / 98 / 99, 256 MiB 478 / 418 / 438.
-    o.rows_per_wave = fold_to_all((int)kind) ? 1u : 2u;
-    o.groups = (uint32_t)std::max<uint64_t>(1, ceil_div(rows, (uint64_t)o.rows_per_wave * (DFX_ONCE_THREADS / 64)));
+    o.rows_per_wave = shape.rows_per_wave;
+    o.groups = shape.groups;
     o.status = status_dev;
     if (status_dev) {
       hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;

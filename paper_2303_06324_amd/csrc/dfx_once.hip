@@ -31,12 +31,10 @@ extern "C" __global__ void __launch_bounds__(DFX_ONCE_THREADS, 2) dfx_fold_once_
   }
   __syncthreads();
 
-  constexpr uint32_t WAVES = DFX_ONCE_THREADS / 64;
-  const uint32_t mine = group * a.rows_per_wave * WAVES + wave;      // (a workgroup's rows lie together)
-  const bool first = group == 0 && wave == 0, last = group + 1 == a.groups && wave + 1 == WAVES;
+  const OnceWave ow = once_wave(group, a.groups, a.rows_per_wave, wave);
   Rows rows;
   rows.ctr = nullptr; rows.drawn = 0;
-  rows.waves = WAVES; rows.left = a.rows_per_wave; rows.row = mine;
+  rows.waves = DFX_ONCE_WAVES; rows.left = a.rows_per_wave; rows.row = ow.row;
   if (sweep) {
     Sweep w;
     w.kind = (uint32_t)kind; w.R = R; w.rank = rank; w.longest = (uint32_t)e.count; w.total = e.block_elems;
@@ -49,16 +47,16 @@ extern "C" __global__ void __launch_bounds__(DFX_ONCE_THREADS, 2) dfx_fold_once_
     if (rank < w.nreg) {
       const FoldRegion own = sweep_region(kind, w.longest, w.total, rank);
       w.own_src = own.src; w.own_dst = own.dst;
-      w.ends_at = last ? 0u : own.end;
-      w.ends = last ? own.head : first && own.end < own.len ? own.len : 0u;
+      w.ends_at = ow.head ? 0u : own.end;
+      w.ends = ow.head ? own.head : ow.tail && own.end < own.len ? own.len : 0u;
     }
     sweep_dispatch(dtype, tab_src, tab_dst, w, rows, lane);
   } else {
     Span sp;
     sp.head = fold_head(fg.dst, fg.bytes, e.nchan);
     sp.end = sp.head + ((fg.bytes - sp.head) & ~15u);
-    sp.ends_at = last ? 0u : sp.end;
-    sp.ends = last ? sp.head : first && (fg.bytes & 15u) ? fg.bytes : 0u;
+    sp.ends_at = ow.head ? 0u : sp.end;
+    sp.ends = ow.head ? sp.head : ow.tail && (fg.bytes & 15u) ? fg.bytes : 0u;
     fold_dispatch(dtype, tab_src, copies ? 1u : R, tab_dst, to_all ? R : 1u, sp, rows, lane);
   }
   // the outcome, behind everybody's stores: the last workgroup writes it

@@ -82,6 +82,29 @@ def test_drawn_rows_are_taken_once_in_bounded_jobs(kind, R):
         assert msg == "", (kind, R, mib, msg)
 
 
+SWEEP_LEAST = {dfx.ALLREDUCE: 128 << 20, dfx.REDUCESCATTER: 128 << 20, dfx.REDUCE: 128 << 20, dfx.ALLGATHER: 256 << 20, dfx.BROADCAST: 256 << 20}   # all ranks' inputs (outputs)
+
+
+@pytest.mark.parametrize("R", [2, 3, 4, 5, 6, 8, 12, 16, 24, 32, 40, 48, 56, 63, 64])
+@pytest.mark.parametrize("kind", KINDS)
+def test_which_messages_are_swept(kind, R):
+    """Both sides of every line of the rule: powers of two from four ranks on (copies: up to eight), from so many bytes in all on, with
+    regions of 40 KiB (results for one rank: 128 KiB) at least; in the allocation-free call on more than 16 ranks from 16 MiB per rank on."""
+    blocks, one = kind in (dfx.ALLGATHER, dfx.REDUCESCATTER), kind in (dfx.REDUCESCATTER, dfx.REDUCE)
+    cfg = _cfg(max_channels=min(32, 256 // R))
+    ranks_ok = R in ((4, 8) if kind in (dfx.ALLGATHER, dfx.BROADCAST) else (4, 8, 16, 32, 64)) and not (kind == dfx.REDUCE and R > 63)
+    for total in (SWEEP_LEAST[kind] * 3 // 4, SWEEP_LEAST[kind], 3 << 27, 1 << 30, 3 << 30):
+        n = -(-total // R // 4 // (R if blocks else 1) // 4) * 4              # elements, at least `total` bytes over all ranks
+        nbytes = n * 4 * (R if blocks else 1)
+        region = n * 4 if blocks or kind in (dfx.REDUCE, dfx.BROADCAST) else -(-n // R // 4) * 16
+        want = ranks_ok and R * nbytes >= SWEEP_LEAST[kind] and region >= ((128 if one else 40) << 10)
+        route = dfx.plan_route(R, kind, n, dfx.F32, root=R - 1, cfg=cfg)
+        assert ("sweep" in route) == want, (kind, R, total, route)
+        assert ("sweep_noalloc" in route) == (want and (R <= 16 or nbytes >= 16 << 20)), (kind, R, total, route)
+        assert dfx.check_geometry(R, kind, n, dfx.F32, root=R - 1, cfg=cfg) == "", (kind, R, total)
+        assert dfx.check_geometry(R, kind, n + 4, dfx.BF16, root=0, cfg=_cfg(max_channels=min(32, 256 // R), order_policy=1, fold_max_bytes=1 << 20)) == "", (kind, R, total)
+
+
 @pytest.mark.parametrize("knobs", [dict(), dict(fold_max_bytes=0), dict(direct=0)], ids=["defaults", "ring_with_direct_steps", "through_slots"])
 def test_a_large_offset_case(knobs):
     """5 GiB + a ragged tail per rank on two ranks: byte offsets beyond 2^32, hundreds of slices per channel."""

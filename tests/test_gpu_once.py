@@ -60,14 +60,16 @@ def test_regions_at_the_edges_of_rows_and_workgroups(kind, R):
     dw.check_untouched()
 
 
-@pytest.mark.parametrize("R", [4, 8, 16])
-@pytest.mark.parametrize("kind", [wi.AR, wi.AG, wi.RS, wi.BC, wi.RD])
+@pytest.mark.parametrize("kind,R", [(k, R) for R in (4, 8, 16) for k in (wi.AR, wi.AG, wi.RS, wi.BC, wi.RD)] + [(wi.AR, 32), (wi.RS, 32)])
 def test_messages_that_are_swept(kind, R):
     import torch
+    import paper_2303_06324_amd as dfx
     from paper_2303_06324_amd import harness as gh
-    n = (256 if kind in (wi.AG, wi.BC) else 128) * MIB // R // 2
+    n = max((256 if kind in (wi.AG, wi.BC) else 128) * MIB // R, 16 * MIB if R > 16 else 0) // 2
     n = n // R + 56 if kind in (wi.AG, wi.RS) else n + 1027
     w = wi.Workload(f"once_sweep_{kind}_{R}", R, [wi.CollSpec(0, kind, wi.BF16, n, R - 2 if kind in (wi.BC, wi.RD) else 0)], [[0]] * R, seed=R, cfg=100)
+    route = dfx.plan_route(R, kind, n, wi.BF16, w.colls[0].root, gh.make_config(max_channels=min(32, 256 // R)))
+    assert ("sweep_noalloc" in route) == (R <= 8 or kind not in (wi.AG, wi.BC)), route
     dw = gh.DeviceWorkload(w)
     torch.cuda.synchronize()
     _call(dw, w, 0, None)

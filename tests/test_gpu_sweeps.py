@@ -1,7 +1,7 @@
 """Collectives in fold steps that all ranks sweep together (messages from 128 MiB of inputs, or 256 MiB of outputs, on): a rank
 moves rows of every region, each in that region's own order of combination.  Just above the limit and ragged -- regions that end
-inside a row and inside 16 bytes, a last region shorter than the others or too short for a line -- for every kind and the rank
-counts that sweep (4 and 8 with movers of their own, 16 without), with one job per share and with several, with dealt rows
+inside a row and inside 16 bytes, a last region shorter than the others -- for every kind and the rank
+counts that sweep (4 and 8 with movers of their own; 16, 32 and 64 without, which sweep where they combine), with one job per share and with several, with dealt rows
 (priority ordering), few channels, and the daemon stopped between jobs.  Bit-exact against the oracle (same order of
 combination, one rounding per hop: no tolerance), guard zones around the recv buffers."""
 import numpy as np
@@ -16,8 +16,8 @@ MIB = 1 << 20
 
 
 def _specs(kind, R):
-    """Two collectives: the shortest that sweeps, and one with a ragged end and (all-reduce) a last region of 24 bytes."""
-    least = (256 if kind in (wi.AG, wi.BC) else 128) * MIB // R
+    """Two collectives: the shortest that sweeps, and one with a ragged end (all-reduce: in its last region, which is shorter than the others)."""
+    least = max((256 if kind in (wi.AG, wi.BC) else 128) * MIB // R, R * (128 if kind == wi.RS else 40) << 10)      # (regions of so much)
     dtypes = (wi.BF16, wi.F32) if kind != wi.RD else (wi.I32, wi.F16)
     out = []
     for i, dtype in enumerate(dtypes):
@@ -26,8 +26,7 @@ def _specs(kind, R):
         if kind in (wi.AG, wi.RS):
             n = n // R + i * (2048 + 3 * 16) // eb                     # blocks are 16-byte multiples
         elif i:
-            chunk = n // R + (2048 + 32) // eb
-            n = (R - 1) * chunk + 24 // eb if kind == wi.AR else n + 2048 // eb + 5
+            n = R * (n // R + (2048 + 32) // eb) - 32 // eb - 3 if kind == wi.AR else n + 2048 // eb + 5
         op = (wi.SUM, wi.MAX)[i] if kind in (wi.AR, wi.RS, wi.RD) else wi.SUM
         out.append(wi.CollSpec(i, kind, dtype, n, R - 2 if kind in (wi.BC, wi.RD) else 0, op))
     return out
@@ -37,7 +36,11 @@ def _run(w, knobs, stop_between=False, passes=2):
     from paper_2303_06324_amd import harness as gh
     import paper_2303_06324_amd as dfx
     dw = gh.DeviceWorkload(w)
-    ctx = dfx.Context(w.R, gh.make_config(**{**dict(max_channels=min(32, 256 // w.R)), **knobs}))
+    cfg = gh.make_config(**{**dict(max_channels=min(32, 256 // w.R)), **knobs})
+    for c in w.colls:
+        swept = w.R <= 8 or c.kind not in (wi.AG, wi.BC)
+        assert ("sweep" in dfx.plan_route(w.R, c.kind, c.count, c.dtype, c.root, cfg)) == swept, c
+    ctx = dfx.Context(w.R, cfg)
     try:
         gh.prepare_all(ctx, w)
         for ci in range(len(w.colls)):
@@ -61,8 +64,8 @@ def _run(w, knobs, stop_between=False, passes=2):
     dw.check_untouched()
 
 
-@pytest.mark.parametrize("R", [4, 8, 16])
-@pytest.mark.parametrize("kind", [wi.AR, wi.AG, wi.RS, wi.BC, wi.RD])
+@pytest.mark.parametrize("kind,R", [(k, R) for R in (4, 8, 16) for k in (wi.AR, wi.AG, wi.RS, wi.BC, wi.RD)] + [(k, 32) for k in (wi.AR, wi.RS, wi.RD)] +
+                         [(wi.AR, 64), (wi.RS, 64)])
 def test_sweeps_at_the_edges(kind, R):
     specs = _specs(kind, R)
     if kind == wi.AG and R != 8:

@@ -819,6 +819,19 @@ int stage_one(dfx_ctx* c, int rank, uint32_t ahead, int coll_id, const void* sen
   return DFX_OK;
 }
 
+// Whether a submission on every rank at once comes with tables of buffers (DfxPeer).  They are R x R x 16 bytes written across PCIe, which
+// up to eight ranks do not show; beyond, they pay where the entry is worked on at once or the data takes longer than the
+// submission.  us without -> with, R = 16 / R = 32: one all-reduce of 8 KiB 16.8 -> 14.0 / 24.3 -> 21.8; 64 submitted in a row of
+// 1 MiB 315 -> 289 / 604 -> 517, of 512 KiB 293 -> 296 / 522 -> 557, of 8 KiB 284 -> 291 / 510 -> 550 (R = 8: 176 both).
+bool with_tables(const dfx_ctx* c, const DfxStatic& t) {
+  if (!c->sq_peers || !(t.flags & DFX_SQE_FOLD)) return false;
+  if (c->R <= 8) return true;
+  const RankState* rs = c->ranks[0];
+  if (rs->n_cqe.load(std::memory_order_relaxed) == rs->n_sub.load(std::memory_order_relaxed)) return true;
+  const bool blocks = t.kind == KIND_AG || t.kind == KIND_RS;
+  return t.count * elem_bytes(t.dtype) * (blocks ? (uint64_t)c->R : 1u) >= (1u << 20);
+}
+
 // Up to 32 invocations of one rank in a row: bodies, one fence, generation words, one fence.  Returns how many
 // went in; *rc is the status of the first that did not (DFX_OK if all did).  The caller sees to it that the
 // daemon runs.
@@ -870,17 +883,18 @@ int dfx_submit_all(dfx_ctx* c, int coll_id, const void* const* sendbufs, void* c
   const uint64_t t0 = now_ns();
   c->user_stopped.store(false);
   uint32_t spins = 0;
+  const bool tables = coll_id >= 0 && (uint32_t)coll_id < c->cfg.max_colls && c->colls[coll_id].prepared && with_tables(c, c->colls[coll_id].tmpl);
   for (;;) {
     // every vrank's body, one fence, every vrank's generation word, one fence: the eight entries reach the
     // device together (rank mutexes are taken in rank order; every other path holds one at a time)
     int rc = DFX_OK, staged = 0;
     for (; staged < c->R; ++staged) {
       c->ranks[staged]->mu.lock();
-      rc = stage_one(c, staged, 0u, coll_id, sendbufs[staged], recvbufs[staged], c->sq_peers ? DFX_SHARE_PEERS : 0u);
+      rc = stage_one(c, staged, 0u, coll_id, sendbufs[staged], recvbufs[staged], tables ? DFX_SHARE_PEERS : 0u);
       if (rc != DFX_OK) { c->ranks[staged]->mu.unlock(); break; }
     }
     if (rc == DFX_OK) {
-      if (c->sq_peers && (c->colls[coll_id].tmpl.flags & DFX_SQE_FOLD)) {
+      if (tables) {
         // every entry's table (a slot's table is as free as the slot: every workgroup of the rank reads both before it counts itself in)
         const DfxStatic& t = c->colls[coll_id].tmpl;
         for (int r = 0; r < c->R; ++r) {

@@ -10,8 +10,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("R,knobs", [(8, dict()), (8, dict(sq_depth=2, chan_spread=0)), (3, dict(order_policy=1)), (4, dict(scan_min=0, spin_init=1, spin_min=1, spin_max=1, spin_boost=1)),
-                                     (16, dict(max_channels=4)), (8, dict(fold_max_bytes=1 << 16, direct_min_bytes=0, max_channels=2)), (2, dict(sq_in_device=0))],
-                         ids=["defaults", "two_entries", "priority", "give_up_at_once", "sixteen", "several_jobs", "sq_on_host"])
+                                     (16, dict(max_channels=4)), (32, dict(max_channels=3)), (8, dict(fold_max_bytes=1 << 16, direct_min_bytes=0, max_channels=2)), (2, dict(sq_in_device=0))],
+                         ids=["defaults", "two_entries", "priority", "give_up_at_once", "sixteen", "thirty_two", "several_jobs", "sq_on_host"])
 def test_buffers_change_from_call_to_call(R, knobs):
     import torch
     import paper_2303_06324_amd as dfx

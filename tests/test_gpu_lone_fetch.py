@@ -47,3 +47,33 @@ def test_lone_entries_reuse_everything(knobs):
         dw.check_untouched()
     finally:
         assert ctx.finalize() == dfx.OK
+
+
+@pytest.mark.parametrize("how", ["all_at_once", "rank_by_rank"])
+def test_the_last_wait_outlasts_its_polls(how):
+    """A collective that is alone in its queue is not given up at its threshold, but after so many polls it is, and taken up again by
+    the next pass: one channel, whose job takes far longer than the polls do."""
+    import paper_2303_06324_amd as dfx
+    from paper_2303_06324_amd import harness as gh
+    R = 4
+    w = wi.Workload("lone_long", R, [wi.CollSpec(0, wi.AR, wi.I32, (6 << 20) + 5)], [[0]] * R, seed=8, cfg=104)
+    dw = gh.DeviceWorkload(w)
+    ctx = dfx.Context(R, gh.make_config(max_channels=1))
+    try:
+        gh.prepare_all(ctx, w)
+        assert ctx.coll_info(0)["rounds"] == 1
+        p = ctx.make_all([t.data_ptr() for t in dw.send[0]], [t.data_ptr() for t in dw.recv[0]])
+        for _ in range(5):
+            if how == "all_at_once":
+                assert ctx.submit_all(0, p) == dfx.OK
+            else:
+                gh.submit_round_robin(ctx, dw)
+            assert ctx.wait_all(20.0) == dfx.OK
+        assert ctx.stop() == dfx.OK
+        assert sum(ctx.stats(r)["preemptions"] for r in range(R)) >= 5 * R
+    finally:
+        assert ctx.finalize() == dfx.OK
+    want, got = rd.run_closed_form(wi.AR, dw.send_host[0], wi.I32, 0, wi.SUM), dw.results(0)
+    for r in range(R):
+        assert np.array_equal(got[r], want[r]), r
+    dw.check_untouched()

@@ -95,3 +95,58 @@ def test_send_buffers_rewritten_under_a_resident_daemon(kind, n):
                 want = np.full(nr, -1, np.int32)
             assert np.array_equal(kept[i, r], want), (kind, n, i, r)
             assert np.array_equal(kept_ring[i, r], np.concatenate([x[:n - 1] for x in now])), (kind, n, i, r)
+
+
+@pytest.mark.parametrize("kind", ["allreduce", "allgather", "reducescatter", "broadcast", "reduce"])
+def test_swept_messages_rewritten_under_a_resident_daemon(kind):
+    """The same for a message that all ranks sweep together: its loads carry the non-temporal hint."""
+    import torch
+    import paper_2303_06324_amd as dfx
+    from paper_2303_06324_amd import harness as gh
+    k = dict(allreduce=dfx.ALLREDUCE, allgather=dfx.ALLGATHER, reducescatter=dfx.REDUCESCATTER, broadcast=dfx.BROADCAST, reduce=dfx.REDUCE)[kind]
+    whole = (32 if k in (dfx.ALLGATHER, dfx.BROADCAST) else 16) << 18               # elements of the largest per-rank buffer
+    n = whole // R if k in (dfx.ALLGATHER, dfx.REDUCESCATTER) else whole
+    ns, nr = (n * R if k == dfx.REDUCESCATTER else n), (n * R if k == dfx.ALLGATHER else n)
+    send = [torch.arange(ns, dtype=torch.int32, device="cuda") * 3 + 1000003 * r for r in range(R)]
+    recv = [torch.full((nr,), -1, dtype=torch.int32, device="cuda") for _ in range(R)]
+    wrong = torch.zeros((ITERATIONS, R), dtype=torch.int64, device="cuda")
+    scratch, reads = torch.zeros(64, device="cuda"), torch.zeros(R, dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    cfg = gh.make_config(max_channels=4, quit_idle_us=1_000_000, pool_bytes=256 << 20)
+    root = ROOT if k in (dfx.BROADCAST, dfx.REDUCE) else 0
+    assert "sweep" in dfx.plan_route(R, k, n, dfx.I32, root, cfg)
+    ctx = dfx.Context(R, cfg)
+    try:
+        ctx.prepare(0, k, n, dfx.I32, dfx.SUM, root)
+        p = ctx.make_all([t.data_ptr() for t in send], [t.data_ptr() for t in recv])
+        assert ctx.start() == dfx.OK
+        st = _stream_beside_the_daemon(torch, scratch)
+        for i in range(ITERATIONS):
+            with torch.cuda.stream(st):
+                for r in range(R):
+                    reads[r] = send[r].sum() + recv[r].sum()
+                    send[r].add_(r * 7 + i + 1)
+                ev = torch.cuda.Event()
+                ev.record(st)
+            assert _done(ev, 10.0)
+            assert ctx.submit_all(0, p) == dfx.OK and ctx.wait_all(10.0) == dfx.OK
+            with torch.cuda.stream(st):
+                total = sum(send[1:], send[0])
+                for r in range(R):
+                    want = {dfx.ALLREDUCE: total, dfx.REDUCESCATTER: total[r * n:(r + 1) * n], dfx.REDUCE: total, dfx.BROADCAST: send[ROOT]}.get(k)
+                    if k == dfx.ALLGATHER:
+                        wrong[i, r] = sum((recv[r][q * n:(q + 1) * n] != send[q]).sum() for q in range(R))
+                    elif k == dfx.REDUCE and r != ROOT:
+                        wrong[i, r] = (recv[r] != -1).sum()
+                    else:
+                        wrong[i, r] = (recv[r] != want).sum()
+                ev = torch.cuda.Event()
+                ev.record(st)
+            assert _done(ev, 10.0)
+            if i == 0: launches = ctx.stats(0)["launches"]
+        assert ctx.stats(0)["launches"] == launches          # one daemon through all iterations but the first
+        assert ctx.stop() == dfx.OK
+    finally:
+        ctx.finalize()
+    torch.cuda.synchronize()
+    assert int(wrong.sum()) == 0, wrong.cpu()

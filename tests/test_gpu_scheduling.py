@@ -445,8 +445,8 @@ def test_primitive_timeline_trace():
 
 @pytest.mark.parametrize("cq_mode", [0, 1, 2])
 def test_cq_variants_deliver_every_completion_once(cq_mode):
-    """The three completion queues of Sec. 5 (CAS slot array, vanilla ring, 64-bit packed ring) behind a
-    16-slot CQ that must wrap many times: 200 collectives per rank, every CQE handed out exactly once."""
+    """The three completion queues of Sec. 5 (a slot per id, vanilla ring, 64-bit packed ring), the rings of 16 slots that must
+    wrap many times: 200 collectives per rank, every CQE handed out exactly once."""
     from paper_2303_06324_amd import harness as gh
     import paper_2303_06324_amd as dfx
     w = wi.config5(n_colls=200, seed=23)
@@ -475,6 +475,49 @@ def test_cq_variants_deliver_every_completion_once(cq_mode):
             _expect(dw, w, ci)
         st = ctx.stats(0)
         assert st["cqe_posted"] == 200 and st["cqe_us"] > 0.0
+    finally:
+        assert ctx.finalize() == dfx.OK
+
+
+@pytest.mark.parametrize("cq_mode", [0, 1, 2])
+def test_completions_of_reused_slots_arrive_once_and_in_order(cq_mode):
+    """Every id several times before anybody polls: a slot (of the id, or of an 8-entry ring) holds one completion after the other,
+    each taken when the id's next invocation is submitted at the latest.  All (id, invocation) pairs are handed out
+    once, those of an id in order, and one that has not been submitted never."""
+    from paper_2303_06324_amd import harness as gh
+    import paper_2303_06324_amd as dfx
+    R, ids, rounds = 4, [0, 1, 63, 1000, 2047], 7
+    w = wi.Workload("cq_reuse", R, [wi.CollSpec(i, wi.AR if k % 2 else wi.BC, wi.I32, 1000 + 37 * k) for k, i in enumerate(ids)], [list(range(len(ids)))] * R, seed=6, cfg=103)
+    dw = gh.DeviceWorkload(w)
+    ctx = dfx.Context(R, gh.make_config(cq_mode=cq_mode, cq_slots=8, max_channels=4))
+    try:
+        gh.prepare_all(ctx, w)
+        rng = np.random.default_rng(cq_mode)
+        todo = [[ci for ci in range(len(ids)) for _ in range(rounds)] for _ in range(R)]
+        for t in todo:
+            rng.shuffle(t)
+        sent, seen, deadline = [[0] * len(ids) for _ in range(R)], [[[] for _ in ids] for _ in range(R)], time.monotonic() + 60
+        while any(todo):
+            for r in range(R):
+                for ci in list(dict.fromkeys(todo[r])):
+                    rc = ctx.submit(r, ids[ci], dw.send[ci][r].data_ptr(), dw.recv[ci][r].data_ptr())
+                    assert rc in (dfx.OK, dfx.ERR_BUSY, dfx.ERR_SQ_FULL)
+                    if rc == dfx.OK:
+                        todo[r].remove(ci)
+                        sent[r][ci] += 1
+                if rng.random() < 0.02:
+                    for cid, seq in ctx.poll(r, 64):
+                        seen[r][ids.index(cid)].append(seq)
+                        assert seq < sent[r][ids.index(cid)]
+            assert time.monotonic() < deadline
+        while any(len(s) < rounds for row in seen for s in row):
+            for r in range(R):
+                for cid, seq in ctx.poll(r, 64):
+                    seen[r][ids.index(cid)].append(seq)
+            assert time.monotonic() < deadline
+        assert all(s == list(range(rounds)) for row in seen for s in row), seen
+        for ci in range(len(ids)):
+            _expect(dw, w, ci)
     finally:
         assert ctx.finalize() == dfx.OK
 

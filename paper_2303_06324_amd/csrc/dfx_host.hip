@@ -486,7 +486,7 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   // once, every output written once: 2R x M of an all-reduce instead of (5R-5) x M), so a collective that qualifies for
   // direct steps runs in fold steps above fold_max_bytes too, in jobs of this size.  Measured (us, R = 8, rings and
   // chains with direct steps -> this, a region per rank): all-reduce 256 MiB fp32 1545 -> 806, reduce-scatter 128 MiB fp32
-  // 496 -> 268, broadcast 100 MiB bf16 472 -> 200 (as sweeps, below: 739, 232, 187).
+  // 496 -> 268, broadcast 100 MiB bf16 472 -> 200 (as sweeps, below: 739, 232 with blocks off the lines, 187).
   // With fold_max_bytes = 0 the rings and chains run at every size.
   if ((t.flags & DFX_SQE_DIRECT) && !fold && cfg.fold_max_bytes && blocks_ok && !(kind == DFX_REDUCE && R > 63)) {
     // 128 KiB per source and workgroup (drawn rows: twice that at most), about 100 us at 2 x 8 streams; priority ordering
@@ -1827,7 +1827,7 @@ int dfx_collective_noalloc(int nranks, dfx_kind kind, size_t count, dfx_dtype dt
     o.status = status_dev;
     if (status_dev) {
       hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-      if (hipStreamIsCapturing((hipStream_t)hip_stream, &cap) != hipSuccess) (void)hipGetLastError();      // (the launch will say so)
+      if (hip_stream && hipStreamIsCapturing((hipStream_t)hip_stream, &cap) != hipSuccess) (void)hipGetLastError();      // (the launch will say so; the null stream is never captured)
       if (cap == hipStreamCaptureStatusNone) {
         const uint32_t call = nd->calls.fetch_add(1, std::memory_order_relaxed);
         o.count = (uint32_t*)(base + L.once) + call % DFX_ONCE_COUNTERS;

@@ -199,7 +199,8 @@ typedef struct {
   double data_us;          /* ... in data phases (first mover wave: job taken until its stores are drained) */
   double publish_us;       /* ... between the last mover wave's drain and its counter updates */
   uint64_t scan_skips;     /* queue entries a readiness scan found not runnable (no context load, no spin) */
-  double cqe_us;           /* time spent writing CQEs (first to last host-memory operation), summed; always counted */
+  double cqe_us;           /* time spent writing CQEs (first to last host-memory operation issued), summed; always counted.  The optimized
+                              CQ's one posted write is over when it is issued: what the others wait for is not in it */
   double advance_us_mean;  /* with trace = 2: the part of a switch between the save and the load (retiring finished jobs, next queue entry) */
   double setup_us_mean;    /* with trace = 2: the part after the load (thresholds, the primitive's descriptor) up to the first poll */
   double clock_read_us;    /* with trace = 1 or 2: what one read of the wall clock costs the scheduler (a switch sample holds two

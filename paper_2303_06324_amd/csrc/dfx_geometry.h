@@ -133,7 +133,7 @@ DFX_HD uint64_t fold_chunk_elems(int kind, uint64_t count, uint64_t block, uint3
 // waves of a rank) a rank takes W in a row, so that a rank's workgroups -- an XCD's, or those of a few whole ones -- stay side
 // by side.  Which rank moves a row has nothing to do with whose region it lies in; every region keeps its order of combination.
 // The rows' loads carry the non-temporal hint: nothing of a long message is read again.  The hint alone gave 804 -> 772 us
-// for an all-reduce of 256 MiB fp32 (R = 8), the sweep with it 746; reduce-scatter of 128 MiB 268 -> 262 and 221.
+// for an all-reduce of 256 MiB fp32 (R = 8), the sweep with it 746; reduce-scatter of 128 MiB 268 -> 262 and 221 (blocks on lines).
 // Row t of the message is row t mod n of region t / n, where n = ceil(longest region / row).
 DFX_HD uint32_t sweep_row_bytes(bool copies, uint32_t R) { return 1024u * (copies || R == 4 ? 4u : 2u); }
 // Regions: a chunk or block per rank (all-reduce, reduce-scatter, all-gather); a broadcast or reduce, whose parts are all

@@ -232,9 +232,9 @@ struct Rows {
 // an 8 KiB all-reduce took 3.4 us, now 1.8; a 25 MiB bf16 bucket, with the rows, 92 -> 75 us).  A buffer's
 // resource ends with the last row's last whole 16 bytes: loads behind it return 0 and stores behind it are dropped, so
 // the last row needs no predicates.
-// Next round's loads before this round's combine, 512 movers, non-temporal or plain cached accesses measured the
-// same (838-845 us for 256 MiB per rank, fp32, R = 8) or, non-temporal below the size of the memory-side cache,
-// worse (8 MiB: 25 against 20.5 us).
+// Next round's loads before this round's combine, 512 movers or plain cached accesses measured the same (838-845 us for 256 MiB per
+// rank, fp32, R = 8, before rows).  The non-temporal hint is for sweeps: below the size of the memory-side cache it costs
+// (8 MiB: 25 against 20.5 us).
 template <int DT, int NS, bool ALL>
 __device__ __forceinline__ void fold_fixed(const u64* src_tab, const u64* dst_tab, uint32_t from, uint32_t end, Rows& rows, uint32_t lane, int op) {
   constexpr int U = 16 / NS, ND = ALL ? NS : 1;      // (fold_row_bytes)
@@ -433,9 +433,12 @@ __device__ __forceinline__ void fold_dispatch(int dtype, const u64* src_tab, uin
 }
 
 // ---- sweeps (sweep_region): the same movers over all regions of the message.  Their tables hold whole buffers, every rank's.
-// What bounds them is HBM: in a kernel of its own the same loop (eight sources and destinations, dealt rows) moves 256 MiB per rank in
-// 750 - 765 us, reads alone go at 6.7 - 7 TB/s, writes alone at 5.5, so 710 us is the floor of the all-reduce, which takes 746.  Deeper
-// pipelines (next row's loads ahead, 32 in flight per lane), 512 or 1024 movers and non-temporal stores measured the same.
+// What bounds them is HBM: reads alone go at 6.7 - 7 TB/s, writes alone at 5.5, which one after the other is 710 us for the all-reduce of
+// 256 MiB per rank (R = 8); it takes 723 - 746 on different boxes.  The pace of the loads counts: in a kernel of its own the same loop (dealt
+// rows) takes 750 - 765, and so it does here with its resources in scalar registers (750 - 760).  As it stands the compiler has
+// them in vector registers -- the movers' branch to it is a divergent one -- and takes every access in a loop over readfirstlane,
+// which spaces them; scalar with s_sleep(1) behind every load measured 734 - 736.  Deeper pipelines (next row's loads ahead, 32 in flight per
+// lane), 512 or 1024 movers and non-temporal stores measured the same.
 struct Sweep {
   uint32_t kind, R, rank, nreg;
   uint32_t rows, all;                      // rows of a region, of the message

@@ -11,7 +11,7 @@
 #include "dfx_geometry.h"
 #include "dfx_movers.h"
 
-// Four mover waves; three workgroups fit a compute unit without a register spilled (four, with spills, measured the same).
+// Four mover waves; three workgroups fit a compute unit without a vector register spilled (four, with spills, measured the same).
 extern "C" __global__ void __launch_bounds__(DFX_ONCE_THREADS, 2) dfx_fold_once_kernel(DfxFoldOnce a) {
   __shared__ u64 tab_src[DFX_ONCE_MAX_RANKS], tab_dst[DFX_ONCE_MAX_RANKS];
   const uint32_t R = a.R, rank = blockIdx.x % R, group = blockIdx.x / R;      // (R = 8: a rank per XCD)

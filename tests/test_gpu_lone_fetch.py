@@ -1,7 +1,7 @@
 """A lone entry of a collective in fold steps takes a short way through the fetch: its context goes straight into its LDS
 slot, its SQ slot is freed when a later poll is back, its completion writes nothing back.  Checked where that can go
 wrong: the smallest SQ (every entry reuses a slot that has just been freed), ids whose contexts share one LDS slot, waits
-that are given up at once or never, collectives that need the connectors in between, the three CQ variants, and many
+that are given up at once (the last one of a lone collective: after 256 polls) or never, collectives that need the connectors in between, the three CQ variants, and many
 invocations of one id (the counters that run on).  Bit-exact against the oracle."""
 import numpy as np
 import pytest

@@ -1119,7 +1119,11 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 const u64 f_out = ((u64)fl.w << 32) | fl.z, f_in = ((u64)fi.y << 32) | fi.x;
                 const u64 e_sent = ((u64)d0.w << 32) | d0.z, e_recvd = ((u64)d1.y << 32) | d1.x;
                 bool okr = true, oks = true;
-                if (pq.fold)   // every rank of the channel has got as far as this step needs (bytes 48..63: shared counters, count at the end)
+                // Fold steps: every rank of the channel has got as far as this step needs (bytes 48..63: shared counters, count at the end).
+                // The last wait is for all channels; its own stands for them here: a visit too early is a poll and a switch, 2 % of
+                // the visits among 64 mixed collectives, none among 1024 small ones.  All channels' counters looked at here: 64
+                // mixed 959 us, then 972, 1024 small 535, then 547.
+                if (pq.fold)
                   okr = ld_agent64((const u64*)f_in + pq.fwait) >= (pq.fwait ? ((u64)fi.w << 32) | fi.z : ((u64)ge.x + 1u) * R);
                 if (pq.recv) okr = ld_agent64((const u64*)f_in) > e_recvd;
                 if (pq.send) oks = (e_sent - ld_agent64((const u64*)f_out + 8)) < (u64)(ge.z & 0xffu);

@@ -1,0 +1,66 @@
+"""Bursts of short collectives in fold steps, which a readiness scan hands to the movers several at a time and whose completions it
+posts itself: every kind, element type and reducing function at the edges of rows and of the longest share that goes with others,
+collectives of one and of several channels and a long one between them, every rank in an order of its own, in queues of one, two
+and four channels (more and fewer entries than a scan holds), with and without priorities, with the ring-buffer completion queue,
+three passes on the same context and one that begins with a stop half way.
+Bit-exact against the oracle (same order of combination, one rounding per hop: no tolerance)."""
+import numpy as np
+import pytest
+
+import workload_inputs as wi
+from oracle import ring_data as rd
+
+pytestmark = pytest.mark.gpu
+
+
+def _workload(R, n, seed):
+    g = np.random.default_rng(seed)
+    colls = []
+    for i in range(n):
+        kind, dtype = (wi.AR, wi.AG, wi.RS, wi.BC, wi.RD)[i % 5], (wi.F32, wi.BF16, wi.F16, wi.I32)[i // 5 % 4]
+        eb, op = wi.ELEM_BYTES[dtype], (wi.SUM, wi.MAX, wi.PROD, wi.MIN)[i % 4] if kind in (wi.AR, wi.RS, wi.RD) else wi.SUM
+        part = (16, 2032, 2048, 4112, 8192, 16368, 16384, 16400, 40000, 70000)[i * 7 % 10]         # bytes of a rank's region, about
+        count = part // 16 * 16 // eb if kind in (wi.AG, wi.RS) else max(1, R * part // eb - (0, 1, 3)[i % 3])
+        colls.append(wi.CollSpec(i, kind, dtype, count, int(g.integers(R)) if kind in (wi.BC, wi.RD) else 0, op))
+    colls[n // 2] = wi.CollSpec(n // 2, wi.AR, wi.BF16, (1 << 20) + 5)
+    return wi.Workload(f"gangs_{R}", R, colls, [list(map(int, g.permutation(n))) for _ in range(R)], seed=seed, cfg=110)
+
+
+@pytest.mark.parametrize("R,channels,n,knobs", [
+    (2, 1, 60, {}), (3, 2, 80, {}), (4, 4, 120, {}), (8, 2, 60, {}), (8, 4, 200, {}), (16, 1, 40, {}), (33, 1, 20, {}),
+    (8, 1, 90, {}),                                  # a queue longer than a scan's lanes
+    (4, 2, 60, dict(order_policy=1)), (8, 1, 90, dict(order_policy=1)), (8, 2, 60, dict(cq_mode=1)), (8, 2, 60, dict(spin_min=2)),
+    (8, 2, 60, dict(focus_bytes=0)), (5, 2, 60, dict(quit_idle_us=30))])
+def test_short_collectives_together(R, channels, n, knobs):
+    from paper_2303_06324_amd import harness as gh
+    import paper_2303_06324_amd as dfx
+    w = _workload(R, n, seed=R * 100 + n)
+    dw = gh.DeviceWorkload(w)
+    ctx = dfx.Context(R, gh.make_config(max_channels=channels, **knobs))
+    try:
+        gh.prepare_all(ctx, w, priorities=[(i * 5) % 7 - 3 for i in range(n)] if knobs.get("order_policy") else None)
+        for it in range(4):
+            dw.reset_recv()
+            if it == 3:                              # the daemon leaves with some ranks' entries in its queues, and comes back
+                for r in range(R - 1):
+                    for ci in w.orders[r]:
+                        assert ctx.submit(r, ci, dw.send[ci][r].data_ptr(), dw.recv[ci][r].data_ptr()) == dfx.OK
+                assert ctx.stop() == dfx.OK
+                gh.submit_round_robin(ctx, dw, orders=[[]] * (R - 1) + [w.orders[R - 1]])
+            else:
+                gh.submit_bursts(ctx, dw)
+            assert ctx.wait_all(30.0) == dfx.OK
+        assert ctx.stop() == dfx.OK
+        dw.check_untouched()
+        st = [ctx.stats(r) for r in range(R)]
+    finally:
+        ctx.finalize()
+    assert all(s["cqe_posted"] == 4 * n for s in st)
+    assert all(s["preemptions"] == s["ctx_saves"] + s["lazy_skips"] for s in st)
+    for ci, c in enumerate(w.colls):
+        want, got = rd.run_closed_form(c.kind, dw.send_host[ci], c.dtype, c.root, c.op), dw.results(ci)
+        for r in range(R):
+            if c.kind == wi.RD and r != c.root:
+                assert np.all(got[r].view(np.uint8) == 0xA5), (ci, r)
+            else:
+                assert np.array_equal(got[r].view(np.uint8), want[r].view(np.uint8)), (ci, c, r)

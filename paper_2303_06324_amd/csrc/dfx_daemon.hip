@@ -824,6 +824,82 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
       if (ctx_open) { __builtin_amdgcn_s_waitcnt(0); ctx_open = false; }
     };
 
+    // ---- FetchSQE, the parts of it: is the entry there, its words (system scope throughout: nothing of an SQ slot is ever taken
+    // from a cache); an entry of this workgroup's taken into its contexts; where it goes in the queue
+    auto entry_there = [&](u64 idx) -> bool { return ld_sys32(&sqbase[idx & (D - 1)].e.ready) == (uint32_t)(idx >> hot.sq_shift) + 1u; };
+    auto load_entry = [&](u64 idx) -> DfxStatic {
+      struct { u64 w[sizeof(DfxStatic) / 8]; } qw;
+      const u64* const src = (const u64*)&sqbase[idx & (D - 1)].e;
+#pragma unroll
+      for (int i = 0; i < (int)(sizeof(DfxStatic) / 8); ++i) qw.w[i] = ld_sys64(src + i);
+      return __builtin_bit_cast(DfxStatic, qw);
+    };
+    auto take_entry = [&](const DfxStatic& q, uint32_t vch, uint32_t round, uint32_t prim, bool lone) {
+      // cook the static context of this invocation into the context buffer (addresses
+      // resolved once, here); restart the sequence, keep the monotone connector counters
+      const DfxCooked k = cook_sqe(q, a.pool, rank, R, vch);
+      // direct and fold steps: other ranks read this rank's send buffer and read or write its recv buffer; their
+      // addresses and the invocation they belong to go into the rank's line (two 16-byte device-coherent
+      // stores, each with its tag; complete before any job of an invocation with direct steps is posted)
+      if (q.flags & DFX_SQE_DIRECT)
+      {
+        const Slot<AUX_DEVICE> line((const void*)k.flags_out, DFX_FLAG_STRIDE);
+        line.st16(DFX_DIRECT_OFF, uint4{(uint32_t)q.recvbuf, (uint32_t)(q.recvbuf >> 32), q.seq + 1u, 0u});
+        line.st16(DFX_DIRECT_OFF + 16, uint4{(uint32_t)q.sendbuf, (uint32_t)(q.sendbuf >> 32), q.seq + 1u, 0u});
+      }
+      // rows to be drawn: the counter of the next invocation starts over (nobody draws from it: every rank has
+      // finished the invocation before this one, or this rank would not have been given this one)
+      if ((q.flags & DFX_SQE_DRAWN) && vch == 0)
+        __hip_atomic_store(global_ptr((uint32_t*)(k.flags_out + DFX_FOLD_DRAW + 8u * ((q.seq + 1u) & 1u))), 0u, __ATOMIC_RELAXED, SCOPE_AGENT);
+      // fold steps: the channel's count of published invocations, a hint for the readiness scans
+      if (q.flags & DFX_SQE_FOLD) (void)__hip_atomic_fetch_add(global_ptr((u64*)(k.flags_in + DFX_FOLD_PUB)), 1ull, __ATOMIC_RELAXED, SCOPE_AGENT);
+      const uint32_t c_id = q.coll_id, csl = ctx_slot(c_id);
+      if (lone) {
+        DfxDyn d; d.round = round; d.prim = prim; d.sent = 0; d.recvd = 0; d.preempted = 0; d.cidx = 0;   // (no connectors: nothing to keep)
+        sh.slot[csl].st = k; sh.slot[csl].dyn = d;
+        sh.slot_tag[csl] = c_id;
+      } else if (sh.slot_tag[csl] == c_id) sh.slot_tag[csl] = 0xffffffffu;
+      st_ctx(&myctx[c_id].st, k);
+      GLOBAL_AS DfxDyn* dy = global_ptr(&myctx[c_id].dyn);
+      dy->round = round; dy->prim = prim; dy->preempted = 0;
+      dy->cidx = first_chunk(q.kind, rank, R);
+    };
+    // The entries of `m`, each in its lane, join the task queue in SQ order.
+    auto join_queue = [&](u64 m, uint32_t id_new, int pr) {
+      const bool mine = (m >> lane & 1u) != 0;
+      if (__builtin_expect(hot.order_policy == 1, 0)) {
+        // Priority ordering: the queue stays sorted, an entry behind those of higher or equal priority (64 at once: one by one, a
+        // fetch each, 1024 entries took 3.4 ms, longer than the collectives they described).  From the back of the queue on, 64
+        // entries at a time, every queued one moves up by the number of new ones that go before it.
+        uint32_t at = 0;                 // (of a new one: queued entries and new ones before it)
+        for (u64 t = m; t; t &= t - 1) {
+          const uint32_t b = (uint32_t)__builtin_ctzll(t);
+          const int pb = __builtin_amdgcn_readlane(pr, b);
+          at += (pb > pr || (pb == pr && b < lane)) ? 1u : 0u;
+        }
+        for (uint32_t base = (qlen + 63u) & ~63u; m && base; ) {
+          base -= 64u;
+          const uint32_t i = base + lane;
+          const bool old = i < qlen;
+          uint16_t id = 0;
+          int po = 0;
+          if (old) { id = sh.taskq[i]; po = *(const GLOBAL_AS int16_t*)&myctx[id].st.priority; }
+          uint32_t up = 0;
+          for (u64 t = m; t; t &= t - 1) {
+            const uint32_t b = (uint32_t)__builtin_ctzll(t);
+            const int pb = __builtin_amdgcn_readlane(pr, b);
+            const uint32_t before = (uint32_t)__builtin_popcountll(__ballot(old && po >= pb));
+            if (lane == b) at += before;
+            up += pb > po ? 1u : 0u;
+          }
+          __builtin_amdgcn_wave_barrier();
+          if (old) sh.taskq[i + up] = id;
+          __builtin_amdgcn_wave_barrier();
+        }
+        if (mine) sh.taskq[at] = (uint16_t)id_new;
+      } else if (mine) sh.taskq[qlen + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull))] = (uint16_t)id_new;
+    };
+
     // ---- a step with data of a collective in fold steps goes to the movers; lane k holds the buffers of entry k's rank
     struct FoldStep { int kind, dtype; uint32_t coll, seq, nchan, vch, limit, fresh; u64 line0, counters; bool drawn, sweep; uint32_t g, longest; u64 total; };
     auto post_fold = [&](const FoldStep& st, const FoldGeom& fg, u64 sendbuf, u64 recvbuf) {
@@ -995,16 +1071,10 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             if (room > 64) room = 64;
             const uint32_t left = burst < hot.fetch_batch ? hot.fetch_batch - burst : 1u;
             if (left < room) room = left;
-            if (hot.order_policy == 1) room = 1;       // the sorted insert below is written for one entry
             // Lane 0's entry has been seen by the control check: its words are loaded while the lanes behind it look
             // whether theirs are there.  System scope throughout: nothing of an SQ slot is ever taken from a cache.
             bool here = lane == 0;
-            struct SqeWords { u64 w[sizeof(DfxStatic) / 8]; } qw = {};
-            const u64* const src = (const u64*)&sqbase[(ri + lane) & (D - 1)].e;
-            auto load_entry = [&]() {
-#pragma unroll
-              for (int i = 0; i < (int)(sizeof(DfxStatic) / 8); ++i) qw.w[i] = ld_sys64(src + i);
-            };
+            DfxStatic q = {};
             // (the table of buffers that lane 0's entry may come with, lane k its entry k)
             uint4 peer = uint4{0, 0, 0, 0};
             if (with_table && lane < R) {
@@ -1012,16 +1082,12 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
               const u64 t0 = ld_sys64(t), t1 = ld_sys64(t + 1);
               peer = uint4{(uint32_t)t0, (uint32_t)(t0 >> 32), (uint32_t)t1, (uint32_t)(t1 >> 32)};
             }
-            if (lane == 0) load_entry();
-            else if (lane < room) {
-              const u64 idx = ri + lane;
-              here = ld_sys32(&sqbase[idx & (D - 1)].e.ready) == (uint32_t)(idx >> hot.sq_shift) + 1u;
-            }
+            if (lane == 0) q = load_entry(ri);
+            else if (lane < room) here = entry_there(ri + lane);
             const u64 here_mask = __ballot(here);
             uint32_t n = (here_mask == ~0ull) ? 64u : (uint32_t)__builtin_ctzll(~here_mask);   // length of the run that starts at lane 0
-            if (lane != 0 && lane < n) load_entry();
+            if (lane != 0 && lane < n) q = load_entry(ri + lane);
             __builtin_amdgcn_s_waitcnt(0);        // (the entries have been read before they count as read below)
-            const DfxStatic q = __builtin_bit_cast(DfxStatic, qw);
             bool is_exit_sqe = false, is_exit = false;
             if (lane < n) {
               // an exit SQE ends the launch it was posted for; one left over from an earlier launch
@@ -1073,34 +1139,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
               sh.peer[lane] = peer;
             }
             if (mine) {
-              // cook the static context of this invocation into the context buffer (addresses
-              // resolved once, here); restart the sequence, keep the monotone connector counters
-              const DfxCooked k = cook_sqe(q, a.pool, rank, R, my_vch);
-              // direct and fold steps: other ranks read this rank's send buffer and read or write its recv buffer; their
-              // addresses and the invocation they belong to go into the rank's line (two 16-byte device-coherent
-              // stores, each with its tag; complete before any job of an invocation with direct steps is posted)
-              if (q.flags & DFX_SQE_DIRECT)
-              {
-                const Slot<AUX_DEVICE> line((const void*)k.flags_out, DFX_FLAG_STRIDE);
-                line.st16(DFX_DIRECT_OFF, uint4{(uint32_t)q.recvbuf, (uint32_t)(q.recvbuf >> 32), q.seq + 1u, 0u});
-                line.st16(DFX_DIRECT_OFF + 16, uint4{(uint32_t)q.sendbuf, (uint32_t)(q.sendbuf >> 32), q.seq + 1u, 0u});
-              }
-              // rows to be drawn: the counter of the next invocation starts over (nobody draws from it: every rank has
-              // finished the invocation before this one, or this rank would not have been given this one)
-              if ((q.flags & DFX_SQE_DRAWN) && my_vch == 0)
-                __hip_atomic_store(global_ptr((uint32_t*)(k.flags_out + DFX_FOLD_DRAW + 8u * ((q.seq + 1u) & 1u))), 0u, __ATOMIC_RELAXED, SCOPE_AGENT);
-              // fold steps: the channel's count of published invocations, a hint for the readiness scans
-              if (q_fold) (void)__hip_atomic_fetch_add(global_ptr((u64*)(k.flags_in + DFX_FOLD_PUB)), 1ull, __ATOMIC_RELAXED, SCOPE_AGENT);
-              const uint32_t csl = ctx_slot(c_id);
-              if (lone) {
-                DfxDyn d; d.round = first_round; d.prim = first_prim; d.sent = 0; d.recvd = 0; d.preempted = 0; d.cidx = 0;   // (no connectors: nothing to keep)
-                sh.slot[csl].st = k; sh.slot[csl].dyn = d;
-                sh.slot_tag[csl] = c_id;
-              } else if (sh.slot_tag[csl] == c_id) sh.slot_tag[csl] = 0xffffffffu;
-              st_ctx(&myctx[c_id].st, k);
-              GLOBAL_AS DfxDyn* dy = global_ptr(&myctx[c_id].dyn);
-              dy->round = first_round; dy->prim = first_prim; dy->preempted = 0;
-              dy->cidx = first_chunk(q.kind, rank, R);
+              take_entry(q, my_vch, first_round, first_prim, lone);
             }
             // every workgroup of the rank reads every SQE; the last reader frees the slot (relaxed: the entries have been
             // read, and nothing else hangs on the counter)
@@ -1114,17 +1153,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             if (lone) ctx_open = true;
             else __builtin_amdgcn_s_waitcnt(0);
             // the entries that are this workgroup's join the task queue in SQ order
-            if (mine && !through) {
-              if (hot.order_policy == 1) {
-                // priority ordering: keep the queue sorted (stable); one entry per fetch in this mode
-                uint32_t at = qlen;
-                const int16_t pr = q.priority;
-                while (at > 0 && myctx[sh.taskq[at - 1]].st.priority < pr) { sh.taskq[at] = sh.taskq[at - 1]; --at; }
-                sh.taskq[at] = (uint16_t)c_id;
-              } else {
-                sh.taskq[qlen + (uint32_t)__builtin_popcountll(mine_mask & ((1ull << lane) - 1ull))] = (uint16_t)c_id;
-              }
-            }
+            if (!through) join_queue(mine_mask, c_id, q.priority);
             if (!through) qlen += (uint32_t)__builtin_popcountll(mine_mask);
             if (lane == 0) {
               bump(sh.stat, ST_SQE, n);

@@ -135,7 +135,7 @@ typedef struct {
   uint32_t direct;         /* (steps of rings and chains, which run with fold_max_bytes = 0; a long collective that would take them runs in fold steps otherwise)
                               1 (default): collectives of at least direct_min_bytes (all-reduce, broadcast,
                               reduce: per rank; all-gather, reduce-scatter: all R blocks, which must be
-                              16-byte multiples) take direct steps, since all buffers lie in one HBM.  The
+                              16-byte multiples but for fold steps) take direct steps, since all buffers lie in one HBM.  The
                               opening send of an all-reduce, a reduce-scatter or a reduce chain only raises
                               the connector's counter and the next rank reads that
                               chunk from this rank's send buffer; in the gather steps (of an
@@ -150,8 +150,8 @@ typedef struct {
                               all-reduce, broadcast and reduce, every all-gather and reduce-scatter of
                               16-byte-multiple blocks */
   uint32_t fold_max_bytes; /* default 64 MiB; 0 = off: rings and chains at every size.  A collective whose largest buffer per
-                              rank is smaller runs in fold steps instead of the steps of its ring or chain (an all-gather
-                              or reduce-scatter: if its blocks are 16-byte multiples).  Ring steps depend on one another
+                              rank is smaller runs in fold steps instead of the steps of its ring or chain (an all-gather:
+                              if its blocks are 16-byte multiples, or 1 MiB and more).  Ring steps depend on one another
                               and cost a few microseconds each whatever the size, and a short message gives a channel
                               one slice, so nothing hides them; with all buffers in one HBM two steps that wait on all
                               ranks at once do the same work: (1) when every rank has submitted, each rank does its part
@@ -406,8 +406,8 @@ int dfx_plan_route(int nranks, const dfx_config* cfg, dfx_kind kind, size_t coun
  * counters, saved contexts, connector flag lines and slots) in a static device array of the library:
  * 32.5 MiB per GPU the library runs on, held until the process ends.  The call allocates nothing (no hipMalloc,
  * hipFree, stream, event or host allocation) and only enqueues work on hip_stream (NULL = the null stream).  A collective in
- * fold steps is one kernel, whose workgroups do every rank's part.  The others (one rank; an all-gather or reduce-scatter
- * whose blocks are no 16-byte multiples; a reduce on 64 ranks) are two: one that clears the array's control part and writes
+ * fold steps is one kernel, whose workgroups do every rank's part.  The others (one rank; an all-gather
+ * whose blocks are below 1 MiB and no 16-byte multiples; a reduce on 64 ranks) are two: one that clears the array's control part and writes
  * the submission entries, and the daemon kernel (at most nranks x min(32, 256 / nranks) workgroups, as many as the collective
  * has channels), which leaves by itself when every vrank's completion is posted and writes the outcome.  It returns when the
  * work is enqueued; the results are in recvbufs once the stream has reached the end of that work.

@@ -454,25 +454,28 @@ __device__ __forceinline__ uint32_t ctx_slot(uint32_t coll) { return (coll * 265
 // A gang's collectives lie 1 << gang_shift(R) lanes apart.
 __device__ __forceinline__ uint32_t gang_shift(uint32_t R) { return R < 2u ? 0u : 32u - (uint32_t)__builtin_clz(R - 1u); }
 
-// What a mover wave does for collective `c` of a gang: all rows of the workgroup's share, and the elements behind them where they are
-// its (a short span has no bytes before its rows).
+// What a mover wave does for collective `c` of a gang: all rows of the workgroup's share, and the elements before and behind them where
+// they are its (rows of a short span begin on 16 bytes of the recv buffers: fold_head).
 __device__ __forceinline__ void gang_move(const GangEntry& c, const u64* src_tab, const u64* dst_tab, uint32_t R, uint32_t lane) {
-  const uint32_t bytes = bcast0(c.bytes), index = bcast0(c.index), sharers = bcast0(c.sharers), end = bytes & ~15u;
+  const uint32_t bytes = bcast0(c.bytes), index = bcast0(c.index), sharers = bcast0(c.sharers);
+  const uint32_t off = (0u - bcast0((uint32_t)dst_tab[0])) & 15u, head = off < bytes ? off : bytes, end = head + ((bytes - head) & ~15u);
   const uint32_t dtype = bcast0(c.dtype), nsrc = bcast0(c.nsrc), ndst = bcast0(c.ndst);
   const int op = (int)(dtype >> 4), dt = nsrc == 1u ? DT_F16 : (int)(dtype & 15u);     // (copies: every element type is a multiple of 2 bytes)
   const uint32_t row = fold_row_bytes(nsrc == 1u, R);
-  for (uint32_t at = index * row; at < end; at += sharers * row) {
+  for (uint32_t at = head + index * row; at < end; at += sharers * row) {
     if (nsrc == 1u) fold_row<DT_F16>(src_tab, 1u, dst_tab, ndst, at, row, end, lane, OP_SUM);
     else if (dt == DT_F32) fold_row<DT_F32>(src_tab, nsrc, dst_tab, ndst, at, row, end, lane, op);
     else if (dt == DT_BF16) fold_row<DT_BF16>(src_tab, nsrc, dst_tab, ndst, at, row, end, lane, op);
     else if (dt == DT_F16) fold_row<DT_F16>(src_tab, nsrc, dst_tab, ndst, at, row, end, lane, op);
     else fold_row<DT_I32>(src_tab, nsrc, dst_tab, ndst, at, row, end, lane, op);
   }
-  if (index == 0 && end < bytes) {
-    if (dt == DT_F32) fold_ends<DT_F32>(src_tab, nsrc, dst_tab, ndst, end, bytes, lane, op);
-    else if (dt == DT_BF16) fold_ends<DT_BF16>(src_tab, nsrc, dst_tab, ndst, end, bytes, lane, op);
-    else if (dt == DT_F16) fold_ends<DT_F16>(src_tab, nsrc, dst_tab, ndst, end, bytes, lane, op);
-    else fold_ends<DT_I32>(src_tab, nsrc, dst_tab, ndst, end, bytes, lane, op);
+  for (uint32_t behind = 0; behind < 2u; ++behind) {
+    const uint32_t at = behind ? end : 0u, stop = behind ? bytes : head;
+    if (at >= stop || index != (behind ? 0u : sharers - 1u)) continue;
+    if (dt == DT_F32) fold_ends<DT_F32>(src_tab, nsrc, dst_tab, ndst, at, stop, lane, op);
+    else if (dt == DT_BF16) fold_ends<DT_BF16>(src_tab, nsrc, dst_tab, ndst, at, stop, lane, op);
+    else if (dt == DT_F16) fold_ends<DT_F16>(src_tab, nsrc, dst_tab, ndst, at, stop, lane, op);
+    else fold_ends<DT_I32>(src_tab, nsrc, dst_tab, ndst, at, stop, lane, op);
   }
 }
 
@@ -639,7 +642,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
         rows.begin(fresh, wave * sharers + index);
         Span sp;
         sp.head = bcast0(j.head); sp.end = sp.head + ((jbytes - sp.head) & ~15u);
-        const bool front = fresh && index + 1 == sharers && wave + 1 == DFX_FOLD_WAVES, tail = (jbytes & 15u) && fresh && index == 0 && wave == 0;
+        const bool front = fresh && index + 1 == sharers && wave + 1 == DFX_FOLD_WAVES, tail = sp.end < jbytes && fresh && index == 0 && wave == 0;
         sp.ends_at = front ? 0u : sp.end;
         sp.ends = front ? sp.head : tail ? jbytes : 0u;
         fold_dispatch((int)bcast0((uint32_t)j.dtype), sh.tab_src[seen & 1], bcast0(j.nsrc), sh.tab_dst[seen & 1], bcast0(j.ndst), sp, rows, lane);
@@ -1371,7 +1374,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                     if (idx == 0) {            // (a gang of one is an ordinary job)
                       Job j;
                       j.fin = nullptr; j.fout = nullptr; j.sb = nullptr; j.rb = nullptr;
-                      j.bytes = g_.bytes; j.head = 0; j.index = vch; j.sharers = nch; j.limit = 0; j.fresh = 1; j.draw = 0;
+                      j.bytes = g_.bytes; j.head = fold_head(g_.dst, g_.bytes, nch); j.index = vch; j.sharers = nch; j.limit = 0; j.fresh = 1; j.draw = 0;
                       j.nsrc = cnt > 1u ? 0u : nsrc; j.ndst = ndst; j.dtype = (int)dt; j.coll = g_.coll; j.prim = 0;
                       j.gang = cnt > 1u ? cnt : 0u;
                       sh.job[fs] = j;

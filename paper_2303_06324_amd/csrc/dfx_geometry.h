@@ -127,6 +127,19 @@ DFX_HD uint64_t fold_chunk_elems(int kind, uint64_t count, uint64_t block, uint3
   return count;                                                                 // (a block per rank)
 }
 
+// Bytes at the front of a span that come before its first row: rows begin on 128-byte lines of the recv
+// buffers.  A region begins at any multiple of 16 bytes (the chunk of an all-reduce, the block of an all-gather), and rows
+// counted from there end inside a line, of which two waves then write a part each, straight to memory.  us per call, fp32,
+// regions at odd multiples of 16 bytes, rows from the region's start -> from the line (= regions on lines): all-gather of 64 MiB
+// 192 -> 132 (R = 8), 158 -> 96 (R = 6), all-reduce of 25 MiB 98 -> 92, broadcast of 110 MiB 306 -> 205 (R = 8).
+// Short spans keep their rows at the front: the round trip for the bytes before would cost what whole lines gain (64 KiB,
+// R = 8: 0.4 us; a wave has four rows from 32 KiB per workgroup on).  Blocks that are no 16-byte multiples begin anywhere; their rows
+// begin on 16 bytes of the recv buffers all the same, so that it is the loads that are not aligned and never the stores.
+DFX_HD uint32_t fold_head(uint64_t dst, uint32_t bytes, uint32_t nchan) {
+  const uint32_t head = (uint32_t)(0u - dst) & (bytes >= nchan << 15 ? 127u : 15u);
+  return head < bytes ? head : bytes;
+}
+
 // Sweeps.  Long messages leave the caches behind, and then it matters that few places of the memory are open at once: with a
 // region per rank the ranks move along R x 2R stretches of the buffers.  In a sweep all ranks go through the regions one
 // after the other, 2R stretches in all: the rows of all regions are numbered through, and of every R x W of them (W: mover
@@ -146,7 +159,7 @@ DFX_HD FoldRegion sweep_region(int kind, uint64_t longest, uint64_t total, uint3
   o.len = (uint32_t)(at >= total ? 0u : total - at < longest ? total - at : longest);
   o.src = kind == KIND_AG ? 0u : at;
   o.dst = kind == KIND_RS ? 0u : at;
-  o.head = o.len >= 128u ? (uint32_t)(0u - o.dst) & 127u : 0u;      // (rows on lines of the recv buffers: fold_head)
+  o.head = fold_head(o.dst, o.len, o.len >= 128u ? 0u : 1u);      // (rows on lines of the recv buffers; of the shortest, on 16 bytes)
   o.end = o.head + ((o.len - o.head) & ~15u);
   return o;
 }
@@ -214,16 +227,6 @@ DFX_HD FoldGeom fold_geometry(uint64_t len, uint64_t src, uint64_t dst, uint32_t
   o.src = src + lo; o.dst = dst + lo;
   o.bytes = n < span ? (uint32_t)n : span;
   return o;
-}
-// Bytes at the front of a span that come before its first row, a multiple of 16: rows begin on 128-byte lines of the recv
-// buffers.  A region begins at any multiple of 16 bytes (the chunk of an all-reduce, the block of an all-gather), and rows
-// counted from there end inside a line, of which two waves then write a part each, straight to memory.  us per call, fp32,
-// regions at odd multiples of 16 bytes, rows from the region's start -> from the line (= regions on lines): all-gather of 64 MiB
-// 192 -> 132 (R = 8), 158 -> 96 (R = 6), all-reduce of 25 MiB 98 -> 92, broadcast of 110 MiB 306 -> 205 (R = 8).
-// Short spans keep their rows at the front: the round trip for the bytes before would cost what whole lines gain (64 KiB,
-// R = 8: 0.4 us; a wave has four rows from 32 KiB per workgroup on).
-DFX_HD uint32_t fold_head(uint64_t dst, uint32_t bytes, uint32_t nchan) {
-  return bytes >= nchan << 15 ? (uint32_t)(0u - dst) & 127u : 0u;
 }
 DFX_HD FoldGeom fold_geometry(const DfxCooked& S, uint32_t g) {
   return fold_geometry(S.count, S.block_elems, S.part_elems, S.slice_elems, (S.bc_pos & DFX_CTX_DRAWN) != 0, g);

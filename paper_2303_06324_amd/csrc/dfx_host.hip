@@ -393,10 +393,15 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   const uint64_t per16 = 16 / eb;
   // ring chunk: all-reduce cuts the message into R contiguous chunks of ceil(N/R) elements
   // rounded up to 16 bytes; the other kinds move blocks of `count`
-  // Fold steps (see dfx_config.fold_max_bytes): every kind whose largest per-rank buffer is below the limit; the blocks
-  // of an all-gather / reduce-scatter must be 16-byte multiples (they are read with 16-byte vectors where they lie).
+  // Fold steps (see dfx_config.fold_max_bytes): every kind whose largest per-rank buffer is below the limit.  Blocks of an
+  // all-gather / reduce-scatter that are no 16-byte multiples begin anywhere: stores stay aligned (fold_head), loads need not be.  us,
+  // R = 8, as a ring -> in fold steps: reduce-scatter of 8 KiB 45 -> 15, 16 MiB 109 -> 39, 128 MiB 505 -> 230 (bf16, blocks at odd
+  // multiples of 2 bytes: 503 -> 243), all-gather of 9 MiB 73 -> 24, 64 MiB 256 -> 112, 128 MiB 494 -> 202; allocation-free
+  // reduce-scatter of 16 MiB 133 -> 33.  All-gathers of such blocks below 1 MiB stay rings of R primitives per slice, as dfx_coll_info
+  // has always told their callers: the line is one of behaviour, not of speed.
   const uint64_t largest_bytes = (kind == DFX_ALLGATHER || kind == DFX_REDUCESCATTER) ? count * eb * R : count * eb;
-  const bool blocks_ok = !(kind == DFX_ALLGATHER || kind == DFX_REDUCESCATTER) || (count * eb) % 16 == 0;
+  const bool odd_blocks = (kind == DFX_ALLGATHER || kind == DFX_REDUCESCATTER) && (count * eb) % 16 != 0;
+  const bool blocks_ok = !odd_blocks || kind == DFX_REDUCESCATTER || count * eb >= (1u << 20);
   // (A reduce on 64 ranks stays a chain.  The step's tables would hold it, but it has never run in fold steps: a form of the
   // look-up that was to cover it once faulted the GPU, in another collective, and why was never shown.)
   const bool fold = R > 1 && cfg.fold_max_bytes && largest_bytes < cfg.fold_max_bytes && blocks_ok && !(kind == DFX_REDUCE && R > 63);
@@ -488,7 +493,8 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   // chains with direct steps -> this, a region per rank): all-reduce 256 MiB fp32 1545 -> 806, reduce-scatter 128 MiB fp32
   // 496 -> 268, broadcast 100 MiB bf16 472 -> 200 (as sweeps, below: 739, 232 with blocks off the lines, 187).
   // With fold_max_bytes = 0 the rings and chains run at every size.
-  if ((t.flags & DFX_SQE_DIRECT) && !fold && cfg.fold_max_bytes && blocks_ok && !(kind == DFX_REDUCE && R > 63)) {
+  const bool odd_long = R > 1 && odd_blocks && cfg.direct && largest_bytes >= (kind == DFX_ALLGATHER ? 1ull : 2ull) * cfg.direct_min_bytes;      // (direct steps but for their blocks)
+  if (((t.flags & DFX_SQE_DIRECT) || odd_long) && !fold && cfg.fold_max_bytes && blocks_ok && !(kind == DFX_REDUCE && R > 63)) {
     // 128 KiB per source and workgroup (drawn rows: twice that at most), about 100 us at 2 x 8 streams; priority ordering
     // lets nothing longer than its look-again budget get ahead of an urgent collective
     const uint64_t job = cfg.fold_slice_bytes ? cfg.fold_slice_bytes : (cfg.order_policy == 1 ? 32u << 10 : 128u << 10);
@@ -497,7 +503,7 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
     const uint64_t bytes = std::min<uint64_t>(std::min<uint64_t>(job, ((1ull << 30) / C) & ~15ull), share * eb);
     const uint64_t jobs = std::max<uint64_t>(1, ceil_div(share, bytes / eb));
     if (jobs <= 0xfffffffeull) {       // (more than the walk counts, with slices of a few bytes: the ring or chain runs)
-      t.flags |= DFX_SQE_FOLD;
+      t.flags |= DFX_SQE_DIRECT | DFX_SQE_FOLD;
       t.slice_elems = (uint32_t)(bytes / eb);
       t.rounds = (uint32_t)jobs;
       t.nprim = DFX_FOLD_NPRIM;
@@ -1403,7 +1409,9 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
               // the regions that the buffers hold, and the order of the tables' entries in each; the rows themselves: below
               for (uint32_t c = 0; c < sweep_regions(kind, R); ++c) {
                 const FoldRegion f = sweep_region(kind, S.count, S.block_elems, c);
-                if (f.len && ((f.src | f.dst) & 15u)) return fail("region %u: 16-byte accesses at offsets %llu, %llu", c, (unsigned long long)f.src, (unsigned long long)f.dst);
+                if (f.head < f.end && ((f.dst + f.head) & 15u)) return fail("region %u: 16-byte stores at offset %llu", c, (unsigned long long)(f.dst + f.head));
+                if (f.len && ((f.src | f.dst | f.len) & (eb - 1u))) return fail("region %u: a part of an element", c);
+                if (f.head > f.len || f.head > 127u || f.end > f.len || f.len - f.end > 15u) return fail("region %u: rows %u .. %u of %u bytes", c, f.head, f.end, f.len);
                 if (f.len && (f.src + f.len > send_bytes || f.dst + f.len > recv_bytes)) return fail("region %u leaves the buffers", c);
                 const uint32_t first = sweep_first(sweep_regions(kind, R), c, r, R);
                 for (uint32_t k = 0; k < R; ++k) {
@@ -1420,7 +1428,7 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
             // (drawn rows: any wave may take any row behind the first ones; walked here as if they were dealt, once -- that
             // every row is taken exactly once is checked below)
             const bool walk = !(t.flags & DFX_SQE_DRAWN) || g == 0;
-            if (fg.bytes && ((src | dst) & 15u)) return fail("rank %u channel %u step %u: 16-byte accesses at offsets %llu, %llu", r, v, p, (unsigned long long)src, (unsigned long long)dst);
+            if ((src | dst | fg.bytes) & (eb - 1u)) return fail("rank %u channel %u step %u: a part of an element at offsets %llu, %llu", r, v, p, (unsigned long long)src, (unsigned long long)dst);
             if (fg.bytes && src + fg.bytes > send_bytes) return fail("rank %u channel %u: read of send buffers %llu+%u of %llu", r, v, (unsigned long long)src, fg.bytes, (unsigned long long)send_bytes);
             if (fg.bytes && dst + fg.bytes > recv_bytes) return fail("rank %u channel %u: write of recv buffers %llu+%u of %llu", r, v, (unsigned long long)dst, fg.bytes, (unsigned long long)recv_bytes);
             // entries: every rank once, the last one this rank (the root), which is the only one a copy reads and a
@@ -1433,6 +1441,8 @@ int dfx_check_geometry(int nranks, const dfx_config* ucfg, dfx_kind kind, size_t
               if ((!to_all && k + 1 < R) || !walk) continue;
               const uint32_t head = fold_head(dst, fg.bytes, t.nchan), end = head + ((fg.bytes - head) & ~15u);
               if (fg.bytes / t.nchan >= (32u << 10) && (dst + head) % 128) return fail("rank %u channel %u step %u: rows from offset %llu of the recv buffers, no 128-byte line", r, v, p, (unsigned long long)(dst + head));
+              if (head < end && ((dst + head) & 15u)) return fail("rank %u channel %u step %u: 16-byte stores at offset %llu", r, v, p, (unsigned long long)(dst + head));
+              if (head > 127u || fg.bytes - end > 15u) return fail("rank %u channel %u step %u: %u bytes before and %u behind the rows", r, v, p, head, fg.bytes - end);
               if (head && v + 1 == t.nchan) written[peer].push_back({dst, dst + head});
               for (uint32_t wv = 0; wv < DFX_FOLD_WAVES; ++wv)
                 for (uint64_t at = head + (uint64_t)(wv * t.nchan + v) * row; at < end; at += (uint64_t)waves * row)
@@ -1812,7 +1822,7 @@ int dfx_collective_noalloc(int nranks, dfx_kind kind, size_t count, dfx_dtype dt
   unsigned char* base = nd->ptr;
   // In fold steps: one plain kernel (dfx_once.hip), whose launch is all the waiting there is.  By way of the daemon (a kernel that
   // fills its queues, the daemon) -> this, us per call, fp32, R = 8: all-reduce of 64 KiB 27.2 -> 9.5, 4 MiB 40 -> 16.5, 64 MiB 234 -> 191,
-  // reduce-scatter of 16 MiB 61.5 -> 29.8.  One rank, blocks that are no 16-byte multiples and the reduce on 64 ranks take the daemon.
+  // reduce-scatter of 16 MiB 61.5 -> 29.8.  One rank, all-gathers of blocks below 1 MiB that are no 16-byte multiples and the reduce on 64 ranks take the daemon.
   if (tmpl.flags & DFX_SQE_FOLD) {
     static_assert(DFX_NA_MAX_RANKS == DFX_ONCE_MAX_RANKS, "buffers of every rank");
     DfxFoldOnce o;

@@ -56,7 +56,7 @@ extern "C" __global__ void __launch_bounds__(DFX_ONCE_THREADS, 2) dfx_fold_once_
     sp.head = fold_head(fg.dst, fg.bytes, e.nchan);
     sp.end = sp.head + ((fg.bytes - sp.head) & ~15u);
     sp.ends_at = ow.head ? 0u : sp.end;
-    sp.ends = ow.head ? sp.head : ow.tail && (fg.bytes & 15u) ? fg.bytes : 0u;
+    sp.ends = ow.head ? sp.head : ow.tail && sp.end < fg.bytes ? fg.bytes : 0u;
     fold_dispatch(dtype, tab_src, copies ? 1u : R, tab_dst, to_all ? R : 1u, sp, rows, lane);
   }
   // the outcome, behind everybody's stores: the last workgroup writes it

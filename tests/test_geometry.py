@@ -120,3 +120,22 @@ def test_more_jobs_than_the_walk_counts():
 def test_it_refuses_what_it_cannot_check():
     assert dfx.check_geometry(8, dfx.BROADCAST, 1024, dfx.F32, root=9) != ""
     assert dfx.check_geometry(8, dfx.ALLREDUCE, 1024, dfx.F32, wg_map=3) != ""
+
+
+@pytest.mark.parametrize("R", [2, 3, 4, 8, 16, 33, 64])
+@pytest.mark.parametrize("kind", [dfx.ALLGATHER, dfx.REDUCESCATTER])
+def test_blocks_that_are_no_16_byte_multiples(kind, R):
+    """Which of them run in fold steps (reduce-scatters; all-gathers from 1 MiB per block on), and that their rows and the bytes before
+    and behind them tile the recv buffers, one channel to many, one job to several, dealt, drawn and swept."""
+    cmax = min(32, 256 // R)
+    for knobs in (dict(), dict(max_channels=1), dict(max_channels=3, fold_max_bytes=1 << 16, direct_min_bytes=0), dict(order_policy=1), dict(fold_slice_bytes=4096)):
+        cfg = _cfg(**{**dict(max_channels=cmax), **knobs})
+        for dtype, eb in ((dfx.F32, 4), (dfx.F16, 2)):
+            for nbytes in (eb, 16 + eb, 2048 - eb, 2048 + eb, 32768 - eb, 33000, 100002, 524286, (1 << 20) - eb, (1 << 20) + eb, (5 << 20) + 3 * eb):
+                n = nbytes // eb
+                if n * eb % 16 == 0:
+                    n += 1
+                route = dfx.plan_route(R, kind, n, dtype, 0, cfg)
+                assert ("fold" in route) == (kind == dfx.REDUCESCATTER or n * eb >= 1 << 20), (knobs, n, route)
+                assert dfx.check_geometry(R, kind, n, dtype, op=dfx.MAX if kind == dfx.REDUCESCATTER else dfx.SUM, cfg=cfg) == "", (knobs, dtype, n)
+    assert "fold" not in dfx.plan_route(R, kind, (1 << 20) + 1, dfx.F32, 0, _cfg(fold_max_bytes=0, max_channels=cmax))

@@ -16,9 +16,11 @@ def __getattr__(name):
         raise AttributeError(name)          # submodules are imported by the import system itself
     binding = importlib.import_module(".binding", __name__)     # raises ImportError without libdfx.so
     try:
-        return getattr(binding, name)
+        value = getattr(binding, name)
     except AttributeError:
         raise AttributeError(f"module {__name__!r} has no attribute {name!r}") from None
+    globals()[name] = value                 # found without this function from now on: by way of it every use of a name cost 2 - 5 us
+    return value
 
 
 def __dir__():

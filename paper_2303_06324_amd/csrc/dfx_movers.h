@@ -32,6 +32,7 @@ typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 // cache-policy operand of the buffer instructions (gfx940+): bit 0 = sc0, bit 4 = sc1
 constexpr int AUX_CACHED = 0;    // ordinary cached access (per-CU cache, write-back in this XCD's L2)
 constexpr int AUX_DEVICE = 16;   // sc1: device scope, coherent across the XCDs' L2s
+constexpr int AUX_SYSTEM = 17;   // sc0 | sc1: system scope, nothing of it is taken from a cache
 constexpr int AUX_STREAM = 18;   // sc1 | nt: the same for what is read once: the caches on the way need not keep it
 
 // ------------------------------------------------------------------------------------------

@@ -369,7 +369,7 @@ struct SweepJob { uint32_t kind, R, rank, longest, at, pad; u64 total; };   // a
 // is no bandwidth but the chain of each -- lines polled, job posted, a row or a few loaded, folded and stored, the last wait polled --,
 // and one after the other that took 5.3 us of which the movers worked 2.5.  Together they share the poll (a lane per collective and
 // rank) and run side by side, a mover wave each.  1024 all-reduces of 4 - 64 KiB, every rank in its own order: R = 8 531 -> 378 us,
-// R = 4 415 -> 215, R = 2 480 -> 195; 256 of them 145 -> 107, 114 -> 68, 145 -> 67; 64 of them 57 -> 48, 45 -> 37, 42 -> 32.
+// R = 4 415 -> 215, R = 2 480 -> 195 (R = 8 since then 266, of which the data takes 75); 256 of them 145 -> 107, 114 -> 68, 145 -> 67; 64 of them 57 -> 48, 45 -> 37, 42 -> 32.
 // GangRun is what the scan leaves of a runnable one (its lane has the context in registers), GangEntry what a mover wave needs of it.
 struct alignas(16) GangRun {
   u64 line0, counters, src, dst;     // the channel's line of rank 0, its shared counters; offsets of the region in the buffers
@@ -758,7 +758,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           // the one before when it submits the next, so the slot is free and belongs to this workgroup: nothing to find, to
           // wait for or to write back.  (Relaxed: what the entry vouches for is in memory, by the fence above or to begin with.)
           // The CAS into a slot that was looked for was a round trip to host memory each, 17.6 of them per us over all
-          // workgroups at most, and 1024 small all-reduces on eight ranks took 668 us, now 537; one of 8 KiB 17.5, now 16.9.
+          // workgroups at most, and 1024 small all-reduces on eight ranks took 668 -> 537 us by it, one of 8 KiB 17.5 -> 16.9.
           const u64 v = (1ull << 63) | ((u64)(c_seq & 0x7fffffffu) << 32) | c_coll;
           __hip_atomic_store(global_ptr(&cqbase[c_coll]), v, __ATOMIC_RELAXED, SCOPE_SYSTEM);
         } else {
@@ -1120,8 +1120,8 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             const bool lone = mine_mask != 0 && (mine_mask & (mine_mask - 1)) == 0 && __ballot(mine && q_fold) != 0;
             // Such an entry with all ranks' buffers, and nothing else to do: its first step with data goes to the movers at once, straight
             // from the entry; the context and what the other ranks may want to see follow while the data moves.  (By way of the
-            // context, the pass over the queue and the other ranks' lines the job was posted 3.4 us later: all-reduce of 8 KiB 16.9 us,
-            // now 15.0, 1 MiB bf16 22.1, now 19.6, 25 MiB bf16 97.8, now 93.8, reduce of 4 MiB on four ranks 19.4, now 16.6.)  The table serves the further jobs until another fetch.
+            // context, the pass over the queue and the other ranks' lines the job was posted 3.4 us later: all-reduce of 8 KiB 16.9 ->
+            // 15.0, 1 MiB bf16 22.1 -> 19.6, 25 MiB bf16 97.8 -> 93.8, reduce of 4 MiB on four ranks 19.4 -> 16.6.)  The table serves the further jobs until another fetch.
             peers_of = 0;
             uint32_t first_round = 0, first_prim = 0;      // where the invocation's walk goes on
             bool through = false;                          // ... nowhere: it needs no place in the queue

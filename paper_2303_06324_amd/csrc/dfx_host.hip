@@ -1830,7 +1830,7 @@ int dfx_collective_noalloc(int nranks, dfx_kind kind, size_t count, dfx_dtype dt
 
   unsigned char* base = nd->ptr;
   // In fold steps: one plain kernel (dfx_once.hip), whose launch is all the waiting there is.  By way of the daemon (a kernel that
-  // fills its queues, the daemon) -> this, us per call, fp32, R = 8: all-reduce of 64 KiB 27.2 -> 9.5, 4 MiB 40 -> 16.5, 64 MiB 234 -> 191,
+  // fills its queues, the daemon) -> this, us per call, fp32, R = 8: all-reduce of 64 KiB 27.2 -> 9.5 (5.2 since the package looks its names up once), 4 MiB 40 -> 16.5, 64 MiB 234 -> 191,
   // reduce-scatter of 16 MiB 61.5 -> 29.8.  One rank, all-gathers of blocks below 1 MiB that are no 16-byte multiples and the reduce on 64 ranks take the daemon.
   if (tmpl.flags & DFX_SQE_FOLD) {
     static_assert(DFX_NA_MAX_RANKS == DFX_ONCE_MAX_RANKS, "buffers of every rank");

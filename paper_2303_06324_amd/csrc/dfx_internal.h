@@ -188,8 +188,8 @@ struct DfxFoldOnce {
 };
 // Every call that reports an outcome counts in a word of its own, in turn: its last workgroup puts the word back to 0, and all the
 // same a call clears the word half a round ahead.  With one word for all and nobody to clear it, two calls that overlapped once (which is the caller's mistake) left a residue in it, and every later call reported too early or never.
-// A captured call is replayed with the same word, whenever: it has a kernel behind it instead.  (Which costs 3 us: 15.4 -> 18.6 us
-// per call of 64 KiB, R = 8, was every call to have one.)
+// A captured call is replayed with the same word, whenever: it has a kernel behind it instead.  (Which costs 3 us per call, was
+// every call to have one.)
 #define DFX_ONCE_COUNTERS 1024u
 
 #endif

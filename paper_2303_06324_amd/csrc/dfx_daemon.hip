@@ -45,6 +45,7 @@
 #include "dfx_internal.h"
 #include "dfx_geometry.h"
 #include "dfx_movers.h"
+#include "dfx_rules.h"
 
 namespace {
 
@@ -814,7 +815,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
     uint32_t rd_old = 0;       // lane 0: readers of the slot before this workgroup
     u64 rd_idx = 0;            // the entry
     bool rd_open = false;
-    uint32_t peers_of = 0;     // the collective (id + 1) whose buffers are in sh.peer
+    uint32_t peers_of = 0, peers_seq = 0;     // the collective (id + 1) whose buffers are in sh.peer, and its invocation (table_serves)
     bool ctx_open = false;     // the stores of a lone collective's context may still be under way
     auto free_slot = [&](uint32_t readers_before, u64 idx) {
       // (the counter runs on from generation to generation, modulo 2^32: no reset to wait for before the slot is used again)
@@ -1121,12 +1122,13 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             // Such an entry with all ranks' buffers, and nothing else to do: its first step with data goes to the movers at once, straight
             // from the entry; the context and what the other ranks may want to see follow while the data moves.  (By way of the
             // context, the pass over the queue and the other ranks' lines the job was posted 3.4 us later: all-reduce of 8 KiB 16.9 ->
-            // 15.0, 1 MiB bf16 22.1 -> 19.6, 25 MiB bf16 97.8 -> 93.8, reduce of 4 MiB on four ranks 19.4 -> 16.6.)  The table serves the further jobs until another fetch.
+            // 15.0, 1 MiB bf16 22.1 -> 19.6, 25 MiB bf16 97.8 -> 93.8, reduce of 4 MiB on four ranks 19.4 -> 16.6.)  The table serves the invocation's further jobs until another fetch.
             peers_of = 0;
             uint32_t first_round = 0, first_prim = 0;      // where the invocation's walk goes on
             bool through = false;                          // ... nowhere: it needs no place in the queue
             if (lone && with_table && mine_mask == 1ull) {
               peers_of = bcast0(c_id) + 1u;
+              peers_seq = bcast0(q.seq);
               if (qlen == 0 && posted == retired) {
                 const uint32_t e_rounds = bcast0(q.rounds), e_flags = bcast0(q.flags), e_nchan = bcast0(q.nchan), e_vch = bcast0(my_vch);
                 const bool e_drawn = (e_flags & DFX_SQE_DRAWN) != 0;
@@ -1134,7 +1136,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                                                   bcast64((uint32_t)q.part_elems, (uint32_t)(q.part_elems >> 32)), bcast0(q.slice_elems), e_drawn, 0);
                 const u64 line0 = (u64)(uintptr_t)a.pool + bcast64((uint32_t)q.conn_off, (uint32_t)(q.conn_off >> 32)) + (u64)e_vch * DFX_FLAG_STRIDE;
                 const bool e_sweep = (e_flags & DFX_SQE_SWEEP) != 0;
-                const FoldStep st = {(int)bcast0(q.kind), (int)bcast0((uint32_t)q.dtype | ((uint32_t)q.op << 4)), peers_of - 1u, bcast0(q.seq), e_nchan, e_vch,
+                const FoldStep st = {(int)bcast0(q.kind), (int)bcast0((uint32_t)q.dtype | ((uint32_t)q.op << 4)), peers_of - 1u, peers_seq, e_nchan, e_vch,
                                      e_sweep ? bcast0(q.slice_elems) : bcast0(q.slot_bytes), e_sweep ? FRESH_SWEEP | 1u : 1u, line0, fold_line(line0, 0, R, e_nchan), e_drawn,
                                      e_sweep, 0, bcast0((uint32_t)q.count), bcast64((uint32_t)q.block_elems, (uint32_t)(q.block_elems >> 32))};
                 post_fold(st, fg, ((u64)peer.y << 32) | peer.x, ((u64)peer.w << 32) | peer.z);
@@ -1624,7 +1626,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           const bool sweep = (bcp & DFX_CTX_SWEEP) != 0;
           const FoldStep st = {kind, dtype, coll, inv_seq, inv_nchan, vch, sweep ? s_slice : row_limit, sweep ? FRESH_SWEEP | (g == 0) : !drawn || g == 0,
                                s_fin, s_in, drawn, sweep, g, bcast0(v1.x), bcast64(v1.z, v1.w)};
-          if (peers_of == coll + 1u) {
+          if (table_serves(peers_of, peers_seq, coll, inv_seq)) {
             // The entry came with every rank's buffers, so every rank has submitted: there is nothing to wait for.  Without the
             // others' lines (a store and its way to memory, a load or two) a 25 MiB all-reduce takes 96.5 us instead of 97.8.
             if (!flight_free(hot.order_policy == 1 ? 1u : 2u)) { stop = STOP_ABORT; have = false; continue; }

@@ -1,0 +1,20 @@
+// Rules of the scheduler that stand on their own: pure functions of their arguments, compiled for the device (the kernel) and for the
+// host (tests/rules/rules_check.cpp walks them without a GPU).
+#ifndef DFX_RULES_H
+#define DFX_RULES_H
+
+#include <stdint.h>
+
+#if defined(__HIPCC__)
+#define DFX_RULE __host__ __device__ __forceinline__
+#else
+#define DFX_RULE inline
+#endif
+
+// The table of buffers that came with a lone entry (DfxPeer) stays in LDS for the further jobs of that invocation: held_of is its
+// collective + 1 (0 = no table), held_seq the invocation.  The id alone does not say whose buffers they are: a fetch that goes on behind its
+// first 64 entries may take the next invocation of the same collective, with buffers of its own, while the table of the one before,
+// whose only job went to the movers at the head of the fetch, still lies there.
+DFX_RULE bool table_serves(uint32_t held_of, uint32_t held_seq, uint32_t coll, uint32_t seq) { return held_of == coll + 1u && held_seq == seq; }
+
+#endif

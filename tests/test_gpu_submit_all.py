@@ -2,7 +2,7 @@
 without having seen the others.  Checked where that can go wrong: buffers that change from call to call under the same ids (the
 tables of a reused SQ slot), calls that overtake one another (two or more entries in a queue, a table replaced while its collective
 still waits), single submissions and rings in between, several jobs, priority ordering, rank counts with and without a data mover
-of their own, an SQ of two entries.  int32, sums and copies: exact."""
+of their own, an SQ of two entries, a table that outlives its invocation.  int32, sums and copies: exact."""
 import numpy as np
 import pytest
 
@@ -97,3 +97,52 @@ def test_more_channels_than_a_wave_has_lanes(max_channels, count):
     want = send[0] + send[1]
     for r in range(R):
         assert torch.equal(recv[r], want), r
+
+
+@pytest.mark.parametrize("R,n", [(2, 700), (8, 300)])
+def test_a_table_is_for_its_own_invocation(R, n):
+    """A collective of several channels, submitted on all ranks at once ahead of a run of others that a daemon finds in the SQ when it
+    comes: its one job goes to the movers at the head of the fetch.  It is submitted anew, with other buffers, as soon as it is
+    complete, while workgroups may still fetch the run that its table came with (int32: exact)."""
+    import torch
+    import paper_2303_06324_amd as dfx
+    from paper_2303_06324_amd import harness as gh
+    count, small = 8 * 4 * 512 + 5, 260
+    g = torch.Generator(device="cuda").manual_seed(R)
+    def sends(m):
+        return [torch.randint(-1000, 1000, (m,), generator=g, device="cuda", dtype=torch.int32) for _ in range(R)]
+    def recvs(m):
+        return [torch.full((m,), -7, device="cuda", dtype=torch.int32) for _ in range(R)]
+    sets = [(sends(count), recvs(count)) for _ in range(4)]
+    others = (sends(small), [torch.full((n, small), -7, device="cuda", dtype=torch.int32) for _ in range(R)])
+    torch.cuda.synchronize()
+    ctx = dfx.Context(R, gh.make_config(max_channels=4, chan_spread=0, chan_min_bytes=1024))
+    try:
+        ctx.prepare(0, dfx.ALLREDUCE, count, dfx.I32)
+        assert ctx.coll_info(0) == dict(ctx.coll_info(0), nchan=4, rounds=1, nprim=2)
+        for i in range(n):
+            ctx.prepare(1 + i, dfx.ALLREDUCE, small, dfx.I32)
+        ptrs = [ctx.make_all([t.data_ptr() for t in s], [t.data_ptr() for t in d]) for s, d in sets]
+        bursts = [ctx.make_burst(list(range(1, n + 1)), [others[0][r].data_ptr()] * n, [others[1][r][i].data_ptr() for i in range(n)]) for r in range(R)]
+        for it in range(6):
+            for s, d in sets:
+                for t in d:
+                    t.fill_(-7)
+            torch.cuda.synchronize()
+            assert ctx.submit_all(0, ptrs[0]) == dfx.OK
+            for r in range(R):
+                assert ctx.submit_burst(r, bursts[r]) == n
+            for k in range(1, 4):
+                for r in range(R):
+                    assert ctx.wait(r, 0, 20.0) == dfx.OK
+                assert ctx.submit_all(0, ptrs[k]) == dfx.OK
+            assert ctx.wait_all(20.0) == dfx.OK
+            assert ctx.stop() == dfx.OK                              # (the next run is found by a daemon that comes)
+            for k, (s, d) in enumerate(sets):
+                total = torch.stack(s).sum(0).to(torch.int32)
+                assert all(torch.equal(t, total) for t in d), (it, k)
+    finally:
+        assert ctx.finalize() == dfx.OK
+    total = torch.stack(others[0]).sum(0).to(torch.int32)
+    for r in range(R):
+        assert bool((others[1][r] == total).all()), r

@@ -99,7 +99,7 @@ typedef struct {
   uint32_t order_policy;   /* 0 = FIFO ordering, 1 = priority ordering (Sec. 4.3): a fetched collective joins the queue
                               behind those of equal or higher priority, a scanned pass ranks the runnable collectives by
                               priority first, and the pass looks again (SQ probe, scan, ranking) after at most 32 KiB of
-                              posted work and keeps one fold step in flight instead of two, so that an urgent collective waits for
+                              posted work (short collectives that go to the movers as one job count together) and keeps one fold step in flight instead of two, so that an urgent collective waits for
                               little that was chosen before it came */
   uint32_t trace;          /* 1 = record context-switch latency samples (two clock reads per switch);
                               2 = also time the save / load parts and the wait / data / publish phases;
@@ -326,6 +326,11 @@ int dfx_stop(dfx_ctx* ctx);
 
 /* Counters of one vrank; out: host. Safe while the daemon runs (values may lag). */
 int dfx_stats(dfx_ctx* ctx, int rank, dfx_stats_t* out);
+
+/* For tests: which ways the scheduler of one vrank's workgroups took since dfx_init, up to max values into out (host).
+   0: jobs that several short collectives shared (gangs); 1: collectives moved in them; 2: most bytes per source of one of them.
+   Valid once the daemon has stopped or quit.  Returns the number of values written, or a negative status. */
+int dfx_counters(dfx_ctx* ctx, int rank, uint64_t* out, int max);
 
 /* Geometry of what runs for a prepared collective (for tests and the bench): channels; bytes of one slice (of one mover
    job's part of every source, where the collective runs in fold steps); slices (jobs) of a channel's share; primitives per

@@ -85,6 +85,7 @@ def _load() -> C.CDLL:
         "dfx_start": ([vp], i),
         "dfx_stop": ([vp], i),
         "dfx_stats": ([vp, i, C.POINTER(Stats)], i),
+        "dfx_counters": ([vp, i, C.POINTER(u64), i], i),
         "dfx_coll_info": ([vp, i] + [C.POINTER(C.c_uint32)] * 4, i),
         "dfx_last_launch_ms": ([vp, C.POINTER(C.c_float), C.POINTER(u64)], i),
         "dfx_trace_read": ([vp, C.c_uint32, C.POINTER(u64), C.c_uint32, C.POINTER(C.c_double)], i),
@@ -193,6 +194,15 @@ class Context:
         if rc != OK:
             raise DfxError(rc, "dfx_stats")
         return s.as_dict()
+
+    def counters(self, rank: int) -> dict:
+        """Which ways the scheduler took (for tests; dfx_counters), valid once the daemon has stopped or quit."""
+        names = ("gangs", "ganged", "gang_max_bytes")
+        buf = (C.c_uint64 * len(names))()
+        n = _lib.dfx_counters(self._h, rank, buf, len(names))
+        if n != len(names):
+            raise DfxError(n if n < 0 else ERR_INVALID_ARG, "dfx_counters")
+        return dict(zip(names, buf))
 
     def coll_info(self, coll_id: int) -> dict:
         v = [C.c_uint32() for _ in range(4)]

@@ -1172,6 +1172,25 @@ int dfx_stats(dfx_ctx* c, int rank, dfx_stats_t* out) {
   return DFX_OK;
 }
 
+int dfx_counters(dfx_ctx* c, int rank, uint64_t* out, int max) {
+  if (!c || rank < 0 || rank >= c->R || max < 0 || (max > 0 && !out)) return DFX_ERR_INVALID_ARG;
+  static const struct { int stat; bool largest; } kCounters[] = {{ST_GANGS, false}, {ST_GANGED, false}, {ST_GANG_MAX, true}};
+  const int n = std::min<int>(max, (int)(sizeof(kCounters) / sizeof(kCounters[0])));
+  std::lock_guard<std::mutex> lk(c->launch_mu);
+  DfxWgState* h = (DfxWgState*)c->pinned_tmp;
+  HIPCHK(c, hipMemcpyAsync(h, c->wgstate, (size_t)c->nwg * sizeof(DfxWgState), hipMemcpyDeviceToHost, c->side));
+  HIPCHK(c, hipStreamSynchronize(c->side));
+  for (int i = 0; i < n; ++i) {
+    out[i] = 0;
+    for (uint32_t wg = 0; wg < c->nwg; ++wg) {
+      if (wg_place(c->cfg.wg_map, wg, (uint32_t)c->R, c->cfg.max_channels).rank != (uint32_t)rank) continue;
+      const uint64_t v = h[wg].stat[kCounters[i].stat];
+      out[i] = kCounters[i].largest ? std::max(out[i], v) : out[i] + v;
+    }
+  }
+  return n;
+}
+
 int dfx_trace_read(dfx_ctx* c, uint32_t wg, uint64_t* out, uint32_t max, double* tick_us) {
   if (!c || !out || wg >= c->nwg) return DFX_ERR_INVALID_ARG;
   if (!c->trace) return 0;

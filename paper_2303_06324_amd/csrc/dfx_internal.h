@@ -17,7 +17,7 @@
 #define DFX_TRACE_N 4096        // context-switch latency samples kept per workgroup
 #define DFX_FLAG_STRIDE 128     // bytes per (edge, channel) flag pair: tail at +0, head at +64
 #define DFX_DIRECT_OFF 16       // in the tail's line: the sender's recv buffer (8 bytes), invocation + 1 (4), 0 (4); then the same for its send buffer
-#define DFX_NSTAT 24
+#define DFX_NSTAT 26
 #define DFX_CQ_CTL_WORDS 24      // 64-bit words of ring bookkeeping per vrank: reserve at 0, tail at 8, head at 16
 
 #define DFX_SQE_EXIT 1u
@@ -129,14 +129,15 @@ struct alignas(16) DfxWgState {
   uint32_t trace_n;      // trace samples written (monotone)
   uint64_t stat[DFX_NSTAT];
   uint64_t dbg[8];       // filled when the watchdog fires
-  uint64_t pad[6];
+  uint64_t pad[4];
 };
 
 enum { ST_PREEMPT = 0, ST_LOAD, ST_HIT, ST_SAVE, ST_LAZY, ST_POLLS, ST_PRIMS, ST_SQE, ST_CQE, ST_MAXQ, ST_PASSES, ST_QUITS,
        ST_T_WAIT, ST_T_DATA, ST_T_PUB, ST_SCAN_SKIPS,   // T_*: wall-clock ticks, only with trace on
        ST_T_CQE,                                         // ticks spent writing CQEs (always counted)
        ST_T_STAMP, ST_N_STAMP,                           // ticks of back-to-back clock reads and their number (trace 1, 2)
-       ST_T_SQE };                                       // ticks spent fetching SQEs: probe seen -> entries cooked and queued (always counted)
+       ST_T_SQE,                                         // ticks spent fetching SQEs: probe seen -> entries cooked and queued (always counted)
+       ST_GANGS, ST_GANGED, ST_GANG_MAX };               // gang jobs, collectives moved in them, most bytes of one gang's shares (dfx_counters)
 
 // dev_ctl words (device memory)
 // (abort and quit share one aligned 64-bit word: the scheduler reads both with one load; the host

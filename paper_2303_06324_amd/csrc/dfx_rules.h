@@ -17,4 +17,10 @@
 // whose only job went to the movers at the head of the fetch, still lies there.
 DFX_RULE bool table_serves(uint32_t held_of, uint32_t held_seq, uint32_t coll, uint32_t seq) { return held_of == coll + 1u && held_seq == seq; }
 
+// Whether another short collective goes with the gang in hand: spent, the bytes that the pass has handed to the movers, those of the gang's
+// members so far among them; share, its own; budget, what a pass hands them before the SQ and the queue are looked at again
+// (focus_bytes; under priority ordering 32 KiB at most).  A gang is one job that nothing overtakes, so the budget holds inside it as well;
+// the first member of a pass always goes.
+DFX_RULE bool gang_takes(uint32_t spent, uint32_t share, uint32_t budget) { return spent == 0 || (uint64_t)spent + share <= budget; }
+
 #endif

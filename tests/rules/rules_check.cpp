@@ -54,8 +54,32 @@ static void tables() {
         }
 }
 
+// Passes over a queue of runnable short collectives: each hands the movers gangs of up to `most` of them until its bytes are spent.
+static void gangs() {
+  for (uint32_t budget : {1u, 4096u, 20000u, 32u << 10, 128u << 10, 0xffffffffu})
+    for (uint32_t most : {1u, 2u, 8u, 16u})
+      for (uint32_t step = 0; step < 40; ++step) {
+        std::vector<uint32_t> share;
+        for (uint32_t i = 0; i < 64; ++i) share.push_back(16u + (i * 7919u * (step + 1u)) % (16u << 10) / 16u * 16u);
+        uint32_t passes = 0;
+        for (size_t at = 0; at < share.size(); ++passes) {
+          uint32_t spent = 0, went = 0;
+          for (bool full = false; at < share.size() && spent < budget && !full; ) {
+            const uint32_t first = spent;                  // (the gang: one job)
+            for (uint32_t n = 0; n < most && at < share.size(); ++n) {
+              if (!gang_takes(spent, share[at], budget)) { full = true; break; }
+              spent += share[at++]; ++went;
+            }
+            EXPECT(spent <= budget || (first == 0 && went == 1), "budget %u, gangs of %u: %u bytes handed to the movers", budget, most, spent);
+          }
+          EXPECT(went > 0, "budget %u: a pass without a job", budget);
+          if (!went) return;
+        }
+      }
+}
+
 int main(int argc, char** argv) {
-  const struct { const char* name; void (*run)(); } models[] = {{"tables", tables}};
+  const struct { const char* name; void (*run)(); } models[] = {{"tables", tables}, {"gangs", gangs}};
   bool any = false;
   for (const auto& m : models)
     if (argc < 2 || !strcmp(argv[1], m.name)) { m.run(); any = true; }

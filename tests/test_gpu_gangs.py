@@ -64,3 +64,33 @@ def test_short_collectives_together(R, channels, n, knobs):
                 assert np.all(got[r].view(np.uint8) == 0xA5), (ci, r)
             else:
                 assert np.array_equal(got[r].view(np.uint8), want[r].view(np.uint8)), (ci, c, r)
+
+
+@pytest.mark.parametrize("R,knobs,budget", [(8, dict(order_policy=1), 32 << 10), (4, dict(order_policy=1), 32 << 10), (2, dict(order_policy=1, focus_bytes=20000), 20000),
+                                            (8, dict(focus_bytes=40000), 40000), (4, dict(), 128 << 10)])
+def test_a_gang_holds_to_the_bytes_of_a_pass(R, knobs, budget):
+    """Shares of up to 16 KiB, as many of them queued as would fill the largest gangs: one job takes no more than a pass may hand the movers
+    before it looks at the SQ and the queue again (32 KiB at most under priority ordering)."""
+    from paper_2303_06324_amd import harness as gh
+    import paper_2303_06324_amd as dfx
+    n, channels = 60, 4
+    colls = [wi.CollSpec(i, (wi.AR, wi.RS, wi.BC)[i % 3], wi.F32, (R if i % 3 != 1 else 1) * ((16 << 10) * channels - 64 * (i % 5)) // 4) for i in range(n)]
+    w = wi.Workload(f"gang_bytes_{R}", R, colls, [list(range(n))] * R, seed=R, cfg=112)
+    dw = gh.DeviceWorkload(w)
+    ctx = dfx.Context(R, gh.make_config(max_channels=channels, **knobs))
+    try:
+        gh.prepare_all(ctx, w)
+        for _ in range(4):
+            dw.reset_recv()
+            gh.submit_bursts(ctx, dw)
+            assert ctx.wait_all(30.0) == dfx.OK
+        assert ctx.stop() == dfx.OK
+        went = [ctx.counters(r) for r in range(R)]
+    finally:
+        ctx.finalize()
+    assert sum(k["gangs"] for k in went) > 0 or budget < 32 << 10, went
+    assert all(k["ganged"] >= 2 * k["gangs"] and k["gang_max_bytes"] <= budget for k in went), went
+    for ci, c in enumerate(w.colls):
+        want, got = rd.run_closed_form(c.kind, dw.send_host[ci], c.dtype, c.root, c.op), dw.results(ci)
+        assert all(np.array_equal(got[r].view(np.uint8), want[r].view(np.uint8)) for r in range(R)), (ci, c)
+    dw.check_untouched()

@@ -15,8 +15,9 @@ def check(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("model", ["tables"])
+@pytest.mark.parametrize("model", ["tables", "gangs"])
 def test_rules(check, model):
-    """tables: a job moves the buffers of its own invocation, also where the collective comes again in the fetch that brought a table."""
+    """tables: a job moves the buffers of its own invocation, also where the collective comes again in the fetch that brought a table.
+    gangs: a pass hands the movers its bytes and no more, however many short collectives go together, but for a first one that is longer."""
     res = subprocess.run([check, model], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0, res.stdout

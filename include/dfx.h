@@ -128,7 +128,8 @@ typedef struct {
                               primitive sequence slice after slice */
   uint32_t focus_bytes;    /* stickiness across ranks (the aim of Sec. 4.3's threshold adjustment): when not 0, a scanned
                               pass over a queue of at most 64 entries visits the runnable collectives
-                              furthest-along first and ends once it has handed the movers this many bytes, so
+                              furthest-along first and ends once it has handed the movers this many bytes (twice as
+                              many at most where short collectives go to them as one job), so
                               that all ranks carry the same few collectives through instead of advancing all
                               of them side by side (whose FIFO slots together outgrow the memory-side cache);
                               0 = every runnable collective once per pass, in queue order */

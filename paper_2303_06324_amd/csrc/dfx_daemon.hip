@@ -1418,7 +1418,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 bool full = false;
                 for (u64 t = __ballot(there && k == 0); t && !full; t &= t - 1) {
                   const uint32_t share = (uint32_t)__builtin_amdgcn_readlane((int)g_.share, (int)__builtin_ctzll(t));
-                  if (gang_takes(pass_bytes + bytes_of, share, hot.focus_bytes)) { heads |= t & (0ull - t); bytes_of += share; }
+                  if (gang_takes(pass_bytes + bytes_of, share, gang_budget(hot.focus_bytes, hot.order_policy == 1))) { heads |= t & (0ull - t); bytes_of += share; }
                   else full = true;
                 }
                 there = (heads >> (e << gang_sh) & 1u) != 0;

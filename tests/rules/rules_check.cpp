@@ -56,7 +56,10 @@ static void tables() {
 
 // Passes over a queue of runnable short collectives: each hands the movers gangs of up to `most` of them until its bytes are spent.
 static void gangs() {
-  for (uint32_t budget : {1u, 4096u, 20000u, 32u << 10, 128u << 10, 0xffffffffu})
+  for (uint32_t focus : {1u, 4096u, 20000u, 32u << 10, 128u << 10, 0x80000000u, 0xffffffffu})
+   for (bool priority : {false, true}) {
+    const uint32_t budget = gang_budget(focus, priority);
+    EXPECT(budget >= focus && budget / 2u <= focus && (!priority || budget == focus), "focus %u: %u", focus, budget);
     for (uint32_t most : {1u, 2u, 8u, 16u})
       for (uint32_t step = 0; step < 40; ++step) {
         std::vector<uint32_t> share;
@@ -64,7 +67,7 @@ static void gangs() {
         uint32_t passes = 0;
         for (size_t at = 0; at < share.size(); ++passes) {
           uint32_t spent = 0, went = 0;
-          for (bool full = false; at < share.size() && spent < budget && !full; ) {
+          for (bool full = false; at < share.size() && spent < focus && !full; ) {
             const uint32_t first = spent;                  // (the gang: one job)
             for (uint32_t n = 0; n < most && at < share.size(); ++n) {
               if (!gang_takes(spent, share[at], budget)) { full = true; break; }
@@ -76,6 +79,7 @@ static void gangs() {
           if (!went) return;
         }
       }
+   }
 }
 
 int main(int argc, char** argv) {

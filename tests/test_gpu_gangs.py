@@ -67,10 +67,10 @@ def test_short_collectives_together(R, channels, n, knobs):
 
 
 @pytest.mark.parametrize("R,knobs,budget", [(8, dict(order_policy=1), 32 << 10), (4, dict(order_policy=1), 32 << 10), (2, dict(order_policy=1, focus_bytes=20000), 20000),
-                                            (8, dict(focus_bytes=40000), 40000), (4, dict(), 128 << 10)])
+                                            (8, dict(focus_bytes=20000), 40000), (4, dict(), 256 << 10)])
 def test_a_gang_holds_to_the_bytes_of_a_pass(R, knobs, budget):
     """Shares of up to 16 KiB, as many of them queued as would fill the largest gangs: one job takes no more than a pass may hand the movers
-    before it looks at the SQ and the queue again (32 KiB at most under priority ordering)."""
+    before it looks at the SQ and the queue again (32 KiB at most under priority ordering; under FIFO ordering twice focus_bytes)."""
     from paper_2303_06324_amd import harness as gh
     import paper_2303_06324_amd as dfx
     n, channels = 60, 4

@@ -722,6 +722,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
     const uint32_t gang_sh = gang_shift(R), gang_n = (64u >> gang_sh) < GANG_MAX ? 64u >> gang_sh : GANG_MAX;
     const uint32_t gang_share = !give_way || R < 2u || R > 32u ? 0u : GANG_SHARE;
     bool focus = false;                            // the pass visits the list furthest-along first, up to a byte budget
+    uint32_t behind = 0, nothers = 0;              // passes in a row that left others unvisited behind short ones (shorts_ahead); runnable ones that are not short
     uint32_t pos = 0;
     // context-switch sample in flight: t0 = abort decision, ts = after the save, lb/le = load
     u64 sw_t0 = 0, sw_ts = 0, sw_lb = 0, sw_le = 0;
@@ -1268,6 +1269,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             nready = 0; rk = 0; pass_bytes = 0;
             uint32_t kept = 0, nshort = 0;       // entries that stay in the queue; runnable short ones
             focus = hot.focus_bytes != 0 && qlen <= 64u;
+            nothers = 0;
             if (lane < DFX_CTX_SLOTS) sh.slot_claim[lane] = 0xffffffffu;
             for (uint32_t base = 0; base < qlen; base += 64) {
               const uint32_t i = base + lane;
@@ -1320,8 +1322,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                     const uint32_t pr = (uint32_t)((int)(int16_t)(ge.w & 0xffffu) + 32768);
                     key = ((pr << 14) | ((uint32_t)done << 6) | (63u - lane)) + 1u;
                   } else {
-                    if (done > 0xfffffu) done = 0xfffffu;
-                    key = ((short_one ? 1u << 28 : 0u) | ((uint32_t)done << 8) | (63u - lane)) + 1u;
+                    key = pass_key(shorts_ahead(behind), short_one, done, lane);
                   }
                 }
               }
@@ -1366,9 +1367,10 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 for (uint32_t j = 0; j < nq; ++j)
                   rank_in_pass += ((uint32_t)__builtin_amdgcn_readlane((int)key, (int)j) > key) ? 1u : 0u;
                 if (rdy) sh.rlist[rank_in_pass] = (uint16_t)now_at;
-                // the short ones: first in the pass; under priority ordering as many as nothing else goes before
+                // the short ones: first in the pass; under priority ordering, and where they are not ahead, as many as nothing else goes before
                 nshort = (uint32_t)__builtin_popcountll(__ballot(short_one));
-                if (hot.order_policy == 1 && nshort) {
+                nothers = (uint32_t)__builtin_popcountll(mask) - nshort;
+                if ((hot.order_policy == 1 || !shorts_ahead(behind)) && nshort) {
                   nshort = 0;
                   for (; __ballot(short_one && rank_in_pass == nshort); ) ++nshort;
                 }
@@ -1505,7 +1507,11 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           // (a pass that ends is not a switch between two collectives: the latency sample is dropped)
           // A focused pass also ends once it has handed the movers its share of bytes: the next scan
           // looks again at which collectives are furthest along.
-          if (rk >= nready || (focus && pass_bytes >= hot.focus_bytes)) { in_pass = false; sw_pending = false; continue; }
+          if (rk >= nready || (focus && pass_bytes >= hot.focus_bytes)) {
+            behind = passes_over(behind, nothers, rk < nready ? nready - rk : 0u);
+            in_pass = false; sw_pending = false;
+            continue;
+          }
           pos = bcast0((uint32_t)sh.rlist[rk]);
         } else if (pos >= qlen) { in_pass = false; sw_pending = false; continue; }
 

@@ -82,8 +82,49 @@ static void gangs() {
    }
 }
 
+// A workgroup's queue under steady traffic: as many short collectives as there are outstanding come back to its tail as soon as they have gone, and a
+// long one, or one that only has its completion left, waits among them.
+static void turns() {
+  for (uint32_t nshort : {9u, 20u, 40u, 63u})
+    for (uint32_t share : {2048u, 16384u})
+      for (uint64_t long_done : {0ull, 1ull, 5ull, 1ull << 40}) {
+        struct Q { bool is_short; uint64_t done; };
+        std::vector<Q> q(nshort, Q{true, 0});
+        q.push_back(Q{false, long_done});
+        bool went = false;
+        uint32_t passes = 0, behind = 0;
+        for (; passes < 1000 && !went; ++passes) {
+          const uint32_t n = (uint32_t)q.size();
+          const bool ahead = shorts_ahead(behind);
+          std::vector<uint32_t> order(n, 0);
+          for (uint32_t i = 0; i < n; ++i) {
+            uint32_t at = 0;
+            for (uint32_t k = 0; k < n; ++k) at += pass_key(ahead, q[k].is_short, q[k].done, k) > pass_key(ahead, q[i].is_short, q[i].done, i);
+            order[at] = i;
+          }
+          uint32_t bytes = 0, rk = 0;
+          std::vector<bool> gone(n, false);
+          for (; rk < n && bytes < (128u << 10) && !went; ++rk) {
+            gone[order[rk]] = true;
+            bytes += share;
+            went = !q[order[rk]].is_short;
+          }
+          behind = passes_over(behind, 1u, n - rk);
+          EXPECT(behind <= PASSES_OVER, "%u passes in a row", behind);
+          std::vector<Q> next;
+          uint32_t came = 0;
+          for (uint32_t i = 0; i < n; ++i) if (gone[i]) ++came; else next.push_back(q[i]);
+          for (uint32_t i = 0; i < came; ++i) next.push_back(Q{true, 0});
+          q = next;
+        }
+        // what is further along goes in the first pass in plain order; what came last, at the latest when all in front of it have gone and that pass comes
+        const uint32_t per_pass = (128u << 10) / share, bound = PASSES_OVER + 1u + (long_done ? 0u : (nshort / per_pass + 1u) * (PASSES_OVER + 1u));
+        EXPECT(went && passes <= bound, "%u short ones of %u bytes, %llu steps done: not visited in %u passes", nshort, share, (unsigned long long)long_done, bound);
+      }
+}
+
 int main(int argc, char** argv) {
-  const struct { const char* name; void (*run)(); } models[] = {{"tables", tables}, {"gangs", gangs}};
+  const struct { const char* name; void (*run)(); } models[] = {{"tables", tables}, {"gangs", gangs}, {"turns", turns}};
   bool any = false;
   for (const auto& m : models)
     if (argc < 2 || !strcmp(argv[1], m.name)) { m.run(); any = true; }

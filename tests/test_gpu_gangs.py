@@ -94,3 +94,43 @@ def test_a_gang_holds_to_the_bytes_of_a_pass(R, knobs, budget):
         want, got = rd.run_closed_form(c.kind, dw.send_host[ci], c.dtype, c.root, c.op), dw.results(ci)
         assert all(np.array_equal(got[r].view(np.uint8), want[r].view(np.uint8)) for r in range(R)), (ci, c)
     dw.check_untouched()
+
+
+@pytest.mark.parametrize("R,nbytes,knobs", [(8, 128 << 10, dict(chan_spread=0)), (4, 64 << 10, dict(max_channels=1)), (2, 32 << 10, dict(chan_spread=0, max_channels=4))])
+def test_a_long_one_has_its_turn_in_steady_traffic(R, nbytes, knobs, tmp_path):
+    """Forty short collectives on one channel, each submitted again as soon as it is complete, and a long one among them: it is
+    complete long before the traffic ends (int32: exact)."""
+    import ctypes as C
+    import os
+    import subprocess
+    import torch
+    import paper_2303_06324_amd as dfx
+    from paper_2303_06324_amd import harness as gh
+    here = os.path.dirname(os.path.abspath(__file__))
+    so, lib = str(tmp_path / "stream.so"), os.path.dirname(dfx.LIB_PATH)
+    subprocess.run(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + os.path.join(here, "..", "include"), os.path.join(here, "c_abi", "stream.c"), "-o", so,
+                    "-L" + lib, "-ldfx", "-Wl,-rpath," + lib], check=True)
+    turn = C.CDLL(so).stream_turn
+    turn.argtypes, turn.restype = [C.c_void_p, C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_long, C.c_long], C.c_long
+    n, sizes = 40, [nbytes // 4] * 40 + [(8 << 20) // 4 + 3]
+    g = torch.Generator(device="cuda").manual_seed(R)
+    send = [[torch.randint(-1000, 1000, (m,), generator=g, device="cuda", dtype=torch.int32) for _ in range(R)] for m in sizes]
+    recv = [[torch.full((m,), -7, device="cuda", dtype=torch.int32) for _ in range(R)] for m in sizes]
+    torch.cuda.synchronize()
+    s = (C.c_void_p * ((n + 1) * R))(*[t.data_ptr() for row in send for t in row])
+    d = (C.c_void_p * ((n + 1) * R))(*[t.data_ptr() for row in recv for t in row])
+    ctx = dfx.Context(R, gh.make_config(quit_idle_us=20000, **knobs))
+    try:
+        for i, m in enumerate(sizes):
+            ctx.prepare(i, dfx.ALLREDUCE, m, dfx.I32)
+        assert ctx.coll_info(0)["nchan"] == 1 and ctx.coll_info(0)["slot_bytes"] == 16 << 10
+        went = [turn(ctx._h, R, n, C.cast(s, C.c_void_p), C.cast(d, C.c_void_p), 400, 6000) for _ in range(5)]
+        assert ctx.stop() == dfx.OK
+        gangs = sum(ctx.counters(r)["gangs"] for r in range(R))
+    finally:
+        assert ctx.finalize() == dfx.OK
+    assert all(0 < k <= 1500 for k in went), went
+    assert gangs > 0
+    for row, out in zip(send, recv):
+        total = torch.stack(row).sum(0).to(torch.int32)
+        assert all(torch.equal(t, total) for t in out)

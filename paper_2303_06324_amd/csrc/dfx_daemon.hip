@@ -1835,7 +1835,8 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
         } else if (__builtin_expect(fold && p == 1u && qlen > 1u, 0)) {
           // The last wait cannot be over while the job just posted is not, and there is other work.  In a scanned pass, whose threshold
           // is one poll, it is left unpolled (polled, it was given up in 9011 of 9011 passes over 1024 small all-reduces, 1.4 us each);
-          // elsewhere it gets the smallest threshold.
+          // elsewhere it gets the smallest threshold where the pass still has entries to visit.  (Those in front have just been given
+          // up: gone back to before this wait, beside a stuck one, an all-reduce of 8 KiB took 34.5 us, now 26.4.)
           if (scanned && give_way) {
             if (lane == 0) {
               DfxDyn d; d.round = g; d.prim = p; d.sent = sent; d.recvd = recvd;
@@ -1847,7 +1848,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             have = false;
             sw_pending = false;
             ++rk;
-          } else if (!scanned) thr = hot.spin_min;
+          } else if (!scanned && pos + 1u < qlen) thr = hot.spin_min;
         }
       } else {
         // ---- PreemptCollective + SaveCollectiveContext (lazy: only if it progressed)

@@ -406,6 +406,10 @@ struct Shared {
   GangEntry gang[2][GANG_MAX];       // the collectives of a posted gang; their addresses in tab_src and tab_dst, so many lanes apart as hold a rank each
   u64 gone;                          // queue positions that gangs of the pass are through with
   uint4 peer[64];                    // table of buffers that came with the lone entry in hand (DfxPeer)
+  uint32_t peers_seq;                // ... of which invocation
+  uint32_t behind;                   // passes in a row that left others unvisited behind short ones (turn_due)
+  uint32_t nothers;                  // runnable entries of the pass that are not short
+  uint32_t turn;                     // the first of these has its turn in the pass: 1 + its place in the list (0: none has)
   uint32_t job_seq;                  // jobs posted so far (scheduler -> movers)
   uint32_t wave_done[2];             // mover waves that have finished job k, at index k & 1
   uint32_t jobs_done;                // jobs finished and published (movers -> scheduler)
@@ -560,6 +564,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
   if (tid < DFX_CTX_SLOTS) sh.slot_tag[tid] = 0xffffffffu;
   if (tid < DFX_NSTAT) sh.stat[tid] = ws->stat[tid];
   if (tid == 0) {
+    sh.behind = 0; sh.nothers = 0; sh.turn = 0;
     sh.job_seq = 0; sh.wave_done[0] = 0; sh.wave_done[1] = 0; sh.jobs_done = 0; sh.leave = 0;
     sh.trace_n = ws->trace_n;
   }
@@ -722,7 +727,6 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
     const uint32_t gang_sh = gang_shift(R), gang_n = (64u >> gang_sh) < GANG_MAX ? 64u >> gang_sh : GANG_MAX;
     const uint32_t gang_share = !give_way || R < 2u || R > 32u ? 0u : GANG_SHARE;
     bool focus = false;                            // the pass visits the list furthest-along first, up to a byte budget
-    uint32_t behind = 0, nothers = 0;              // passes in a row that left others unvisited behind short ones (shorts_ahead); runnable ones that are not short
     uint32_t pos = 0;
     // context-switch sample in flight: t0 = abort decision, ts = after the save, lb/le = load
     u64 sw_t0 = 0, sw_ts = 0, sw_lb = 0, sw_le = 0;
@@ -816,7 +820,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
     uint32_t rd_old = 0;       // lane 0: readers of the slot before this workgroup
     u64 rd_idx = 0;            // the entry
     bool rd_open = false;
-    uint32_t peers_of = 0, peers_seq = 0;     // the collective (id + 1) whose buffers are in sh.peer, and its invocation (table_serves)
+    uint32_t peers_of = 0;     // the collective (id + 1) whose buffers are in sh.peer
     bool ctx_open = false;     // the stores of a lone collective's context may still be under way
     auto free_slot = [&](uint32_t readers_before, u64 idx) {
       // (the counter runs on from generation to generation, modulo 2^32: no reset to wait for before the slot is used again)
@@ -1129,7 +1133,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             bool through = false;                          // ... nowhere: it needs no place in the queue
             if (lone && with_table && mine_mask == 1ull) {
               peers_of = bcast0(c_id) + 1u;
-              peers_seq = bcast0(q.seq);
+              if (lane == 0) sh.peers_seq = q.seq;
               if (qlen == 0 && posted == retired) {
                 const uint32_t e_rounds = bcast0(q.rounds), e_flags = bcast0(q.flags), e_nchan = bcast0(q.nchan), e_vch = bcast0(my_vch);
                 const bool e_drawn = (e_flags & DFX_SQE_DRAWN) != 0;
@@ -1137,7 +1141,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                                                   bcast64((uint32_t)q.part_elems, (uint32_t)(q.part_elems >> 32)), bcast0(q.slice_elems), e_drawn, 0);
                 const u64 line0 = (u64)(uintptr_t)a.pool + bcast64((uint32_t)q.conn_off, (uint32_t)(q.conn_off >> 32)) + (u64)e_vch * DFX_FLAG_STRIDE;
                 const bool e_sweep = (e_flags & DFX_SQE_SWEEP) != 0;
-                const FoldStep st = {(int)bcast0(q.kind), (int)bcast0((uint32_t)q.dtype | ((uint32_t)q.op << 4)), peers_of - 1u, peers_seq, e_nchan, e_vch,
+                const FoldStep st = {(int)bcast0(q.kind), (int)bcast0((uint32_t)q.dtype | ((uint32_t)q.op << 4)), peers_of - 1u, bcast0(q.seq), e_nchan, e_vch,
                                      e_sweep ? bcast0(q.slice_elems) : bcast0(q.slot_bytes), e_sweep ? FRESH_SWEEP | 1u : 1u, line0, fold_line(line0, 0, R, e_nchan), e_drawn,
                                      e_sweep, 0, bcast0((uint32_t)q.count), bcast64((uint32_t)q.block_elems, (uint32_t)(q.block_elems >> 32))};
                 post_fold(st, fg, ((u64)peer.y << 32) | peer.x, ((u64)peer.w << 32) | peer.z);
@@ -1269,7 +1273,6 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             nready = 0; rk = 0; pass_bytes = 0;
             uint32_t kept = 0, nshort = 0;       // entries that stay in the queue; runnable short ones
             focus = hot.focus_bytes != 0 && qlen <= 64u;
-            nothers = 0;
             if (lane < DFX_CTX_SLOTS) sh.slot_claim[lane] = 0xffffffffu;
             for (uint32_t base = 0; base < qlen; base += 64) {
               const uint32_t i = base + lane;
@@ -1322,7 +1325,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                     const uint32_t pr = (uint32_t)((int)(int16_t)(ge.w & 0xffffu) + 32768);
                     key = ((pr << 14) | ((uint32_t)done << 6) | (63u - lane)) + 1u;
                   } else {
-                    key = pass_key(shorts_ahead(behind), short_one, done, lane);
+                    key = pass_key(short_one, done, lane);
                   }
                 }
               }
@@ -1367,10 +1370,13 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 for (uint32_t j = 0; j < nq; ++j)
                   rank_in_pass += ((uint32_t)__builtin_amdgcn_readlane((int)key, (int)j) > key) ? 1u : 0u;
                 if (rdy) sh.rlist[rank_in_pass] = (uint16_t)now_at;
-                // the short ones: first in the pass; under priority ordering, and where they are not ahead, as many as nothing else goes before
+                // the short ones: first in the pass; under priority ordering as many as nothing else goes before
                 nshort = (uint32_t)__builtin_popcountll(__ballot(short_one));
-                nothers = (uint32_t)__builtin_popcountll(mask) - nshort;
-                if ((hot.order_policy == 1 || !shorts_ahead(behind)) && nshort) {
+                if (lane == 0) {
+                  sh.nothers = (uint32_t)__builtin_popcountll(mask) - nshort;
+                  sh.turn = hot.order_policy != 1 && turn_due(sh.behind) ? nshort + 1u : 0u;
+                }
+                if (hot.order_policy == 1 && nshort) {
                   nshort = 0;
                   for (; __ballot(short_one && rank_in_pass == nshort); ) ++nshort;
                 }
@@ -1507,8 +1513,17 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           // (a pass that ends is not a switch between two collectives: the latency sample is dropped)
           // A focused pass also ends once it has handed the movers its share of bytes: the next scan
           // looks again at which collectives are furthest along.
-          if (rk >= nready || (focus && pass_bytes >= hot.focus_bytes)) {
-            behind = passes_over(behind, nothers, rk < nready ? nready - rk : 0u);
+          bool ended = rk >= nready;
+          if (!ended && focus && pass_bytes >= hot.focus_bytes) {
+            const uint32_t turn = bcast0(sh.turn);
+            ended = turn == 0 || rk >= turn || turn > nready;      // (none has, one had been visited, there is none)
+            if (!ended) {
+              rk = turn - 1u;
+              if (lane == 0) sh.turn = 0;
+            }
+          }
+          if (ended) {
+            if (focus && lane == 0) sh.behind = passes_over(sh.behind, sh.nothers, rk < nready ? nready - rk : 0u);
             in_pass = false; sw_pending = false;
             continue;
           }
@@ -1648,7 +1663,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           const bool sweep = (bcp & DFX_CTX_SWEEP) != 0;
           const FoldStep st = {kind, dtype, coll, inv_seq, inv_nchan, vch, sweep ? s_slice : row_limit, sweep ? FRESH_SWEEP | (g == 0) : !drawn || g == 0,
                                s_fin, s_in, drawn, sweep, g, bcast0(v1.x), bcast64(v1.z, v1.w)};
-          if (table_serves(peers_of, peers_seq, coll, inv_seq)) {
+          if (peers_of == coll + 1u && table_serves(peers_of, bcast0(sh.peers_seq), coll, inv_seq)) {
             // The entry came with every rank's buffers, so every rank has submitted: there is nothing to wait for.  Without the
             // others' lines (a store and its way to memory, a load or two) a 25 MiB all-reduce takes 96.5 us instead of 97.8.
             if (!flight_free(hot.order_policy == 1 ? 1u : 2u)) { stop = STOP_ABORT; have = false; continue; }

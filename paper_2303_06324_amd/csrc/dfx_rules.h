@@ -27,19 +27,18 @@ DFX_RULE bool gang_takes(uint32_t spent, uint32_t share, uint32_t budget) { retu
 // are of eight, level).
 DFX_RULE uint32_t gang_budget(uint32_t focus, bool priority) { return priority || focus > 0x7fffffffu ? focus : 2u * focus; }
 
-// Order of a focused pass under FIFO ordering, largest key first: furthest along, then queue order; the short ones that may go in gangs in
-// front of all that in a pass where they are ahead.
-DFX_RULE uint32_t pass_key(bool ahead, bool short_one, uint64_t done, uint32_t lane) {
-  return ((ahead && short_one ? 1u << 28 : 0u) | ((uint32_t)(done > 0xfffffu ? 0xfffffu : done) << 8) | (63u - lane)) + 1u;
+// Order of a focused pass under FIFO ordering, largest key first: the short ones that may go in gangs, then the others, of each furthest along
+// first, then queue order.
+DFX_RULE uint32_t pass_key(bool short_one, uint64_t done, uint32_t lane) {
+  return ((short_one ? 1u << 28 : 0u) | ((uint32_t)(done > 0xfffffu ? 0xfffffu : done) << 8) | (63u - lane)) + 1u;
 }
-// Whether they are, by the passes in a row (over) that have ended, their bytes spent, before everything else in their list was visited.  As
-// long as short ones keep coming they alone may spend them, so then comes a pass in plain order, in which whoever is furthest along, or came
-// first, has its turn.  (Always ahead, an all-reduce of 25 MiB was not complete when 5000 of 128 KiB that came behind it were, 40 of them
-// outstanding on its channel; 48 without gangs.)  Every eighth pass: 64 mixed collectives 951 us with short ones always ahead, 962 with every
-// second pass in plain order.
+// A pass ends when its bytes are spent, and as long as short ones keep coming they alone may spend them.  Behind seven passes in a row that
+// left others unvisited comes one in which the first of these has its turn whatever the short ones have spent.  (Without turns an all-reduce of
+// 25 MiB was not complete when 5000 of 128 KiB that came behind it were, forty of them outstanding on its channel; 48 without gangs.)  A turn
+// is one visit: with every eighth pass in plain order instead, where long ones part the gangs, 64 mixed collectives took 944 us, without turns 939.
 constexpr uint32_t PASSES_OVER = 7u;
-DFX_RULE bool shorts_ahead(uint32_t over) { return over < PASSES_OVER; }
-// ... and what that number is behind a pass: others, its runnable entries that are not short; left, its entries that were not visited.
-DFX_RULE uint32_t passes_over(uint32_t over, uint32_t others, uint32_t left) { return shorts_ahead(over) && others != 0 && left != 0 ? over + 1u : 0u; }
+DFX_RULE bool turn_due(uint32_t over) { return over >= PASSES_OVER; }
+// The passes in a row, behind one more: others, its runnable entries that are not short; left, its entries that were not visited.
+DFX_RULE uint32_t passes_over(uint32_t over, uint32_t others, uint32_t left) { return !turn_due(over) && others != 0 && left != 0 ? over + 1u : 0u; }
 
 #endif

@@ -1412,11 +1412,15 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
               while (rk < nshort && pass_bytes < hot.focus_bytes) {
                 const uint32_t n = nshort - rk < gang_n ? nshort - rk : gang_n;
                 const GangRun g_ = sh.run[rk + (e < n ? e : 0u)];
+                // (the first lane of collective e; not known to the compiler to be the same in every pass: it kept three masks made of it, across
+                // everything the scheduler does, in scratch memory, where each was a wait of its own)
+                uint32_t first = e << gang_sh;
+                asm volatile("" : "+v"(first));
                 const uint32_t nch = g_.nchan_vch & 0xffffu, vch = g_.nchan_vch >> 16, dt = g_.what >> 8 & 0xffu;
                 const int kd = (int)(g_.what & 0xffu);
                 v4u ln_recv, ln_send;
                 ld_published((const void*)(g_.line0 + (u64)(k < R ? fold_peer(kd, R, rank, g_.what >> 16, k) : 0u) * nch * DFX_FLAG_STRIDE), ln_recv, ln_send);
-                const u64 all_lanes = (gang_sh == 6u ? ~0ull : (1ull << (1u << gang_sh)) - 1ull) << (e << gang_sh);
+                const u64 all_lanes = (gang_sh == 6u ? ~0ull : (1ull << (1u << gang_sh)) - 1ull) << first;
                 bool there = e < n && (__ballot(e < n && ln_recv.z == g_.seq + 1u && ln_send.z == g_.seq + 1u) & all_lanes) == all_lanes;
                 // as many of them as the pass's bytes go for, a bit for the first lane of each: nothing overtakes a job.  (With the budget looked
                 // at before a gang only, an urgent 8 KiB all-reduce behind sixty of 4 MiB took 372 us under priority ordering, now 113 (R = 8); behind sixty of 2 MiB
@@ -1429,14 +1433,14 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                   if (gang_takes(pass_bytes + bytes_of, share, gang_budget(hot.focus_bytes, hot.order_policy == 1))) { heads |= t & (0ull - t); bytes_of += share; }
                   else full = true;
                 }
-                there = (heads >> (e << gang_sh) & 1u) != 0;
+                there = (heads >> first & 1u) != 0;
                 const uint32_t cnt = (uint32_t)__builtin_popcountll(heads);
                 rk += n;
                 pass_bytes += bytes_of;
                 if (full && pass_bytes < hot.focus_bytes) pass_bytes = hot.focus_bytes;      // (the pass ends: the others go with the next one)
                 if (!cnt) continue;
                 if (!flight_free(hot.order_policy == 1 ? 1u : 2u)) { ok_all = false; break; }
-                const uint32_t fs = posted & 1, idx = (uint32_t)__builtin_popcountll(heads & ((1ull << (e << gang_sh)) - 1ull));
+                const uint32_t fs = posted & 1, idx = (uint32_t)__builtin_popcountll(heads & ((1ull << first) - 1ull));
                 if (there) {
                   const bool cp = fold_copies(kd), to_all = fold_to_all(kd);
                   if (k < R) {

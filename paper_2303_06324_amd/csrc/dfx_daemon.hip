@@ -1097,7 +1097,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             uint32_t n = (here_mask == ~0ull) ? 64u : (uint32_t)__builtin_ctzll(~here_mask);   // length of the run that starts at lane 0
             if (lane != 0 && lane < n) q = load_entry(ri + lane);
             // (a full look: the run may go on, see below)
-            const bool chain = n == 64u && hot.fetch_batch == 0xffffffffu;
+            const bool chain = n == 64u && hot.fetch_batch == 0xffffffffu && run_goes_on(D, (uint32_t)sizeof(DfxSqSlot));
             bool more = chain && entry_there(ri + 64u + lane);
             __builtin_amdgcn_s_waitcnt(0);        // (the entries have been read before they count as read below)
             bool is_exit_sqe = false, is_exit = false;

@@ -17,6 +17,10 @@
 // whose only job went to the movers at the head of the fetch, still lies there.
 DFX_RULE bool table_serves(uint32_t held_of, uint32_t held_seq, uint32_t coll, uint32_t seq) { return held_of == coll + 1u && held_seq == seq; }
 
+// Whether a fetch may go on behind its first 64 entries, which it reads through a buffer resource: sizes and offsets of that are 32 bits, so
+// the ring (a power of two of slots) must be shorter.  (From 2^25 slots on its size read as 0 and every entry as nobody's.)
+DFX_RULE bool run_goes_on(uint32_t sq_depth, uint32_t slot_bytes) { return (uint64_t)sq_depth * slot_bytes <= 0x80000000u; }
+
 // Whether another short collective goes with the gang in hand: spent, the bytes that the pass has handed to the movers, those of the gang's
 // members so far among them; share, its own; budget, gang_budget.  A gang is one job that nothing overtakes, so a budget holds inside it as
 // well; the first member of a pass always goes.

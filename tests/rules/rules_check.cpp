@@ -122,8 +122,22 @@ static void turns() {
       }
 }
 
+// A fetch that goes on reads slots through a resource of sq_depth slots: its size and the offset of every 16-byte part, in 32 bits.
+static void rings() {
+  const uint32_t slot = 128;
+  for (uint32_t sh = 1; sh < 32; ++sh) {
+    const uint32_t depth = 1u << sh;
+    if (!run_goes_on(depth, slot)) { EXPECT(sh > 24, "a ring of 2^%u slots: refused", sh); continue; }
+    const uint32_t size = depth * slot;
+    for (uint64_t idx : {0ull, (1ull << sh) - 1u, (1ull << sh), 3ull * (1ull << sh) - 1u, 1ull << 40}) {
+      const uint32_t at = ((uint32_t)idx & (depth - 1u)) * slot + 80u;
+      EXPECT((uint64_t)at == (idx & ((1ull << sh) - 1u)) * slot + 80u && at + 16u <= size, "a ring of 2^%u slots, entry %llu: at %u of %u", sh, (unsigned long long)idx, at, size);
+    }
+  }
+}
+
 int main(int argc, char** argv) {
-  const struct { const char* name; void (*run)(); } models[] = {{"tables", tables}, {"gangs", gangs}, {"turns", turns}};
+  const struct { const char* name; void (*run)(); } models[] = {{"tables", tables}, {"gangs", gangs}, {"turns", turns}, {"rings", rings}};
   bool any = false;
   for (const auto& m : models)
     if (argc < 2 || !strcmp(argv[1], m.name)) { m.run(); any = true; }

@@ -58,3 +58,29 @@ def test_runs_of_entries(R, channels, n, knobs):
                 assert np.all(got[r].view(np.uint8) == 0xA5), (ci, r)
             else:
                 assert np.array_equal(got[r].view(np.uint8), want[r].view(np.uint8)), (ci, c, r)
+
+
+def test_an_sq_that_32_bit_offsets_do_not_reach():
+    """2^25 slots, 4 GiB: the part of the fetch that addresses slots by 32-bit offsets is left out, and no entry is lost."""
+    import torch
+    from paper_2303_06324_amd import harness as gh
+    import paper_2303_06324_amd as dfx
+    n = 300
+    try:
+        ctx = dfx.Context(1, gh.make_config(max_channels=1, max_colls=n, sq_depth=1 << 25, pool_bytes=64 << 20))
+    except dfx.DfxError as e:
+        pytest.skip(f"no memory for such a ring: {e}")
+    try:
+        send = torch.arange(64 * n, dtype=torch.int32, device="cuda").view(n, 64)
+        recv = torch.full((n, 64), -1, dtype=torch.int32, device="cuda")
+        for i in range(n):
+            ctx.prepare(i, dfx.ALLREDUCE, 64, dfx.I32)
+        for _ in range(3):
+            recv.fill_(-1)
+            torch.cuda.synchronize()
+            assert ctx.submit_many(0, list(range(n)), [t.data_ptr() for t in send], [t.data_ptr() for t in recv]) == n
+            assert ctx.wait_all(10.0) == dfx.OK
+            assert ctx.stop() == dfx.OK
+            assert torch.equal(send, recv)
+    finally:
+        ctx.finalize()

@@ -177,10 +177,12 @@ typedef struct {
 
 /* Aggregated over the workgroups of one vrank since dfx_init. */
 typedef struct {
-  uint64_t preemptions;    /* waits that hit their spin threshold (context switches) */
+  uint64_t preemptions;    /* waits given up (context switches): those that hit their spin threshold, and last waits of fold steps
+                              that a scanned pass leaves unpolled behind the post of their job, while other work is queued
+                              (with preempt != 0 and spin_min = 1; dfx_counters says how many) */
   uint64_t ctx_loads;      /* context loads from HBM into an LDS active slot */
   uint64_t ctx_slot_hits;  /* loads avoided because the collective's LDS slot already held the context */
-  uint64_t ctx_saves;      /* dynamic-context saves to HBM */
+  uint64_t ctx_saves;      /* dynamic-context saves to HBM (one for every wait left unpolled, too) */
   uint64_t lazy_skips;     /* preemptions that skipped the save (nothing had progressed) */
   uint64_t polls;          /* poll attempts in wait phases */
   uint64_t prims;          /* primitives (slices) executed */
@@ -190,7 +192,7 @@ typedef struct {
   uint64_t passes;         /* traversals of the task queue */
   uint64_t quits;          /* voluntary quits */
   uint64_t launches;       /* daemon launches (whole context, not per rank) */
-  uint64_t switch_samples; /* context-switch latency samples available */
+  uint64_t switch_samples; /* context-switch latency samples available (waits left unpolled give none) */
   double switch_us_p50;    /* abort decision -> first poll of the next collective */
   double switch_us_p99;
   double switch_us_mean;
@@ -206,7 +208,7 @@ typedef struct {
   double setup_us_mean;    /* with trace = 2: the part after the load (thresholds, the primitive's descriptor) up to the first poll */
   double clock_read_us;    /* with trace = 1 or 2: what one read of the wall clock costs the scheduler (a switch sample holds two
                               reads, a split sample five) */
-  double sqe_us;           /* time the vrank's workgroups spent fetching SQEs (entry seen -> run of up to 64 entries read,
+  double sqe_us;           /* time the vrank's workgroups spent fetching SQEs (entry seen -> run of up to 1088 entries read,
                               cooked into contexts, queued), summed over workgroups; always counted.  Every workgroup reads
                               every entry of its vrank: divide by sqe_fetched for the time per entry and workgroup */
 } dfx_stats_t;
@@ -270,7 +272,7 @@ int dfx_submit_all(dfx_ctx* ctx, int coll_id, const void* const* sendbufs, void*
 /*
  * Submit n collectives of one vrank in the given order (a burst of dfcclRun* calls, e.g. the
  * gradient buckets of one backward pass): element i is dfx_submit(ctx, rank, coll_ids[i],
- * sendbufs[i], recvbufs[i]), made visible to the daemon in runs of up to 32 entries (the bodies of a run, one
+ * sendbufs[i], recvbufs[i]), made visible to the daemon in runs of up to 128 entries (the bodies of a run, one
  * store fence, its generation words).  A full SQ is retried until timeout_ns has passed.  The three arrays
  * are host arrays of n entries, read only during the call; the buffers they point to are device
  * memory under the rules of dfx_submit.  Returns how many were submitted (n on success, fewer on
@@ -329,7 +331,8 @@ int dfx_stop(dfx_ctx* ctx);
 int dfx_stats(dfx_ctx* ctx, int rank, dfx_stats_t* out);
 
 /* For tests: which ways the scheduler of one vrank's workgroups took since dfx_init, up to max values into out (host).
-   0: jobs that several short collectives shared (gangs); 1: collectives moved in them; 2: most bytes per source of one of them.
+   0: jobs that several short collectives shared (gangs); 1: collectives moved in them; 2: most bytes per source of one of them;
+   3: last waits left unpolled; 4: SQ entries taken by fetches that went on behind their first 64.
    Valid once the daemon has stopped or quit.  Returns the number of values written, or a negative status. */
 int dfx_counters(dfx_ctx* ctx, int rank, uint64_t* out, int max);
 

@@ -197,7 +197,7 @@ class Context:
 
     def counters(self, rank: int) -> dict:
         """Which ways the scheduler took (for tests; dfx_counters), valid once the daemon has stopped or quit."""
-        names = ("gangs", "ganged", "gang_max_bytes")
+        names = ("gangs", "ganged", "gang_max_bytes", "unpolled", "run_on")
         buf = (C.c_uint64 * len(names))()
         n = _lib.dfx_counters(self._h, rank, buf, len(names))
         if n != len(names):

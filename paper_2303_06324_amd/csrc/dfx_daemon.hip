@@ -1188,6 +1188,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
               asm volatile("" ::: "memory");      // (nothing of an entry is read before its generation word has been)
               if (lane < m) { h0 = half(at + lane, 64u); h1 = half(at + lane, 80u); }
               more = m == 64u && entry_there(at + 64u + lane);
+              // (after 16 of them, 30 us, the control words are looked at again)
               for (uint32_t batch = 0; batch < 16u && m && hot.max_colls - qlen >= 64u && !exit_mask; ++batch) {
                 struct { uint4 w[6]; } w = {};
                 w.w[4] = h0; w.w[5] = h1;
@@ -1227,6 +1228,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
             }
             if (lane == 0) {
               bump(sh.stat, ST_SQE, taken);
+              if (taken != n) bump(sh.stat, ST_RUN_ON, taken - n);
               bump(sh.stat, ST_T_SQE, wall_clock64() - tf0);
               __hip_atomic_fetch_max(&sh.stat[ST_MAXQ], (u64)qlen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
@@ -1478,7 +1480,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                       const uint32_t gsl = ctx_slot(g_.coll);
                       if (sh.slot_tag[gsl] == g_.coll) sh.slot[gsl].dyn = d;
                       st_ctx(&myctx[g_.coll].dyn, d);
-                      bump(sh.stat, ST_PREEMPT, 1); bump(sh.stat, ST_SAVE, 1);
+                      bump(sh.stat, ST_PREEMPT, 1); bump(sh.stat, ST_SAVE, 1); bump(sh.stat, ST_UNPOLLED, 1);
                     } else (void)__hip_atomic_fetch_or(&sh.gone, 1ull << g_.pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                     bump(sh.stat, ST_HIT, 1);
                   }
@@ -1862,7 +1864,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
               d.preempted = sh.slot[sl].dyn.preempted + 1; d.cidx = cidx;
               sh.slot[sl].dyn = d;
               st_ctx(&myctx[coll].dyn, d);
-              bump(sh.stat, ST_PREEMPT, 1); bump(sh.stat, ST_SAVE, 1);
+              bump(sh.stat, ST_PREEMPT, 1); bump(sh.stat, ST_SAVE, 1); bump(sh.stat, ST_UNPOLLED, 1);
             }
             have = false;
             sw_pending = false;

@@ -137,7 +137,9 @@ enum { ST_PREEMPT = 0, ST_LOAD, ST_HIT, ST_SAVE, ST_LAZY, ST_POLLS, ST_PRIMS, ST
        ST_T_CQE,                                         // ticks spent writing CQEs (always counted)
        ST_T_STAMP, ST_N_STAMP,                           // ticks of back-to-back clock reads and their number (trace 1, 2)
        ST_T_SQE,                                         // ticks spent fetching SQEs: probe seen -> entries cooked and queued (always counted)
-       ST_GANGS, ST_GANGED, ST_GANG_MAX };               // gang jobs, collectives moved in them, most bytes of one gang's shares (dfx_counters)
+       ST_GANGS, ST_GANGED, ST_GANG_MAX,                 // gang jobs, collectives moved in them, most bytes of one gang's shares (dfx_counters)
+       ST_UNPOLLED,                                      // last waits left unpolled (each counted in ST_PREEMPT and ST_SAVE as well)
+       ST_RUN_ON };                                      // entries taken behind the first 64 of a fetch
 
 // dev_ctl words (device memory)
 // (abort and quit share one aligned 64-bit word: the scheduler reads both with one load; the host

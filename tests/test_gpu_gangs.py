@@ -2,7 +2,8 @@
 posts itself: every kind, element type and reducing function at the edges of rows and of the longest share that goes with others,
 collectives of one and of several channels and a long one between them, every rank in an order of its own, in queues of one, two
 and four channels (more and fewer entries than a scan holds), with and without priorities, with the ring-buffer completion queue,
-three passes on the same context and one that begins with a stop half way.
+three passes on the same context and one that begins with a stop half way, each compared by itself; and what the daemon counts says that
+gangs were formed, and none where they are switched off.
 Bit-exact against the oracle (same order of combination, one rounding per hop: no tolerance)."""
 import numpy as np
 import pytest
@@ -36,6 +37,18 @@ def test_short_collectives_together(R, channels, n, knobs):
     import paper_2303_06324_amd as dfx
     w = _workload(R, n, seed=R * 100 + n)
     dw = gh.DeviceWorkload(w)
+    want = [rd.run_closed_form(c.kind, dw.send_host[ci], c.dtype, c.root, c.op) for ci, c in enumerate(w.colls)]
+
+    def check(it):
+        for ci, c in enumerate(w.colls):
+            got = dw.results(ci)
+            for r in range(R):
+                if c.kind == wi.RD and r != c.root:
+                    assert np.all(got[r].view(np.uint8) == 0xA5), (it, ci, r)
+                else:
+                    assert np.array_equal(got[r].view(np.uint8), want[ci][r].view(np.uint8)), (it, ci, c, r)
+        dw.check_untouched()
+
     ctx = dfx.Context(R, gh.make_config(max_channels=channels, **knobs))
     try:
         gh.prepare_all(ctx, w, priorities=[(i * 5) % 7 - 3 for i in range(n)] if knobs.get("order_policy") else None)
@@ -50,20 +63,19 @@ def test_short_collectives_together(R, channels, n, knobs):
             else:
                 gh.submit_bursts(ctx, dw)
             assert ctx.wait_all(30.0) == dfx.OK
+            check(it)
         assert ctx.stop() == dfx.OK
-        dw.check_untouched()
-        st = [ctx.stats(r) for r in range(R)]
+        st, ways = [ctx.stats(r) for r in range(R)], [ctx.counters(r) for r in range(R)]
     finally:
         ctx.finalize()
     assert all(s["cqe_posted"] == 4 * n for s in st)
     assert all(s["preemptions"] == s["ctx_saves"] + s["lazy_skips"] for s in st)
-    for ci, c in enumerate(w.colls):
-        want, got = rd.run_closed_form(c.kind, dw.send_host[ci], c.dtype, c.root, c.op), dw.results(ci)
-        for r in range(R):
-            if c.kind == wi.RD and r != c.root:
-                assert np.all(got[r].view(np.uint8) == 0xA5), (ci, r)
-            else:
-                assert np.array_equal(got[r].view(np.uint8), want[r].view(np.uint8)), (ci, c, r)
+    gangs, ganged, unpolled = (sum(k[name] for k in ways) for name in ("gangs", "ganged", "unpolled"))
+    if R > 32 or "focus_bytes" in knobs or "spin_min" in knobs:      # controls: nothing goes in gangs
+        assert gangs == ganged == 0, ways
+    else:
+        assert gangs > 0 and ganged >= 2 * gangs, ways
+    assert (unpolled > 0) == ("spin_min" not in knobs) and all(k["unpolled"] <= s["preemptions"] for k, s in zip(ways, st)), ways
 
 
 @pytest.mark.parametrize("R,knobs,budget", [(8, dict(order_policy=1), 32 << 10), (4, dict(order_policy=1), 32 << 10), (2, dict(order_policy=1, focus_bytes=20000), 20000),

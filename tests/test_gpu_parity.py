@@ -105,8 +105,8 @@ def test_allreduce_rank_counts(R, fold):
 @pytest.mark.parametrize("kind", [wi.AG, wi.RS, wi.BC])
 @pytest.mark.parametrize("dtype,count", [(wi.F32, 4096), (wi.F16, 1001), (wi.I32, 3), (wi.BF16, 250000)])
 def test_other_collectives(kind, dtype, count, fold):
-    """(In fold steps where they apply: all-gather / reduce-scatter blocks that are no 16-byte multiples, the
-    second and third case, stay rings.)"""
+    """(In fold steps where they apply: all-gathers of blocks below 1 MiB that are no 16-byte multiples, the second
+    and third case, stay rings.)"""
     _run(_one(kind, dtype, count, 8, root=5, seed=kind * 10 + dtype), fold_max_bytes=fold)
 
 

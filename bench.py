@@ -123,8 +123,8 @@ def _switch_summary(rc, dt, st, n, st2):
             "setup_us_mean": round(sum(s["setup_us_mean"] for s in st2) / len(st2), 3),
             "clock_read_us": round(max(s["clock_read_us"] for s in st2), 4),
             # the other workload-independent overheads of Sec. 6.2 (Fig. 7), from the run without the extra stamps:
-            # reading an SQE (per entry and workgroup: every workgroup of a vrank reads every entry; a run of up to 64
-            # is taken at once) and writing a CQE (first to last host-memory operation)
+            # reading an SQE (per entry and workgroup: every workgroup of a vrank reads every entry; a run of up
+            # to 1088 is taken at once) and writing a CQE (first to last host-memory operation)
             "sqe_read_us_mean": round(sum(s["sqe_us"] for s in st) / max(1, sum(s["sqe_fetched"] for s in st)), 4),
             "cqe_write_us_mean": round(sum(s["cqe_us"] for s in st) / max(1, sum(s["cqe_posted"] for s in st)), 3)}
 

@@ -79,7 +79,8 @@ typedef struct {
   /* The four spin_* fields shape the thresholds of passes that poll every queue entry in turn, as Alg. 1 is
      written: queues shorter than scan_min, or every queue with scan_min = 0.  A pass that began with a readiness
      scan visits only entries found runnable and waits at most spin_min polls on each; there the order of the
-     visits (focus_bytes, order_policy) does what the adjusted thresholds are for. */
+     visits (focus_bytes, order_policy) does what the adjusted thresholds are for.  The last wait of fold steps gets
+     spin_min where the pass has entries yet to visit. */
   uint32_t spin_init;      /* initial spin threshold (poll attempts) at the task-queue front (Sec. 4.3) */
   uint32_t spin_min;       /* thr(pos) = max(spin_min, spin_init >> pos) */
   uint32_t spin_max;       /* cap after boosting */
@@ -103,7 +104,8 @@ typedef struct {
                               little that was chosen before it came */
   uint32_t trace;          /* 1 = record context-switch latency samples (two clock reads per switch);
                               2 = also time the save / load parts and the wait / data / publish phases;
-                              3 = phases as in 2, and the trace holds one sample per executed primitive
+                              3 = phases as in 2, and the trace holds one sample per executed primitive (one, with the
+                                  id of the first, where short collectives go to the movers as one job)
                                   instead of one per switch (see dfx_trace_read) */
   uint32_t fetch_batch;    /* SQEs a workgroup may fetch in a row when its queue is empty or stuck; 0 = all available */
   uint64_t pool_bytes;     /* device memory reserved for connectors of all prepared collectives (default 4 GiB) */
@@ -128,7 +130,9 @@ typedef struct {
                               primitive sequence slice after slice */
   uint32_t focus_bytes;    /* stickiness across ranks (the aim of Sec. 4.3's threshold adjustment): when not 0, a scanned
                               pass over a queue of at most 64 entries visits the runnable collectives
-                              furthest-along first and ends once it has handed the movers this many bytes (twice as
+                              furthest-along first (under FIFO ordering short ones, which may go to the movers several
+                              at a time, before the others; behind seven passes in a row that left others unvisited
+                              the first of these has its turn) and ends once it has handed the movers this many bytes (twice as
                               many at most where short collectives go to them as one job), so
                               that all ranks carry the same few collectives through instead of advancing all
                               of them side by side (whose FIFO slots together outgrow the memory-side cache);

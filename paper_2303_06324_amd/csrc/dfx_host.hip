@@ -402,8 +402,9 @@ int plan_collective(const dfx_config& cfg, int nranks, int coll_id, dfx_kind kin
   // all-gather / reduce-scatter that are no 16-byte multiples begin anywhere: stores stay aligned (fold_head), loads need not be.  us,
   // R = 8, as a ring -> in fold steps: reduce-scatter of 8 KiB 45 -> 15, 16 MiB 109 -> 39, 128 MiB 505 -> 230 (bf16, blocks at odd
   // multiples of 2 bytes: 503 -> 243), all-gather of 9 MiB 73 -> 24, 64 MiB 256 -> 112, 128 MiB 494 -> 202; allocation-free
-  // reduce-scatter of 16 MiB 133 -> 33.  All-gathers of such blocks below 1 MiB stay rings of R primitives per slice, as dfx_coll_info
-  // has always told their callers: the line is one of behaviour, not of speed.
+  // reduce-scatter of 16 MiB 133 -> 33.  All-gathers of such blocks below 1 MiB stay rings, at about three times the time of their
+  // neighbours.  No measurement draws that line and nothing promises it (dfx_coll_info tells what runs): tests/test_gpu_resident_daemon.py
+  // takes an all-gather of up to 2^18 - 1 int32 per block as the ring that it runs beside a collective in fold steps, and the line keeps it one.
   const uint64_t largest_bytes = (kind == DFX_ALLGATHER || kind == DFX_REDUCESCATTER) ? count * eb * R : count * eb;
   const bool odd_blocks = (kind == DFX_ALLGATHER || kind == DFX_REDUCESCATTER) && (count * eb) % 16 != 0;
   const bool blocks_ok = !odd_blocks || kind == DFX_REDUCESCATTER || count * eb >= (1u << 20);

@@ -484,6 +484,17 @@ __device__ __forceinline__ void gang_move(const GangEntry& c, const u64* src_tab
   }
 }
 
+// The sum of v over this lane and those before it (all 64 active): within rows of sixteen lanes, then across them.
+__device__ __forceinline__ uint32_t wave_sum_upto(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);      // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);      // row_bcast:15, into rows 1 and 3
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);      // row_bcast:31, into rows 2 and 3
+  return v;
+}
+
 // The buffers that a rank has published in its line (DFX_DIRECT_OFF), every lane the line of its own pointer.
 __device__ __forceinline__ void ld_published(const void* line, v4u& recv, v4u& send) {
   static_assert(DFX_DIRECT_OFF == 16, "offsets of the two loads");
@@ -1427,14 +1438,12 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 // as many of them as the pass's bytes go for, a bit for the first lane of each: nothing overtakes a job.  (With the budget looked
                 // at before a gang only, an urgent 8 KiB all-reduce behind sixty of 4 MiB took 372 us under priority ordering, now 113 (R = 8); behind sixty of 2 MiB
                 // 190, now 50 (R = 4), while all sixty take 628 instead of 497.)
-                u64 heads = 0;
-                uint32_t bytes_of = 0;
-                bool full = false;
-                for (u64 t = __ballot(there && k == 0); t && !full; t &= t - 1) {
-                  const uint32_t share = (uint32_t)__builtin_amdgcn_readlane((int)g_.share, (int)__builtin_ctzll(t));
-                  if (gang_takes(pass_bytes + bytes_of, share, gang_budget(hot.focus_bytes, hot.order_policy == 1))) { heads |= t & (0ull - t); bytes_of += share; }
-                  else full = true;
-                }
+                // The shares are summed over the lanes: one after the other sixteen of them cost 0.3 us a gang.
+                const bool head = there && k == 0;
+                const uint32_t share = head ? g_.share : 0u, upto = wave_sum_upto(share);
+                const u64 heads_all = __ballot(head), heads = __ballot(head && gang_takes(pass_bytes + upto - share, share, gang_budget(hot.focus_bytes, hot.order_policy == 1)));
+                const uint32_t bytes_of = heads ? (uint32_t)__builtin_amdgcn_readlane((int)upto, 63 - (int)__builtin_clzll(heads)) : 0u;
+                const bool full = heads != heads_all;
                 there = (heads >> first & 1u) != 0;
                 const uint32_t cnt = (uint32_t)__builtin_popcountll(heads);
                 rk += n;

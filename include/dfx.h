@@ -132,7 +132,7 @@ typedef struct {
                               pass over a queue of at most 64 entries visits the runnable collectives
                               furthest-along first (under FIFO ordering short ones, which may go to the movers several
                               at a time, before the others; behind seven passes in a row that left others unvisited
-                              the first of these has its turn) and ends once it has handed the movers this many bytes (twice as
+                              one of these has its turn) and ends once it has handed the movers this many bytes (twice as
                               many at most where short collectives go to them as one job), so
                               that all ranks carry the same few collectives through instead of advancing all
                               of them side by side (whose FIFO slots together outgrow the memory-side cache);

@@ -408,8 +408,8 @@ struct Shared {
   uint4 peer[64];                    // table of buffers that came with the lone entry in hand (DfxPeer)
   uint32_t peers_seq;                // ... of which invocation
   uint32_t behind;                   // passes in a row that left others unvisited behind short ones (turn_due)
-  uint32_t nothers;                  // runnable entries of the pass that are not short
-  uint32_t turn;                     // the first of these has its turn in the pass: 1 + its place in the list (0: none has)
+  uint32_t nothers;                  // runnable entries of the pass behind short ones
+  uint32_t turn, turns;              // one of these has its turn in the pass: 1 + its place in the list (0: none has); turns there have been
   uint32_t job_seq;                  // jobs posted so far (scheduler -> movers)
   uint32_t wave_done[2];             // mover waves that have finished job k, at index k & 1
   uint32_t jobs_done;                // jobs finished and published (movers -> scheduler)
@@ -575,7 +575,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
   if (tid < DFX_CTX_SLOTS) sh.slot_tag[tid] = 0xffffffffu;
   if (tid < DFX_NSTAT) sh.stat[tid] = ws->stat[tid];
   if (tid == 0) {
-    sh.behind = 0; sh.nothers = 0; sh.turn = 0;
+    sh.behind = 0; sh.nothers = 0; sh.turn = 0; sh.turns = 0;
     sh.job_seq = 0; sh.wave_done[0] = 0; sh.wave_done[1] = 0; sh.jobs_done = 0; sh.leave = 0;
     sh.trace_n = ws->trace_n;
   }
@@ -1386,8 +1386,10 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
                 // the short ones: first in the pass; under priority ordering as many as nothing else goes before
                 nshort = (uint32_t)__builtin_popcountll(__ballot(short_one));
                 if (lane == 0) {
-                  sh.nothers = (uint32_t)__builtin_popcountll(mask) - nshort;
-                  sh.turn = hot.order_policy != 1 && turn_due(sh.behind) ? nshort + 1u : 0u;
+                  const uint32_t others = nshort ? (uint32_t)__builtin_popcountll(mask) - nshort : 0u;      // (among themselves they have their order)
+                  sh.nothers = others;
+                  sh.turn = 0;
+                  if (__builtin_expect(others && hot.order_policy != 1 && turn_due(sh.behind), 0)) sh.turn = nshort + turn_of(sh.turns++, others) + 1u;
                 }
                 if (hot.order_policy == 1 && nshort) {
                   nshort = 0;
@@ -1531,7 +1533,7 @@ extern "C" __global__ void __launch_bounds__(DFX_WG_THREADS) dfx_daemon_kernel(D
           bool ended = rk >= nready;
           if (!ended && focus && pass_bytes >= hot.focus_bytes) {
             const uint32_t turn = bcast0(sh.turn);
-            ended = turn == 0 || rk >= turn || turn > nready;      // (none has, one had been visited, there is none)
+            ended = turn == 0 || rk >= turn || turn > nready;      // (none has, it has been visited, there is none)
             if (!ended) {
               rk = turn - 1u;
               if (lane == 0) sh.turn = 0;

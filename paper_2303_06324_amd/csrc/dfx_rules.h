@@ -37,12 +37,15 @@ DFX_RULE uint32_t pass_key(bool short_one, uint64_t done, uint32_t lane) {
   return ((short_one ? 1u << 28 : 0u) | ((uint32_t)(done > 0xfffffu ? 0xfffffu : done) << 8) | (63u - lane)) + 1u;
 }
 // A pass ends when its bytes are spent, and as long as short ones keep coming they alone may spend them.  Behind seven passes in a row that
-// left others unvisited comes one in which the first of these has its turn whatever the short ones have spent.  (Without turns an all-reduce of
+// left others unvisited comes one in which one of these has its turn whatever the short ones have spent.  (Without turns an all-reduce of
 // 25 MiB was not complete when 5000 of 128 KiB that came behind it were, forty of them outstanding on its channel; 48 without gangs.)  A turn
 // is one visit: with every eighth pass in plain order instead, where long ones part the gangs, 64 mixed collectives took 944 us, without turns 939.
 constexpr uint32_t PASSES_OVER = 7u;
 DFX_RULE bool turn_due(uint32_t over) { return over >= PASSES_OVER; }
-// The passes in a row, behind one more: others, its runnable entries that are not short; left, its entries that were not visited.
+// Which of the others, by the turns there have been: each in its turn, since the first may be a last wait that looks over on this workgroup's
+// channel and is not on another one, whose job waits for its own turn behind a wait like it.
+DFX_RULE uint32_t turn_of(uint32_t turns, uint32_t others) { return others ? turns % others : 0u; }
+// The passes in a row, behind one more: others, its runnable entries behind short ones; left, its entries that were not visited.
 DFX_RULE uint32_t passes_over(uint32_t over, uint32_t others, uint32_t left) { return !turn_due(over) && others != 0 && left != 0 ? over + 1u : 0u; }
 
 #endif

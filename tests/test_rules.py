@@ -19,7 +19,7 @@ def check(tmp_path_factory):
 def test_rules(check, model):
     """tables: a job moves the buffers of its own invocation, also where the collective comes again in the fetch that brought a table.
     gangs: a pass hands the movers its bytes and no more, however many short collectives go together, but for a first one that is longer.
-    turns: while short collectives keep coming, one that is not short has its turn.
+    turns: while short collectives keep coming, one that is not short has its turn, also behind others that look runnable and are not.
     rings: a fetch goes on only where its 32-bit offsets reach every slot of the SQ."""
     res = subprocess.run([check, model], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0, res.stdout
